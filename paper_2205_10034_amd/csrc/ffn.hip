@@ -105,6 +105,7 @@ int32_t launch_f32(const moe_config* cfg, int epi, const float* act, const float
   return check_hip(hipGetLastError(), "float32 FFN launch");
 }
 
+// Any shape and alignment: 32 x 32 elements per workgroup, one at a time.
 template <typename T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ src, T* __restrict__ dst, int rows, int cols) {
   __shared__ T tile[32][33];
@@ -116,6 +117,58 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ sr
   __syncthreads();
   for (int i = ty; i < 32; i += 8)
     if (c0 + i < cols && r0 + tx < rows) dst[base + (size_t)(c0 + i) * rows + r0 + tx] = tile[tx][i];
+}
+
+// Rows, columns and pointers in whole 16-byte vectors (V elements): 64 x 64 elements per workgroup, 16-byte loads along
+// a source row and 16-byte stores along a destination row, so that both sides move whole 128-byte lines (bf16).  HBM
+// bound; the 2-byte accesses of the kernel above need eight times the instructions for the same bytes.  The transposition
+// itself happens on the way out of LDS, where a thread collects V elements of one column; an LDS row is padded by one
+// dword, which puts the eight row groups that a wavefront reads at once on different banks.  Measured on MI355X, 16 bf16
+// matrices of 4096 x 1024: 121 us with the kernel above, 40 us with this one (6.7 TB/s of reads and writes); 8 of
+// 14336 x 4096, which no cache holds: 368 us (5.1 TB/s).
+template <typename T>
+__global__ __launch_bounds__(256) void transpose_vec_kernel(const T* __restrict__ src, T* __restrict__ dst, int rows, int cols) {
+  constexpr int V = 16 / sizeof(T), N = 64, CH = N / V;  // elements per vector, tile edge, vectors per tile row
+  constexpr int PITCH = N + 4 / sizeof(T);
+  __shared__ __attribute__((aligned(16))) T tile[N * PITCH];
+  const size_t base = (size_t)blockIdx.z * rows * cols;
+  const int c0 = blockIdx.x * N, r0 = blockIdx.y * N;
+  uint4 v[N * CH / 256];
+#pragma unroll
+  for (int q = 0; q < N * CH / 256; ++q) {
+    const int i = q * 256 + threadIdx.x, r = i / CH, c = (i % CH) * V;
+    v[q] = uint4{0u, 0u, 0u, 0u};
+    if (r0 + r < rows && c0 + c < cols) v[q] = *reinterpret_cast<const uint4*>(src + base + (size_t)(r0 + r) * cols + c0 + c);
+  }
+#pragma unroll
+  for (int q = 0; q < N * CH / 256; ++q) {
+    const int i = q * 256 + threadIdx.x, r = i / CH, c = (i % CH) * V;
+    uint32_t* p = reinterpret_cast<uint32_t*>(tile + r * PITCH + c);  // (a padded row starts on a dword, not on 16 bytes)
+    p[0] = v[q].x; p[1] = v[q].y; p[2] = v[q].z; p[3] = v[q].w;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < N * CH / 256; ++q) {
+    const int i = q * 256 + threadIdx.x, c = i / CH, r = (i % CH) * V;  // destination row c, elements r .. r + V - 1
+    T o[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) o[j] = tile[(r + j) * PITCH + c];
+    if (c0 + c < cols && r0 + r < rows) {
+      uint4 w;
+      __builtin_memcpy(&w, o, 16);
+      *reinterpret_cast<uint4*>(dst + base + (size_t)(c0 + c) * rows + r0 + r) = w;
+    }
+  }
+}
+
+template <typename T>
+void launch_transpose(const void* src, void* dst, int E, int rows, int cols, hipStream_t s) {
+  constexpr int V = 16 / sizeof(T);
+  const bool vec = rows % V == 0 && cols % V == 0 && (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
+  const int n = vec ? 64 : 32;
+  const dim3 grid((cols + n - 1) / n, (rows + n - 1) / n, E), block(256);
+  if (vec) hipLaunchKernelGGL(transpose_vec_kernel<T>, grid, block, 0, s, (const T*)src, (T*)dst, rows, cols);
+  else hipLaunchKernelGGL(transpose_kernel<T>, grid, block, 0, s, (const T*)src, (T*)dst, rows, cols);
 }
 
 __global__ void clear_ints_kernel(int32_t* p, int n) {
@@ -185,11 +238,8 @@ extern "C" int32_t moe_transpose_expert_weights(const void* src, void* dst, int3
   if (!src || !dst || src == dst) return fail(MOE_ERR_INVALID_ARG, "moe_transpose_expert_weights: src/dst NULL or aliased");
   if (E < 1 || rows < 1 || cols < 1 || E > 65535) return fail(MOE_ERR_INVALID_ARG, "moe_transpose_expert_weights: bad shape");
   if (dtype != MOE_F32 && dtype != MOE_BF16) return fail(MOE_ERR_INVALID_ARG, "moe_transpose_expert_weights: dtype unknown");
-  dim3 grid((cols + 31) / 32, (rows + 31) / 32, E), block(256);
-  if (grid.y > 65535) return fail(MOE_ERR_UNSUPPORTED, "moe_transpose_expert_weights: rows too large");
-  if (dtype == MOE_BF16)
-    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, block, 0, (hipStream_t)stream, (const uint16_t*)src, (uint16_t*)dst, rows, cols);
-  else
-    hipLaunchKernelGGL(transpose_kernel<float>, grid, block, 0, (hipStream_t)stream, (const float*)src, (float*)dst, rows, cols);
+  if ((rows + 31) / 32 > 65535) return fail(MOE_ERR_UNSUPPORTED, "moe_transpose_expert_weights: rows too large");
+  if (dtype == MOE_BF16) launch_transpose<uint16_t>(src, dst, E, rows, cols, (hipStream_t)stream);
+  else launch_transpose<float>(src, dst, E, rows, cols, (hipStream_t)stream);
   return check_hip(hipGetLastError(), "transpose launch");
 }
