@@ -9,8 +9,8 @@
 // Assignment a = j*T + t.  Bookkeeping kernels and one copy kernel:
 //   count : per block of DISPATCH_BLOCK assignments, a per-expert histogram
 //   scan  : per expert, exclusive scan of the block histograms -> block bases
-//           (only for many blocks; with few blocks every assign block sums the
-//           histograms before it by itself, which saves a launch)
+//           (only for long histograms; with short ones every assign block sums
+//           the histograms before it by itself, which saves a launch)
 //   assign: totals -> counts, kept = min(count, C), expert_offsets; each block
 //           ranks its assignments per expert in order (wave ballots + cross-wave
 //           prefix), slot = block base + rank, row = offset + slot if slot < C
@@ -35,7 +35,11 @@ namespace {
 
 constexpr int BT = 256;  // threads per bookkeeping block = assignments per block
 static_assert(BT == DISPATCH_BLOCK, "one assignment per thread");
-constexpr int FUSED_SCAN_MAX_BLOCKS = 256;  // above this the block bases come from the scan kernel
+// Up to this many histogram words every assign block sums what it needs by itself (their reads go over 256 threads);
+// beyond, the block bases come from the scan kernel.  Measured on MI355X (us for the whole bookkeeping, own sums against
+// scan kernel), words = blocks x experts: 1024: 6.4-6.5 / 7.3-7.6, 2048: 7.8 / 7.9, 3840: 10.5 / 9.5, 4096: 10.5 / 7.7-8.7,
+// 9088: 17.3 / 9.3, 39168: 57.9 / 13.8.
+constexpr int64_t FUSED_SCAN_MAX_WORDS = 2048;
 
 __device__ __forceinline__ int expert_of(const int32_t* topk_idx, int a, int T, int k) {
   const int j = a / T, t = a - j * T;
@@ -58,20 +62,41 @@ __global__ __launch_bounds__(BT) void dispatch_count_kernel(const int32_t* __res
   for (int e = threadIdx.x; e < E; e += BT) block_hist[(size_t)blockIdx.x * E + e] = hist[e];
 }
 
-// One block; thread e walks expert e's column of block_hist (coalesced across e) and turns it into the
-// exclusive prefix; the totals go to the extra row block_hist[nblocks][.].
-__global__ __launch_bounds__(MOE_MAX_EXPERTS) void dispatch_scan_kernel(int32_t* __restrict__ block_hist,
-                                                                        int nblocks, int E) {
-  const int e = threadIdx.x;
+// Turns expert e's column of block_hist into its exclusive prefix over the blocks (the block's base slot); the totals
+// go to the extra row block_hist[nblocks][.].  A workgroup serves SCAN_E experts: thread (s, e) sums the s-th of
+// SCAN_S runs of blocks, the run sums meet in LDS, and the run is walked once more with its prefix.  All loads of a run
+// are independent of each other (one thread walking a whole column waited for every load in turn: the whole
+// bookkeeping of 612 blocks x 64 experts took 137 us, 13.8 us now).
+constexpr int SCAN_E = 16, SCAN_S = 16;
+__global__ __launch_bounds__(SCAN_E * SCAN_S) void dispatch_scan_kernel(int32_t* __restrict__ block_hist, int nblocks, int E) {
+  __shared__ int run_sum[SCAN_S][SCAN_E];
+  const int el = threadIdx.x % SCAN_E, seg = threadIdx.x / SCAN_E;
+  const int e = blockIdx.x * SCAN_E + el;
+  const int per = (nblocks + SCAN_S - 1) / SCAN_S;
+  const int b0 = min(seg * per, nblocks), b1 = min(b0 + per, nblocks);
+  int sum = 0;
   if (e < E) {
-    int run = 0;
-    for (int b = 0; b < nblocks; ++b) {
-      const int h = block_hist[(size_t)b * E + e];
-      block_hist[(size_t)b * E + e] = run;  // becomes the block's base slot
-      run += h;
-    }
-    block_hist[(size_t)nblocks * E + e] = run;
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) sum += block_hist[(size_t)b * E + e];
   }
+  run_sum[seg][el] = sum;
+  __syncthreads();
+  if (e >= E) return;
+  int run = 0;
+#pragma unroll
+  for (int s = 0; s < SCAN_S; ++s) run += s < seg ? run_sum[s][el] : 0;
+  for (int b = b0; b < b1; b += 8) {
+    int h[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) h[j] = block_hist[(size_t)min(b + j, b1 - 1) * E + e];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (b + j < b1) {
+        block_hist[(size_t)(b + j) * E + e] = run;
+        run += h[j];
+      }
+  }
+  if (seg == SCAN_S - 1) block_hist[(size_t)nblocks * E + e] = run;
 }
 
 // prefixed = 1: block_hist holds exclusive prefixes and a totals row (scan kernel ran);
@@ -110,34 +135,45 @@ __global__ __launch_bounds__(BT) void dispatch_assign_kernel(const int32_t* __re
     }
     __syncthreads();
   }
+  // exclusive prefix of the kept rows per expert by the first wavefront: lane l owns the experts 4l .. 4l + 3
   auto prefix_offsets = [&]() {
-    if (threadIdx.x == 0) {
-      int off = 0;
-      for (int e = 0; e < E; ++e) {
-        off_s[e] = off;
-        off += min(total_s[e], C);
-      }
-      off_s[E] = off;
+    if (wave != 0) return;
+    static_assert(MOE_MAX_EXPERTS == 256, "four experts per lane");
+    int own[4], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int e = 4 * lane + j;
+      own[j] = sum;
+      sum += e < E ? min(total_s[e], C) : 0;
     }
+    int incl = sum;
+    for (int m = 1; 4 * m <= E; m <<= 1) {  // (lanes 0 .. E / 4 meet: the last writes off_s[E])
+      const int up = __shfl_up(incl, m, 64);
+      incl += lane >= m ? up : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int e = 4 * lane + j;
+      if (e <= E) off_s[e] = incl - sum + own[j];  // (e == E: the experts before it are all there are)
+    }
+    if (E == MOE_MAX_EXPERTS && lane == 63) off_s[E] = incl;
   };
   if (prefixed != 2) prefix_offsets();
   const int a = blockIdx.x * DISPATCH_BLOCK + threadIdx.x;
   const int e_in = a < T * k ? expert_of(topk_idx, a, T, k) : -1;
   const bool valid = (unsigned)e_in < (unsigned)E;
   const int e = valid ? e_in : -1;
-  // rank among the wave's lanes with the same expert, in lane (= assignment) order
-  int rank = 0;
-  unsigned long long todo = __ballot(valid);
-  while (todo) {
-    const int leader = __ffsll((long long)todo) - 1;
-    const int e0 = __shfl(e, leader, 64);
-    const unsigned long long same = __ballot(e == e0);
-    if (e == e0) {
-      rank = __popcll(same & ((1ull << lane) - 1ull));
-      if (lane == leader) wave_cnt[wave][e0] = __popcll(same);
-    }
-    todo &= ~same;
+  // rank among the wave's lanes with the same expert, in lane (= assignment) order: one ballot per bit of the expert
+  // index leaves every lane the mask of the lanes that agree with it in all bits (a walk over the distinct experts
+  // took as many dependent steps as there are of them, up to 64)
+  unsigned long long same = __ballot(valid);
+  for (int bit = 1; bit < E; bit <<= 1) {
+    const bool one = (e & bit) != 0;
+    const unsigned long long with = __ballot(one);
+    same &= one ? with : ~with;
   }
+  const int rank = __popcll(same & ((1ull << lane) - 1ull));
+  if (valid && rank == 0) wave_cnt[wave][e] = __popcll(same);
   __syncthreads();
   if (prefixed == 2) {  // the totals are this block's own counts
     for (int e2 = threadIdx.x; e2 < E; e2 += BT) {
@@ -222,9 +258,9 @@ int32_t launch_dispatch(const moe_config* cfg, const void* x, const int32_t* top
                        r2a, clear8);
   } else {
     hipLaunchKernelGGL(dispatch_count_kernel, dim3(nblocks), dim3(BT), 0, s, topk_idx, T, k, E, block_hist, clear8);
-    const int prefixed = nblocks > FUSED_SCAN_MAX_BLOCKS;
+    const int prefixed = (int64_t)nblocks * E > FUSED_SCAN_MAX_WORDS;
     if (prefixed)
-      hipLaunchKernelGGL(dispatch_scan_kernel, dim3(1), dim3(MOE_MAX_EXPERTS), 0, s, block_hist, nblocks, E);
+      hipLaunchKernelGGL(dispatch_scan_kernel, dim3((E + SCAN_E - 1) / SCAN_E), dim3(SCAN_E * SCAN_S), 0, s, block_hist, nblocks, E);
     hipLaunchKernelGGL(dispatch_assign_kernel, dim3(nblocks), dim3(BT), 0, s, topk_idx, T, k, E, C, block_hist, nblocks,
                        prefixed, counts, offsets, a2r, r2a, (int32_t*)nullptr);
   }
