@@ -1,8 +1,6 @@
 // Top-k softmax gate (GShard top-2 / top-1 gating, Section 5.2; softmax in fp32, Section 5.2).
 //
-// Two kernels.
-//
-// Fast path (bf16 activations, E <= 64), HBM-bound: the logits are a skinny GEMM on the MFMA units.
+// Fast path (bf16 activations, E <= 64; the rules that choose are at launch_gate), HBM-bound: the logits are a skinny GEMM on the MFMA units.
 // Activations are bfloat16 already; every float32 router weight is split into three bfloat16 pieces
 // (w = hi + mid + lo exactly), so every product is exact in float32 and the only rounding is the
 // accumulation: float32 inside a 64-wide K chunk (24 roundings at most), float64 across chunks and
@@ -11,45 +9,16 @@
 // k+1 leading logits have two neighbours closer than GATE_MARGIN_REL times its largest |logit| is recomputed by the whole workgroup
 // with float64 accumulation of the (exact) products and ranked on those values.
 //
-// Exact path (float32 activations, or E > 64): one wavefront works on TPW tokens at a time.  Each lane owns a
-// strided slice of d_model and accumulates the logits of NE experts in
-// float64 (the product of two float32 / bfloat16 values is exact in float64,
-// so only the summation rounds, at 2^-53 relative).  A reduce-scatter over the
-// 64 lanes leaves one expert's logit per lane group, the logits go through
-// LDS, and the wave then does the fp32 softmax and k rounds of arg-max
-// (ties -> lower expert index) with cross-lane shuffles.
+// Exact path (float32 activations, E > 64, or many tokens on more than 16 experts): the products of two float32 / bfloat16 values are exact in float64, and
+// v_mfma_f64_16x16x4_f64 accumulates them there, so only the summation rounds, at 2^-53 relative, and nothing has to be
+// recomputed; see gate_f64_kernel.
 #include <type_traits>
 #include "moesys_internal.h"
 
 namespace moesys {
 namespace {
 
-constexpr int NE = 16;   // experts per accumulation pass
-constexpr int TPW = 4;   // tokens per wavefront
-constexpr int WAVES = 4; // wavefronts per block
-
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
-template <typename XT> struct XLoad;
-template <> struct XLoad<float> {
-  static constexpr int V = 4;
-  static __device__ __forceinline__ void load(const float* p, float (&o)[4]) {
-    float4 v = *reinterpret_cast<const float4*>(p);
-    o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
-  }
-};
-template <> struct XLoad<uint16_t> {
-  static constexpr int V = 8;
-  static __device__ __forceinline__ void load(const uint16_t* p, float (&o)[8]) {
-    uint4 v = *reinterpret_cast<const uint4*>(p);
-    uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      o[2 * i] = __uint_as_float(w[i] << 16);
-      o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-};
 
 __device__ __forceinline__ double shfl_xor_f64(double v, int m) {
   int lo = __double2loint(v), hi = __double2hiint(v);
@@ -85,29 +54,6 @@ __device__ __forceinline__ void group8_steps(F&& f) {
 // also waits for every global load and store in flight: for the results just stored, a microsecond at the end of a
 // kernel that lasts ten, and for refill loads that nobody will use.)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-template <int W, int M>
-__device__ __forceinline__ void rs_step(double (&acc)[NE], int lane) {
-  const bool upper = (lane & M) != 0;
-#pragma unroll
-  for (int i = 0; i < W; ++i) {
-    double send = upper ? acc[i] : acc[i + W];
-    double keep = upper ? acc[i + W] : acc[i];
-    acc[i] = keep + shfl_xor_f64(send, M);
-  }
-}
-
-// After the call every lane holds the wave-wide sum of acc[(lane >> 2) & 15].
-__device__ __forceinline__ double reduce_scatter16(double (&acc)[NE], int lane) {
-  rs_step<8, 32>(acc, lane);
-  rs_step<4, 16>(acc, lane);
-  rs_step<2, 8>(acc, lane);
-  rs_step<1, 4>(acc, lane);
-  double v = acc[0];
-  v += shfl_xor_f64(v, 2);
-  v += shfl_xor_f64(v, 1);
-  return v;
-}
 
 // One wavefront ranks one token from its float64 logits z[0..E): softmax in float32 (row maximum subtracted),
 // k rounds of arg-max on the float64 logits (ties -> lower expert index), weights p or p / sum of the selected.
@@ -173,60 +119,6 @@ __device__ __forceinline__ int rank_token(const double* z, int lane, int E, int 
     topk_w[(size_t)t * k + lane] = renorm ? wsel / wsum : wsel;
   }
   return isel;
-}
-
-template <typename XT>
-__global__ __launch_bounds__(WAVES * 64) void gate_exact_kernel(
-    const XT* __restrict__ x, const float* __restrict__ wr, const float* __restrict__ br, int T, int d,
-    int E, int k, int renorm, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
-    float* __restrict__ probs) {
-  extern __shared__ double zs_all[];  // [WAVES][TPW][Epad]
-  constexpr int V = XLoad<XT>::V;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int Epad = (E + NE - 1) / NE * NE;
-  double* zs = zs_all + (size_t)wave * TPW * Epad;
-  const int t0 = (blockIdx.x * WAVES + wave) * TPW;
-
-  for (int c0 = 0; c0 < E; c0 += NE) {
-    const int ne = min(NE, E - c0);
-    double acc[TPW][NE];
-#pragma unroll
-    for (int q = 0; q < TPW; ++q)
-#pragma unroll
-      for (int e = 0; e < NE; ++e) acc[q][e] = 0.0;
-    for (int i = lane * V; i < d; i += 64 * V) {
-      float xv[TPW][V];
-#pragma unroll
-      for (int q = 0; q < TPW; ++q) {
-        const int t = min(t0 + q, T - 1);  // clamp: tail tokens recompute the last row, never stored
-        XLoad<XT>::load(x + (size_t)t * d + i, xv[q]);
-      }
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const float* wrow = wr + (size_t)(i + v) * E + c0;
-        float wv[NE];
-#pragma unroll
-        for (int e = 0; e < NE; ++e) wv[e] = e < ne ? wrow[e] : 0.f;
-#pragma unroll
-        for (int q = 0; q < TPW; ++q)
-#pragma unroll
-          for (int e = 0; e < NE; ++e) acc[q][e] = fma((double)xv[q][v], (double)wv[e], acc[q][e]);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      double z = reduce_scatter16(acc[q], lane);
-      const int e = (lane >> 2) & 15;
-      if ((lane & 3) == 0 && e < ne) zs[q * Epad + c0 + e] = z + (br ? (double)br[c0 + e] : 0.0);
-    }
-  }
-  __syncthreads();
-
-  for (int q = 0; q < TPW; ++q) {
-    const int t = t0 + q;
-    if (t >= T) break;  // uniform per wave
-    rank_token(zs + q * Epad, lane, E, k, renorm, t, topk_idx, topk_w, probs);
-  }
 }
 
 // Few tokens (T <= FEW_MAX_T; E = 4, 8, 16, 32 or 64): one workgroup per token, so that the whole router matrix
@@ -401,6 +293,163 @@ __device__ __forceinline__ bool finalize_group(double (&z)[NPL], int sub, int E,
     w_out[sub] = w;
   }
   return close;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Exact path: 16 tokens per workgroup, every expert; the wavefronts split the contraction index and their float64 sums
+// meet in LDS in wavefront order.
+//
+// One v_mfma_f64_16x16x4_f64 takes 16 experts x 16 tokens x 4 values: lane l supplies router row k = l / 16 for expert
+// q = l mod 16 and the activation of token l mod 16.  A dot product does not care about the order of its terms, so lane
+// group g = l / 16 takes a run of KPL consecutive values of a chunk of 4 KPL (one load of the token's row for KPL MFMA
+// steps), and expert q of an MFMA is any expert as long as the result is read back the same way: with EV experts per
+// lane, one load of EV consecutive router weights feeds the EV MFMAs of a group of 16 EV experts.  Operands are
+// converted in registers; the loads of the next chunk are in flight while a chunk is multiplied.
+// Bound by the latency of that chain for few tokens and by the float64 matrix rate for many: the vector-ALU kernel that
+// was here re-read its token rows once per 16 experts and its router weights uncoalesced and element by element.  Measured
+// on MI355X (us, before -> now): bf16, 128 experts: 3001 x 1600 499 -> 45, 16384 x 4096 4612 -> 329 (52 TFLOP/s of the
+// 78.6 that float64 MFMAs can do); 256 experts, 2048 x 2048 1068 -> 100; float32, 16 experts, 2048 x 1024 45 -> 7.4;
+// 64 experts, 4096 x 1024 158 -> 17.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int F64_TOK = 16;
+
+template <typename XT, int EV, int NG, bool VEC, int NW>
+__global__ __launch_bounds__(NW * 64) void gate_f64_kernel(const XT* __restrict__ x, const float* __restrict__ wr,
+                                                           const float* __restrict__ br, int T, int d, int E, int k, int renorm,
+                                                           int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+                                                           float* __restrict__ probs) {
+  // values of the contraction index per lane and chunk (two chunks have to fit the registers beside the sums)
+  constexpr int KPL = sizeof(XT) == 4 || NG > 2 || (EV == 4 && (NG == 1 || !VEC)) ? 4 : 8;
+  constexpr int KC = 4 * KPL, EP = 16 * EV * NG, NPL = EP / 8;
+  extern __shared__ double part64[];  // [NW][EP][F64_TOK]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane & 15, g = lane >> 4;
+  const int t0 = blockIdx.x * F64_TOK;
+  const XT* xrow = x + (size_t)min(t0 + q, T - 1) * d + g * KPL;  // (tail tokens redo the last row and are not stored)
+
+  int e0[NG];  // first of this lane's EV experts in group n, moved into range (what a row past the last expert yields is not read)
+#pragma unroll
+  for (int n = 0; n < NG; ++n) e0[n] = (n * 16 + q) * EV < E ? (n * 16 + q) * EV : 0;
+  struct Chunk { float w[KPL][NG][EV]; float xv[KPL]; };
+  auto load = [&](int c, Chunk& b) {
+    const XT* xp = xrow + (size_t)c * KC;
+    if constexpr (sizeof(XT) == 4) {
+      const float4 v = *reinterpret_cast<const float4*>(xp);
+      b.xv[0] = v.x; b.xv[1] = v.y; b.xv[2] = v.z; b.xv[3] = v.w;
+    } else {
+      uint32_t u[KPL / 2];
+      if constexpr (KPL == 8) {
+        const uint4 v = *reinterpret_cast<const uint4*>(xp);
+        u[0] = v.x; u[1] = v.y; u[2] = v.z; u[3] = v.w;
+      } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(xp);
+        u[0] = v.x; u[1] = v.y;
+      }
+#pragma unroll
+      for (int i = 0; i < KPL / 2; ++i) {
+        b.xv[2 * i] = __uint_as_float(u[i] << 16);
+        b.xv[2 * i + 1] = __uint_as_float(u[i] & 0xffff0000u);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < KPL; ++s) {
+      const float* row = wr + (size_t)(c * KC + g * KPL + s) * E;
+#pragma unroll
+      for (int n = 0; n < NG; ++n) {
+        if constexpr (VEC && EV == 4) {
+          const float4 v = *reinterpret_cast<const float4*>(row + e0[n]);
+          b.w[s][n][0] = v.x; b.w[s][n][1] = v.y; b.w[s][n][2] = v.z; b.w[s][n][3] = v.w;
+        } else if constexpr (VEC && EV == 2) {
+          const float2 v = *reinterpret_cast<const float2*>(row + e0[n]);
+          b.w[s][n][0] = v.x; b.w[s][n][1] = v.y;
+        } else {
+#pragma unroll
+          for (int j = 0; j < EV; ++j) b.w[s][n][j] = row[min(e0[n] + j, E - 1)];
+        }
+      }
+    }
+  };
+  f64x4 acc[NG][EV];
+#pragma unroll
+  for (int n = 0; n < NG; ++n)
+#pragma unroll
+    for (int j = 0; j < EV; ++j) acc[n][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  auto multiply = [&](const Chunk& b) {
+#pragma unroll
+    for (int s = 0; s < KPL; ++s) {
+      const double xd = (double)b.xv[s];
+#pragma unroll
+      for (int n = 0; n < NG; ++n)
+#pragma unroll
+        for (int j = 0; j < EV; ++j) acc[n][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)b.w[s][n][j], xd, acc[n][j], 0, 0, 0);
+    }
+  };
+  const int n_chunks = d / KC;  // d is a multiple of 64
+  if (wave < n_chunks) {
+    Chunk b[2];
+    load(wave, b[0]);
+    int c = wave;
+    for (; c + NW < n_chunks; c += 2 * NW) {
+      load(c + NW, b[1]);
+      multiply(b[0]);
+      load(min(c + 2 * NW, n_chunks - 1), b[0]);
+      multiply(b[1]);
+    }
+    if (c < n_chunks) multiply(b[0]);
+  }
+  // accumulator register i of lane (q, g): row 4 i + g of the MFMA, token q
+#pragma unroll
+  for (int n = 0; n < NG; ++n)
+#pragma unroll
+    for (int j = 0; j < EV; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        part64[((size_t)wave * EP + (n * 16 + 4 * i + g) * EV + j) * F64_TOK + q] = acc[n][j][i];
+  lds_barrier();
+  for (int i = tid; i < EP * F64_TOK; i += NW * 64) {  // (a sum's first term is its own place: nobody else touches it)
+    double v = part64[i];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += part64[(size_t)w * EP * F64_TOK + i];
+    const int e = i / F64_TOK;
+    part64[i] = v + (br && e < E ? (double)br[e] : 0.0);
+  }
+  lds_barrier();
+  for (int i = tid; i < F64_TOK * 8; i += NW * 64) {
+    const int tok = i >> 3, sub = i & 7, t = t0 + tok;
+    double z[NPL];
+#pragma unroll
+    for (int m = 0; m < NPL; ++m) z[m] = sub + 8 * m < E ? part64[(sub + 8 * m) * F64_TOK + tok] : -INFINITY;
+    if (t < T)
+      finalize_group<NPL>(z, sub, E, k, renorm, 0.f, topk_idx + (size_t)t * k, topk_w + (size_t)t * k,
+                          probs ? probs + (size_t)t * E : nullptr);
+  }
+}
+
+template <typename XT, int EV, int NG, int NW>
+int32_t launch_f64_shape(const moe_config* cfg, const void* x, const float* w_router, const float* b_router, int32_t* topk_idx,
+                         float* topk_w, float* probs, hipStream_t s) {
+  constexpr size_t shmem = (size_t)NW * 16 * EV * NG * F64_TOK * sizeof(double);
+  static_assert(shmem <= 128 * 1024, "the partial sums do not fit the LDS");
+  const bool vec = cfg->E % EV == 0 && ((uintptr_t)w_router & (4 * EV - 1)) == 0;
+  auto kern = vec ? gate_f64_kernel<XT, EV, NG, true, NW> : gate_f64_kernel<XT, EV, NG, false, NW>;
+  if (shmem > 65536) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(gate LDS)");
+  }
+  hipLaunchKernelGGL(kern, dim3((cfg->T + F64_TOK - 1) / F64_TOK), dim3(NW * 64), shmem, s, (const XT*)x, w_router, b_router, cfg->T,
+                     cfg->d_model, cfg->E, cfg->k, cfg->renormalize, topk_idx, topk_w, probs);
+  return check_hip(hipGetLastError(), "gate launch");
+}
+
+// wavefronts: as many as keep the partial sums within 128 KB of LDS
+template <typename XT>
+int32_t launch_f64(const moe_config* cfg, const void* x, const float* w_router, const float* b_router, int32_t* topk_idx,
+                   float* topk_w, float* probs, hipStream_t s) {
+  if (cfg->E <= 16) return launch_f64_shape<XT, 1, 1, 16>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
+  if (cfg->E <= 32) return launch_f64_shape<XT, 2, 1, 16>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
+  if (cfg->E <= 64) return launch_f64_shape<XT, 4, 1, 16>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
+  if (cfg->E <= 128) return launch_f64_shape<XT, 4, 2, 8>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
+  return launch_f64_shape<XT, 4, 4, 4>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
 }
 
 // EB = number of 16-expert blocks (E <= 16*EB).  One workgroup = 16 tokens (one MFMA token tile); its NWV
@@ -1059,6 +1108,14 @@ int32_t launch_gate_dispatch_one_token(const moe_config* cfg, const void* x, con
   return launch_few<uint16_t>(cfg, x, w_router, b_router, topk_idx, topk_w, nullptr, s, counts, offsets, a2r, r2a, clear8);
 }
 
+// bfloat16 activations, up to 64 experts: where the float64 kernel takes over from the one that splits the router into
+// bfloat16 pieces.  Splitting costs every workgroup of 16 tokens the whole router on the vector ALU, a float64 MFMA costs
+// 16 times a bfloat16 one.  Measured on MI355X (us, split / float64): 16 experts, d 2048: T 4096 14.5 / 12.0, T 16384
+// 27 / 33, and two token tiles per workgroup take over from T 8192, so up to 16 experts stay with the split; 24 experts,
+// d 2048: T 300 13.3 / 15.8, T 1024 18.6 / 15.9, T 4096 19.8 / 17.7, T 32768 106 / 104; 64 experts, d 2048: T 300 22-37 / 23,
+// T 4096 49 / 26, T 16384 110 / 91; 64 experts, d 4096: T 300 35.9 / 40.0, T 1024 37-50 / 40.7, T 4096 77 / 44.
+bool gate_f64_pays(const moe_config* cfg) { return cfg->E > 16 && cfg->T >= 1024; }
+
 int32_t launch_gate(const moe_config* cfg, const void* x, const float* w_router, const float* b_router,
                     int32_t* topk_idx, float* topk_w, float* probs, hipStream_t s) {
   if (cfg->T == 0) return MOE_OK;
@@ -1066,23 +1123,13 @@ int32_t launch_gate(const moe_config* cfg, const void* x, const float* w_router,
     if (cfg->dtype == MOE_BF16) return launch_few<uint16_t>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
     return launch_few<float>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
   }
-  if (cfg->dtype == MOE_BF16 && cfg->E <= 64) {
+  if (cfg->dtype == MOE_BF16 && cfg->E <= 64 && !gate_f64_pays(cfg)) {
     if (cfg->E <= 16) return launch_fast<1>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
     if (cfg->E <= 32) return launch_fast<2>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
     return launch_fast<4>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
   }
-  const int per_block = WAVES * TPW;
-  dim3 grid((cfg->T + per_block - 1) / per_block), block(WAVES * 64);
-  const int Epad = (cfg->E + NE - 1) / NE * NE;
-  size_t shmem = (size_t)WAVES * TPW * Epad * sizeof(double);
-  if (cfg->dtype == MOE_BF16)
-    hipLaunchKernelGGL(gate_exact_kernel<uint16_t>, grid, block, shmem, s, (const uint16_t*)x, w_router,
-                       b_router, cfg->T, cfg->d_model, cfg->E, cfg->k, cfg->renormalize, topk_idx, topk_w,
-                       probs);
-  else
-    hipLaunchKernelGGL(gate_exact_kernel<float>, grid, block, shmem, s, (const float*)x, w_router, b_router,
-                       cfg->T, cfg->d_model, cfg->E, cfg->k, cfg->renormalize, topk_idx, topk_w, probs);
-  return check_hip(hipGetLastError(), "gate launch");
+  if (cfg->dtype == MOE_BF16) return launch_f64<uint16_t>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
+  return launch_f64<float>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
 }
 
 // The pre-split router serves bfloat16 activations and up to 64 experts (3 E rows in at most six blocks of 32).
@@ -1094,12 +1141,13 @@ size_t router_pack_bytes(int d_model, int E) {
 bool gate_packed_applies(const moe_config* cfg, const float* w_router) {
   return cfg->dtype == MOE_BF16 && cfg->E <= 64 && !gate_few_applies(cfg, w_router);
 }
-// Inside a layer the packed router is used where it measured faster than splitting on the fly: long token streams
-// (from about 64 M activation elements; below, the kernels are bound by their chain of dependent steps and by the
-// second launch that recomputes the near-ties, not by the split) and wide routers (more than 42 experts: there
-// the split, which every workgroup repeats for the whole router, is most of the other kernel's time).
+// Inside a layer the packed router is used where it measured faster than the kernels that need no preparation: long token
+// streams (from about 64 M activation elements; below, narrow routers are bound by their chain of dependent steps and by
+// the second launch that recomputes the near-ties), and routers of more than 16 experts from 8192 tokens (us, float64
+// kernel / packed with its second launch, d 2048: 24 experts T 4096 17.7 / 16.3, T 8192 31 / 25, T 16384 55 / 39;
+// 64 experts T 4096 25.7 / 34.7, T 8192 48.5 / 37.3, T 32768 179 / 96).
 bool gate_packed_pays(const moe_config* cfg) {
-  return (int64_t)cfg->T * cfg->d_model >= ((int64_t)1 << 26) || (gate_frags(cfg->E) >= 4 && cfg->T >= 1024);
+  return (int64_t)cfg->T * cfg->d_model >= ((int64_t)1 << 26) || (cfg->E > 16 && cfg->T >= 8192);
 }
 
 int32_t launch_gate_packed(const moe_config* cfg, const void* x, const void* packed, const float* w_router, const float* b_router,
