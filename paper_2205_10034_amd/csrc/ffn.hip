@@ -2,8 +2,7 @@
 // and the one-time expert weight transpose.
 //
 // The bf16 MFMA grouped GEMM lives in grouped_gemm_bf16.hip; the float32 path
-// below is a plain LDS-tiled FMA kernel used by the small all-fp32 case, where
-// launch latency, not arithmetic, sets the time.
+// below multiplies on the float32 matrix instructions.
 #include "moesys_internal.h"
 
 namespace moesys {
@@ -16,93 +15,319 @@ int32_t launch_gemm2_combine_bf16(const moe_config*, const moe_weights*, const v
 
 namespace {
 
-constexpr int FT = 64;   // tile edge (tokens and features)
-constexpr int FK = 16;   // K step
-
 enum { F_GELU = 0, F_SWIGLU = 1, F_BIAS = 2 };
 
 __device__ __forceinline__ float gelu_exact(float u) { return 0.5f * u * (1.f + erff(u * 0.70710678118654752f)); }
 __device__ __forceinline__ float silu_exact(float u) { return u / (1.f + expf(-u)); }
 
-// out[r, n] = epi(sum_k act[r,k] * W_e(n,k) (+ bias)), W_e(n,k) = w[e*N*K + n*sn + k*sk].
-template <int EPI>
-__global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ act, const float* __restrict__ wa,
-                                                      const float* __restrict__ wb, const float* __restrict__ bias,
-                                                      const int32_t* __restrict__ offsets, float* __restrict__ out,
-                                                      int E, int N, int K, long sn, long sk) {
-  __shared__ float As[FK][FT + 4];
-  __shared__ float Ba[FK][FT + 4];
-  __shared__ float Bb[EPI == F_SWIGLU ? FK : 1][FT + 4];
-  const int e = blockIdx.z;
-  const int row0 = offsets[e] + blockIdx.x * FT;
-  const int rows = min(FT, offsets[e + 1] - row0);
-  if (rows <= 0) return;
-  const int n0 = blockIdx.y * FT;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {}, accb[4][4] = {};
-  const float* wae = wa + (size_t)e * N * K;
-  const float* wbe = EPI == F_SWIGLU ? wb + (size_t)e * N * K : nullptr;
-  for (int k0 = 0; k0 < K; k0 += FK) {
-    for (int i = threadIdx.x; i < FT * FK; i += 256) {
-      const int r = i / FK, kk = i % FK;
-      As[kk][r] = act[(size_t)(row0 + min(r, rows - 1)) * K + k0 + kk];
-      const int n = min(n0 + r, N - 1);
-      Ba[kk][r] = wae[(size_t)n * sn + (size_t)(k0 + kk) * sk];
-      if (EPI == F_SWIGLU) Bb[kk][r] = wbe[(size_t)n * sn + (size_t)(k0 + kk) * sk];
-    }
-    __syncthreads();
+// Four floats from any float address (one 16-byte load; the hardware asks for no more than 4-byte alignment).
+typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4a4*>(p); }
+
+// out[r, n] = epi(sum_k act[r,k] * W_e(n,k) (+ bias)) in float32 on v_mfma_f32_32x32x2_f32 (fused multiply-adds, float32
+// accumulation): out rows are the MFMA's rows, output features its columns.  Lane l supplies row (column) l mod 32 and,
+// of eight consecutive values of the contraction index, the four of its half l / 32: the order of a dot product's terms
+// is free, so four MFMAs of two values each take one 16-byte piece per lane and operand.
+// OUTPUT_MAJOR weights [n][k] are such pieces already; INPUT_MAJOR ones [k][n] (IM) are read one value per lane, 32
+// consecutive features at a time.
+struct F32Tile { int expert, row0, rows, nt; };
+
+// Tile of workgroup blockIdx.x, false if there is none.  Tiles are numbered expert by expert, feature tile by feature
+// tile, row tiles innermost, and every XCD (workgroup b runs on XCD b mod 8) takes one contiguous eighth: the row tiles
+// that share a weight tile, and the feature tiles that share the rows, meet in one L2.  Every wavefront finds its tile
+// by itself (lane l looks at the experts 4l .. 4l+3), so no barrier is spent on it.
+template <int TM>
+__device__ __forceinline__ bool f32_tile(const int32_t* __restrict__ offsets, int E, int n_tiles, F32Tile& t) {
+  const int lane = threadIdx.x & 63;
+  static_assert(MOE_MAX_EXPERTS == 256, "four experts per lane");
+  int cnt[4], sum = 0;
 #pragma unroll
-    for (int kk = 0; kk < FK; ++kk) {
-      float a[4], b[4], bb[4];
+  for (int j = 0; j < 4; ++j) {
+    const int e = 4 * lane + j;
+    cnt[j] = e < E ? (offsets[e + 1] - offsets[e] + TM - 1) / TM : 0;
+    sum += cnt[j];
+  }
+  int incl = sum;
+  for (int m = 1; 4 * m <= E; m <<= 1) {
+    const int up = __shfl_up(incl, m, 64);
+    incl += lane >= m ? up : 0;
+  }
+  // (the first E / 4 + 1 lanes have met; the later ones hold no expert)
+  const int total = __builtin_amdgcn_readlane(incl, min((E + 3) / 4, 64) - 1) * n_tiles;
+  const int chunk = (total + 7) / 8, i = blockIdx.x / 8, id = (int)(blockIdx.x % 8) * chunk + i;
+  if (i >= chunk || id >= total) return false;
+  int p = incl - sum, e = -1, base = 0, tiles = 1;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Ba[kk][tx * 4 + i]; }
-      if (EPI == F_SWIGLU) {
+  for (int j = 0; j < 4; ++j) {
+    if (4 * lane + j < E && id >= p * n_tiles && id < (p + cnt[j]) * n_tiles) { e = 4 * lane + j; base = p; tiles = cnt[j]; }
+    p += cnt[j];
+  }
+  const int src = __builtin_ctzll(__ballot(e >= 0));  // (exactly one lane has it)
+  e = __builtin_amdgcn_readlane(e, src);
+  base = __builtin_amdgcn_readlane(base, src);
+  tiles = __builtin_amdgcn_readlane(tiles, src);
+  const int r = id - base * n_tiles, nt = r / tiles, m = r - nt * tiles;
+  t.expert = e;
+  t.row0 = offsets[e] + m * TM;
+  t.rows = min(TM, offsets[e + 1] - t.row0);
+  t.nt = nt;
+  return true;
+}
+
+// Many tiles: 64 rows x 64 features per workgroup, four wavefronts of 32 x 32, 32 values of the contraction index per
+// step.  A step's operands go through registers into one of two LDS stages while the other is multiplied (rows padded
+// to 36 floats: the 16-byte reads of 16 rows hit all banks once); one barrier per step.  Bound by the float32 MFMA rate
+// (1024 clocks per step) once several workgroups per CU cover each other's barriers; small tiles, because an expert's last
+// row tile is half empty on average and experts are many.  (64 x 128 tiles measured 2-30 % slower except for INPUT_MAJOR
+// weights at the largest size, 346 against 353 us.)  SwiGLU: a gate block and the up block of the same features per wavefront.
+// Measured on MI355X at 4096 rows over 16 experts, d_model 1024, d_ff 4096 (two products of 34.4 GFLOP): 764 + 837 us on
+// the vector ALU (10 times that without a capacity bound: its grid had a workgroup for every row tile of every expert),
+// 350 + 371 us here (98 and 93 TFLOP/s of the 154 that the vendor's dense product of 8192^3 reaches).
+constexpr int FM = 64, FKS = 32, FPITCH = FKS + 4;
+template <int EPI, bool IM>
+__global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict__ act, const float* __restrict__ wa,
+                                                         const float* __restrict__ wb, const float* __restrict__ bias,
+                                                         const int32_t* __restrict__ offsets, float* __restrict__ out, int E,
+                                                         int N, int K, int n_tiles) {
+  constexpr int OUTF = 64;                             // output features per tile
+  constexpr int NB = EPI == F_SWIGLU ? 2 : 1;          // 32-feature blocks per wavefront
+  constexpr int TN = OUTF * NB;                        // weight rows per tile
+  constexpr int BP = IM ? TN + 4 : FPITCH, BROWS = IM ? FKS : TN;
+  __shared__ __attribute__((aligned(16))) float sa[2][FM * FPITCH];
+  __shared__ __attribute__((aligned(16))) float sb[2][BROWS * BP];
+  F32Tile t;
+  if (!f32_tile<FM>(offsets, E, n_tiles, t)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, wc = wave >> 1, l32 = lane & 31, h = lane >> 5;
+  const int n0 = t.nt * OUTF;
+  const size_t we = (size_t)t.expert * N * K;
+
+  // this thread's 16-byte pieces of a stage: two of the rows, TN / 32 of the weights; pieces past the last row or
+  // feature re-read the last one
+  const float* pa[2];
+  const float* pb[TN / 32];
+  int la[2], lb[TN / 32];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) bb[i] = Bb[kk][tx * 4 + i];
+  for (int q = 0; q < 2; ++q) {
+    const int i = q * 256 + tid, r = i / 8, c = i % 8;
+    pa[q] = act + (size_t)(t.row0 + min(r, t.rows - 1)) * K + 4 * c;
+    la[q] = r * FPITCH + 4 * c;
+  }
+#pragma unroll
+  for (int q = 0; q < TN / 32; ++q) {
+    const int i = q * 256 + tid;
+    const int r = IM ? i / (TN / 4) : i / 8, c = IM ? i % (TN / 4) : i % 8;  // IM: contraction row r, features 4c; else feature r
+    const int f = IM ? 4 * c : r;                                            // feature inside the tile
+    const float* w = EPI == F_SWIGLU && f >= OUTF ? wb : wa;
+    const int n = EPI == F_SWIGLU && f >= OUTF ? n0 + f - OUTF : n0 + f;
+    if (IM) pb[q] = w + we + (size_t)r * N + min(n, N - 4);                   // (N is a multiple of 64)
+    else pb[q] = w + we + (size_t)min(n, N - 1) * K + 4 * c;
+    lb[q] = IM ? r * BP + 4 * c : r * BP + 4 * c;
+  }
+  const size_t b_step = IM ? (size_t)FKS * N : FKS;
+  f32x4 ra[2], rb[TN / 32];
+  auto load = [&](int kt) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) ra[q] = load4(pa[q] + (size_t)kt * FKS);
+#pragma unroll
+    for (int q = 0; q < TN / 32; ++q) rb[q] = load4(pb[q] + kt * b_step);
+  };
+  auto store = [&](int s) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) *reinterpret_cast<f32x4*>(&sa[s][la[q]]) = ra[q];
+#pragma unroll
+    for (int q = 0; q < TN / 32; ++q) *reinterpret_cast<f32x4*>(&sb[s][lb[q]]) = rb[q];
+  };
+  f32x16 acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+  auto compute = [&](int s) {
+#pragma unroll
+    for (int kk = 0; kk < FKS / 8; ++kk) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(&sa[s][(wm * 32 + l32) * FPITCH + kk * 8 + 4 * h]);
+      f32x4 b[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int f = j * (TN / NB) + wc * 32 + l32;
+        if (IM) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) b[j][i] = sb[s][(kk * 8 + 4 * h + i) * BP + f];
+        } else {
+          b[j] = *reinterpret_cast<const f32x4*>(&sb[s][f * BP + kk * 8 + 4 * h]);
+        }
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-          if (EPI == F_SWIGLU) accb[i][j] = fmaf(a[i], bb[j], accb[i][j]);
-        }
+        for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j][i], acc[j], 0, 0, 0);
     }
+  };
+  const int KT = K / FKS;  // K is a multiple of 64
+  const bool busy = wm * 32 < t.rows;  // (a wavefront without a row leaves the matrix pipe to the others)
+  load(0);
+  store(0);
+  load(1);
+  __syncthreads();
+  for (int kt = 0; kt < KT; ++kt) {
+    if (kt + 1 < KT) store((kt + 1) & 1);       // (nobody has read that stage since the last barrier)
+    if (kt + 2 < KT) load(kt + 2);
+    if (busy) compute(kt & 1);
     __syncthreads();
   }
+  // register v of lane (l32, h): row (v & 3) + 8 (v >> 2) + 4 h of the wavefront's 32, feature l32 of the block
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = ty * 4 + i;
-    if (r >= rows) continue;
+  for (int j = 0; j < (EPI == F_SWIGLU ? 1 : NB); ++j) {
+    const int n = n0 + j * (TN / NB) + wc * 32 + l32;
+    if (n >= N) continue;
+    const float b = EPI != F_SWIGLU && bias ? bias[(size_t)t.expert * N + n] : 0.f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float u = acc[i][j];
-      if (EPI == F_SWIGLU) u = silu_exact(u) * accb[i][j];
-      else {
-        if (bias) u += bias[(size_t)e * N + n];
-        if (EPI == F_GELU) u = gelu_exact(u);
-      }
-      out[(size_t)(row0 + r) * N + n] = u;
+    for (int v = 0; v < 16; ++v) {
+      const int r = wm * 32 + (v & 3) + 8 * (v >> 2) + 4 * h;
+      if (r >= t.rows) continue;
+      float u = acc[j][v];
+      if constexpr (EPI == F_SWIGLU) u = silu_exact(u) * acc[NB - 1][v];
+      else if (EPI == F_GELU) u = gelu_exact(u + b);
+      else u += b;
+      out[(size_t)(t.row0 + r) * N + n] = u;
     }
   }
 }
 
-int32_t launch_f32(const moe_config* cfg, int epi, const float* act, const float* wa, const float* wb,
-                   const float* bias, const int32_t* offsets, float* out, int N, int K, int layout, hipStream_t s) {
+// Few tiles: 32 rows x 32 features per workgroup, whose eight wavefronts split the contraction index (runs of 32 values,
+// one 128-byte line per row, straight from global memory into MFMA operands); their sums meet in LDS in wavefront
+// order.  Bound by latency: a quarter of the tile, an eighth of the chain.
+constexpr int SPLIT_WAVES = 8;
+template <int EPI, bool IM>
+__global__ __launch_bounds__(SPLIT_WAVES * 64) void ffn_f32_split_kernel(
+    const float* __restrict__ act, const float* __restrict__ wa, const float* __restrict__ wb, const float* __restrict__ bias,
+    const int32_t* __restrict__ offsets, float* __restrict__ out, int E, int N, int K, int n_tiles) {
+  constexpr int NM = EPI == F_SWIGLU ? 2 : 1;  // weight matrices
+  __shared__ float red[SPLIT_WAVES][NM][1024];
+  F32Tile t;
+  if (!f32_tile<32>(offsets, E, n_tiles, t)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  const int n0 = t.nt * 32;
+  const size_t we = (size_t)t.expert * N * K;
+  const float* pa = act + (size_t)(t.row0 + min(l32, t.rows - 1)) * K + 4 * h;
+  const float* pw[NM];
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    const float* w = (m ? wb : wa) + we;
+    pw[m] = IM ? w + (size_t)(4 * h) * N + n0 + l32 : w + (size_t)(n0 + l32) * K + 4 * h;
+  }
+  struct Chunk { f32x4 a[4], b[NM][4]; };
+  auto load = [&](int c, Chunk& x) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      x.a[kk] = load4(pa + (size_t)c * 32 + 8 * kk);
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        if (IM) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x.b[m][kk][i] = pw[m][(size_t)(c * 32 + 8 * kk + i) * N];
+        } else {
+          x.b[m][kk] = load4(pw[m] + (size_t)c * 32 + 8 * kk);
+        }
+      }
+    }
+  };
+  f32x16 acc[NM];
+#pragma unroll
+  for (int m = 0; m < NM; ++m)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[m][v] = 0.f;
+  auto multiply = [&](const Chunk& x) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[kk][i], x.b[m][kk][i], acc[m], 0, 0, 0);
+  };
+  const int n_chunks = K / 32;
+  if (wave < n_chunks) {
+    Chunk x[2];
+    load(wave, x[0]);
+    int c = wave;
+    for (; c + SPLIT_WAVES < n_chunks; c += 2 * SPLIT_WAVES) {
+      load(c + SPLIT_WAVES, x[1]);
+      multiply(x[0]);
+      load(min(c + 2 * SPLIT_WAVES, n_chunks - 1), x[0]);
+      multiply(x[1]);
+    }
+    if (c < n_chunks) multiply(x[0]);
+  }
+#pragma unroll
+  for (int m = 0; m < NM; ++m)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) red[wave][m][v * 64 + lane] = acc[m][v];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 1024 / (SPLIT_WAVES * 64); ++q) {
+    const int i = q * SPLIT_WAVES * 64 + tid, v = i >> 6, l = i & 63;
+    const int r = (v & 3) + 8 * (v >> 2) + 4 * (l >> 5), n = n0 + (l & 31);
+    float u[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      u[m] = red[0][m][i];
+#pragma unroll
+      for (int w = 1; w < SPLIT_WAVES; ++w) u[m] += red[w][m][i];
+    }
+    if (r >= t.rows) continue;
+    float y = u[0];
+    if constexpr (EPI == F_SWIGLU) y = silu_exact(y) * u[NM - 1];
+    else {
+      if (bias) y += bias[(size_t)t.expert * N + n];
+      if (EPI == F_GELU) y = gelu_exact(y);
+    }
+    out[(size_t)(t.row0 + r) * N + n] = y;
+  }
+}
+
+template <int EPI, bool IM>
+int32_t launch_f32_layout(const moe_config* cfg, const float* act, const float* wa, const float* wb, const float* bias,
+                          const int32_t* offsets, float* out, int N, int K, hipStream_t s) {
   const int64_t rmax = max_rows(cfg);
   if (rmax == 0) return MOE_OK;
-  int64_t per_expert = rmax;  // one expert may hold every row
   const int64_t C = moe_capacity(cfg);
-  if (C != MOE_DROPLESS && C < per_expert) per_expert = C;
-  dim3 grid((unsigned)((per_expert + FT - 1) / FT), (unsigned)((N + FT - 1) / FT), (unsigned)cfg->E), block(256);
-  if (grid.x > 65535u * 32u) return fail(MOE_ERR_UNSUPPORTED, "float32 FFN: too many row tiles");
-  const long sn = layout == MOE_LAYOUT_OUTPUT_MAJOR ? K : 1, sk = layout == MOE_LAYOUT_OUTPUT_MAJOR ? 1 : N;
-  if (epi == F_GELU) hipLaunchKernelGGL(ffn_f32_kernel<F_GELU>, grid, block, 0, s, act, wa, wb, bias, offsets, out, cfg->E, N, K, sn, sk);
-  else if (epi == F_SWIGLU) hipLaunchKernelGGL(ffn_f32_kernel<F_SWIGLU>, grid, block, 0, s, act, wa, wb, bias, offsets, out, cfg->E, N, K, sn, sk);
-  else hipLaunchKernelGGL(ffn_f32_kernel<F_BIAS>, grid, block, 0, s, act, wa, wb, bias, offsets, out, cfg->E, N, K, sn, sk);
+  // upper bound of the tiles of tm rows x tn features (the device counts the real ones), in eighths
+  auto grid_of = [&](int tm, int tn) {
+    int64_t mt = rmax / tm + cfg->E;  // every expert may end in one partial tile
+    if (C != MOE_DROPLESS && (int64_t)cfg->E * ((C + tm - 1) / tm) < mt) mt = (int64_t)cfg->E * ((C + tm - 1) / tm);
+    return (mt * ((N + tn - 1) / tn) + 7) / 8 * 8;
+  };
+  // The 64-row kernel from 257 tiles on (one for every CU), for evenly loaded experts; below, the kernel that splits the
+  // contraction index.  Measured (us, 64 rows / split): 112 tiles, K 2624: 60 / 50; 144 tiles, K 640: 21 / 18; 256 tiles of
+  // 16 rows, K 4096: 99 / 78; 288 tiles, K 2048: 85 / 92; 656 tiles, K 448: 38 / 67; 1280 tiles, K 4096: 380 / 548.
+  constexpr int OUTF = 64;
+  const int64_t rows_each = (rmax + cfg->E - 1) / cfg->E;
+  const bool split = cfg->E * ((rows_each + FM - 1) / FM) * ((N + OUTF - 1) / OUTF) <= 256;
+  const int tm = split ? 32 : FM, tn = split ? 32 : OUTF;
+  const int64_t grid = grid_of(tm, tn);
+  if (grid > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "float32 FFN: too many tiles");
+  const dim3 g((unsigned)grid);
+  const int n_tiles = (N + tn - 1) / tn;
+  if (split)
+    hipLaunchKernelGGL((ffn_f32_split_kernel<EPI, IM>), g, dim3(SPLIT_WAVES * 64), 0, s, act, wa, wb, bias, offsets, out, cfg->E, N, K, n_tiles);
+  else
+    hipLaunchKernelGGL((ffn_f32_kernel<EPI, IM>), g, dim3(256), 0, s, act, wa, wb, bias, offsets, out, cfg->E, N, K, n_tiles);
   return check_hip(hipGetLastError(), "float32 FFN launch");
+}
+
+int32_t launch_f32(const moe_config* cfg, int epi, const float* act, const float* wa, const float* wb,
+                   const float* bias, const int32_t* offsets, float* out, int N, int K, int layout, hipStream_t s) {
+  const bool im = layout == MOE_LAYOUT_INPUT_MAJOR;
+#define MOE_F32_(e) (im ? launch_f32_layout<e, true>(cfg, act, wa, wb, bias, offsets, out, N, K, s) \
+                       : launch_f32_layout<e, false>(cfg, act, wa, wb, bias, offsets, out, N, K, s))
+  if (epi == F_GELU) return MOE_F32_(F_GELU);
+  if (epi == F_SWIGLU) return MOE_F32_(F_SWIGLU);
+  return MOE_F32_(F_BIAS);
+#undef MOE_F32_
 }
 
 // Any shape and alignment: 32 x 32 elements per workgroup, one at a time.
