@@ -422,7 +422,14 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wt = wave / WF, wf = wave % WF;
   const uint32_t row_bytes = (uint32_t)K * 2u;
-  const int n_tiles = N / OUT_FEAT;
+  const int n_tiles = (N + OUT_FEAT - 1) / OUT_FEAT;
+  // A feature count that is no multiple of the tile: the last feature tile starts at N - OUT_FEAT, so that every load is
+  // in range without a mask, and the wavefronts whose features belong to the tile before it neither multiply nor store
+  // (they are whole wavefronts: N is a multiple of 64).  The 320-row kernel has no register left for it.
+  constexpr bool RAGGED_N = TOK <= 256;
+  constexpr int WAVE_OUT = OUT_FEAT / WF;  // output features per wavefront
+  auto first_feature = [&](int ntile) { return RAGGED_N ? min(ntile * OUT_FEAT, N - OUT_FEAT) : ntile * OUT_FEAT; };
+  auto idle_wave = [&](int ntile) { return RAGGED_N && first_feature(ntile) + wf * WAVE_OUT < ntile * OUT_FEAT; };
 
   if (clear_ctr && blockIdx.x == 0 && tid < NUM_XCD) clear_ctr[tid] = 0;
   if (EPI == EPI_GELU) fill_phi_table(s_phi);
@@ -492,7 +499,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
   uint32_t a_bytes = 0;
   const uint32_t b_bytes = (uint32_t)B_ROWS * row_bytes;
   auto bind_tile = [&](const TileInfo& t) {
-    const size_t woff = (eoff ? (size_t)eoff[t.expert] : (size_t)t.expert * N * K) + (size_t)t.ntile * OUT_FEAT * K;
+    const size_t woff = (eoff ? (size_t)eoff[t.expert] : (size_t)t.expert * N * K) + (size_t)first_feature(t.ntile) * K;
     a_ptr = GATHER ? act : act + (size_t)t.row0 * K;
     b_ptr = wa + woff;
     b2_ptr = (swiglu_tile(EPI) ? wb : wa) + woff;
@@ -578,7 +585,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
       // this wavefront's WFEAT bias values: lanes 0..WFEAT/2-1 move one dword each, the others read out of
       // range, which stores zeros
       const uint16_t* brow = bias + (eoff ? (size_t)eoff[t.expert] : (size_t)t.expert * N) +
-                             (size_t)t.ntile * OUT_FEAT + wf * WFEAT;
+                             (size_t)first_feature(t.ntile) + wf * WFEAT;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(brow, (uint32_t)WFEAT * 2u),
                                                (__attribute__((address_space(3))) void*)(s_bias + (bias_set * NW + wave) * 256), 4, lane * 4, 0, 0, 0);
     }
@@ -844,7 +851,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
                pf.last = t; ++pf.tiles; })
     draw_next();
     // token blocks of this wavefront with at least one valid row (wave-uniform)
-    const int tbv = min(TB, max(0, (ti.rows - wt * 32 + 32 * WT - 1) / (32 * WT)));
+    const int tbv = idle_wave(ti.ntile) ? 0 : min(TB, max(0, (ti.rows - wt * 32 + 32 * WT - 1) / (32 * WT)));
     switch (tbv) {
       case 0: run_tile(std::integral_constant<int, 0>{}); break;
       case 1: run_tile(std::integral_constant<int, (1 < TB ? 1 : TB)>{}); break;
@@ -892,7 +899,8 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     // as the feature half: lanes l and l+16 hold features 4m..4m+3 and 4m+4..4m+7 of both feature halves and
     // trade (v_permlane16_swap), after which the even 16-lane row owns 8 features of the first half and the odd
     // row 8 of the second.
-    const int feat0 = done.ntile * OUT_FEAT;
+    const int feat0 = first_feature(done.ntile);
+    const bool idle = idle_wave(done.ntile);
     // where this lane's four features of member g of pair i0 start inside a 32-feature block (before the trade)
     auto run_off = [&](int i0, int g) { return MI16 ? 16 * g + 4 * fhalf : 8 * (i0 + g) + 4 * fhalf; };
     // where the eight features this lane stores for pair i0 start (after the trade)
@@ -936,7 +944,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
       // after a skipped block is processed either.  16x16x32: a block is left when it holds no row at all (the
       // same for the whole wavefront); inside a block only the stores depend on the row, because the second
       // half's rows may lie past the end when the first half's do not.
-      if (MI16 ? (tb * WT + wt) * 32 >= done.rows : tile_row(tb, 0) >= done.rows) continue;
+      if (idle || (MI16 ? (tb * WT + wt) * 32 >= done.rows : tile_row(tb, 0) >= done.rows)) continue;
       auto live_row = [&](int i0) { return !MI16 || tile_row(tb, i0) < done.rows; };
       auto out_row = [&](int i0) {
         return EPI == EPI_COMBINE ? (size_t)row_tok[tb * RSETS + (MI16 ? i0 >> 1 : 0)] : (size_t)(done.row0 + tile_row(tb, i0));
@@ -1049,7 +1057,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     }
     if (!have) break;
     // the epilogue above ran all its stores with every lane alive: this wavefront's last row of the tile exists
-    stores_behind = done.rows >= ((TB - 1) * WT + wt + 1) * 32;
+    stores_behind = !idle && done.rows >= ((TB - 1) * WT + wt + 1) * 32;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // only zero-length loads and stores remain; retire them
   MOE_PROF(if (g_gemm_prof && lane == 0) {
@@ -1067,7 +1075,7 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
                int32_t* tile_ctr, int32_t* clear_ctr, int N, int K, hipStream_t s, const int64_t* eoff,
                const float* gate_w = nullptr, const uint16_t* residual = nullptr) {
   constexpr int OUT_FEAT = swiglu_tile(EPI) ? FEAT / 2 : FEAT;
-  if (N % OUT_FEAT) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: N=%d is not a multiple of %d", N, OUT_FEAT);
+  if (N < OUT_FEAT || N % (TOK <= 256 ? 64 : OUT_FEAT)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: N=%d does not fit tiles of %d features", N, OUT_FEAT);
   if (K % KS) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: K=%d is not a multiple of %d", K, KS);
   if ((int64_t)TOK * K * 2 >= ((int64_t)1 << 31)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: K=%d too large", K);
   const int64_t rmax = max_rows(cfg);
@@ -1078,7 +1086,7 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
     const int64_t by_cap = (int64_t)cfg->E * token_tiles((int)(C > INT32_MAX - TOK ? INT32_MAX - TOK : C), TOK);
     if (by_cap < mt) mt = by_cap;
   }
-  const int64_t blocks = block_count(mt, N / OUT_FEAT);  // upper bound of the device's block count
+  const int64_t blocks = block_count(mt, (N + OUT_FEAT - 1) / OUT_FEAT);  // upper bound of the device's block count
   if (blocks > INT32_MAX / 64) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: too many tiles");
   // persistent: one workgroup per CU (the LDS stages leave room for one), a multiple of the XCD count;
   // fewer when even the upper bound of the tile count cannot occupy every CU
@@ -1157,16 +1165,17 @@ bool prefer_mi16(const moe_config* cfg) {
 }
 
 // One grouped GEMM.  256x256x64 tiles (8 wavefronts, the highest arithmetic intensity that fits the
-// 160 KB LDS) whenever the feature count allows; feature counts that are multiples of 64 but not of 256
-// use narrow tiles.
+// 160 KB LDS) whenever there are that many features; smaller feature counts use narrow tiles.  (Narrow tiles also served
+// feature counts that are no multiple of 256: at 26103 tokens, top-6 of 64 experts, d_ff 2560, d_model 1344 the second
+// GEMM took 2975 us with 128x64 tiles, 1035 us with a last tile that overlaps the one before.)
 template <int EPI>
 int32_t gemm_any(const moe_config* cfg, const uint16_t* a, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                  const int32_t* offsets, uint16_t* o, const int32_t* row_map, int32_t* tile_ctr, int32_t* clear_ctr, int N,
                  int K, hipStream_t s, const int64_t* eoff, const float* gate_w = nullptr,
                  const uint16_t* residual = nullptr) {
   constexpr int BF = swiglu_tile(EPI) ? 128 : 256;  // output features of the big tile
-  if (N % BF == 0) {
-    if (pick_tile_rows(cfg, N / BF) == 320)
+  if (N >= BF) {
+    if (N % BF == 0 && pick_tile_rows(cfg, N / BF) == 320)
       return launch<320, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
     if (use_mi16(256, 2, EPI) && prefer_mi16(cfg))
       return launch<256, 256, 2, 4, 64, 2, EPI, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
@@ -1185,6 +1194,11 @@ bool expert_gemv_applies(const moe_config* cfg, int N, int K);
 int32_t launch_expert_gemv_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
                                 const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
                                 const void* residual, const int64_t* eoff, int N, int K, hipStream_t s);
+// steps of few rows per expert take the weight-streaming kernels
+bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu);
+int32_t launch_expert_stream_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
+                                  const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
+                                  const void* residual, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s);
 
 // row_map (nullable): row_to_assign; the token rows are then gathered from x[T, d_model] instead of read
 // from a dispatched copy.
@@ -1196,6 +1210,13 @@ int32_t launch_gemm1_bf16(const moe_config* cfg, const moe_weights* w, const voi
                                      w->expert_elem_offset, cfg->d_ff, cfg->d_model, s);
     return launch_expert_gemv_bf16(EPI_GELU, cfg, xd, w->w1, nullptr, w->b1, offsets, h, row_map, nullptr, nullptr,
                                    w->expert_elem_offset, cfg->d_ff, cfg->d_model, s);
+  }
+  if (expert_stream_applies(cfg, cfg->d_ff, cfg->d_model, cfg->act == MOE_ACT_SWIGLU)) {
+    if (cfg->act == MOE_ACT_SWIGLU)
+      return launch_expert_stream_bf16(EPI_SWIGLU, cfg, xd, w->w_gate_proj, w->w_up, nullptr, offsets, h, row_map, nullptr, nullptr,
+                                       w->expert_elem_offset, tile_counters + NUM_XCD, cfg->d_ff, cfg->d_model, s);
+    return launch_expert_stream_bf16(EPI_GELU, cfg, xd, w->w1, nullptr, w->b1, offsets, h, row_map, nullptr, nullptr,
+                                     w->expert_elem_offset, tile_counters + NUM_XCD, cfg->d_ff, cfg->d_model, s);
   }
   // the first GEMM draws from counters [0,8) and clears [8,16) for the second, which in turn clears [0,8): after
   // the pair has run the first GEMM's counters are back at zero, so the expert half of a layer can run again
@@ -1215,6 +1236,9 @@ int32_t launch_gemm2_bf16(const moe_config* cfg, const moe_weights* w, const voi
   if (expert_gemv_applies(cfg, cfg->d_model, cfg->d_ff))
     return launch_expert_gemv_bf16(EPI_BIAS, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, yd, nullptr,
                                    nullptr, nullptr, w->expert_elem_offset, cfg->d_model, cfg->d_ff, s);
+  if (expert_stream_applies(cfg, cfg->d_model, cfg->d_ff, false))
+    return launch_expert_stream_bf16(EPI_BIAS, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, yd, nullptr,
+                                     nullptr, nullptr, w->expert_elem_offset, tile_counters, cfg->d_model, cfg->d_ff, s);
   return gemm_any<EPI_BIAS>(
       cfg, (const uint16_t*)h, (const uint16_t*)(sw ? w->w_down : w->w2), nullptr,
       (const uint16_t*)(sw ? nullptr : w->b2), offsets, (uint16_t*)yd, nullptr, tile_counters + NUM_XCD, tile_counters,
@@ -1230,6 +1254,9 @@ int32_t launch_gemm2_combine_bf16(const moe_config* cfg, const moe_weights* w, c
   if (expert_gemv_applies(cfg, cfg->d_model, cfg->d_ff))
     return launch_expert_gemv_bf16(EPI_COMBINE, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, out,
                                    row_to_assign, topk_w, residual, w->expert_elem_offset, cfg->d_model, cfg->d_ff, s);
+  if (expert_stream_applies(cfg, cfg->d_model, cfg->d_ff, false))
+    return launch_expert_stream_bf16(EPI_COMBINE, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, out,
+                                     row_to_assign, topk_w, residual, w->expert_elem_offset, tile_counters, cfg->d_model, cfg->d_ff, s);
   return gemm_any<EPI_COMBINE>(
       cfg, (const uint16_t*)h, (const uint16_t*)(sw ? w->w_down : w->w2), nullptr,
       (const uint16_t*)(sw ? nullptr : w->b2), offsets, (uint16_t*)out, row_to_assign, tile_counters + NUM_XCD, tile_counters,
@@ -1241,6 +1268,8 @@ int32_t launch_gemm2_combine_bf16(const moe_config* cfg, const moe_weights* w, c
 // recomputing the pre-activations.  counters8: eight zeroed ints.
 int32_t launch_grouped_matmul_bf16(const moe_config* cfg, const void* act, const void* w, const void* bias,
                                    const int32_t* offsets, void* out, int N, int K, int32_t* counters8, hipStream_t s) {
+  if (expert_stream_applies(cfg, N, K, false))
+    return launch_expert_stream_bf16(EPI_BIAS, cfg, act, w, nullptr, bias, offsets, out, nullptr, nullptr, nullptr, nullptr, nullptr, N, K, s);
   return gemm_any<EPI_BIAS>(cfg, (const uint16_t*)act, (const uint16_t*)w, nullptr, (const uint16_t*)bias, offsets,
                             (uint16_t*)out, nullptr, counters8, nullptr, N, K, s, nullptr);
 }
