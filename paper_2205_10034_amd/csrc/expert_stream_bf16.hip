@@ -1,0 +1,324 @@
+// Expert FFN products (bf16) for steps with few rows per expert: more than the matrix-vector kernels serve, fewer than
+// fill the grouped GEMM's 256-row tiles (a serving batch that generates, Section 3.3).
+//
+//   out[r, n] = epilogue( sum_k act[r, k] * W_e[n, k] )      for the rows r of every expert
+//
+// The product's time is the time to stream the activated experts' weights once.  The 256 x 256 tiles of the grouped GEMM
+// have one 64 KB stage in flight per CU, half of it rows that are not there, and their number is too small for the chip
+// when the feature count is: 8 experts x 4096 features are 128 tiles for 256 CUs.  Here a workgroup owns 64 or 128 weight
+// rows and 32 to 192 rows of one expert and keeps all but one of its three to five LDS stages (64 values of the
+// contraction index each) requested ahead: weights and rows go from global memory straight into LDS, swizzled like the
+// grouped GEMM's, one barrier per stage.  A wavefront multiplies blocks of 16 weight rows by blocks of 16 rows
+// (v_mfma_f32_16x16x32_bf16, weights as the first operand: a lane ends up with four consecutive features of one row).
+// SwiGLU: half of the weight rows are the gate's and half the up projection's; a block of 16 is eight and eight of the
+// same features.
+#include <type_traits>
+#include "moesys_internal.h"
+#include "row_tiles.h"
+
+namespace moesys {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+enum StreamEpi { ST_GELU = 0, ST_SWIGLU = 1, ST_BIAS = 2, ST_COMBINE = 3 };
+
+constexpr int ST_KS = 64;     // values of the contraction index per stage: LDS rows of 128 bytes, eight 16-byte chunks
+
+// NWF x NWM wavefronts, each FB blocks of 16 weight rows x RB blocks of 16 rows
+template <int NWF_, int NWM_, int FB_, int RB_, int STAGES_>
+struct StreamShape {
+  static constexpr int NWF = NWF_, NWM = NWM_, FB = FB_, RB = RB_, STAGES = STAGES_;
+  static constexpr int WAVES = NWF * NWM, WROWS = NWF * FB * 16, TM = NWM * RB * 16;
+};
+
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
+}
+__device__ __forceinline__ float lo16(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi16(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+__device__ __forceinline__ float gelu_exact(float u) { return 0.5f * u * erfcf(-u * 0.70710678118654752f); }
+// s_waitcnt operand: at most n vector memory operations and no LDS operation in flight
+constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
+
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t stream_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+#endif
+
+template <int EPI, bool GATHER, typename S>
+__global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
+    const uint16_t* __restrict__ act, const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb,
+    const uint16_t* __restrict__ bias, const int32_t* __restrict__ offsets, uint16_t* out,
+    const int32_t* __restrict__ row_map, const float* __restrict__ gate_w, const uint16_t* residual,
+    const int64_t* __restrict__ eoff, int32_t* __restrict__ clear_ctr, int T, int E, int N, int K, int n_tiles) {
+#if defined(__HIP_DEVICE_COMPILE__)  // (buffer descriptors are device-only types)
+  constexpr int TM = S::TM, STAGES = S::STAGES, ST_WAVES = S::WAVES, FB = S::FB, RB = S::RB;
+  constexpr int OUTF = EPI == ST_SWIGLU ? S::WROWS / 2 : S::WROWS;  // output features per workgroup
+  constexpr int W_BYTES = S::WROWS * 128, STAGE = W_BYTES + TM * 128;
+  constexpr int W_LOADS = W_BYTES / 1024 / ST_WAVES, A_LOADS = TM * 128 / 1024 / ST_WAVES, LOADS = W_LOADS + A_LOADS;
+  static_assert(W_BYTES % (1024 * ST_WAVES) == 0 && TM * 128 % (1024 * ST_WAVES) == 0, "whole loads of 8 rows per wavefront");
+  static_assert(STAGES >= 3 && STAGES <= 6, "the K loop below");
+  // one array per stage: the compiler can then tell the stages being filled from the one being read
+  __shared__ __attribute__((aligned(1024))) unsigned char s0[STAGE];
+  __shared__ __attribute__((aligned(1024))) unsigned char s1[STAGE];
+  __shared__ __attribute__((aligned(1024))) unsigned char s2[STAGE];
+  __shared__ __attribute__((aligned(1024))) unsigned char s3[STAGES > 3 ? STAGE : 16];
+  __shared__ __attribute__((aligned(1024))) unsigned char s4[STAGES > 4 ? STAGE : 16];
+  __shared__ __attribute__((aligned(1024))) unsigned char s5[STAGES > 5 ? STAGE : 16];
+  if (clear_ctr && blockIdx.x == 0 && threadIdx.x < 8) clear_ctr[threadIdx.x] = 0;  // (a grouped GEMM may run next)
+  RowTile t;
+  if (!find_row_tile<TM>(offsets, E, n_tiles, t)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // a feature count that is no multiple of the tile: the last tile starts at N - OUTF and leaves to the one before what is its
+  const int n0 = min(t.nt * OUTF, N - OUTF);
+  const int KT = K / ST_KS;
+  const int64_t wbase = (eoff ? eoff[t.expert] : (int64_t)t.expert * N * K) + (int64_t)n0 * K;
+
+  // ---- loads: one instruction moves 8 rows of 128 bytes; lane l lands at row l / 8, physical chunk l mod 8 of the eight
+  // rows, which holds the logical chunk (l mod 8) ^ key, key = (row / 2) mod 8.  SwiGLU: LDS rows 16 w .. 16 w + 7 are the
+  // gate rows of features 8 w .. 8 w + 7, the eight after them their up rows.
+  const int k2 = K * 2;  // bytes of a row
+  int voff[LOADS];
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) {
+    const int blk = (i < W_LOADS ? i : i - W_LOADS) * ST_WAVES + wave;  // which eight LDS rows
+    const int row = blk * 8 + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+    int r = row;
+    if (i < W_LOADS) {
+      if (EPI == ST_SWIGLU) r = (blk >> 1) * 8 + (lane >> 3);
+    } else {
+      r = min(row, t.rows - 1);  // (rows past the last re-read it; their results are not stored)
+      if (GATHER) {
+        r = row_map[t.row0 + r];
+        while (r >= T) r -= T;  // assignment id j*T + t -> token (j < k <= 8)
+      }
+    }
+    voff[i] = r * k2 + chunk * 16;
+  }
+  const uint16_t* a_ptr = GATHER ? act : act + (int64_t)t.row0 * K;
+  const uint32_t a_bytes = (uint32_t)(GATHER ? T : t.rows) * (uint32_t)k2, w_bytes = (uint32_t)OUTF * (uint32_t)k2;
+  // (past the last stage the descriptors are empty: nothing is read, and the number of loads in flight is always the same)
+  auto issue = [&](int kt, unsigned char* stage) {
+    const bool live = kt < KT;
+    const __amdgpu_buffer_rsrc_t ra = stream_rsrc(a_ptr, live ? a_bytes : 0u), rw = stream_rsrc(wa + wbase, live ? w_bytes : 0u);
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const int blk = (i < W_LOADS ? i : i - W_LOADS) * ST_WAVES + wave;
+      __amdgpu_buffer_rsrc_t r = i < W_LOADS ? rw : ra;
+      if (EPI == ST_SWIGLU && i < W_LOADS) r = stream_rsrc(((blk & 1) ? wb : wa) + wbase, live ? w_bytes : 0u);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(stage + (i < W_LOADS ? 0 : W_BYTES) + blk * 1024),
+                                               16, voff[i], kt * 128, 0, 0);
+    }
+  };
+  // ---- fragments: 16 rows x 32 values, lane = row + 16 * (chunk of the four)
+  const int frow = lane & 15, fch = lane >> 4;
+  const int wf = wave % S::NWF, wm = wave / S::NWF;  // row block b of row group wm is block b * NWM + wm of the tile
+  const int in_row = frow * 128 + ((fch ^ ((frow >> 1) & 7)) << 4);   // (the key repeats every 16 rows) second 32 values: ^ 64
+  const int w_off = wf * FB * 2048 + in_row, a_off = W_BYTES + wm * 2048 + in_row;
+  f32x4 acc[FB][RB];
+#pragma unroll
+  for (int f = 0; f < FB; ++f)
+#pragma unroll
+    for (int b = 0; b < RB; ++b) acc[f][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](const unsigned char* stage) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      bf16x8 w[FB];
+#pragma unroll
+      for (int f = 0; f < FB; ++f) w[f] = *reinterpret_cast<const bf16x8*>(stage + (w_off ^ (kk << 6)) + f * 2048);
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        const bf16x8 r = *reinterpret_cast<const bf16x8*>(stage + (a_off ^ (kk << 6)) + b * S::NWM * 2048);
+#pragma unroll
+        for (int f = 0; f < FB; ++f) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[f], r, acc[f][b], 0, 0, 0);
+      }
+    }
+  };
+  auto stage_of = [&](auto i) -> unsigned char* {
+    constexpr int I = decltype(i)::value % STAGES;
+    if constexpr (I == 0) return s0;
+    else if constexpr (I == 1) return s1;
+    else if constexpr (I == 2) return s2;
+    else if constexpr (I == 3) return s3;
+    else if constexpr (I == 4) return s4;
+    else return s5;
+  };
+  // Stage kt is multiplied while stages kt+1 .. kt+STAGES-1 are on their way.  A wavefront waits for its own share of
+  // stage kt (loads retire in order) and for its reads of the stage before, then the workgroup meets: stage kt is whole
+  // and the buffer of stage kt-1 is free for stage kt+STAGES-1.
+  auto step = [&](auto i, int kt) {
+    __builtin_amdgcn_s_waitcnt(wait_vm((STAGES - 2) * LOADS));
+    __builtin_amdgcn_s_barrier();
+    issue(kt + STAGES - 1, stage_of(std::integral_constant<int, decltype(i)::value + STAGES - 1>{}));
+    compute(stage_of(i));
+  };
+  issue(0, s0);
+  issue(1, s1);
+  if constexpr (STAGES > 3) issue(2, s2);
+  if constexpr (STAGES > 4) issue(3, s3);
+  if constexpr (STAGES > 5) issue(4, s4);
+  // (left by breaks: on every way round the loop all stages were requested, which is what lets the compiler see that no
+  // further wait is needed before a stage is read)
+  for (int kt = 0;;) {
+    step(std::integral_constant<int, 0>{}, kt);
+    if (++kt == KT) break;
+    step(std::integral_constant<int, 1>{}, kt);
+    if (++kt == KT) break;
+    step(std::integral_constant<int, 2>{}, kt);
+    if (++kt == KT) break;
+    if constexpr (STAGES > 3) { step(std::integral_constant<int, 3>{}, kt); if (++kt == KT) break; }
+    if constexpr (STAGES > 4) { step(std::integral_constant<int, 4>{}, kt); if (++kt == KT) break; }
+    if constexpr (STAGES > 5) { step(std::integral_constant<int, 5>{}, kt); if (++kt == KT) break; }
+  }
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));  // (the empty loads retire)
+
+  // ---- epilogue: lane holds weight rows 4 fch + 0..3 of every 16-row weight block, for row frow of every row block
+#pragma unroll
+  for (int f = 0; f < FB; ++f) {
+    const int fblk = wf * FB + f;
+    if (n0 + fblk * (EPI == ST_SWIGLU ? 8 : 16) < t.nt * OUTF) continue;  // (uniform; N is a multiple of 64)
+    const int n = n0 + (EPI == ST_SWIGLU ? fblk * 8 + (fch & 1) * 4 : fblk * 16 + fch * 4);
+    float bv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (EPI != ST_SWIGLU && bias) {
+      const u32x2 b = *reinterpret_cast<const u32x2*>(bias + (eoff ? eoff[t.expert] : (int64_t)t.expert * N) + n);
+      bv[0] = lo16(b.x); bv[1] = hi16(b.x); bv[2] = lo16(b.y); bv[3] = hi16(b.y);
+    }
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      const int r = (b * S::NWM + wm) * 16 + frow;
+      float p[4];
+      if constexpr (EPI == ST_SWIGLU) {
+        // the lower half of the lanes holds gate rows, lane + 32 the up rows of the same features and row: both get both
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t v = __float_as_uint(acc[f][b][i]);
+          const u32x2 gu = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+          const float g = __uint_as_float(gu.x);
+          p[i] = g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * __uint_as_float(gu.y);
+        }
+        if (lane >= 32) continue;
+      }
+      if (r >= t.rows) continue;
+      size_t o = (size_t)(t.row0 + r) * N + n;
+      if constexpr (EPI != ST_SWIGLU) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = acc[f][b][i] + bv[i];
+      }
+      if constexpr (EPI == ST_GELU) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = gelu_exact(p[i]);
+      }
+      if constexpr (EPI == ST_COMBINE) {  // k = 1: the row's token
+        const int token = row_map[t.row0 + r];
+        o = (size_t)token * N + n;
+        u32x2 res = {0u, 0u};
+        if (residual) res = *reinterpret_cast<const u32x2*>(residual + o);
+        const float g = gate_w[token];
+        p[0] = fmaf(g, p[0], lo16(res.x)); p[1] = fmaf(g, p[1], hi16(res.x));
+        p[2] = fmaf(g, p[2], lo16(res.y)); p[3] = fmaf(g, p[3], hi16(res.y));
+      }
+      *reinterpret_cast<u32x2*>(out + o) = u32x2{pack2(p[0], p[1]), pack2(p[2], p[3])};
+    }
+  }
+#endif
+}
+
+template <int EPI, bool GATHER, typename S>
+int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
+                     const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
+                     const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
+  constexpr int OUTF = EPI == ST_SWIGLU ? S::WROWS / 2 : S::WROWS;
+  const int n_tiles = (N + OUTF - 1) / OUTF;
+  const int64_t grid = row_tile_grid(cfg, S::TM, n_tiles);
+  if (grid > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "expert stream: too many tiles");
+  if (max_rows(cfg) == 0) return MOE_OK;
+  hipLaunchKernelGGL((expert_stream_kernel<EPI, GATHER, S>), dim3((unsigned)grid), dim3(S::WAVES * 64), 0, s, act, wa, wb, bias,
+                     offsets, out, row_map, gate_w, residual, eoff, clear_ctr, cfg->T, cfg->E, N, K, n_tiles);
+  return check_hip(hipGetLastError(), "expert stream launch");
+}
+
+// Which shape (weight rows x rows) serves a product of N features over K values, for evenly loaded experts (every shape
+// handles any routing); none: the grouped GEMM.  Measured on MI355X (us, grouped GEMM / here), rows = rows per expert:
+//  - up to 24 rows the time is the weights': 64x32, three workgroups per CU.  SwiGLU d 4096, f 14336, 8 experts, 24 rows:
+//    395 / 335 (5.6 TB/s) and, with 128 big tiles for 256 CUs, 337 / 169;
+//  - up to 36: 128x64.  64 experts, d 2048, f 8192, 32 rows: 441 / 413 and 424 / 383;
+//  - few tiles of any kind: 64x64.  4 experts, 150 rows, d 320, f 1088: 12.8 / 9.7 and 17.4 / 10.0;
+//  - up to 96 rows with long rows of weights or few big tiles: 128x128.  64 experts, f 8192 -> d 2048, 47 rows 433 / 386,
+//    94 rows 442 / 417, but 107 rows (some experts over 128) 450 / 494; with 2048-long rows 94 rows 453 / 522;
+//  - few big tiles, any rows: 128x192.  16 experts, f 4096 -> d 1024, 256 rows (64 big tiles) 114 / 57; 8 experts, f 3072 ->
+//    d 768, 750 rows (72) 72 / 43; 8 experts, f 14336 -> d 4096 (128), 128 rows 360 / 219, 175 rows 367 / 385; 128 big tiles of
+//    437 rows 110 / 106.
+enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192 };
+int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
+  if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
+  // (the switches ask for the grouped GEMM's kernels)
+  if (!tuning(MOE_TUNE_FEW_TOKEN_KERNELS) || tuning(MOE_TUNE_GEMM_TILE_ROWS) || tuning(MOE_TUNE_GEMM_MFMA)) return STREAM_NONE;
+  int64_t rows = ((int64_t)cfg->k * cfg->T + cfg->E - 1) / cfg->E;
+  const int64_t C = moe_capacity(cfg);
+  if (rows > C) rows = C;
+  if (rows <= 24) return STREAM_64x32;
+  // tiles of fr weight rows x tm rows
+  auto tiles = [&](int fr, int tm) {
+    const int outf = swiglu ? fr / 2 : fr;
+    return cfg->E * ((rows + tm - 1) / tm) * ((N + outf - 1) / outf);
+  };
+  const int64_t big = tiles(256, 256);
+  const bool wide = N >= (swiglu ? 64 : 128);
+  if (wide && rows <= 36) return STREAM_128x64;
+  if (tiles(128, 192) < 128 && tiles(64, 64) <= 512) return STREAM_64x64;
+  if (wide && rows <= 96 && (K >= 4096 || big < 256)) return STREAM_128x128;
+  if (wide && (big <= 96 || (big <= 128 && rows <= 152))) return STREAM_128x192;
+  return STREAM_NONE;
+}
+
+template <int EPI, bool GATHER>
+int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
+               const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
+               const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
+#define MOE_STREAM(...) return launch_shape<EPI, GATHER, StreamShape<__VA_ARGS__>>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, eoff, clear_ctr, N, K, s)
+  switch (pick_stream(cfg, N, K, EPI == ST_SWIGLU)) {
+    case STREAM_64x32: MOE_STREAM(4, 1, 1, 2, 4);
+    case STREAM_64x64: MOE_STREAM(4, 1, 1, 4, 4);
+    case STREAM_128x64: MOE_STREAM(4, 2, 2, 2, 5);
+    case STREAM_128x128: MOE_STREAM(4, 2, 2, 4, 4);
+    case STREAM_128x192: MOE_STREAM(4, 2, 2, 6, 4);
+  }
+#undef MOE_STREAM
+  return fail(MOE_ERR_UNSUPPORTED, "expert stream: shape outside its range");
+}
+
+}  // namespace
+
+bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu) { return pick_stream(cfg, N, K, swiglu) != STREAM_NONE; }
+
+// epi: 0 GELU (+bias), 1 SwiGLU (wa = gate, wb = up), 2 plain (+bias), 3 combine for k = 1 (row_map = row_to_assign,
+// gate_w, residual).  row_map with epi 0/1: gather the rows from x[T, K].  eoff: per-expert element offsets or NULL.
+// clear_ctr (nullable): eight ints cleared on the way, the tile counters that the grouped GEMM in this place would clear.
+int32_t launch_expert_stream_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
+                                  const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
+                                  const void* residual, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
+  const uint16_t *a = (const uint16_t*)act, *w0 = (const uint16_t*)wa, *w1 = (const uint16_t*)wb, *b = (const uint16_t*)bias;
+  const uint16_t* res = (const uint16_t*)residual;
+  uint16_t* o = (uint16_t*)out;
+  switch (epi) {
+    case ST_GELU:
+      return row_map ? launch<ST_GELU, true>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s)
+                     : launch<ST_GELU, false>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s);
+    case ST_SWIGLU:
+      return row_map ? launch<ST_SWIGLU, true>(cfg, a, w0, w1, nullptr, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s)
+                     : launch<ST_SWIGLU, false>(cfg, a, w0, w1, nullptr, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s);
+    case ST_BIAS: return launch<ST_BIAS, false>(cfg, a, w0, w1, b, offsets, o, nullptr, gate_w, res, eoff, clear_ctr, N, K, s);
+    case ST_COMBINE:
+      if (!row_map || !gate_w || cfg->k != 1) return fail(MOE_ERR_INVALID_ARG, "expert stream: combine epilogue needs k = 1, row map and gate weights");
+      return launch<ST_COMBINE, false>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s);
+  }
+  return fail(MOE_ERR_INVALID_ARG, "expert stream: unknown epilogue");
+}
+
+}  // namespace moesys

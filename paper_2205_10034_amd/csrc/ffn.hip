@@ -4,6 +4,7 @@
 // The bf16 MFMA grouped GEMM lives in grouped_gemm_bf16.hip; the float32 path
 // below multiplies on the float32 matrix instructions.
 #include "moesys_internal.h"
+#include "row_tiles.h"
 
 namespace moesys {
 
@@ -32,50 +33,6 @@ __device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cas
 // is free, so four MFMAs of two values each take one 16-byte piece per lane and operand.
 // OUTPUT_MAJOR weights [n][k] are such pieces already; INPUT_MAJOR ones [k][n] (IM) are read one value per lane, 32
 // consecutive features at a time.
-struct F32Tile { int expert, row0, rows, nt; };
-
-// Tile of workgroup blockIdx.x, false if there is none.  Tiles are numbered expert by expert, feature tile by feature
-// tile, row tiles innermost, and every XCD (workgroup b runs on XCD b mod 8) takes one contiguous eighth: the row tiles
-// that share a weight tile, and the feature tiles that share the rows, meet in one L2.  Every wavefront finds its tile
-// by itself (lane l looks at the experts 4l .. 4l+3), so no barrier is spent on it.
-template <int TM>
-__device__ __forceinline__ bool f32_tile(const int32_t* __restrict__ offsets, int E, int n_tiles, F32Tile& t) {
-  const int lane = threadIdx.x & 63;
-  static_assert(MOE_MAX_EXPERTS == 256, "four experts per lane");
-  int cnt[4], sum = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int e = 4 * lane + j;
-    cnt[j] = e < E ? (offsets[e + 1] - offsets[e] + TM - 1) / TM : 0;
-    sum += cnt[j];
-  }
-  int incl = sum;
-  for (int m = 1; 4 * m <= E; m <<= 1) {
-    const int up = __shfl_up(incl, m, 64);
-    incl += lane >= m ? up : 0;
-  }
-  // (the first E / 4 + 1 lanes have met; the later ones hold no expert)
-  const int total = __builtin_amdgcn_readlane(incl, min((E + 3) / 4, 64) - 1) * n_tiles;
-  const int chunk = (total + 7) / 8, i = blockIdx.x / 8, id = (int)(blockIdx.x % 8) * chunk + i;
-  if (i >= chunk || id >= total) return false;
-  int p = incl - sum, e = -1, base = 0, tiles = 1;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (4 * lane + j < E && id >= p * n_tiles && id < (p + cnt[j]) * n_tiles) { e = 4 * lane + j; base = p; tiles = cnt[j]; }
-    p += cnt[j];
-  }
-  const int src = __builtin_ctzll(__ballot(e >= 0));  // (exactly one lane has it)
-  e = __builtin_amdgcn_readlane(e, src);
-  base = __builtin_amdgcn_readlane(base, src);
-  tiles = __builtin_amdgcn_readlane(tiles, src);
-  const int r = id - base * n_tiles, nt = r / tiles, m = r - nt * tiles;
-  t.expert = e;
-  t.row0 = offsets[e] + m * TM;
-  t.rows = min(TM, offsets[e + 1] - t.row0);
-  t.nt = nt;
-  return true;
-}
-
 // Many tiles: 64 rows x 64 features per workgroup, four wavefronts of 32 x 32, 32 values of the contraction index per
 // step.  A step's operands go through registers into one of two LDS stages while the other is multiplied (rows padded
 // to 36 floats: the 16-byte reads of 16 rows hit all banks once); one barrier per step.  Bound by the float32 MFMA rate
@@ -97,8 +54,8 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
   constexpr int BP = IM ? TN + 4 : FPITCH, BROWS = IM ? FKS : TN;
   __shared__ __attribute__((aligned(16))) float sa[2][FM * FPITCH];
   __shared__ __attribute__((aligned(16))) float sb[2][BROWS * BP];
-  F32Tile t;
-  if (!f32_tile<FM>(offsets, E, n_tiles, t)) return;
+  RowTile t;
+  if (!find_row_tile<FM>(offsets, E, n_tiles, t)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wc = wave >> 1, l32 = lane & 31, h = lane >> 5;
   const int n0 = t.nt * OUTF;
@@ -207,8 +164,8 @@ __global__ __launch_bounds__(SPLIT_WAVES * 64) void ffn_f32_split_kernel(
     const int32_t* __restrict__ offsets, float* __restrict__ out, int E, int N, int K, int n_tiles) {
   constexpr int NM = EPI == F_SWIGLU ? 2 : 1;  // weight matrices
   __shared__ float red[SPLIT_WAVES][NM][1024];
-  F32Tile t;
-  if (!f32_tile<32>(offsets, E, n_tiles, t)) return;
+  RowTile t;
+  if (!find_row_tile<32>(offsets, E, n_tiles, t)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
   const int n0 = t.nt * 32;
@@ -294,13 +251,6 @@ int32_t launch_f32_layout(const moe_config* cfg, const float* act, const float* 
                           const int32_t* offsets, float* out, int N, int K, hipStream_t s) {
   const int64_t rmax = max_rows(cfg);
   if (rmax == 0) return MOE_OK;
-  const int64_t C = moe_capacity(cfg);
-  // upper bound of the tiles of tm rows x tn features (the device counts the real ones), in eighths
-  auto grid_of = [&](int tm, int tn) {
-    int64_t mt = rmax / tm + cfg->E;  // every expert may end in one partial tile
-    if (C != MOE_DROPLESS && (int64_t)cfg->E * ((C + tm - 1) / tm) < mt) mt = (int64_t)cfg->E * ((C + tm - 1) / tm);
-    return (mt * ((N + tn - 1) / tn) + 7) / 8 * 8;
-  };
   // The 64-row kernel from 257 tiles on (one for every CU), for evenly loaded experts; below, the kernel that splits the
   // contraction index.  Measured (us, 64 rows / split): 112 tiles, K 2624: 60 / 50; 144 tiles, K 640: 21 / 18; 256 tiles of
   // 16 rows, K 4096: 99 / 78; 288 tiles, K 2048: 85 / 92; 656 tiles, K 448: 38 / 67; 1280 tiles, K 4096: 380 / 548.
@@ -308,7 +258,7 @@ int32_t launch_f32_layout(const moe_config* cfg, const float* act, const float* 
   const int64_t rows_each = (rmax + cfg->E - 1) / cfg->E;
   const bool split = cfg->E * ((rows_each + FM - 1) / FM) * ((N + OUTF - 1) / OUTF) <= 256;
   const int tm = split ? 32 : FM, tn = split ? 32 : OUTF;
-  const int64_t grid = grid_of(tm, tn);
+  const int64_t grid = row_tile_grid(cfg, tm, (N + tn - 1) / tn);
   if (grid > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "float32 FFN: too many tiles");
   const dim3 g((unsigned)grid);
   const int n_tiles = (N + tn - 1) / tn;

@@ -1,0 +1,116 @@
+"""Expert products (bf16) where their tiles end beside the data: the weight-streaming kernels in every shape (the rule is on
+rows per expert and tile counts), and the grouped GEMM with feature counts that are no multiple of its tile.  The bar is
+the bf16 one of the other tests: relative Frobenius error below 1e-2 (measured 2-3e-3: h, yd and out rounded once each)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2205_10034_amd as M
+from oracle import moe_oracle as O
+from workloads import WORKLOADS, bf16_round, make_layer
+
+from gpu_util import alloc_ws, rel_fro, run_layer, to_dev, to_np, upload_weights
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-2
+RAGGED = [0, 1, 15, 16, 17, 31, 32, 33, 0, 47, 48, 49, 63, 64, 65, 2]
+
+
+def ffn_case(act, rows, T, d, f, seed, bias=True):
+    rng = np.random.default_rng(seed)
+    E, R = len(rows), sum(rows)
+    assert R <= T
+    offsets = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    xd = bf16_round(rng.standard_normal((R, d)).astype(np.float32))
+    names = [("w1", d, f), ("w2", f, d)] if act == "gelu" else [("w_gate_proj", d, f), ("w_up", d, f), ("w_down", f, d)]
+    L = {n: bf16_round((rng.standard_normal((E, a, b)) * a ** -0.5).astype(np.float32)) for n, a, b in names}
+    if act == "gelu" and bias:
+        L["b1"], L["b2"] = (bf16_round(rng.standard_normal((E, n)).astype(np.float32)) for n in (f, d))
+    ref = O.expert_ffn(xd, offsets, L, act)
+    L["w_router"] = np.zeros((d, E), np.float32)
+    W = upload_weights(L, "bf16")
+    cfg = M.MoEConfig(T=T, d_model=d, d_ff=f, E=E, k=1, act=act)
+    yd = torch.full((T + 1, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = alloc_ws(cfg, 2)
+    ws.fill_(0xAB)  # (nothing in the workspace is expected to be clear)
+    M.moe_expert_ffn(cfg, W, to_dev(xd, "bf16"), torch.from_numpy(offsets).cuda(), yd, ws)
+    torch.cuda.synchronize()
+    assert bool((yd[R:] == 7.0).all())                                   # nothing past the last row
+    err = rel_fro(to_np(yd[:R]), ref)
+    print("rel fro", err, flush=True)
+    assert err < TOL
+
+
+# T only says what an evenly loaded expert would hold, which is what picks the shape; the rows themselves are ragged
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+@pytest.mark.parametrize("mean,E,d,f", [
+    (24, 40, 64, 64), (20, 40, 128, 320), (9, 60, 832, 192),             # 64 x 32: one to thirteen stages, ragged last tiles
+    (36, 24, 192, 320), (30, 24, 512, 448),                              # 128 x 64
+    (40, 16, 320, 192), (150, 4, 320, 1088), (500, 3, 64, 128),          # 64 x 64: few tiles
+    (60, 32, 576, 576), (90, 40, 512, 832),                              # 128 x 128
+    (120, 32, 512, 576), (250, 16, 704, 1216)])                          # 128 x 192
+def test_stream_shapes(act, mean, E, d, f):
+    print(act, mean, E, d, f, flush=True)
+    rows = [RAGGED[(3 * i + E) % len(RAGGED)] for i in range(E)]
+    rows[E // 2] += max(0, mean * E - sum(rows)) // 2                    # one expert far above the mean
+    ffn_case(act, rows, max(mean * E, sum(rows)), d, f, mean + E)
+
+
+@pytest.mark.parametrize("name,kw", [
+    ("gpt", dict(T=60, E=16, k=2, capacity_factor=0.0)), ("large", dict(T=130, E=8, k=2, d_model=320, d_ff=448)),
+    ("skew", dict(T=150, E=8, d_model=192, d_ff=320)), ("skew", dict(T=700, E=8, d_model=320, d_ff=832, capacity_factor=0.8)),
+    ("large", dict(T=300, E=4, k=1, d_model=192, d_ff=320, capacity_factor=0.0)), ("gpt", dict(T=24, E=2, k=1, d_model=64, d_ff=64))],
+    ids=str)
+def test_stream_layer(name, kw):
+    """Rows gathered from x, the top-1 combine in the second product (with drops), a residual that is also the output."""
+    wl = WORKLOADS[name].scaled(**kw)
+    print(wl, flush=True)
+    L = make_layer(wl, with_bias=True)
+    ref = O.layer_forward(L["x"], L, E=wl.E, k=wl.k, capacity_factor=wl.capacity_factor, renormalize=wl.renormalize, act=wl.act)
+    cfg, W, x = M.MoEConfig.from_workload(wl), upload_weights(L, "bf16"), to_dev(L["x"], "bf16")
+    assert rel_fro(run_layer(cfg, W, x)["out"], ref["out"]) < TOL
+    res = to_dev(L["x"][::-1].copy(), "bf16")
+    M.moe_layer_forward(cfg, W, x, res, res, alloc_ws(cfg))
+    torch.cuda.synchronize()
+    assert rel_fro(to_np(res) - L["x"][::-1], ref["out"]) < 2 * TOL      # (the sum's rounding is counted against the term)
+
+
+@pytest.mark.parametrize("mfma", [16, 32])
+@pytest.mark.parametrize("act,d,f", [("gelu", 320, 1088), ("swiglu", 320, 192), ("swiglu", 448, 832), ("gelu", 576, 256)])
+def test_grouped_gemm_ragged_features(act, d, f, mfma):
+    print(act, d, f, mfma, flush=True)
+    M.moe_set_tuning(M.MOE_TUNE_GEMM_MFMA, mfma)
+    try:
+        rows = [700, 0, 257, 256, 1, 130, 63, 320]
+        for bias in (True, False):
+            ffn_case(act, rows, sum(rows), d, f, d + mfma, bias)
+        wl = WORKLOADS["skew"].scaled(T=900, E=4, d_model=d, d_ff=f, act=act, capacity_factor=0.7)   # top-1: combine in the epilogue
+        L = make_layer(wl, with_bias=True)
+        ref = O.layer_forward(L["x"], L, E=wl.E, k=1, capacity_factor=0.7, renormalize=False, act=act)
+        cfg, W, x = M.MoEConfig.from_workload(wl), upload_weights(L, "bf16"), to_dev(L["x"], "bf16")
+        out = x.clone()
+        M.moe_layer_forward(cfg, W, x, out, out, alloc_ws(cfg))
+        torch.cuda.synchronize()
+        assert rel_fro(to_np(out) - L["x"], ref["out"]) < 2 * TOL
+    finally:
+        M.moe_set_tuning(M.MOE_TUNE_GEMM_MFMA, 0)
+
+
+def test_workspace_counters_between_kernels():
+    """First product streaming, second product on the grouped GEMM and the reverse, run twice from one routing: each leaves
+    the other's tile counters as it needs them."""
+    for d, f in ((2048, 256), (256, 2048)):
+        wl = WORKLOADS["gpt"].scaled(T=1200, E=16, k=2, d_model=d, d_ff=f, capacity_factor=0.0)
+        L = make_layer(wl)
+        cfg, W, x = M.MoEConfig.from_workload(wl), upload_weights(L, "bf16"), to_dev(L["x"], "bf16")
+        ws = alloc_ws(cfg)
+        ws.fill_(0xAB)
+        outs = [torch.empty_like(x) for _ in range(3)]
+        M.moe_layer_forward(cfg, W, x, None, outs[0], ws)
+        M.moe_layer_experts(cfg, W, x, None, outs[1], ws)
+        M.moe_layer_experts(cfg, W, x, None, outs[2], ws)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+        ref = O.layer_forward(L["x"], L, E=wl.E, k=2, capacity_factor=0.0, renormalize=True, act="gelu")
+        assert rel_fro(to_np(outs[0]), ref["out"]) < TOL
