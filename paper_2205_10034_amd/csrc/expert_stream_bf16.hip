@@ -14,6 +14,7 @@
 // same features.
 #include <type_traits>
 #include "moesys_internal.h"
+#include "phi_table.h"
 #include "row_tiles.h"
 
 namespace moesys {
@@ -61,8 +62,9 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   constexpr int TM = S::TM, STAGES = S::STAGES, ST_WAVES = S::WAVES, FB = S::FB, RB = S::RB;
   constexpr int OUTF = EPI == ST_SWIGLU ? S::WROWS / 2 : S::WROWS;  // output features per workgroup
   constexpr int W_BYTES = S::WROWS * 128, STAGE = W_BYTES + TM * 128;
-  constexpr int W_LOADS = W_BYTES / 1024 / ST_WAVES, A_LOADS = TM * 128 / 1024 / ST_WAVES, LOADS = W_LOADS + A_LOADS;
-  static_assert(W_BYTES % (1024 * ST_WAVES) == 0 && TM * 128 % (1024 * ST_WAVES) == 0, "whole loads of 8 rows per wavefront");
+  constexpr int A_BLKS = TM / 8;  // blocks of eight rows, one load each
+  constexpr int W_LOADS = W_BYTES / 1024 / ST_WAVES, A_LOADS = (A_BLKS + ST_WAVES - 1) / ST_WAVES, LOADS = W_LOADS + A_LOADS;
+  static_assert(W_BYTES % (1024 * ST_WAVES) == 0 && 2 * A_BLKS % ST_WAVES == 0, "whole loads of 8 rows per wavefront");
   static_assert(STAGES >= 3 && STAGES <= 6, "the K loop below");
   // one array per stage: the compiler can then tell the stages being filled from the one being read
   __shared__ __attribute__((aligned(1024))) unsigned char s0[STAGE];
@@ -83,11 +85,17 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   // ---- loads: one instruction moves 8 rows of 128 bytes; lane l lands at row l / 8, physical chunk l mod 8 of the eight
   // rows, which holds the logical chunk (l mod 8) ^ key, key = (row / 2) mod 8.  SwiGLU: LDS rows 16 w .. 16 w + 7 are the
   // gate rows of features 8 w .. 8 w + 7, the eight after them their up rows.
+  // Half a round of row blocks left: the upper half of the wavefronts repeats the lower half's loads (same bytes to the same
+  // place), so that every wavefront has as many in flight.
+  auto block = [&](int i) {
+    const int blk = (i < W_LOADS ? i : i - W_LOADS) * ST_WAVES + wave;
+    return i >= W_LOADS && blk >= A_BLKS ? blk - ST_WAVES / 2 : blk;
+  };
   const int k2 = K * 2;  // bytes of a row
   int voff[LOADS];
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {
-    const int blk = (i < W_LOADS ? i : i - W_LOADS) * ST_WAVES + wave;  // which eight LDS rows
+    const int blk = block(i);  // which eight LDS rows
     const int row = blk * 8 + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
     int r = row;
     if (i < W_LOADS) {
@@ -109,7 +117,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     const __amdgpu_buffer_rsrc_t ra = stream_rsrc(a_ptr, live ? a_bytes : 0u), rw = stream_rsrc(wa + wbase, live ? w_bytes : 0u);
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      const int blk = (i < W_LOADS ? i : i - W_LOADS) * ST_WAVES + wave;
+      const int blk = block(i);
       __amdgpu_buffer_rsrc_t r = i < W_LOADS ? rw : ra;
       if (EPI == ST_SWIGLU && i < W_LOADS) r = stream_rsrc(((blk & 1) ? wb : wa) + wbase, live ? w_bytes : 0u);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(stage + (i < W_LOADS ? 0 : W_BYTES) + blk * 1024),
@@ -178,6 +186,17 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   }
   __builtin_amdgcn_s_waitcnt(wait_vm(0));  // (the empty loads retire)
 
+  // GELU: by the exact function for a few elements per lane, by the table (built in the first stage's buffer) for many
+  constexpr bool TABLE = EPI == ST_GELU && FB * RB >= 8;
+  static_assert(PHI_N * 8 <= STAGE, "the table fits a stage");
+  phi_f32x2* const phi = reinterpret_cast<phi_f32x2*>(s0);
+  const float phi_add = phi_addend(phi);
+  if constexpr (TABLE) {
+    __syncthreads();
+    fill_phi_table(phi);
+    __syncthreads();
+  }
+
   // ---- epilogue: lane holds weight rows 4 fch + 0..3 of every 16-row weight block, for row frow of every row block
 #pragma unroll
   for (int f = 0; f < FB; ++f) {
@@ -210,7 +229,9 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
 #pragma unroll
         for (int i = 0; i < 4; ++i) p[i] = acc[f][b][i] + bv[i];
       }
-      if constexpr (EPI == ST_GELU) {
+      if constexpr (TABLE) {
+        gelu_table_n<4>(p, phi_add, phi);
+      } else if constexpr (EPI == ST_GELU) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) p[i] = gelu_exact(p[i]);
       }
@@ -253,7 +274,10 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    94 rows 442 / 417, but 107 rows (some experts over 128) 450 / 494; with 2048-long rows 94 rows 453 / 522;
 //  - few big tiles, any rows: 128x192.  16 experts, f 4096 -> d 1024, 256 rows (64 big tiles) 114 / 57; 8 experts, f 3072 ->
 //    d 768, 750 rows (72) 72 / 43; 8 experts, f 14336 -> d 4096 (128), 128 rows 360 / 219, 175 rows 367 / 385; 128 big tiles of
-//    437 rows 110 / 106.
+//    437 rows 110 / 106;
+//  - three quarters of a round of big tiles against at most two rounds of 128x128 (with a whole round of them the big tiles
+//    win: 16 experts, d 1024 -> f 4096, 128 rows 38 / 56).  16 experts, f 8704 -> d 640, 590 rows (144) 219 / 198 and, with
+//    skewed routing, 239 / 98; f 3072 -> d 768 73 / 64; but 8 experts, f 4096 -> d 1024, 1500 rows (three rounds) 107 / 142.
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192 };
 int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
@@ -274,6 +298,7 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (tiles(128, 192) < 128 && tiles(64, 64) <= 512) return STREAM_64x64;
   if (wide && rows <= 96 && (K >= 4096 || big < 256)) return STREAM_128x128;
   if (wide && (big <= 96 || (big <= 128 && rows <= 152))) return STREAM_128x192;
+  if (wide && big > 128 && big <= 192 && tiles(128, 128) <= 512) return STREAM_128x128;
   return STREAM_NONE;
 }
 
