@@ -20,7 +20,7 @@ int32_t launch_gemm1_dgelu_bf16(const moe_config*, const void*, const void*, con
                                 int32_t*, hipStream_t);
 int32_t launch_gemm1_dswiglu_bf16(const moe_config*, const void*, const void*, const void*, const int32_t*, const void*, void*,
                                   int32_t*, hipStream_t);
-int32_t launch_wgrad_bf16(const uint16_t*, const uint16_t*, const int32_t*, void*, int, float*, int, int, int, int64_t, hipStream_t);
+int32_t launch_wgrad_bf16(const uint16_t*, const uint16_t*, const int32_t*, void*, int, float*, int, int, int, int64_t, int64_t, hipStream_t);
 
 namespace {
 
@@ -313,19 +313,20 @@ static int32_t ffn_backward_impl(const char* who, const moe_config* cfg, const m
   int64_t per_expert = rmax;
   const int64_t C = moe_capacity(cfg);
   if (C != MOE_DROPLESS && C < per_expert) per_expert = C;
+  const int64_t rows_each = (rmax + E - 1) / E;  // of an evenly loaded expert
   // every product draws its tiles from eight zeroed counters of its own
   hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, ctr, 24);
   if ((st = check_hip(hipGetLastError(), "counter clear launch")) != MOE_OK) return st;
   // weight gradients that need nothing recomputed: dW2_e = d_yd_e^T h_e, with db2_e = column sums of d_yd_e on the side
   if ((st = launch_wgrad_bf16((const uint16_t*)d_yd, (const uint16_t*)h, expert_offsets, d_w2, d_w_dtype, (!sw && w->b2) ? d_b2 : nullptr, E, d, f,
-                              per_expert, s)) != MOE_OK) return st;
+                              per_expert, rows_each, s)) != MOE_OK) return st;
   if (sw) {
     // d_h = d_yd W_down; [d_g | d_u] from d_h and the recomputed gate and up products; the gradient of the
     // stacked [W_gate; W_up] in one product, d_xd in one product over the 2 d_ff columns of [d_g | d_u]
     void* dgu = base + rf;
     if ((st = launch_grouped_matmul_bf16(cfg, d_yd, w2_input_major, nullptr, expert_offsets, dh, f, d, ctr, s)) != MOE_OK) return st;
     if ((st = launch_gemm1_dswiglu_bf16(cfg, xd, w->w_gate_proj, w->w_up, expert_offsets, dh, dgu, ctr + 8, s)) != MOE_OK) return st;
-    if ((st = launch_wgrad_bf16((const uint16_t*)dgu, (const uint16_t*)xd, expert_offsets, d_w1, d_w_dtype, nullptr, E, 2 * f, d, per_expert, s)) != MOE_OK) return st;
+    if ((st = launch_wgrad_bf16((const uint16_t*)dgu, (const uint16_t*)xd, expert_offsets, d_w1, d_w_dtype, nullptr, E, 2 * f, d, per_expert, rows_each, s)) != MOE_OK) return st;
     return launch_grouped_matmul_bf16(cfg, dgu, w1_input_major, nullptr, expert_offsets, d_xd, d, 2 * f, ctr + 16, s);
   }
   // d_h = d_yd W2, then d_u = d_h * gelu'(u) in place, u = xd W1^T + b1 being recomputed by the product whose
@@ -335,7 +336,7 @@ static int32_t ffn_backward_impl(const char* who, const moe_config* cfg, const m
   if ((st = launch_gemm1_dgelu_bf16(cfg, xd, w->w1, w->b1, expert_offsets, dh, dh, ctr + 8, s)) != MOE_OK) return st;
   // dW1_e = d_u_e^T xd_e (db1_e = column sums of d_u_e on the side), d_xd = d_u W1
   if ((st = launch_wgrad_bf16((const uint16_t*)dh, (const uint16_t*)xd, expert_offsets, d_w1, d_w_dtype, w->b1 ? d_b1 : nullptr, E, f, d, per_expert,
-                              s)) != MOE_OK) return st;
+                              rows_each, s)) != MOE_OK) return st;
   return launch_grouped_matmul_bf16(cfg, dh, w1_input_major, nullptr, expert_offsets, d_xd, d, f, ctr + 16, s);
 }
 

@@ -7,8 +7,8 @@
 // forward pass.  The contraction runs over an expert's rows, the SLOW index of both row-major operands,
 // and its length differs per expert.
 //
-// CDNA4 mapping.  One workgroup (8 wavefronts, 2 x 4) per 256 x 256 tile of one expert's C; it walks the
-// expert's rows 32 at a time.  Both operand chunks [32 rows x 256 columns] go from global memory straight
+// CDNA4 mapping.  One workgroup (8 wavefronts, 2 x 4) per 256 x 256 tile of one expert's C (or 4 wavefronts, 2 x 2,
+// per 128 x 128 tile where the large tiles are too few); it walks the expert's rows 32 at a time.  Both operand chunks [32 rows x 256 columns] go from global memory straight
 // into LDS as they are (buffer_load ... lds, 16 bytes per lane; rows past the expert's end read as zero
 // through the buffer descriptor, so the ragged length needs no padding), three stages deep.  The MFMA
 // operand fragments need 8 consecutive contraction indices per lane, i.e. a COLUMN of the LDS tile: they
@@ -22,12 +22,13 @@
 // Tile order.  The 8 XCDs have an L2 each, and the hardware deals workgroups out to them round robin.  A tile
 // streams a 256-column slab of A and one of B; tiles of one expert with the same n1 (n2) tile share the A (B)
 // slab.  Workgroups are therefore numbered so that the 32 that start together on one XCD are a block of
-// BY x BX tiles of ONE expert (BX = min(8, n2 tiles), BY = 32 / BX): BY + BX slabs for 32 tiles through that L2
+// BY x BX tiles of ONE expert (BX = min(8, n2 tiles), with few rows up to 32; BY = 32 / BX): BY + BX slabs for 32 tiles through that L2
 // instead of the 6 for 8 that the plain (n2, n1, expert) grid order gives at 16 x 4 tiles per expert.
 // Column sums of A per expert (the bias gradients: db2_e = sum_r d_y[r, :], db1_e = sum_r d_u[r, :]) come from
 // the same fragments: the workgroups of the first n2 tile multiply one n1 fragment per wavefront and K-step
 // by a fragment of ones (one more MFMA on top of eight), which leaves the column's sum in every element of
 // that accumulator.  No extra pass over A.
+#include <type_traits>
 #include "moesys_internal.h"
 
 namespace moesys {
@@ -43,13 +44,19 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int WG_N = 256;        // tile edge (both n1 and n2)
+constexpr int WG_N = 256;        // multiple that N1 and N2 must be of
 constexpr int WG_KS = 32;        // rows per K-step
-constexpr int WG_ROW = WG_N * 2; // bytes of one LDS row
-constexpr int WG_CHUNK = WG_KS * WG_ROW;  // one operand chunk: 16 KB
 constexpr int WG_STAGES = 3;
-constexpr int WG_WAVES = 8;
-constexpr int WG_LOADS = WG_CHUNK / 1024 / WG_WAVES;  // wave-wide 1 KB loads per wavefront, operand and stage: 2
+// Tile of TN x TN: 256 with eight wavefronts (2 x 4, each 128 x 64), or 128 with four (2 x 2, each 64 x 64)
+template <int TN>
+struct WgShape {
+  static constexpr int WAVES = TN / 32, W2 = TN / 64;      // wavefronts, of which W2 side by side along n2
+  static constexpr int N1B = TN / 64;                      // 32-column n1 blocks per wavefront (and two n2 blocks)
+  static constexpr int ROW = TN * 2;                       // bytes of one LDS row
+  static constexpr int CHUNK = WG_KS * ROW;                // one operand chunk: 16 or 8 KB
+  static constexpr int LOADS = CHUNK / 1024 / WAVES;       // wave-wide 1 KB loads per wavefront, operand and stage: 2
+  static_assert(LOADS == 2, "the waits of the K loop");
+};
 
 #if defined(__HIP_DEVICE_COMPILE__)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t wg_rsrc(const void* base, uint32_t bytes) {
@@ -57,8 +64,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wg_rsrc(const void* base, uint
 }
 #endif
 
-template <bool COLSUM, bool OUT_BF16>
-__global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
+template <bool COLSUM, bool OUT_BF16, int TN>
+__global__ __launch_bounds__(WgShape<TN>::WAVES * 64, 2) void grouped_wgrad_kernel(
     const uint16_t* __restrict__ a,       // [R, N1]
     const uint16_t* __restrict__ b,       // [R, N2]
     const int32_t* __restrict__ offsets,  // [E+1]
@@ -66,14 +73,16 @@ __global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
     float* __restrict__ a_colsum,         // COLSUM: [E, N1]
     int N1, int N2, int E, int BY, int BX) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int WG_WAVES = WgShape<TN>::WAVES, W2 = WgShape<TN>::W2, N1B = WgShape<TN>::N1B, WG_ROW = WgShape<TN>::ROW;
+  constexpr int WG_CHUNK = WgShape<TN>::CHUNK, WG_LOADS = WgShape<TN>::LOADS;
   // one array per stage: the compiler can then tell the stage being filled from the one being read
   __shared__ __attribute__((aligned(1024))) unsigned char s0[2 * WG_CHUNK];
   __shared__ __attribute__((aligned(1024))) unsigned char s1[2 * WG_CHUNK];
   __shared__ __attribute__((aligned(1024))) unsigned char s2[2 * WG_CHUNK];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int w1 = wave >> 2, w2 = wave & 3;  // this wavefront: n1 columns [128*w1, +128), n2 columns [64*w2, +64)
+  const int w1 = wave / W2, w2 = wave % W2;  // this wavefront: n1 columns [32*N1B*w1, +32*N1B), n2 columns [64*w2, +64)
   // workgroup -> (expert, n1 tile, n2 tile): see "Tile order" above
-  const int n1t = N1 / WG_N, n2t = N2 / WG_N;
+  const int n1t = N1 / TN, n2t = N2 / TN;
   const int nby = (n1t + BY - 1) / BY, nbx = (n2t + BX - 1) / BX;
   const int slot = blockIdx.x / 8;                            // position in this XCD's sequence of workgroups
   const int blk = (slot / (BY * BX)) * 8 + (int)(blockIdx.x % 8);  // blocks are dealt out to the XCDs in turn
@@ -82,15 +91,15 @@ __global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
   const int ty = ((blk / nbx) % nby) * BY + in_blk / BX, tx = (blk % nbx) * BX + in_blk % BX;
   if (e >= E || ty >= n1t || tx >= n2t) return;                // (wave-uniform: padding of the grid and of partial blocks)
   const int row0 = offsets[e], rows = offsets[e + 1] - row0;
-  const int t1 = ty * WG_N, t2 = tx * WG_N;
+  const int t1 = ty * TN, t2 = tx * TN;
   const size_t c_tile = ((size_t)e * N1 + t1) * N2 + t2;  // element offset of this tile in c
   const int KT = (rows + WG_KS - 1) / WG_KS;
 
-  // ---- direct-to-LDS loads: one instruction = 2 rows of a chunk; lane -> (row = lane / 32, physical slot =
-  // lane % 32), which holds the logical slot (lane % 32) ^ key(row), key = 4 * (row mod 4).  Wavefront w
-  // moves rows 2w, 2w+1 and 16 + 2w, 16 + 2w + 1.
-  const int ld_row = 2 * wave + (lane >> 5);
-  const int ld_slot = (lane & 31) ^ (4 * (ld_row & 3));
+  // ---- direct-to-LDS loads: one instruction = 2 (4) rows of a chunk, 32 (16) slots of 16 bytes each; a lane's physical
+  // slot holds the logical slot ^ key(row), key = 4 * (row mod 4).  The wavefronts together move 16 rows, twice per stage.
+  constexpr int SLOTS = WG_ROW / 16;
+  const int ld_row = (64 / SLOTS) * wave + lane / SLOTS;
+  const int ld_slot = (lane % SLOTS) ^ (4 * (ld_row & 3));
   const uint32_t a_pitch = (uint32_t)N1 * 2u, b_pitch = (uint32_t)N2 * 2u;
   const int a_voff = ld_row * (int)a_pitch + (t1 * 2 + ld_slot * 16);
   const int b_voff = ld_row * (int)b_pitch + (t2 * 2 + ld_slot * 16);
@@ -121,9 +130,9 @@ __global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
     const int col = col0 + fr_col;
     return (((col >> 3) ^ fr_key) << 4) + ((col >> 2) & 1) * 8;
   };
-  int n1_addr[4], n2_addr[2];
+  int n1_addr[N1B], n2_addr[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) n1_addr[i] = frag_addr(128 * w1 + 32 * i) + fr_row * WG_ROW;
+  for (int i = 0; i < N1B; ++i) n1_addr[i] = frag_addr(32 * N1B * w1 + 32 * i) + fr_row * WG_ROW;
 #pragma unroll
   for (int j = 0; j < 2; ++j) n2_addr[j] = frag_addr(64 * w2 + 32 * j) + fr_row * WG_ROW;
   auto read_frag = [&](const unsigned char* chunk, int addr, int ks) {
@@ -137,15 +146,15 @@ __global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
     return f;
   };
 
-  f32x16 acc[4][2];
+  f32x16 acc[N1B][2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < N1B; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  // column sums: wavefront (w1, w2) of the first n2 tile's workgroups sums the n1 block i = w2 of its 128 columns
+  // column sums: wavefront (w1, w2) of the first n2 tile's workgroups sums the n1 block i = w2 of its columns
   const bool do_colsum = COLSUM && tx == 0;
   f32x16 acc_sum;
   bf16x8 ones;
@@ -157,18 +166,20 @@ __global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
   auto compute = [&](const unsigned char* stage) {
 #pragma unroll
     for (int ks = 0; ks < WG_KS / 16; ++ks) {
-      bf16x8 f1[4], f2[2];
+      bf16x8 f1[N1B], f2[2];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) f1[i] = read_frag(stage, n1_addr[i], ks);
+      for (int i = 0; i < N1B; ++i) f1[i] = read_frag(stage, n1_addr[i], ks);
 #pragma unroll
       for (int j = 0; j < 2; ++j) f2[j] = read_frag(stage + WG_CHUNK, n2_addr[j], ks);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < N1B; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[j], f1[i], acc[i][j], 0, 0, 0);
       if constexpr (COLSUM) {
         if (do_colsum) {
-          const bf16x8 mine = w2 == 0 ? f1[0] : w2 == 1 ? f1[1] : w2 == 2 ? f1[2] : f1[3];
+          bf16x8 mine = f1[0];
+#pragma unroll
+          for (int i = 1; i < N1B; ++i) mine = w2 == i ? f1[i] : mine;
           acc_sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, mine, acc_sum, 0, 0, 0);
         }
       }
@@ -208,8 +219,8 @@ __global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
   // ---- epilogue: lane holds n1 = lane & 31 of each n1 block and n2 = 8*q + 4*(lane >> 5) + 0..3 of each n2 block
   const int o1 = lane & 31, o2 = 4 * (lane >> 5);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const size_t crow = c_tile + (size_t)(128 * w1 + 32 * i + o1) * N2 + 64 * w2;
+  for (int i = 0; i < N1B; ++i) {
+    const size_t crow = c_tile + (size_t)(32 * N1B * w1 + 32 * i + o1) * N2 + 64 * w2;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       if constexpr (OUT_BF16) {
@@ -236,8 +247,8 @@ __global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
     }
   }
   if constexpr (COLSUM) {
-    // every element of acc_sum in lane l (and l + 32) is the sum of column 128*w1 + 32*w2 + (l & 31)
-    if (do_colsum && lane < 32) a_colsum[(size_t)e * N1 + t1 + 128 * w1 + 32 * w2 + lane] = acc_sum[0];
+    // every element of acc_sum in lane l (and l + 32) is the sum of column 32*N1B*w1 + 32*w2 + (l & 31)
+    if (do_colsum && lane < 32) a_colsum[(size_t)e * N1 + t1 + 32 * N1B * w1 + 32 * w2 + lane] = acc_sum[0];
   }
 #endif
 }
@@ -245,22 +256,35 @@ __global__ __launch_bounds__(WG_WAVES * 64, 2) void grouped_wgrad_kernel(
 }  // namespace
 
 int32_t launch_wgrad_bf16(const uint16_t* a, const uint16_t* b, const int32_t* offsets, void* c, int c_dtype, float* a_colsum, int E,
-                          int N1, int N2, int64_t max_rows_per_expert, hipStream_t s) {
+                          int N1, int N2, int64_t max_rows_per_expert, int64_t rows_per_expert, hipStream_t s) {
   if (c_dtype != MOE_F32 && c_dtype != MOE_BF16) return fail(MOE_ERR_INVALID_ARG, "weight gradient: output type must be MOE_F32 or MOE_BF16");
   if (N1 % WG_N || N2 % WG_N) return fail(MOE_ERR_UNSUPPORTED, "weight gradient: N1=%d and N2=%d must be multiples of %d", N1, N2, WG_N);
   const int64_t widest = N1 > N2 ? N1 : N2;
   if ((max_rows_per_expert + WG_KS) * widest * 2 >= ((int64_t)1 << 31))
     return fail(MOE_ERR_UNSUPPORTED, "weight gradient: an expert's operand block exceeds 2 GiB");
-  const int n1t = N1 / WG_N, n2t = N2 / WG_N;
-  const int BX = n2t < 8 ? n2t : 8, BY = 32 / BX;  // (BX in 1..8, so BY * BX is 32, or 28, 30 for BX = 7, 5, 6, 3)
+  const bool h = c_dtype == MOE_BF16;
+  // Tile edge: 256 (the loop is bound by its transposing LDS reads, 3 per 2 MFMAs against 2 per 2 for 128) unless those tiles
+  // leave a quarter of their rounds of 256 CUs empty.  Measured on MI355X (us, 256 / 128): 8 experts of 2000 rows, 512 x 512
+  // (32 tiles) 51 / 22; 8 of 1200 rows, 768 x 3072 (288) 81 / 58; 16 of 1024, 1024 x 4096 (1024) 164 / 205; 16 of 256,
+  // 1024 x 4096 78 / 81.
+  const int64_t tiles = (int64_t)E * (N1 / 256) * (N2 / 256), rounds = (tiles + 255) / 256;
+  const int TN = tiles <= 512 && 4 * tiles < 3 * 256 * rounds ? 128 : 256;
+  const int n1t = N1 / TN, n2t = N2 / TN;
+  // Blocks of tiles: see "Tile order".  With few rows the product is bound by its stores, and a block as wide as the
+  // gradient's rows writes them whole (8 columns of tiles / 32: 64 experts of 128 rows, 2048 x 8192 bf16 984 / 788; 32 of 29 rows,
+  // 1536 x 2560 190 / 107; 16 of 256 rows, 1024 x 4096 78 / 81).
+  const int BXM = rows_per_expert <= 160 && TN == 256 ? 32 : 8;
+  const int BX = n2t < BXM ? n2t : BXM, BY = 32 / BX;
   const int64_t blocks = (int64_t)E * ((n1t + BY - 1) / BY) * ((n2t + BX - 1) / BX);
   const int64_t wgs = ((blocks + 7) / 8) * 8 * BY * BX;
   if (wgs > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "weight gradient: too many tiles");
-  const dim3 grid((unsigned)wgs), block(WG_WAVES * 64);
-  const bool h = c_dtype == MOE_BF16;
-  auto kern = a_colsum ? (h ? grouped_wgrad_kernel<true, true> : grouped_wgrad_kernel<true, false>)
-                       : (h ? grouped_wgrad_kernel<false, true> : grouped_wgrad_kernel<false, false>);
-  hipLaunchKernelGGL(kern, grid, block, 0, s, a, b, offsets, c, a_colsum, N1, N2, E, BY, BX);
+  auto pick = [&](auto tn) {
+    constexpr int N = decltype(tn)::value;
+    return a_colsum ? (h ? grouped_wgrad_kernel<true, true, N> : grouped_wgrad_kernel<true, false, N>)
+                    : (h ? grouped_wgrad_kernel<false, true, N> : grouped_wgrad_kernel<false, false, N>);
+  };
+  auto kern = TN == 128 ? pick(std::integral_constant<int, 128>{}) : pick(std::integral_constant<int, 256>{});
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(TN * 2), 0, s, a, b, offsets, c, a_colsum, N1, N2, E, BY, BX);
   return check_hip(hipGetLastError(), "weight gradient launch");
 }
 
@@ -275,5 +299,5 @@ extern "C" int32_t moe_expert_wgrad(const void* a, const void* b, const int32_t*
   if (E < 1 || E > MOE_MAX_EXPERTS || N1 < 1 || N2 < 1 || max_rows_per_expert < 0)
     return fail(MOE_ERR_INVALID_ARG, "moe_expert_wgrad: bad shape");
   return launch_wgrad_bf16((const uint16_t*)a, (const uint16_t*)b, expert_offsets, c, c_dtype, a_column_sums, E, N1, N2,
-                           max_rows_per_expert, (hipStream_t)stream);
+                           max_rows_per_expert, max_rows_per_expert, (hipStream_t)stream);
 }
