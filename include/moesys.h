@@ -153,10 +153,13 @@ int32_t moe_workspace_layout(const moe_config* cfg, moe_ws_layout* out);
  * results, only the kernels that compute them differ.  Set them while no call of the
  * library is running on another thread.
  *   MOE_TUNE_GEMM_TILE_ROWS    token rows per tile of the bf16 grouped GEMM: 256 or 320;
- *                              0 (default) = chosen per call from the expected rows per expert
- *   MOE_TUNE_FEW_TOKEN_KERNELS 1 (default): steps of at most 16 tokens / assignments use the
- *                              matrix-vector expert kernels and the one-workgroup-per-token
- *                              gate; 0: the general kernels at every size
+ *                              0 (default) = chosen per call from the expected rows per expert;
+ *                              a value given here or for MOE_TUNE_GEMM_MFMA also keeps the
+ *                              weight-streaming kernels out
+ *   MOE_TUNE_FEW_TOKEN_KERNELS 1 (default): steps of few tokens use the matrix-vector (at most 8
+ *                              assignments) and weight-streaming expert kernels and the
+ *                              one-workgroup-per-token gate (at most 16 tokens); 0: the general
+ *                              kernels at every size
  *   MOE_TUNE_GATE_TOKENS       tokens per workgroup of the gate on a packed router: 32, 64 or 128 (where
  *                              the expert count allows; otherwise the next smaller); 0 (default) = by T
  *   MOE_TUNE_GEMM_MFMA         matrix instruction of the 256-row grouped GEMM kernels: 16 (16x16x32) or 32

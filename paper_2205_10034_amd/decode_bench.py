@@ -61,7 +61,7 @@ def main():
             "workload": f"ring layer, resident: T={T} d_model={d} d_ff={f} E={E} top-{wl.k}",
             "layer_us": ms * 1e3, "tokens_per_s": T / (ms * 1e-3), "experts_activated": active,
             "weights_streamed_mib": wbytes / 2 ** 20, "weights_tb_per_s": wbytes / (ms * 1e-3) / 1e12,
-            "matrix_vector_kernels": wl.k * T <= 16 and not args.general_kernels,
+            "matrix_vector_kernels": wl.k * T <= 8 and not args.general_kernels,
         }), flush=True)
 
 
