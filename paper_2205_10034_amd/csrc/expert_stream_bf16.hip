@@ -5,7 +5,7 @@
 //
 // The product's time is the time to stream the activated experts' weights once.  The 256 x 256 tiles of the grouped GEMM
 // have one 64 KB stage in flight per CU, half of it rows that are not there, and their number is too small for the chip
-// when the feature count is: 8 experts x 4096 features are 128 tiles for 256 CUs.  Here a workgroup owns 64 or 128 weight
+// when the feature count is: 8 experts x 4096 features are 128 tiles for 256 CUs.  Here a workgroup owns 64 to 256 weight
 // rows and 32 to 192 rows of one expert and keeps all but one of its three to five LDS stages (64 values of the
 // contraction index each) requested ahead: weights and rows go from global memory straight into LDS, swizzled like the
 // grouped GEMM's, one barrier per stage.  A wavefront multiplies blocks of 16 weight rows by blocks of 16 rows
@@ -268,7 +268,11 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 // handles any routing); none: the grouped GEMM.  Measured on MI355X (us, grouped GEMM / here), rows = rows per expert:
 //  - up to 24 rows the time is the weights': 64x32, three workgroups per CU.  SwiGLU d 4096, f 14336, 8 experts, 24 rows:
 //    395 / 335 (5.6 TB/s) and, with 128 big tiles for 256 CUs, 337 / 169;
-//  - up to 36: 128x64.  64 experts, d 2048, f 8192, 32 rows: 441 / 413 and 424 / 383;
+//  - up to 44 rows 256x64 and up to 96 rows 256x128 where such tiles come in nearly whole rounds of the chip (one workgroup
+//    per CU, twice the weights per stage).  64 experts, d 2048, f 8192, 32 rows: 441 / 382 and 424 / 375 (128x64: 416 and
+//    384); 64 rows 448 / 414 and 435 / 385; 94 rows 454 / 438 and 442 / 402; 128 SwiGLU experts, 1600 x 832, 38 rows 173 / 148
+//    and 99 / 83; 8 of 4096 x 14336, 40 rows, would be 3.5 rounds: 128x128 348, 256x128 373;
+//  - up to 36 otherwise: 128x64;
 //  - few tiles of any kind: 64x64.  4 experts, 150 rows, d 320, f 1088: 12.8 / 9.7 and 17.4 / 10.0;
 //  - up to 96 rows with long rows of weights or few big tiles: 128x128.  64 experts, f 8192 -> d 2048, 47 rows 433 / 386,
 //    94 rows 442 / 417, but 107 rows (some experts over 128) 450 / 494; with 2048-long rows 94 rows 453 / 522;
@@ -278,7 +282,7 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //  - three quarters of a round of big tiles against at most two rounds of 128x128 (with a whole round of them the big tiles
 //    win: 16 experts, d 1024 -> f 4096, 128 rows 38 / 56).  16 experts, f 8704 -> d 640, 590 rows (144) 219 / 198 and, with
 //    skewed routing, 239 / 98; f 3072 -> d 768 73 / 64; but 8 experts, f 4096 -> d 1024, 1500 rows (three rounds) 107 / 142.
-enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192 };
+enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128 };
 int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
   // (the switches ask for the grouped GEMM's kernels)
@@ -294,9 +298,17 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   };
   const int64_t big = tiles(256, 256);
   const bool wide = N >= (swiglu ? 64 : 128);
+  // share of its rounds of 256 workgroups (one per CU) that a shape of 256 weight rows fills
+  auto fill = [&](int tm) {
+    const int64_t t = N >= (swiglu ? 128 : 256) ? tiles(256, tm) : 0;
+    return t < 256 ? 0.0 : (double)t / (double)((t + 255) / 256 * 256);
+  };
+  if (rows <= 44 && fill(64) >= 0.95) return STREAM_256x64;
   if (wide && rows <= 36) return STREAM_128x64;
   if (tiles(128, 192) < 128 && tiles(64, 64) <= 512) return STREAM_64x64;
-  if (wide && rows <= 96 && (K >= 4096 || big < 256)) return STREAM_128x128;
+  const bool long_rows = K >= 4096 || big < 256;
+  if (rows <= 96 && fill(128) >= (long_rows ? 0.95 : 0.85)) return STREAM_256x128;
+  if (wide && rows <= 96 && long_rows) return STREAM_128x128;
   if (wide && (big <= 96 || (big <= 128 && rows <= 152))) return STREAM_128x192;
   if (wide && big > 128 && big <= 192 && tiles(128, 128) <= 512) return STREAM_128x128;
   return STREAM_NONE;
@@ -313,6 +325,8 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
     case STREAM_128x64: MOE_STREAM(4, 2, 2, 2, 5);
     case STREAM_128x128: MOE_STREAM(4, 2, 2, 4, 4);
     case STREAM_128x192: MOE_STREAM(4, 2, 2, 6, 4);
+    case STREAM_256x64: MOE_STREAM(4, 2, 4, 2, 4);
+    case STREAM_256x128: MOE_STREAM(4, 2, 4, 4, 3);
   }
 #undef MOE_STREAM
   return fail(MOE_ERR_UNSUPPORTED, "expert stream: shape outside its range");

@@ -49,7 +49,8 @@ def ffn_case(act, rows, T, d, f, seed, bias=True):
     (36, 24, 192, 320), (30, 24, 512, 448),                              # 128 x 64
     (40, 16, 320, 192), (150, 4, 320, 1088), (500, 3, 64, 128),          # 64 x 64: few tiles
     (60, 32, 576, 576), (90, 40, 512, 832),                              # 128 x 128
-    (120, 32, 512, 576), (250, 16, 704, 1216)])                          # 128 x 192
+    (120, 32, 512, 576), (250, 16, 704, 1216),                           # 128 x 192
+    (40, 130, 512, 576), (80, 130, 512, 448)])                           # 256 x 64, 256 x 128
 def test_stream_shapes(act, mean, E, d, f):
     print(act, mean, E, d, f, flush=True)
     rows = [RAGGED[(3 * i + E) % len(RAGGED)] for i in range(E)]
