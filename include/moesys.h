@@ -157,7 +157,8 @@ int32_t moe_workspace_layout(const moe_config* cfg, moe_ws_layout* out);
  *                              a value given here or for MOE_TUNE_GEMM_MFMA also keeps the
  *                              weight-streaming kernels out
  *   MOE_TUNE_FEW_TOKEN_KERNELS 1 (default): steps of few tokens use the matrix-vector (at most 8
- *                              assignments) and weight-streaming expert kernels and the
+ *                              assignments; 16 where the weight-streaming kernels do not serve)
+ *                              and weight-streaming expert kernels and the
  *                              one-workgroup-per-token gate (at most 16 tokens); 0: the general
  *                              kernels at every size
  *   MOE_TUNE_GATE_TOKENS       tokens per workgroup of the gate on a packed router: 32, 64 or 128 (where

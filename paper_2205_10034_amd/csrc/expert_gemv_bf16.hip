@@ -1,5 +1,6 @@
 // Expert FFN products for steps of very few tokens (k*T <= 8 assignments in all, so no expert has more rows
-// than that): the single-request end of the paper's inference scenario (Section 3.3, batch size 1).
+// than that; up to 16 where the weight-streaming kernels do not serve): the single-request end of the paper's
+// inference scenario (Section 3.3, batch size 1).
 //
 //   out[r, n] = epilogue( sum_k act[r, k] * W_e[n, k] )      for the rows r of every expert e that has any
 //
@@ -10,17 +11,20 @@
 // wave-wide contiguous 1 KB loads, FPW of them in flight per wavefront and K block), keeps the partial sums
 // of its weight rows x the expert's rows in registers, and adds them across the lanes at the end (a fixed
 // butterfly: results do not depend on scheduling).  Workgroup (bx, r0) serves the expert whose FIRST row is
-// dispatched row r0 and exits if there is none, so the grid needs no list of the activated experts.  Beyond 8
-// assignments the FPW x ROWS partial sums leave room for 4 weight rows only, and the weight-streaming MFMA kernels
-// (expert_stream_bf16.hip) are faster: 16 assignments over 64 experts of 2048 x 8192 118 + 111 us here, 99 + 95 there; with 8
-// assignments 56 + 52 here, 58 + 57 there.
+// dispatched row r0 and exits if there is none, so the grid needs no list of the activated experts.  Two shapes
+// (the FPW x ROWS partial sums must fit the registers): 8 weight rows x up to 8 rows, 4 x up to 16.  With 9 to 16
+// assignments the weight-streaming MFMA kernels (expert_stream_bf16.hip) are faster: 16 assignments over 64 experts of
+// 2048 x 8192 118 + 111 us here, 99 + 95 there; with 8 assignments 56 + 52 here, 58 + 57 there.  The 4 x 16 shape serves
+// what those kernels leave: contraction lengths beyond their 32-bit offsets, and calls whose tuning keys keep them out.
 #include "moesys_internal.h"
 
 namespace moesys {
+
+bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu);
+
 namespace {
 
-constexpr int GV_MAX_ROWS = 8;  // rows of one expert, at most (= assignments of the whole step)
-constexpr int GV_FPW = 8;       // weight rows per wavefront
+constexpr int GV_MAX_ROWS = 16;  // rows of one expert, at most (= assignments of the whole step)
 constexpr int GV_WAVES = 4;
 
 enum GvEpi { GV_GELU = 0, GV_SWIGLU = 1, GV_BIAS = 2, GV_COMBINE = 3 };
@@ -41,7 +45,7 @@ __device__ __forceinline__ float gelu_exact(float u) { return 0.5f * u * erfcf(-
 // GATHER: act is x[T, K] and row r reads token row_map[r] mod T.
 // KSPLIT: the four wavefronts of a workgroup share one set of GV_FPW weight rows and split the contraction index
 // (their sums meet in LDS, in wavefront order): four times the workgroups, for long rows and few experts.
-template <int EPI, bool GATHER, bool KSPLIT>
+template <int EPI, bool GATHER, int GV_ROWS, int GV_FPW, bool KSPLIT>
 __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
     const uint16_t* __restrict__ act, const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb,
     const uint16_t* __restrict__ bias, const int32_t* __restrict__ offsets, uint16_t* out,
@@ -49,7 +53,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
     const int64_t* __restrict__ eoff, int T, int E, int N, int K, int reps) {
   constexpr int OUTF = EPI == GV_SWIGLU ? GV_FPW / 2 : GV_FPW;  // output features per wavefront
   __shared__ int s_e;
-  __shared__ float red[KSPLIT ? GV_WAVES : 1][GV_MAX_ROWS][GV_FPW];
+  __shared__ float red[KSPLIT ? GV_WAVES : 1][GV_ROWS][GV_FPW];
   const int r0 = blockIdx.y;
   if (threadIdx.x == 0) s_e = -1;
   __syncthreads();
@@ -58,13 +62,13 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
   __syncthreads();
   const int e = s_e;
   if (e < 0) return;
-  const int rows = min(offsets[e + 1] - r0, GV_MAX_ROWS);
+  const int rows = min(offsets[e + 1] - r0, GV_ROWS);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t wbase = eoff ? eoff[e] : (int64_t)e * N * K;
-  const uint16_t* xrow[GV_MAX_ROWS];
-  int token[GV_MAX_ROWS];
+  const uint16_t* xrow[GV_ROWS];
+  int token[GV_ROWS];
 #pragma unroll
-  for (int r = 0; r < GV_MAX_ROWS; ++r) {
+  for (int r = 0; r < GV_ROWS; ++r) {
     const int rr = r0 + min(r, rows - 1);  // (rows past the expert's last re-read it; their sums are not used)
     int src = rr;
     token[r] = 0;
@@ -88,21 +92,21 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
       if (EPI == GV_SWIGLU) wrow[j] = (j < OUTF ? wa : wb) + wbase + (int64_t)(n0 + j % OUTF) * K;
       else wrow[j] = wa + wbase + (int64_t)(n0 + j) * K;
     }
-    float acc[GV_FPW][GV_MAX_ROWS];
+    float acc[GV_FPW][GV_ROWS];
   #pragma unroll
     for (int j = 0; j < GV_FPW; ++j)
   #pragma unroll
-      for (int r = 0; r < GV_MAX_ROWS; ++r) acc[j][r] = 0.f;
+      for (int r = 0; r < GV_ROWS; ++r) acc[j][r] = 0.f;
 
     for (int kb = (KSPLIT ? (int)threadIdx.x : lane) * 8; kb < K; kb += (KSPLIT ? GV_WAVES : 1) * 64 * 8) {
-      uint4 wv[GV_FPW], xv[GV_MAX_ROWS];
+      uint4 wv[GV_FPW], xv[GV_ROWS];
   #pragma unroll
       for (int j = 0; j < GV_FPW; ++j) wv[j] = *reinterpret_cast<const uint4*>(wrow[j] + kb);
   #pragma unroll
-      for (int r = 0; r < GV_MAX_ROWS; ++r)
+      for (int r = 0; r < GV_ROWS; ++r)
         if (r < rows) xv[r] = *reinterpret_cast<const uint4*>(xrow[r] + kb);
   #pragma unroll
-      for (int r = 0; r < GV_MAX_ROWS; ++r) {
+      for (int r = 0; r < GV_ROWS; ++r) {
         if (r < rows) {  // (wave-uniform)
           const float x0 = lo16(xv[r].x), x1 = hi16(xv[r].x), x2 = lo16(xv[r].y), x3 = hi16(xv[r].y);
           const float x4 = lo16(xv[r].z), x5 = hi16(xv[r].z), x6 = lo16(xv[r].w), x7 = hi16(xv[r].w);
@@ -121,7 +125,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
 
     // sums over the lanes; afterwards every lane holds every total
   #pragma unroll
-    for (int r = 0; r < GV_MAX_ROWS; ++r) {
+    for (int r = 0; r < GV_ROWS; ++r) {
       if (r < rows) {
   #pragma unroll
         for (int j = 0; j < GV_FPW; ++j) {
@@ -136,7 +140,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
     if constexpr (KSPLIT) {  // the wavefronts' sums meet: lane j < GV_FPW carries weight row j
       if (rep) __syncthreads();  // (the previous block's sums have been read)
 #pragma unroll
-      for (int r = 0; r < GV_MAX_ROWS; ++r) {
+      for (int r = 0; r < GV_ROWS; ++r) {
         if (r < rows && lane < GV_FPW) {
           float v = acc[0][r];
 #pragma unroll
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
       __syncthreads();
       if (wave == 0 && lane < GV_FPW) {
 #pragma unroll
-        for (int r = 0; r < GV_MAX_ROWS; ++r) {
+        for (int r = 0; r < GV_ROWS; ++r) {
           if (r < rows) {
             float v = red[0][r][lane];
 #pragma unroll
@@ -158,7 +162,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
       }
       __syncthreads();
 #pragma unroll
-      for (int r = 0; r < GV_MAX_ROWS; ++r)
+      for (int r = 0; r < GV_ROWS; ++r)
         if (r < rows)
 #pragma unroll
           for (int j = 0; j < GV_FPW; ++j) acc[j][r] = red[0][r][j];  // every lane holds every total again
@@ -169,7 +173,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
       float b = 0.f;
       if (EPI != GV_SWIGLU && bias) b = lo16((uint32_t)bias[(eoff ? eoff[e] : (int64_t)e * N) + n]);  // (eoff: as for the weights)
   #pragma unroll
-      for (int r = 0; r < GV_MAX_ROWS; ++r) {
+      for (int r = 0; r < GV_ROWS; ++r) {
         if (r < rows) {
           float v = acc[0][r], u = 0.f;
   #pragma unroll
@@ -268,12 +272,11 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_combine1_kernel(
   if (wave == 0 && lane < C1_FPW) out[n0 + lane] = bf16_of(o);
 }
 
-template <int EPI>
-int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
+template <int EPI, int ROWS, int FPW>
+int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                      const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
                      const int64_t* eoff, int N, int K, bool gather, hipStream_t s) {
-  if (cfg->k * cfg->T == 0) return MOE_OK;
-  constexpr int OUTF = EPI == GV_SWIGLU ? GV_FPW / 2 : GV_FPW;
+  constexpr int OUTF = EPI == GV_SWIGLU ? FPW / 2 : FPW;
   // About 256 KB of weights per workgroup, in whole blocks of output features, as long as that leaves about two
   // workgroups per CU (the experts with rows are at most k*T).  Long rows and too few workgroups even so: the
   // wavefronts of a workgroup split the contraction index instead of the output features.
@@ -281,12 +284,12 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
   int blocks = N / (GV_WAVES * OUTF);
   const bool ksplit = K >= 4096 && (int64_t)blocks * A < 512;
   if (ksplit) blocks *= GV_WAVES;
-  int reps = ksplit ? 1 : (int)((256 * 1024) / ((int64_t)GV_WAVES * GV_FPW * K * 2));
+  int reps = ksplit ? 1 : (int)((256 * 1024) / ((int64_t)GV_WAVES * FPW * K * 2));
   reps = reps < 1 ? 1 : reps > 8 ? 8 : reps;
   while (reps > 1 && (blocks % reps || (int64_t)(blocks / reps) * A < 512)) --reps;
   const dim3 grid(blocks / reps, A), block(GV_WAVES * 64);
 #define MOESYS_GEMV(G, S)                                                                                                  \
-  hipLaunchKernelGGL((expert_gemv_kernel<EPI, G, S>), grid, block, 0, s, act, wa, wb, bias, offsets, out, row_map, \
+  hipLaunchKernelGGL((expert_gemv_kernel<EPI, G, ROWS, FPW, S>), grid, block, 0, s, act, wa, wb, bias, offsets, out, row_map, \
                      gate_w, residual, eoff, cfg->T, cfg->E, N, K, reps)
   if (gather) { if (ksplit) MOESYS_GEMV(true, true); else MOESYS_GEMV(true, false); }
   else { if (ksplit) MOESYS_GEMV(false, true); else MOESYS_GEMV(false, false); }
@@ -294,12 +297,25 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
   return check_hip(hipGetLastError(), "expert GEMV launch");
 }
 
+template <int EPI>
+int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
+               const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
+               const int64_t* eoff, int N, int K, bool gather, hipStream_t s) {
+  const int A = cfg->k * cfg->T;
+  if (A == 0) return MOE_OK;
+  if (A <= 8) return launch_shape<EPI, 8, 8>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, eoff, N, K, gather, s);
+  return launch_shape<EPI, 16, 4>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, eoff, N, K, gather, s);
+}
+
 }  // namespace
 
 // Whether the few-row path serves this product: so few assignments that no expert exceeds GV_MAX_ROWS rows,
 // whole workgroups of output features, 16-byte chunks of the contraction index.
 bool expert_gemv_applies(const moe_config* cfg, int N, int K) {
-  return tuning(MOE_TUNE_FEW_TOKEN_KERNELS) != 0 && cfg->dtype == MOE_BF16 && (int64_t)cfg->k * cfg->T <= GV_MAX_ROWS && N % (GV_WAVES * 8) == 0 && K % 8 == 0;
+  const int64_t A = (int64_t)cfg->k * cfg->T;
+  if (!tuning(MOE_TUNE_FEW_TOKEN_KERNELS) || cfg->dtype != MOE_BF16 || N % (GV_WAVES * 8) || K % 8) return false;
+  // (with so few rows per expert the choice of the weight-streaming kernels does not depend on the activation)
+  return A <= 8 || (A <= GV_MAX_ROWS && !expert_stream_applies(cfg, N, K, false));
 }
 
 // Second product + combine of a one-token step (k >= 2); see the kernel.  residual nullable; out may be residual.

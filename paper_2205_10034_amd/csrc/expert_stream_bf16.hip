@@ -285,6 +285,9 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128 };
 int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
+  // Buffer sizes and offsets of a tile are 32-bit.  The line is that of the grouped GEMM's largest row tile, so that what
+  // that kernel refuses stays refused whichever of the two would serve the row count.
+  if ((int64_t)320 * K * 2 >= ((int64_t)1 << 31)) return STREAM_NONE;
   // (the switches ask for the grouped GEMM's kernels)
   if (!tuning(MOE_TUNE_FEW_TOKEN_KERNELS) || tuning(MOE_TUNE_GEMM_TILE_ROWS) || tuning(MOE_TUNE_GEMM_MFMA)) return STREAM_NONE;
   int64_t rows = ((int64_t)cfg->k * cfg->T + cfg->E - 1) / cfg->E;
@@ -335,6 +338,12 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
 }  // namespace
 
 bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu) { return pick_stream(cfg, N, K, swiglu) != STREAM_NONE; }
+
+// name of the shape (weight rows x rows), for tests
+const char* expert_stream_shape(const moe_config* cfg, int N, int K, bool swiglu) {
+  static const char* const names[] = {"", "stream 64x32", "stream 64x64", "stream 128x64", "stream 128x128", "stream 128x192", "stream 256x64", "stream 256x128"};
+  return names[pick_stream(cfg, N, K, swiglu)];
+}
 
 // epi: 0 GELU (+bias), 1 SwiGLU (wa = gate, wb = up), 2 plain (+bias), 3 combine for k = 1 (row_map = row_to_assign,
 // gate_w, residual).  row_map with epi 0/1: gather the rows from x[T, K].  eoff: per-expert element offsets or NULL.

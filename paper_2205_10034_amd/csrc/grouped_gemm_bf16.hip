@@ -1016,6 +1016,9 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
 #endif
 }
 
+// the byte offsets inside a tile of `rows` rows are 32-bit
+bool tile_offsets_fit(int rows, int K) { return (int64_t)rows * K * 2 < ((int64_t)1 << 31); }
+
 template <int TOK, int FEAT, int WT, int WF, int KS, int WPE, int EPI, bool MI16_ = false>
 int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb,
                const uint16_t* bias, const int32_t* offsets, uint16_t* out, const int32_t* row_map,
@@ -1024,7 +1027,7 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
   constexpr int OUT_FEAT = swiglu_tile(EPI) ? FEAT / 2 : FEAT;
   if (N < OUT_FEAT || N % (TOK <= 256 ? 64 : OUT_FEAT)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: N=%d does not fit tiles of %d features", N, OUT_FEAT);
   if (K % KS) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: K=%d is not a multiple of %d", K, KS);
-  if ((int64_t)TOK * K * 2 >= ((int64_t)1 << 31)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: K=%d too large", K);
+  if (!tile_offsets_fit(TOK, K)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: K=%d too large", K);
   const int64_t rmax = max_rows(cfg);
   if (rmax == 0) return MOE_OK;
   int64_t mt = rmax / TOK + cfg->E;  // every expert may end in one partial tile
@@ -1111,18 +1114,25 @@ bool prefer_mi16(const moe_config* cfg) {
   return rows >= 192;
 }
 
-// One grouped GEMM.  256x256x64 tiles (8 wavefronts, the highest arithmetic intensity that fits the
-// 160 KB LDS) whenever there are that many features; smaller feature counts use narrow tiles.  (Narrow tiles also served
-// feature counts that are no multiple of 256: at 26103 tokens, top-6 of 64 experts, d_ff 2560, d_model 1344 the second
-// GEMM took 2975 us with 128x64 tiles, 1035 us with a last tile that overlaps the one before.)
+// Rows of the tile that serves a product of N features: 256x256x64 tiles (8 wavefronts, the highest arithmetic intensity
+// that fits the 160 KB LDS; 320 rows by pick_tile_rows) whenever there are that many features (BF); smaller feature counts
+// use narrow tiles (128 rows).  (Narrow tiles also served feature counts that are no multiple of 256: at 26103 tokens, top-6
+// of 64 experts, d_ff 2560, d_model 1344 the second GEMM took 2975 us with 128x64 tiles, 1035 us with a last tile that
+// overlaps the one before.  They still do where the contraction index is too long for the offsets of a 256-row tile.)
+int grouped_tile_rows(const moe_config* cfg, int N, int K, int BF) {
+  if (N < BF || (N % BF && !tile_offsets_fit(256, K))) return 128;
+  return N % BF == 0 ? pick_tile_rows(cfg, N / BF) : 256;
+}
+
 template <int EPI>
 int32_t gemm_any(const moe_config* cfg, const uint16_t* a, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                  const int32_t* offsets, uint16_t* o, const int32_t* row_map, int32_t* tile_ctr, int32_t* clear_ctr, int N,
                  int K, hipStream_t s, const int64_t* eoff, const float* gate_w = nullptr,
                  const uint16_t* residual = nullptr) {
   constexpr int BF = swiglu_tile(EPI) ? 128 : 256;  // output features of the big tile
-  if (N >= BF) {
-    if (N % BF == 0 && pick_tile_rows(cfg, N / BF) == 320)
+  const int rows = grouped_tile_rows(cfg, N, K, BF);
+  if (rows != 128) {
+    if (rows == 320)
       return launch<320, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
     if (use_mi16(256, 2, EPI) && prefer_mi16(cfg))
       return launch<256, 256, 2, 4, 64, 2, EPI, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
@@ -1143,6 +1153,7 @@ int32_t launch_expert_gemv_bf16(int epi, const moe_config* cfg, const void* act,
                                 const void* residual, const int64_t* eoff, int N, int K, hipStream_t s);
 // steps of few rows per expert take the weight-streaming kernels
 bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu);
+const char* expert_stream_shape(const moe_config* cfg, int N, int K, bool swiglu);
 int32_t launch_expert_stream_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
                                   const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
                                   const void* residual, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s);
@@ -1245,6 +1256,20 @@ bool gemm1_can_gather(const moe_config* cfg) {
 }
 
 }  // namespace moesys
+
+// Which kernel serves the layer's first (second = 0) or second product: for the tests of the rules above, which could
+// otherwise move a case off the kernel it is meant for without a sign.  Host only; not part of the interface in moesys.h.
+extern "C" const char* moe_test_product_kernel(const moe_config* cfg, int32_t second) {
+  using namespace moesys;
+  if (moe_config_check(cfg) != MOE_OK || cfg->dtype != MOE_BF16) return "";
+  const int N = second ? cfg->d_model : cfg->d_ff, K = second ? cfg->d_ff : cfg->d_model;
+  const bool swiglu = !second && cfg->act == MOE_ACT_SWIGLU;
+  if (expert_gemv_applies(cfg, N, K)) return (int64_t)cfg->k * cfg->T <= 8 ? "gemv 8" : "gemv 16";
+  if (expert_stream_applies(cfg, N, K, swiglu)) return expert_stream_shape(cfg, N, K, swiglu);
+  const int rows = grouped_tile_rows(cfg, N, K, swiglu ? 128 : 256);
+  if (!tile_offsets_fit(rows, K)) return "refused";
+  return rows == 320 ? "grouped 320" : rows == 256 ? "grouped 256" : "grouped 128";
+}
 
 #ifdef MOESYS_GEMM_PROFILE
 // buf: device, 2 * 256 * 8 * 16 uint64, zeroed by the caller; NULL switches the recording off.

@@ -115,3 +115,41 @@ def test_workspace_counters_between_kernels():
         assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
         ref = O.layer_forward(L["x"], L, E=wl.E, k=2, capacity_factor=0.0, renormalize=True, act="gelu")
         assert rel_fro(to_np(outs[0]), ref["out"]) < TOL
+
+
+def test_sixteen_assignments_over_a_contraction_beyond_32_bit_tiles():
+    """64 weight rows of 2^25 bf16 values are 4 GiB, past what the weight-streaming tiles can address: the matrix-vector
+    kernel serves the second product.  Against the same product in float32 pieces (bar as above)."""
+    T, d, f, P = 12, 64, 1 << 25, 1 << 22
+    print(T, d, f, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    w1 = torch.empty(1, f, d, dtype=torch.bfloat16, device="cuda").normal_(0, d ** -0.5, generator=g)
+    w2 = torch.empty(1, d, f, dtype=torch.bfloat16, device="cuda").normal_(0, f ** -0.5, generator=g)
+    x = torch.randn(T, d, generator=g, device="cuda").bfloat16()
+    cfg = M.MoEConfig(T=T, d_model=d, d_ff=f, E=1, k=1)
+    W = M.Weights({"w1": w1, "w2": w2, "w_router": torch.zeros(d, 1, device="cuda")})
+    y = torch.full_like(x, float("nan"))
+    M.moe_expert_ffn(cfg, W, x, torch.tensor([0, T], dtype=torch.int32, device="cuda"), y, alloc_ws(cfg, 2))
+    want = torch.zeros(T, d, dtype=torch.float64, device="cuda")
+    for i in range(0, f, P):
+        h = torch.nn.functional.gelu(x.float() @ w1[0, i:i + P].float().t()).bfloat16().float()
+        want += (h @ w2[0, :, i:i + P].float().t()).double()
+    err = float((y.double() - want).norm() / want.norm())
+    print("rel fro", err, flush=True)
+    assert err < TOL
+
+
+@pytest.mark.parametrize("name,kw", [
+    ("ring", dict(T=8, d_model=256, d_ff=512, E=64)), ("gpt", dict(T=6, E=2, d_model=256, d_ff=4096, capacity_factor=0.0)),
+    ("skew", dict(T=13, d_model=256, d_ff=512)), ("large", dict(T=7, d_model=512, d_ff=1024, E=4))], ids=str)
+def test_matrix_vector_kernel_of_nine_to_sixteen_assignments(name, kw):
+    """Its 4 x 16 shape, with the weight-streaming kernels kept out by a tuning key."""
+    wl = WORKLOADS[name].scaled(**kw)
+    print(wl, flush=True)
+    L = make_layer(wl, with_bias=True)
+    ref = O.layer_forward(L["x"], L, E=wl.E, k=wl.k, capacity_factor=wl.capacity_factor, renormalize=wl.renormalize, act=wl.act)
+    M.moe_set_tuning(M.MOE_TUNE_GEMM_TILE_ROWS, 256)
+    try:
+        assert rel_fro(run_layer(M.MoEConfig.from_workload(wl), upload_weights(L, "bf16"), to_dev(L["x"], "bf16"))["out"], ref["out"]) < TOL
+    finally:
+        M.moe_set_tuning(M.MOE_TUNE_GEMM_TILE_ROWS, 0)

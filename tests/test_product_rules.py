@@ -1,0 +1,75 @@
+"""The rules that choose the kernel of an expert product, on the host: what each range of sizes is served by, and that long
+contraction indices reach only kernels whose offsets hold them."""
+import ctypes as C
+
+import pytest
+
+import paper_2205_10034_amd as M
+
+
+def product_kernel(cfg, second):
+    f = M.lib().moe_test_product_kernel
+    f.restype, f.argtypes = C.c_char_p, [C.c_void_p, C.c_int32]
+    c = cfg.c()
+    return f(C.byref(c), second).decode()
+
+
+def second_product(N, K, A, E=1, k=1):
+    return product_kernel(M.MoEConfig(T=A // k, d_model=N, d_ff=K, E=E, k=k), 1)
+
+
+LONG = 3355456          # first multiple of 64 whose 320 rows of bf16 reach 2 GiB
+L22, L23, L24, L25 = (1 << n for n in (22, 23, 24, 25))
+
+
+@pytest.mark.parametrize("N", [64, 320, 512])
+def test_few_assignments_take_any_contraction_length(N):
+    """Up to 16 assignments the matrix-vector kernels (64-bit offsets) serve what the weight-streaming ones cannot."""
+    for K in (64, 4096, LONG - 64, LONG, L22, L24, L25, 1 << 27):
+        for A in (1, 8):
+            assert second_product(N, K, A) == "gemv 8"
+        for A in (9, 12, 16):
+            assert second_product(N, K, A) == ("stream 64x32" if K < LONG else "gemv 16")
+            assert second_product(N, K, A, E=8, k=2 if A % 2 == 0 else 1) == ("stream 64x32" if K < LONG else "gemv 16")
+
+
+@pytest.mark.parametrize("A", [17, 30, 200, 700, 3000])
+def test_long_contractions_beyond_sixteen_assignments(A):
+    """256-row tiles hold up to 2^22 values of the contraction index, narrow ones (feature counts that are no multiple of
+    256, or below) up to 2^23; beyond, the call is refused."""
+    for K in (LONG, L22 - 64, L22, L22 + 64, L23 - 64, L23, L24, L25):
+        assert second_product(64, K, A) == ("grouped 128" if K < L23 else "refused")
+        assert second_product(320, K, A) == ("grouped 256" if K < L22 else "grouped 128" if K < L23 else "refused")
+        assert second_product(512, K, A) in (("grouped 256", "refused") if K < L22 else ("refused",))
+
+
+def test_no_kernel_is_chosen_beyond_its_offsets():
+    rows = {"stream 64x32": 64, "stream 64x64": 64, "stream 128x64": 128, "stream 128x128": 128, "stream 128x192": 192,
+            "stream 256x64": 256, "stream 256x128": 256, "grouped 128": 128, "grouped 256": 256, "grouped 320": 320}
+    seen = set()
+    for act in ("gelu", "swiglu"):
+        for E, k in ((1, 1), (3, 1), (8, 2), (64, 2), (128, 6)):
+            for per in (1, 7, 12, 20, 33, 41, 60, 90, 120, 150, 400, 1100):
+                T = max(1, per * E // k)
+                for N in (64, 128, 448, 1024, 4096):
+                    for K in (64, 1024, 4096, 8192, LONG - 64, LONG, L22, L23 - 64, L23, L25):
+                        for second, cfg in ((0, M.MoEConfig(T=T, d_model=K, d_ff=N, E=E, k=k, act=act)), (1, M.MoEConfig(T=T, d_model=N, d_ff=K, E=E, k=k, act=act))):
+                            name = product_kernel(cfg, second)
+                            seen.add(name)
+                            if name in rows:
+                                assert rows[name] * K * 2 < 1 << 31, (name, cfg)
+    assert seen >= set(rows) | {"gemv 8", "gemv 16", "refused"}, seen
+
+
+def test_tuning_keys_keep_the_streaming_kernels_out():
+    for key, value in ((M.MOE_TUNE_GEMM_TILE_ROWS, 256), (M.MOE_TUNE_GEMM_MFMA, 16)):
+        M.moe_set_tuning(key, value)
+        try:
+            assert second_product(512, 1024, 12) == "gemv 16" and second_product(512, 1024, 200) == "grouped 256"
+        finally:
+            M.moe_set_tuning(key, 0)
+    M.moe_set_tuning(M.MOE_TUNE_FEW_TOKEN_KERNELS, 0)
+    try:
+        assert second_product(512, 1024, 4).startswith("grouped") and second_product(512, 1024, 12).startswith("grouped")
+    finally:
+        M.moe_set_tuning(M.MOE_TUNE_FEW_TOKEN_KERNELS, 1)
