@@ -267,21 +267,28 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 // Which shape (weight rows x rows) serves a product of N features over K values, for evenly loaded experts (every shape
 // handles any routing); none: the grouped GEMM.  Measured on MI355X (us, grouped GEMM / here), rows = rows per expert:
 //  - up to 24 rows the time is the weights': 64x32, three workgroups per CU.  SwiGLU d 4096, f 14336, 8 experts, 24 rows:
-//    395 / 335 (5.6 TB/s) and, with 128 big tiles for 256 CUs, 337 / 169;
+//    386 / 359 and, with 128 big tiles for 256 CUs, 329 / 165;
 //  - up to 44 rows 256x64 and up to 96 rows 256x128 where such tiles come in nearly whole rounds of the chip (one workgroup
-//    per CU, twice the weights per stage).  64 experts, d 2048, f 8192, 32 rows: 441 / 382 and 424 / 375 (128x64: 416 and
-//    384); 64 rows 448 / 414 and 435 / 385; 94 rows 454 / 438 and 442 / 402; 128 SwiGLU experts, 1600 x 832, 38 rows 173 / 148
-//    and 99 / 83; 8 of 4096 x 14336, 40 rows, would be 3.5 rounds: 128x128 348, 256x128 373;
-//  - up to 36 otherwise: 128x64;
-//  - few tiles of any kind: 64x64.  4 experts, 150 rows, d 320, f 1088: 12.8 / 9.7 and 17.4 / 10.0;
-//  - up to 96 rows with long rows of weights or few big tiles: 128x128.  64 experts, f 8192 -> d 2048, 47 rows 433 / 386,
-//    94 rows 442 / 417, but 107 rows (some experts over 128) 450 / 494; with 2048-long rows 94 rows 453 / 522;
-//  - few big tiles, any rows: 128x192.  16 experts, f 4096 -> d 1024, 256 rows (64 big tiles) 114 / 57; 8 experts, f 3072 ->
-//    d 768, 750 rows (72) 72 / 43; 8 experts, f 14336 -> d 4096 (128), 128 rows 360 / 219, 175 rows 367 / 385; 128 big tiles of
-//    437 rows 110 / 106;
+//    per CU, twice the weights per stage).  64 experts, d 2048, f 8192, 32 rows: 396 / 363 and 386 / 366 (128x64: 378 and
+//    363); 64 rows 439 / 394 and 430 / 368; 94 rows 445 / 409 and 428 / 379; 128 SwiGLU experts, 1600 x 832, 38 rows 175 / 145;
+//  - up to 36 otherwise: 128x64.  64 experts, 1280 x 1280, 30 rows 47 / 37;
+//  - few tiles of any kind: 64x64.  4 experts, 150 rows, d 320, f 1088: 9.2 / 2.0 and 18.8 / 5.2;
+//  - up to 96 rows with long rows of weights or few big tiles: 128x128.  8 experts of 4096 x 14336, 40 rows 230 / 204; 32
+//    experts, f 2560 -> d 1664, 62 rows 66 / 58; but f 8192 -> d 2048, 64 experts, 107 rows (some over 128) 428 / 474;
+//  - few big tiles: 128x192 as long as they are one round, or two with long rows.  16 experts, f 4096 -> d 1024, 256 rows
+//    (64 big tiles) 86 / 49; 8 experts, f 3072 -> d 768, 750 rows (72) 59 / 33; 8 experts, f 14336 -> d 4096 (128), 128 rows
+//    347 / 203, 175 rows with uneven routing 355 / 367; two rounds of short rows: 16 experts, f 704 -> d 1408, 209 rows 22.7 / 23.4;
 //  - three quarters of a round of big tiles against at most two rounds of 128x128 (with a whole round of them the big tiles
-//    win: 16 experts, d 1024 -> f 4096, 128 rows 38 / 56).  16 experts, f 8704 -> d 640, 590 rows (144) 219 / 198 and, with
-//    skewed routing, 239 / 98; f 3072 -> d 768 73 / 64; but 8 experts, f 4096 -> d 1024, 1500 rows (three rounds) 107 / 142.
+//    win: 16 experts, d 1024 -> f 4096, 128 rows 29 / 31, uneven 28 / 46).  16 experts, f 8704 -> d 640, 590 rows (144) 194 /
+//    171 and, with Zipf(1.2) routing, 238 / 169; f 1408 -> d 1216, 330 rows 31 / 28, but 381 rows, where an uneven routing takes
+//    a fourth row tile, 33 / 39.  97 to 192 rows gain at most a tenth and lose a fifth to the same edge;
+//  - beyond one round, short rows: these workgroups are not persistent, so every tile pays its own start and end.  Over 4400
+//    random shapes, even routing, grouped / here: 128x64 at K below 768 0.96 (0.78 at worst), from 1024 1.05 to 1.5; 256x128
+//    below 768 1.0 (0.90), up to 1024 1.05; 128x128 below 2048 1.02 (0.90).
+// Skewed routing costs row tiles that the rule does not see.  Over the same shapes under Zipf(1.2) masses the mean gain is
+// within a tenth of that under even routing, but 128x192 loses 7 to 14 % where the hot expert's extra tiles open a second
+// round (16 experts, f 1600 -> d 1792, 115 rows: even 33 / 22, Zipf 35 / 40), and 64x32 up to 20 % with every row of a
+// step on one expert of 64.
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128 };
 int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
@@ -294,11 +301,13 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   const int64_t C = moe_capacity(cfg);
   if (rows > C) rows = C;
   if (rows <= 24) return STREAM_64x32;
-  // tiles of fr weight rows x tm rows
-  auto tiles = [&](int fr, int tm) {
+  // tiles of fr weight rows x tm rows, for `each` rows per expert
+  auto tiles_of = [&](int fr, int tm, int64_t each) {
     const int outf = swiglu ? fr / 2 : fr;
-    return cfg->E * ((rows + tm - 1) / tm) * ((N + outf - 1) / outf);
+    return cfg->E * ((each + tm - 1) / tm) * ((N + outf - 1) / outf);
   };
+  auto tiles = [&](int fr, int tm) { return tiles_of(fr, tm, rows); };
+  auto one_round = [&](int fr, int tm) { return tiles(fr, tm) <= 256; };
   const int64_t big = tiles(256, 256);
   const bool wide = N >= (swiglu ? 64 : 128);
   // share of its rounds of 256 workgroups (one per CU) that a shape of 256 weight rows fills
@@ -306,14 +315,15 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
     const int64_t t = N >= (swiglu ? 128 : 256) ? tiles(256, tm) : 0;
     return t < 256 ? 0.0 : (double)t / (double)((t + 255) / 256 * 256);
   };
-  if (rows <= 44 && fill(64) >= 0.95) return STREAM_256x64;
-  if (wide && rows <= 36) return STREAM_128x64;
+  if (rows <= 44 && fill(64) >= 0.95 && (one_round(256, 64) || K >= 768)) return STREAM_256x64;
+  if (wide && rows <= 36 && (one_round(128, 64) || K >= 1024)) return STREAM_128x64;
   if (tiles(128, 192) < 128 && tiles(64, 64) <= 512) return STREAM_64x64;
   const bool long_rows = K >= 4096 || big < 256;
-  if (rows <= 96 && fill(128) >= (long_rows ? 0.95 : 0.85)) return STREAM_256x128;
-  if (wide && rows <= 96 && long_rows) return STREAM_128x128;
-  if (wide && (big <= 96 || (big <= 128 && rows <= 152))) return STREAM_128x192;
-  if (wide && big > 128 && big <= 192 && tiles(128, 128) <= 512) return STREAM_128x128;
+  if (rows <= 96 && fill(128) >= (long_rows ? 0.95 : 0.85) && (one_round(256, 128) || K > 768)) return STREAM_256x128;
+  if (wide && rows <= 96 && long_rows && (one_round(128, 128) || K >= 2048)) return STREAM_128x128;
+  if (wide && (big <= 96 || (big <= 128 && rows <= 152)) && tiles(128, 192) <= (K >= 4096 ? 512 : 256)) return STREAM_128x192;
+  // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)
+  if (wide && rows > 192 && big > 128 && big <= 192 && tiles_of(128, 128, rows + (rows * 2 + 24) / 25) <= 512) return STREAM_128x128;
   return STREAM_NONE;
 }
 
