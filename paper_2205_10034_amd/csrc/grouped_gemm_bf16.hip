@@ -299,7 +299,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 // WT-th 32-row block) x FEAT/WF LDS feature rows.  WPE = wavefronts per SIMD the register budget is sized for.
 // HASB = false: the caller passed no bias; its staging and the two vector instructions per element that add it
 // are compiled out (SwiGLU never has one).
-template <int TOK, int FEAT, int WT, int WF, int KS, int WPE, int EPI, bool GATHER, bool HASB, bool MI16_>
+template <int TOK, int FEAT, int WT, int WF, int KS, int WPE, int EPI, bool GATHER, bool HASB, bool MI16_, bool RAGGED_N>
 __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     const uint16_t* __restrict__ act,     // [R, K]
     const uint16_t* __restrict__ wa,      // [E, N, K]   (W1 / Wg / W2)
@@ -369,11 +369,11 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wt = wave / WF, wf = wave % WF;
   const uint32_t row_bytes = (uint32_t)K * 2u;
-  const int n_tiles = (N + OUT_FEAT - 1) / OUT_FEAT;
+  const int n_tiles = RAGGED_N ? (N + OUT_FEAT - 1) / OUT_FEAT : N / OUT_FEAT;
   // A feature count that is no multiple of the tile: the last feature tile starts at N - OUT_FEAT, so that every load is
   // in range without a mask, and the wavefronts whose features belong to the tile before it neither multiply nor store
-  // (they are whole wavefronts: N is a multiple of 64).  The 320-row kernel has no register left for it.
-  constexpr bool RAGGED_N = TOK <= 256;
+  // (they are whole wavefronts: N is a multiple of 64).  A kernel of its own (RAGGED_N): evaluated in the kernel of
+  // the whole tiles, the conditions cost those 0.4 % (216 products at 24 to 400 rows per expert, 2 % at worst).
   constexpr int WAVE_OUT = OUT_FEAT / WF;  // output features per wavefront
   auto first_feature = [&](int ntile) { return RAGGED_N ? min(ntile * OUT_FEAT, N - OUT_FEAT) : ntile * OUT_FEAT; };
   auto idle_wave = [&](int ntile) { return RAGGED_N && first_feature(ntile) + wf * WAVE_OUT < ntile * OUT_FEAT; };
@@ -1019,13 +1019,13 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
 // the byte offsets inside a tile of `rows` rows are 32-bit
 bool tile_offsets_fit(int rows, int K) { return (int64_t)rows * K * 2 < ((int64_t)1 << 31); }
 
-template <int TOK, int FEAT, int WT, int WF, int KS, int WPE, int EPI, bool MI16_ = false>
+template <int TOK, int FEAT, int WT, int WF, int KS, int WPE, int EPI, bool MI16_ = false, bool RAGGED_N = false>
 int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb,
                const uint16_t* bias, const int32_t* offsets, uint16_t* out, const int32_t* row_map,
                int32_t* tile_ctr, int32_t* clear_ctr, int N, int K, hipStream_t s, const int64_t* eoff,
                const float* gate_w = nullptr, const uint16_t* residual = nullptr) {
   constexpr int OUT_FEAT = swiglu_tile(EPI) ? FEAT / 2 : FEAT;
-  if (N < OUT_FEAT || N % (TOK <= 256 ? 64 : OUT_FEAT)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: N=%d does not fit tiles of %d features", N, OUT_FEAT);
+  if (N < OUT_FEAT || N % (RAGGED_N ? 64 : OUT_FEAT)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: N=%d does not fit tiles of %d features", N, OUT_FEAT);
   if (K % KS) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: K=%d is not a multiple of %d", K, KS);
   if (!tile_offsets_fit(TOK, K)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: K=%d too large", K);
   const int64_t rmax = max_rows(cfg);
@@ -1043,18 +1043,18 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
   const int64_t per_xcd = ((blocks + NUM_XCD - 1) / NUM_XCD) * CU_PER_XCD;  // tiles one XCD may own
   const int64_t grid = (per_xcd < CU_PER_XCD ? per_xcd : CU_PER_XCD) * NUM_XCD;
   // the gathering variant exists for the first GEMM's epilogues only
-  auto kern = grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, false, false, MI16_>;
+  auto kern = grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, false, false, MI16_, RAGGED_N>;
   if constexpr (EPI == EPI_DSWIGLU) {
     if (row_map || !residual || bias) return fail(MOE_ERR_INVALID_ARG, "grouped GEMM: the SwiGLU-gradient epilogue reads contiguous rows, needs the activations' gradient and has no bias");
   } else if constexpr (EPI == EPI_SWIGLU) {
-    if (row_map) kern = grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, true, false, MI16_>;
+    if (row_map) kern = grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, true, false, MI16_, RAGGED_N>;
   } else {
-    if (bias) kern = grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, false, true, MI16_>;
+    if (bias) kern = grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, false, true, MI16_, RAGGED_N>;
   }
   if constexpr (EPI == EPI_GELU) {
     if (row_map)
-      kern = bias ? grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, true, true, MI16_>
-                  : grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, true, false, MI16_>;
+      kern = bias ? grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, true, true, MI16_, RAGGED_N>
+                  : grouped_gemm_kernel<TOK, FEAT, WT, WF, KS, WPE, EPI, true, false, MI16_, RAGGED_N>;
   } else if constexpr (swiglu_tile(EPI)) {
   } else if constexpr (EPI == EPI_BIAS) {
     if (row_map) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: the second GEMM reads contiguous rows");
@@ -1134,9 +1134,14 @@ int32_t gemm_any(const moe_config* cfg, const uint16_t* a, const uint16_t* wa, c
   if (rows != 128) {
     if (rows == 320)
       return launch<320, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
-    if (use_mi16(256, 2, EPI) && prefer_mi16(cfg))
-      return launch<256, 256, 2, 4, 64, 2, EPI, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
-    return launch<256, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
+    const bool mi16 = use_mi16(256, 2, EPI) && prefer_mi16(cfg);
+    if constexpr (EPI != EPI_DGELU && EPI != EPI_DSWIGLU) {  // (the weight gradients beside these want multiples of 256 anyway)
+      if (N % BF)
+        return mi16 ? launch<256, 256, 2, 4, 64, 2, EPI, true, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual)
+                    : launch<256, 256, 2, 4, 64, 2, EPI, false, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
+    }
+    return mi16 ? launch<256, 256, 2, 4, 64, 2, EPI, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual)
+                : launch<256, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
   }
   if constexpr (swiglu_tile(EPI))
     return launch<128, 128, 2, 2, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
