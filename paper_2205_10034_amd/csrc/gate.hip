@@ -9,7 +9,7 @@
 // k+1 leading logits have two neighbours closer than GATE_MARGIN_REL times its largest |logit| is recomputed by the whole workgroup
 // with float64 accumulation of the (exact) products and ranked on those values.
 //
-// Exact path (float32 activations, E > 64, or many tokens on more than 16 experts): the products of two float32 / bfloat16 values are exact in float64, and
+// Exact path (float32 activations, E > 64, or many tokens on more than 16 experts by gate_f64_pays): the products of two float32 / bfloat16 values are exact in float64, and
 // v_mfma_f64_16x16x4_f64 accumulates them there, so only the summation rounds, at 2^-53 relative, and nothing has to be
 // recomputed; see gate_f64_kernel.
 #include <type_traits>
@@ -1109,12 +1109,25 @@ int32_t launch_gate_dispatch_one_token(const moe_config* cfg, const void* x, con
 }
 
 // bfloat16 activations, up to 64 experts: where the float64 kernel takes over from the one that splits the router into
-// bfloat16 pieces.  Splitting costs every workgroup of 16 tokens the whole router on the vector ALU, a float64 MFMA costs
-// 16 times a bfloat16 one.  Measured on MI355X (us, split / float64): 16 experts, d 2048: T 4096 14.5 / 12.0, T 16384
-// 27 / 33, and two token tiles per workgroup take over from T 8192, so up to 16 experts stay with the split; 24 experts,
-// d 2048: T 300 13.3 / 15.8, T 1024 18.6 / 15.9, T 4096 19.8 / 17.7, T 32768 106 / 104; 64 experts, d 2048: T 300 22-37 / 23,
-// T 4096 49 / 26, T 16384 110 / 91; 64 experts, d 4096: T 300 35.9 / 40.0, T 1024 37-50 / 40.7, T 4096 77 / 44.
-bool gate_f64_pays(const moe_config* cfg) { return cfg->E > 16 && cfg->T >= 1024; }
+// bfloat16 pieces.  Splitting costs every workgroup of 16 tokens the whole router on the vector ALU, and an element-wise read
+// of it where E is no multiple of 4; a float64 MFMA costs 32 times a bfloat16 one, which grows with d, and its workgroups
+// (16 tokens, one per CU) run in rounds of 4096 tokens.  Measured on MI355X (us, split / float64, means over four inputs):
+//   16 experts, d 2048: T 4096 14.5 / 12.0, T 16384 27 / 33, and two token tiles per workgroup take over from T 8192, so up
+//     to 16 experts stay with the split; below 1024 tokens too: 24 experts, d 2048, T 300 13.3 / 15.8;
+//   24 experts: d 1024 T 1024 11 / 11, T 4096 13 / 12, T 16384 39 / 34; d 1536 T 4096 18 / 14; d 2048 T 1536 16 / 17, T 4097
+//     26 / 29; d 4096 T 1024 25 / 27, T 4097 40 / 50: float64 up to d 1536;
+//   64 experts: d 1024 T 4096 26 / 17, T 4097 32 / 30; d 2048 T 1024 27 / 24, T 4096 49 / 26, T 4097 49 / 47; d 4096 T 4096
+//     70 / 43, T 4097 80 / 81, T 8193 113 / 119, T 10000 120 / 121: float64, but not for a last round that is nearly empty
+//     where d is above 2048 (48 experts, d 3072, T 4097: 58 / 62);
+//   E no multiple of 4: 31 experts, d 2048, T 1024 43 / 18; 63 experts, d 4096, T 4096 156 / 81: float64.
+bool gate_f64_pays(const moe_config* cfg) {
+  const int T = cfg->T, d = cfg->d_model, E = cfg->E;
+  if (E <= 16 || T < 1024) return false;
+  if (E % 4) return true;
+  if (E <= 32) return d <= 1536;
+  const int last = T % 4096;  // tokens of the last round
+  return d <= 2048 || T <= 4096 || last == 0 || last > 1024;
+}
 
 int32_t launch_gate(const moe_config* cfg, const void* x, const float* w_router, const float* b_router,
                     int32_t* topk_idx, float* topk_w, float* probs, hipStream_t s) {
@@ -1143,11 +1156,20 @@ bool gate_packed_applies(const moe_config* cfg, const float* w_router) {
 }
 // Inside a layer the packed router is used where it measured faster than the kernels that need no preparation: long token
 // streams (from about 64 M activation elements; below, narrow routers are bound by their chain of dependent steps and by
-// the second launch that recomputes the near-ties), and routers of more than 16 experts from 8192 tokens (us, float64
-// kernel / packed with its second launch, d 2048: 24 experts T 4096 17.7 / 16.3, T 8192 31 / 25, T 16384 55 / 39;
-// 64 experts T 4096 25.7 / 34.7, T 8192 48.5 / 37.3, T 32768 179 / 96).
+// the second launch that recomputes the near-ties), and, for more than 16 experts,
+//  - beyond the float64 kernel's first round of 4096 tokens, except for the cheapest routers (us, float64 / packed with its
+//    second launch, means over four inputs: 64 experts, d 2048: T 4096 26 / 35, T 4097 47 / 35, T 6144 47 / 36, T 8191 47 / 43,
+//    T 32768 177 / 102; d 1024: T 4097 30 / 29, T 8191 29 / 28; 24 experts, d 2048: T 4097 29 / 23, T 16384 56 / 40; d 512:
+//    T 4097 12 / 16, T 8192 13 / 16, T 16384 21 / 22, T 32768 38 / 37);
+//  - from 1024 tokens where the router is wide and its rows cannot be read four at a time (63 experts, d 2048, T 2048 46 / 38,
+//    d 4096, T 1536 80 / 46) or the float64 sums are long and the tokens few (48 experts, d 3072, T 1024 32 / 24; 40 experts,
+//    d 4096, T 3072 42 / 37; but 64 experts, d 4096, T 4096 43 / 50).
 bool gate_packed_pays(const moe_config* cfg) {
-  return (int64_t)cfg->T * cfg->d_model >= ((int64_t)1 << 26) || (cfg->E > 16 && cfg->T >= 8192);
+  const int T = cfg->T, d = cfg->d_model, E = cfg->E;
+  if ((int64_t)T * d >= ((int64_t)1 << 26)) return true;
+  if (E <= 16) return false;
+  if (T > 4096) return d >= 1024 || E > 32 || T >= 16384;
+  return T >= 1024 && E > 32 && ((E % 4 != 0 && d >= 1024) || (d >= 3072 && (T < 2048 || E <= 40)));
 }
 
 int32_t launch_gate_packed(const moe_config* cfg, const void* x, const void* packed, const float* w_router, const float* b_router,
@@ -1196,6 +1218,15 @@ extern "C" int32_t moe_gate(const moe_config* cfg, const void* x, const float* w
   if (cfg->T > 0 && (!x || !w_router || !topk_idx || !topk_w))
     return fail(MOE_ERR_INVALID_ARG, "moe_gate: x, w_router, topk_idx and topk_w must be non-NULL");
   return launch_gate(cfg, x, w_router, b_router, topk_idx, topk_w, probs, (hipStream_t)stream);
+}
+
+// Which kernel the gate of a layer takes, with or without a packed router (16-byte aligned weights): for the tests of the
+// rules above.  Host only; not part of the interface in moesys.h.
+extern "C" const char* moe_test_gate_kernel(const moe_config* cfg, int32_t packed) {
+  if (moe_config_check(cfg) != MOE_OK) return "";
+  if (packed && gate_packed_applies(cfg, nullptr) && gate_packed_pays(cfg)) return "packed";
+  if (gate_few_applies(cfg, nullptr)) return "few";
+  return cfg->dtype == MOE_BF16 && cfg->E <= 64 && !gate_f64_pays(cfg) ? "split" : "float64";
 }
 
 extern "C" size_t moe_router_pack_bytes(int32_t d_model, int32_t E) { return router_pack_bytes(d_model, E); }
