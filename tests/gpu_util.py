@@ -1,6 +1,8 @@
 """Helpers for the GPU parity tests: upload a seeded workload, run stages through the C ABI."""
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -35,6 +37,14 @@ def run_layer(cfg: M.MoEConfig, W: M.Weights, x: torch.Tensor, residual=None):
             r[name] = to_np(ws_view(ws, L[name], L["r_max"] * cfg.d_model, dt).reshape(L["r_max"], cfg.d_model)[:R])
     r["out_tensor"] = out
     return r
+
+
+def product_kernel(cfg: M.MoEConfig, second: int) -> str:
+    """Name of the kernel that the library's rules choose for a layer's first or second expert product."""
+    f = M.lib().moe_test_product_kernel
+    f.restype, f.argtypes = C.c_char_p, [C.c_void_p, C.c_int32]
+    c = cfg.c()
+    return f(C.byref(c), second).decode()
 
 
 def rel_fro(a: np.ndarray, b: np.ndarray) -> float:

@@ -9,7 +9,7 @@ import paper_2205_10034_amd as M
 from oracle import moe_oracle as O
 from workloads import WORKLOADS, bf16_round, make_layer
 
-from gpu_util import alloc_ws, rel_fro, run_layer, to_dev, to_np, upload_weights
+from gpu_util import alloc_ws, product_kernel, rel_fro, run_layer, to_dev, to_np, upload_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -42,20 +42,37 @@ def ffn_case(act, rows, T, d, f, seed, bias=True):
     assert err < TOL
 
 
-# T only says what an evenly loaded expert would hold, which is what picks the shape; the rows themselves are ragged
+# T only says what an evenly loaded expert would hold, which is what picks the shape (named for the first and second product of
+# GELU and of SwiGLU experts; a "grouped" one is in another case's name); the rows themselves are ragged
+SHAPES = [
+    (24, 40, 64, 64, "64x32 64x32", "64x32 64x32"), (20, 40, 128, 320, "64x32 64x32", "64x32 64x32"),      # one to thirteen stages,
+    (9, 60, 832, 192, "64x32 64x32", "64x32 64x32"),                                                       # ragged last tiles
+    (36, 24, 192, 320, "128x64 128x64", "128x64 128x64"), (30, 24, 512, 448, "128x64 128x64", "128x64 128x64"),
+    (40, 16, 320, 192, "64x64 64x64", "64x64 64x64"), (150, 4, 320, 1088, "64x64 64x64", "64x64 64x64"),   # few tiles
+    (500, 3, 64, 128, "64x64 64x64", "64x64 64x64"), (31, 40, 64, 64, "64x64 64x64", "128x64 64x64"),
+    (60, 24, 576, 576, "64x64 64x64", "128x128 64x64"), (60, 32, 576, 576, "128x128 128x128", "grouped 128x128"),
+    (90, 40, 512, 832, "grouped 128x128", "grouped 128x128"), (60, 32, 2048, 576, "128x128 256x128", "128x128 256x128"),
+    (330, 16, 128, 1216, "128x128 64x64", "grouped 64x64"),
+    (120, 32, 512, 576, "128x192 128x192", "grouped 128x192"), (250, 16, 704, 1216, "grouped 128x192", "grouped 128x192"),
+    (120, 16, 320, 832, "64x64 64x64", "128x192 64x64"),
+    (40, 128, 512, 448, "256x64 256x64", "grouped 256x64"), (80, 128, 512, 448, "256x128 256x128", "grouped 256x128"),
+    (40, 128, 832, 448, "256x64 grouped", "256x64 grouped"), (80, 128, 832, 448, "256x128 grouped", "256x128 grouped"),
+    (40, 64, 1024, 1024, "256x64 256x64", "256x64 256x64")]
+
+
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
-@pytest.mark.parametrize("mean,E,d,f", [
-    (24, 40, 64, 64), (20, 40, 128, 320), (9, 60, 832, 192),             # 64 x 32: one to thirteen stages, ragged last tiles
-    (36, 24, 192, 320), (30, 24, 512, 448),                              # 128 x 64
-    (40, 16, 320, 192), (150, 4, 320, 1088), (500, 3, 64, 128),          # 64 x 64: few tiles
-    (60, 32, 576, 576), (90, 40, 512, 832),                              # 128 x 128
-    (120, 32, 512, 576), (250, 16, 704, 1216),                           # 128 x 192
-    (40, 130, 512, 576), (80, 130, 512, 448)])                           # 256 x 64, 256 x 128
-def test_stream_shapes(act, mean, E, d, f):
+@pytest.mark.parametrize("mean,E,d,f,gelu,swiglu", SHAPES)
+def test_stream_shapes(act, mean, E, d, f, gelu, swiglu):
     print(act, mean, E, d, f, flush=True)
-    rows = [RAGGED[(3 * i + E) % len(RAGGED)] for i in range(E)]
+    some = RAGGED if mean > 24 else [r if r < 34 else r - 40 for r in RAGGED]   # (on average 13 rows instead of 31)
+    rows = [some[(3 * i + E) % len(some)] for i in range(E)]
     rows[E // 2] += max(0, mean * E - sum(rows)) // 2                    # one expert far above the mean
-    ffn_case(act, rows, max(mean * E, sum(rows)), d, f, mean + E)
+    T = max(mean * E, sum(rows))
+    assert max(rows) > -(-T // E)
+    got = [product_kernel(M.MoEConfig(T=T, d_model=d, d_ff=f, E=E, k=1, act=act), second) for second in (0, 1)]
+    want = (gelu if act == "gelu" else swiglu).split()
+    assert all(g == "stream " + w or g.startswith(w) for g, w in zip(got, want)), got
+    ffn_case(act, rows, T, d, f, mean + E)
 
 
 @pytest.mark.parametrize("name,kw", [

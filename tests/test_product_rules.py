@@ -1,17 +1,10 @@
 """The rules that choose the kernel of an expert product, on the host: what each range of sizes is served by, and that long
 contraction indices reach only kernels whose offsets hold them."""
-import ctypes as C
-
 import pytest
 
 import paper_2205_10034_amd as M
 
-
-def product_kernel(cfg, second):
-    f = M.lib().moe_test_product_kernel
-    f.restype, f.argtypes = C.c_char_p, [C.c_void_p, C.c_int32]
-    c = cfg.c()
-    return f(C.byref(c), second).decode()
+from gpu_util import product_kernel
 
 
 def second_product(N, K, A, E=1, k=1):
