@@ -119,7 +119,9 @@ def test_workspace_counters_between_kernels():
     """First product streaming, second product on the grouped GEMM and the reverse, run twice from one routing: each leaves
     the other's tile counters as it needs them."""
     for d, f in ((2048, 256), (256, 2048)):
-        wl = WORKLOADS["gpt"].scaled(T=1200, E=16, k=2, d_model=d, d_ff=f, capacity_factor=0.0)
+        wl = WORKLOADS["gpt"].scaled(T=1300, E=16, k=2, d_model=d, d_ff=f, capacity_factor=0.0)
+        names = [product_kernel(M.MoEConfig.from_workload(wl), second) for second in (0, 1)]
+        assert names == (["stream 64x64", "grouped 256"] if f < d else ["grouped 256", "stream 64x64"])
         L = make_layer(wl)
         cfg, W, x = M.MoEConfig.from_workload(wl), upload_weights(L, "bf16"), to_dev(L["x"], "bf16")
         ws = alloc_ws(cfg)
