@@ -253,6 +253,22 @@ __global__ __launch_bounds__(WgShape<TN>::WAVES * 64, 2) void grouped_wgrad_kern
 #endif
 }
 
+// Tile edge: 256 (the loop is bound by its transposing LDS reads, 3 per 2 MFMAs against 4 per 2 for 128) unless those tiles
+// leave a quarter of their rounds of 256 CUs empty.  Measured on MI355X (us, 256 / 128): 8 experts of 2000 rows, 512 x 512
+// (32 tiles) 51 / 22; 8 of 1200 rows, 768 x 3072 (288) 81 / 58; 16 of 1024, 1024 x 4096 (1024) 164 / 205; 16 of 256,
+// 1024 x 4096 78 / 81.
+// Blocks of BY x BX tiles: see "Tile order".  With few rows the product is bound by its stores, and a block as wide as the
+// gradient's rows writes them whole (8 columns of tiles / 32: 64 experts of 128 rows, 2048 x 8192 bf16 984 / 788; 32 of 29 rows,
+// 1536 x 2560 190 / 107; 16 of 256 rows, 1024 x 4096 78 / 81).
+struct WgTiles { int TN, BX, BY; };
+WgTiles wgrad_tiles(int E, int N1, int N2, int64_t rows_per_expert) {
+  const int64_t tiles = (int64_t)E * (N1 / 256) * (N2 / 256), rounds = (tiles + 255) / 256;
+  const int TN = tiles <= 512 && 4 * tiles < 3 * 256 * rounds ? 128 : 256;
+  const int widest = rows_per_expert <= 160 && TN == 256 ? 32 : 8, n2t = N2 / TN;
+  const int BX = n2t < widest ? n2t : widest;
+  return {TN, BX, 32 / BX};
+}
+
 }  // namespace
 
 int32_t launch_wgrad_bf16(const uint16_t* a, const uint16_t* b, const int32_t* offsets, void* c, int c_dtype, float* a_colsum, int E,
@@ -263,18 +279,8 @@ int32_t launch_wgrad_bf16(const uint16_t* a, const uint16_t* b, const int32_t* o
   if ((max_rows_per_expert + WG_KS) * widest * 2 >= ((int64_t)1 << 31))
     return fail(MOE_ERR_UNSUPPORTED, "weight gradient: an expert's operand block exceeds 2 GiB");
   const bool h = c_dtype == MOE_BF16;
-  // Tile edge: 256 (the loop is bound by its transposing LDS reads, 3 per 2 MFMAs against 2 per 2 for 128) unless those tiles
-  // leave a quarter of their rounds of 256 CUs empty.  Measured on MI355X (us, 256 / 128): 8 experts of 2000 rows, 512 x 512
-  // (32 tiles) 51 / 22; 8 of 1200 rows, 768 x 3072 (288) 81 / 58; 16 of 1024, 1024 x 4096 (1024) 164 / 205; 16 of 256,
-  // 1024 x 4096 78 / 81.
-  const int64_t tiles = (int64_t)E * (N1 / 256) * (N2 / 256), rounds = (tiles + 255) / 256;
-  const int TN = tiles <= 512 && 4 * tiles < 3 * 256 * rounds ? 128 : 256;
-  const int n1t = N1 / TN, n2t = N2 / TN;
-  // Blocks of tiles: see "Tile order".  With few rows the product is bound by its stores, and a block as wide as the
-  // gradient's rows writes them whole (8 columns of tiles / 32: 64 experts of 128 rows, 2048 x 8192 bf16 984 / 788; 32 of 29 rows,
-  // 1536 x 2560 190 / 107; 16 of 256 rows, 1024 x 4096 78 / 81).
-  const int BXM = rows_per_expert <= 160 && TN == 256 ? 32 : 8;
-  const int BX = n2t < BXM ? n2t : BXM, BY = 32 / BX;
+  const WgTiles t = wgrad_tiles(E, N1, N2, rows_per_expert);
+  const int TN = t.TN, BX = t.BX, BY = t.BY, n1t = N1 / TN, n2t = N2 / TN;
   const int64_t blocks = (int64_t)E * ((n1t + BY - 1) / BY) * ((n2t + BX - 1) / BX);
   const int64_t wgs = ((blocks + 7) / 8) * 8 * BY * BX;
   if (wgs > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "weight gradient: too many tiles");
@@ -300,4 +306,11 @@ extern "C" int32_t moe_expert_wgrad(const void* a, const void* b, const int32_t*
     return fail(MOE_ERR_INVALID_ARG, "moe_expert_wgrad: bad shape");
   return launch_wgrad_bf16((const uint16_t*)a, (const uint16_t*)b, expert_offsets, c, c_dtype, a_column_sums, E, N1, N2,
                            max_rows_per_expert, max_rows_per_expert, (hipStream_t)stream);
+}
+
+// Tile edge and width of a block of tiles (TN * 100 + BX): for the tests of the rule above.  Host only; not part of the
+// interface in moesys.h.
+extern "C" int32_t moe_test_wgrad_tiles(int32_t E, int32_t N1, int32_t N2, int64_t rows_per_expert) {
+  const moesys::WgTiles t = moesys::wgrad_tiles(E, N1, N2, rows_per_expert);
+  return t.TN * 100 + t.BX;
 }

@@ -1,6 +1,8 @@
 """Weight gradients on either side of the tile rule: enough 256x256 tiles for a round of the chip (with few and with many
 rows per expert, which changes the order of the tiles), and the 128x128 tiles that serve fewer.  float32 sums of exact
 products against float64; the bf16 form is the float32 one rounded once."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -12,13 +14,16 @@ pytestmark = pytest.mark.gpu
 RAGGED = [0, 1, 31, 32, 33, 64, 95, 96, 97, 7]
 
 
-@pytest.mark.parametrize("E,scale,N1,N2", [
-    (64, 1, 512, 512),                       # 256 tiles of 256
-    (70, 1, 256, 1280), (24, 1, 768, 2560),  # rows of five and ten tiles: blocks as wide as the rows, partial blocks
-    (60, 3, 512, 768),                       # more rows per expert: blocks of 8 x 4
-    (3, 4, 768, 1280), (40, 1, 256, 512)])   # 128x128 tiles
-def test_wgrad_tiles(E, scale, N1, N2):
+@pytest.mark.parametrize("E,scale,N1,N2,tile,wide", [
+    (64, 1, 512, 512, 256, 2),                                            # 256 tiles of 256
+    (100, 1, 256, 1280, 256, 5), (24, 1, 768, 2560, 256, 10),             # rows of five and ten tiles: blocks as wide as the rows, partial blocks
+    (80, 3, 512, 768, 256, 3), (24, 3, 768, 2560, 256, 8),                # more rows per expert: blocks of 10 x 3 and 4 x 8
+    (70, 1, 256, 1280, 128, 8), (60, 3, 512, 768, 128, 6), (3, 4, 768, 1280, 128, 8), (40, 1, 256, 512, 128, 4)])
+def test_wgrad_tiles(E, scale, N1, N2, tile, wide):
     print(E, scale, N1, N2, flush=True)
+    f = M.lib().moe_test_wgrad_tiles
+    f.restype, f.argtypes = C.c_int32, [C.c_int32] * 3 + [C.c_int64]
+    assert f(E, N1, N2, max(RAGGED) * scale) == tile * 100 + wide
     rows = [RAGGED[i % len(RAGGED)] * scale for i in range(E)]
     offsets = torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int32)
     g = torch.Generator(device="cuda").manual_seed(E + N2)
