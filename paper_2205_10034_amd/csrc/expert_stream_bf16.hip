@@ -63,16 +63,15 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   constexpr int OUTF = EPI == ST_SWIGLU ? S::WROWS / 2 : S::WROWS;  // output features per workgroup
   constexpr int W_BYTES = S::WROWS * 128, STAGE = W_BYTES + TM * 128;
   constexpr int A_BLKS = TM / 8;  // blocks of eight rows, one load each
-  constexpr int W_LOADS = W_BYTES / 1024 / ST_WAVES, A_LOADS = (A_BLKS + ST_WAVES - 1) / ST_WAVES, LOADS = W_LOADS + A_LOADS;
-  static_assert(W_BYTES % (1024 * ST_WAVES) == 0 && 2 * A_BLKS % ST_WAVES == 0, "whole loads of 8 rows per wavefront");
-  static_assert(STAGES >= 3 && STAGES <= 6, "the K loop below");
+  constexpr int W_LOADS = W_BYTES / 1024 / ST_WAVES, A_LOADS = A_BLKS / ST_WAVES, LOADS = W_LOADS + A_LOADS;
+  static_assert(W_BYTES % (1024 * ST_WAVES) == 0 && A_BLKS % ST_WAVES == 0, "whole loads of 8 rows per wavefront");
+  static_assert(STAGES >= 3 && STAGES <= 5, "the K loop below");
   // one array per stage: the compiler can then tell the stages being filled from the one being read
   __shared__ __attribute__((aligned(1024))) unsigned char s0[STAGE];
   __shared__ __attribute__((aligned(1024))) unsigned char s1[STAGE];
   __shared__ __attribute__((aligned(1024))) unsigned char s2[STAGE];
   __shared__ __attribute__((aligned(1024))) unsigned char s3[STAGES > 3 ? STAGE : 16];
   __shared__ __attribute__((aligned(1024))) unsigned char s4[STAGES > 4 ? STAGE : 16];
-  __shared__ __attribute__((aligned(1024))) unsigned char s5[STAGES > 5 ? STAGE : 16];
   if (clear_ctr && blockIdx.x == 0 && threadIdx.x < 8) clear_ctr[threadIdx.x] = 0;  // (a grouped GEMM may run next)
   RowTile t;
   if (!find_row_tile<TM>(offsets, E, n_tiles, t)) return;
@@ -85,12 +84,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   // ---- loads: one instruction moves 8 rows of 128 bytes; lane l lands at row l / 8, physical chunk l mod 8 of the eight
   // rows, which holds the logical chunk (l mod 8) ^ key, key = (row / 2) mod 8.  SwiGLU: LDS rows 16 w .. 16 w + 7 are the
   // gate rows of features 8 w .. 8 w + 7, the eight after them their up rows.
-  // Half a round of row blocks left: the upper half of the wavefronts repeats the lower half's loads (same bytes to the same
-  // place), so that every wavefront has as many in flight.
-  auto block = [&](int i) {
-    const int blk = (i < W_LOADS ? i : i - W_LOADS) * ST_WAVES + wave;
-    return i >= W_LOADS && blk >= A_BLKS ? blk - ST_WAVES / 2 : blk;
-  };
+  auto block = [&](int i) { return (i < W_LOADS ? i : i - W_LOADS) * ST_WAVES + wave; };
   const int k2 = K * 2;  // bytes of a row
   int voff[LOADS];
 #pragma unroll
@@ -154,8 +148,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     else if constexpr (I == 1) return s1;
     else if constexpr (I == 2) return s2;
     else if constexpr (I == 3) return s3;
-    else if constexpr (I == 4) return s4;
-    else return s5;
+    else return s4;
   };
   // Stage kt is multiplied while stages kt+1 .. kt+STAGES-1 are on their way.  A wavefront waits for its own share of
   // stage kt (loads retire in order) and for its reads of the stage before, then the workgroup meets: stage kt is whole
@@ -170,7 +163,6 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   issue(1, s1);
   if constexpr (STAGES > 3) issue(2, s2);
   if constexpr (STAGES > 4) issue(3, s3);
-  if constexpr (STAGES > 5) issue(4, s4);
   // (left by breaks: on every way round the loop all stages were requested, which is what lets the compiler see that no
   // further wait is needed before a stage is read)
   for (int kt = 0;;) {
@@ -182,7 +174,6 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     if (++kt == KT) break;
     if constexpr (STAGES > 3) { step(std::integral_constant<int, 3>{}, kt); if (++kt == KT) break; }
     if constexpr (STAGES > 4) { step(std::integral_constant<int, 4>{}, kt); if (++kt == KT) break; }
-    if constexpr (STAGES > 5) { step(std::integral_constant<int, 5>{}, kt); if (++kt == KT) break; }
   }
   __builtin_amdgcn_s_waitcnt(wait_vm(0));  // (the empty loads retire)
 

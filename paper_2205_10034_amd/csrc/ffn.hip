@@ -42,15 +42,14 @@ __device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cas
 // Measured on MI355X at 4096 rows over 16 experts, d_model 1024, d_ff 4096 (two products of 34.4 GFLOP): 764 + 837 us on
 // the vector ALU (10 times that without a capacity bound: its grid had a workgroup for every row tile of every expert),
 // 350 + 371 us here (98 and 93 TFLOP/s of the 154 that the vendor's dense product of 8192^3 reaches).
-constexpr int FM = 64, FKS = 32, FPITCH = FKS + 4;
+constexpr int FM = 64, FN = 64, FKS = 32, FPITCH = FKS + 4;  // rows and output features per tile, values per step, LDS pitch
 template <int EPI, bool IM>
 __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict__ act, const float* __restrict__ wa,
                                                          const float* __restrict__ wb, const float* __restrict__ bias,
                                                          const int32_t* __restrict__ offsets, float* __restrict__ out, int E,
                                                          int N, int K, int n_tiles) {
-  constexpr int OUTF = 64;                             // output features per tile
   constexpr int NB = EPI == F_SWIGLU ? 2 : 1;          // 32-feature blocks per wavefront
-  constexpr int TN = OUTF * NB;                        // weight rows per tile
+  constexpr int TN = FN * NB;                          // weight rows per tile
   constexpr int BP = IM ? TN + 4 : FPITCH, BROWS = IM ? FKS : TN;
   __shared__ __attribute__((aligned(16))) float sa[2][FM * FPITCH];
   __shared__ __attribute__((aligned(16))) float sb[2][BROWS * BP];
@@ -58,7 +57,7 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
   if (!find_row_tile<FM>(offsets, E, n_tiles, t)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wc = wave >> 1, l32 = lane & 31, h = lane >> 5;
-  const int n0 = t.nt * OUTF;
+  const int n0 = t.nt * FN;
   const size_t we = (size_t)t.expert * N * K;
 
   // this thread's 16-byte pieces of a stage: two of the rows, TN / 32 of the weights; pieces past the last row or
@@ -77,11 +76,11 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
     const int i = q * 256 + tid;
     const int r = IM ? i / (TN / 4) : i / 8, c = IM ? i % (TN / 4) : i % 8;  // IM: contraction row r, features 4c; else feature r
     const int f = IM ? 4 * c : r;                                            // feature inside the tile
-    const float* w = EPI == F_SWIGLU && f >= OUTF ? wb : wa;
-    const int n = EPI == F_SWIGLU && f >= OUTF ? n0 + f - OUTF : n0 + f;
+    const float* w = EPI == F_SWIGLU && f >= FN ? wb : wa;
+    const int n = EPI == F_SWIGLU && f >= FN ? n0 + f - FN : n0 + f;
     if (IM) pb[q] = w + we + (size_t)r * N + min(n, N - 4);                   // (N is a multiple of 64)
     else pb[q] = w + we + (size_t)min(n, N - 1) * K + 4 * c;
-    lb[q] = IM ? r * BP + 4 * c : r * BP + 4 * c;
+    lb[q] = r * BP + 4 * c;
   }
   const size_t b_step = IM ? (size_t)FKS * N : FKS;
   f32x4 ra[2], rb[TN / 32];
@@ -109,7 +108,7 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
       f32x4 b[NB];
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
-        const int f = j * (TN / NB) + wc * 32 + l32;
+        const int f = j * FN + wc * 32 + l32;
         if (IM) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) b[j][i] = sb[s][(kk * 8 + 4 * h + i) * BP + f];
@@ -136,21 +135,17 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
     __syncthreads();
   }
   // register v of lane (l32, h): row (v & 3) + 8 (v >> 2) + 4 h of the wavefront's 32, feature l32 of the block
+  const int n = n0 + wc * 32 + l32;  // (N is a multiple of 64)
+  const float b = EPI != F_SWIGLU && bias ? bias[(size_t)t.expert * N + n] : 0.f;
 #pragma unroll
-  for (int j = 0; j < (EPI == F_SWIGLU ? 1 : NB); ++j) {
-    const int n = n0 + j * (TN / NB) + wc * 32 + l32;
-    if (n >= N) continue;
-    const float b = EPI != F_SWIGLU && bias ? bias[(size_t)t.expert * N + n] : 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = wm * 32 + (v & 3) + 8 * (v >> 2) + 4 * h;
-      if (r >= t.rows) continue;
-      float u = acc[j][v];
-      if constexpr (EPI == F_SWIGLU) u = silu_exact(u) * acc[NB - 1][v];
-      else if (EPI == F_GELU) u = gelu_exact(u + b);
-      else u += b;
-      out[(size_t)(t.row0 + r) * N + n] = u;
-    }
+  for (int v = 0; v < 16; ++v) {
+    const int r = wm * 32 + (v & 3) + 8 * (v >> 2) + 4 * h;
+    if (r >= t.rows) continue;
+    float u = acc[0][v];
+    if constexpr (EPI == F_SWIGLU) u = silu_exact(u) * acc[NB - 1][v];
+    else if (EPI == F_GELU) u = gelu_exact(u + b);
+    else u += b;
+    out[(size_t)(t.row0 + r) * N + n] = u;
   }
 }
 
@@ -254,10 +249,9 @@ int32_t launch_f32_layout(const moe_config* cfg, const float* act, const float* 
   // The 64-row kernel from 257 tiles on (one for every CU), for evenly loaded experts; below, the kernel that splits the
   // contraction index.  Measured (us, 64 rows / split): 112 tiles, K 2624: 60 / 50; 144 tiles, K 640: 21 / 18; 256 tiles of
   // 16 rows, K 4096: 99 / 78; 288 tiles, K 2048: 85 / 92; 656 tiles, K 448: 38 / 67; 1280 tiles, K 4096: 380 / 548.
-  constexpr int OUTF = 64;
   const int64_t rows_each = (rmax + cfg->E - 1) / cfg->E;
-  const bool split = cfg->E * ((rows_each + FM - 1) / FM) * ((N + OUTF - 1) / OUTF) <= 256;
-  const int tm = split ? 32 : FM, tn = split ? 32 : OUTF;
+  const bool split = cfg->E * ((rows_each + FM - 1) / FM) * ((N + FN - 1) / FN) <= 256;
+  const int tm = split ? 32 : FM, tn = split ? 32 : FN;
   const int64_t grid = row_tile_grid(cfg, tm, (N + tn - 1) / tn);
   if (grid > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "float32 FFN: too many tiles");
   const dim3 g((unsigned)grid);
