@@ -32,7 +32,7 @@ def tables(cfg, idx, x, static):
     return counts.cpu().numpy(), offsets.cpu().numpy(), a2r.cpu().numpy()[:A], r2a.cpu().numpy()[:R], xd[:R].cpu()
 
 
-# in this order on one GPU: large (scan kernel: more than 256 blocks), smaller, tiny (single block), empty,
+# in this order on one GPU: large (scan kernel: more than 2048 histogram words), smaller, tiny (single block), empty,
 # larger again
 CASES = [dict(T=40000, E=16, k=2, cf=1.25), dict(T=5000, E=16, k=2, cf=0.5), dict(T=37, E=64, k=3, cf=0.0),
          dict(T=0, E=4, k=1, cf=1.0), dict(T=9000, E=130, k=4, cf=1.0)]
