@@ -22,7 +22,7 @@
 // Tile order.  The 8 XCDs have an L2 each, and the hardware deals workgroups out to them round robin.  A tile
 // streams a 256-column slab of A and one of B; tiles of one expert with the same n1 (n2) tile share the A (B)
 // slab.  Workgroups are therefore numbered so that the 32 that start together on one XCD are a block of
-// BY x BX tiles of ONE expert (BX = min(8, n2 tiles), with few rows up to 32; BY = 32 / BX): BY + BX slabs for 32 tiles through that L2
+// BY x BX tiles of ONE expert (BX = min(8, n2 tiles), up to 32 by wgrad_tiles; BY = 32 / BX): BY + BX slabs for 32 tiles through that L2
 // instead of the 6 for 8 that the plain (n2, n1, expert) grid order gives at 16 x 4 tiles per expert.
 // Column sums of A per expert (the bias gradients: db2_e = sum_r d_y[r, :], db1_e = sum_r d_u[r, :]) come from
 // the same fragments: the workgroups of the first n2 tile multiply one n1 fragment per wavefront and K-step
@@ -253,19 +253,47 @@ __global__ __launch_bounds__(WgShape<TN>::WAVES * 64, 2) void grouped_wgrad_kern
 #endif
 }
 
+// Tiles of the XCD that gets most of them (blocks go to the XCDs in turn, see "Tile order"): where an expert ends in smaller
+// blocks and their number has a factor in common with eight, all of these meet on the same XCDs.
+int64_t busiest_xcd(int E, int n1t, int n2t, int BX, int BY) {
+  int64_t load[8] = {}, most = 0;
+  int x = 0;
+  for (int e = 0; e < E; ++e)
+    for (int y = 0; y < n1t; y += BY)
+      for (int c = 0; c < n2t; c += BX, x = (x + 1) % 8) load[x] += (int64_t)(n1t - y < BY ? n1t - y : BY) * (n2t - c < BX ? n2t - c : BX);
+  for (int64_t l : load) most = l > most ? l : most;
+  return most;
+}
+
 // Tile edge: 256 (the loop is bound by its transposing LDS reads, 3 per 2 MFMAs against 4 per 2 for 128) unless those tiles
-// leave a quarter of their rounds of 256 CUs empty.  Measured on MI355X (us, 256 / 128): 8 experts of 2000 rows, 512 x 512
-// (32 tiles) 51 / 22; 8 of 1200 rows, 768 x 3072 (288) 81 / 58; 16 of 1024, 1024 x 4096 (1024) 164 / 205; 16 of 256,
-// 1024 x 4096 78 / 81.
-// Blocks of BY x BX tiles: see "Tile order".  With few rows the product is bound by its stores, and a block as wide as the
-// gradient's rows writes them whole (8 columns of tiles / 32: 64 experts of 128 rows, 2048 x 8192 bf16 984 / 788; 32 of 29 rows,
-// 1536 x 2560 190 / 107; 16 of 256 rows, 1024 x 4096 78 / 81).
+// leave a quarter of their rounds of 256 CUs empty and the busiest XCD's share takes longer that way: in whole rounds of 32
+// large tiles, or at 64 small ones in 0.62 of that time (39 and 24 us for 1024 rows).  Measured on MI355X (float32 gradients,
+// us, 256 / 128): 8 experts of 2000 rows, 512 x 512 (32 tiles) 50 / 23; 8 of 1200 rows, 768 x 3072 (288) 76 / 58; 16 of 1024,
+// 1024 x 4096 (1024) 156 / 193; 16 of 256, 1024 x 4096 71 / 81; and where the small ones load the XCDs unevenly: 19 of 2048,
+// 512 x 1280 (190 tiles in blocks of 10, 760 in blocks of 32 and 8) 65 / 73; 30 of 2048, 768 x 1024 118 / 142.
+// Columns of tiles per block (BX; BY = 32 / BX): eight.  As wide as the gradient's rows, up to 32, with few rows per expert,
+// where the product is bound by its stores: up to 32 rows if that loads the XCDs no less evenly (96 experts of 16 rows,
+// 512 x 5120 230 / 201; uneven: 24 of 16, 768 x 4096 63 / 76); up to 160 where eight would leave partial blocks (9 to 15 columns:
+// 32 experts of 29 rows, 1536 x 2560 189 / 108) and for 16-bit gradients of 32 columns and a gibibyte (64 experts of 128 rows,
+// 2048 x 8192 955 / 780; in float32 975 / 1085; 8 experts, 2304 x 8192 bf16 105 / 116).  20 and 24 columns
+// lose 4 to 9 % in either type from 128 rows on, 16 columns 2 to 3 %.
 struct WgTiles { int TN, BX, BY; };
-WgTiles wgrad_tiles(int E, int N1, int N2, int64_t rows_per_expert) {
+WgTiles wgrad_tiles(int E, int N1, int N2, int c_dtype, int64_t rows_per_expert) {
+  auto busiest = [&](int tn, int bx) { return busiest_xcd(E, N1 / tn, N2 / tn, bx, 32 / bx); };
+  auto columns = [&](int tn) {
+    const int n2t = N2 / tn, eight = n2t < 8 ? n2t : 8, all = n2t < 32 ? n2t : 32;
+    if (tn != 256 || n2t <= 8 || rows_per_expert > 160) return eight;
+    if (n2t < 16) return all;
+    if (c_dtype == MOE_BF16 && n2t % 32 == 0 && (int64_t)E * N1 * N2 * 2 >= ((int64_t)1 << 30)) return all;
+    return rows_per_expert <= 32 && busiest(256, all) <= busiest(256, 8) ? all : eight;
+  };
   const int64_t tiles = (int64_t)E * (N1 / 256) * (N2 / 256), rounds = (tiles + 255) / 256;
-  const int TN = tiles <= 512 && 4 * tiles < 3 * 256 * rounds ? 128 : 256;
-  const int widest = rows_per_expert <= 160 && TN == 256 ? 32 : 8, n2t = N2 / TN;
-  const int BX = n2t < widest ? n2t : widest;
+  int TN = 256;
+  if (tiles <= 512 && 4 * tiles < 3 * 256 * rounds) {
+    const int64_t large = (busiest(256, columns(256)) + 31) / 32, small = busiest(128, columns(128));
+    if (small * 62 < large * 64 * 100) TN = 128;
+  }
+  const int BX = columns(TN);
   return {TN, BX, 32 / BX};
 }
 
@@ -279,7 +307,7 @@ int32_t launch_wgrad_bf16(const uint16_t* a, const uint16_t* b, const int32_t* o
   if ((max_rows_per_expert + WG_KS) * widest * 2 >= ((int64_t)1 << 31))
     return fail(MOE_ERR_UNSUPPORTED, "weight gradient: an expert's operand block exceeds 2 GiB");
   const bool h = c_dtype == MOE_BF16;
-  const WgTiles t = wgrad_tiles(E, N1, N2, rows_per_expert);
+  const WgTiles t = wgrad_tiles(E, N1, N2, c_dtype, rows_per_expert);
   const int TN = t.TN, BX = t.BX, BY = t.BY, n1t = N1 / TN, n2t = N2 / TN;
   const int64_t blocks = (int64_t)E * ((n1t + BY - 1) / BY) * ((n2t + BX - 1) / BX);
   const int64_t wgs = ((blocks + 7) / 8) * 8 * BY * BX;
@@ -310,7 +338,7 @@ extern "C" int32_t moe_expert_wgrad(const void* a, const void* b, const int32_t*
 
 // Tile edge and width of a block of tiles (TN * 100 + BX): for the tests of the rule above.  Host only; not part of the
 // interface in moesys.h.
-extern "C" int32_t moe_test_wgrad_tiles(int32_t E, int32_t N1, int32_t N2, int64_t rows_per_expert) {
-  const moesys::WgTiles t = moesys::wgrad_tiles(E, N1, N2, rows_per_expert);
+extern "C" int32_t moe_test_wgrad_tiles(int32_t E, int32_t N1, int32_t N2, int32_t c_dtype, int64_t rows_per_expert) {
+  const moesys::WgTiles t = moesys::wgrad_tiles(E, N1, N2, c_dtype, rows_per_expert);
   return t.TN * 100 + t.BX;
 }

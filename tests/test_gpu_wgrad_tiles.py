@@ -14,16 +14,21 @@ pytestmark = pytest.mark.gpu
 RAGGED = [0, 1, 31, 32, 33, 64, 95, 96, 97, 7]
 
 
-@pytest.mark.parametrize("E,scale,N1,N2,tile,wide", [
-    (64, 1, 512, 512, 256, 2),                                            # 256 tiles of 256
-    (100, 1, 256, 1280, 256, 5), (24, 1, 768, 2560, 256, 10),             # rows of five and ten tiles: blocks as wide as the rows, partial blocks
-    (80, 3, 512, 768, 256, 3), (24, 3, 768, 2560, 256, 8),                # more rows per expert: blocks of 10 x 3 and 4 x 8
-    (70, 1, 256, 1280, 128, 8), (60, 3, 512, 768, 128, 6), (3, 4, 768, 1280, 128, 8), (40, 1, 256, 512, 128, 4)])
-def test_wgrad_tiles(E, scale, N1, N2, tile, wide):
+# tile edge and columns of tiles per block, for float32 and bf16 gradients
+@pytest.mark.parametrize("E,scale,N1,N2,tile,wide,wide_bf16", [
+    (64, 1, 512, 512, 256, 2, 2),                                           # 256 tiles of 256
+    (70, 1, 256, 1280, 256, 5, 5), (19, 4, 512, 1280, 256, 5, 5),           # few, but as 128 in blocks of eight and two columns
+    (100, 1, 256, 1280, 256, 5, 5), (24, 1, 768, 2560, 256, 10, 10),        # rows of five and ten tiles: whole rows, partial blocks of them
+    (16, 1, 256, 8192, 256, 8, 8), (18, 1, 256, 6144, 256, 8, 8), (256, 1, 256, 8192, 256, 8, 32),  # 32 columns: whole rows of large 16-bit gradients
+    (80, 3, 512, 768, 256, 3, 3), (24, 3, 768, 2560, 256, 8, 8), (16, 3, 256, 8192, 256, 8, 8),  # more rows per expert
+    (60, 3, 512, 768, 128, 6, 6), (3, 4, 768, 1280, 128, 8, 8), (40, 1, 256, 512, 128, 4, 4)])
+def test_wgrad_tiles(E, scale, N1, N2, tile, wide, wide_bf16):
     print(E, scale, N1, N2, flush=True)
     f = M.lib().moe_test_wgrad_tiles
-    f.restype, f.argtypes = C.c_int32, [C.c_int32] * 3 + [C.c_int64]
-    assert f(E, N1, N2, max(RAGGED) * scale) == tile * 100 + wide
+    f.restype, f.argtypes = C.c_int32, [C.c_int32] * 4 + [C.c_int64]
+    assert f(96, 512, 5120, M.binding.MOE_F32, 16) == 25620 and f(24, 768, 4096, M.binding.MOE_F32, 16) == 25608
+    assert f(E, N1, N2, M.binding.MOE_F32, max(RAGGED) * scale) == tile * 100 + wide
+    assert f(E, N1, N2, M.binding.MOE_BF16, max(RAGGED) * scale) == tile * 100 + wide_bf16
     rows = [RAGGED[i % len(RAGGED)] * scale for i in range(E)]
     offsets = torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int32)
     g = torch.Generator(device="cuda").manual_seed(E + N2)
