@@ -273,9 +273,12 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    win: 16 experts, d 1024 -> f 4096, 128 rows 29 / 31, uneven 28 / 46).  16 experts, f 8704 -> d 640, 590 rows (144) 194 /
 //    171 and, with Zipf(1.2) routing, 238 / 169; f 1408 -> d 1216, 330 rows 31 / 28, but 381 rows, where an uneven routing takes
 //    a fourth row tile, 33 / 39.  97 to 192 rows gain at most a tenth and lose a fifth to the same edge;
-//  - beyond one round, short rows: these workgroups are not persistent, so every tile pays its own start and end.  Over 4400
-//    random shapes, even routing, grouped / here: 128x64 at K below 768 0.96 (0.78 at worst), from 1024 1.05 to 1.5; 256x128
-//    below 768 1.0 (0.90), up to 1024 1.05; 128x128 below 2048 1.02 (0.90).
+//  - beyond one round, short rows: these workgroups are not persistent, so every tile pays its own start and end (a SwiGLU
+//    tile has two products to spread them over).  Over 4400 random shapes and 600 of 448 to 1300 values, even routing, grouped
+//    / here: 128x64 (where 256x64 does not serve), SwiGLU up to 576 values 0.96 (0.88 at worst), above 1.0 to 1.3; others up to
+//    768 0.9 (0.74), from 832 1.0 to 1.1 where the big tiles leave a fifth of their rounds empty, where they do not 0.86 to
+//    1.07 up to 1024 and 1.05 and more above; 256x128 up to 704 0.97 to 1.02 (0.86), above 1.04 to 1.14; 128x128 below 2048 1.02
+//    (0.90).
 // Skewed routing costs row tiles that the rule does not see.  Over the same shapes under Zipf(1.2) masses the mean gain is
 // within a tenth of that under even routing, but 128x192 loses 7 to 14 % where the hot expert's extra tiles open a second
 // round (16 experts, f 1600 -> d 1792, 115 rows: even 33 / 22, Zipf 35 / 40), and 64x32 up to 20 % with every row of a
@@ -307,10 +310,11 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
     return t < 256 ? 0.0 : (double)t / (double)((t + 255) / 256 * 256);
   };
   if (rows <= 44 && fill(64) >= 0.95 && (one_round(256, 64) || K >= 768)) return STREAM_256x64;
-  if (wide && rows <= 36 && (one_round(128, 64) || K >= 1024)) return STREAM_128x64;
+  const bool big_fit = 5 * big >= 4 * ((big + 255) / 256 * 256);  // the big tiles fill four fifths of their rounds
+  if (wide && rows <= 36 && (one_round(128, 64) || K >= (swiglu ? 640 : big_fit ? 1088 : 832))) return STREAM_128x64;
   if (tiles(128, 192) < 128 && tiles(64, 64) <= 512) return STREAM_64x64;
   const bool long_rows = K >= 4096 || big < 256;
-  if (rows <= 96 && fill(128) >= (long_rows ? 0.95 : 0.85) && (one_round(256, 128) || K > 768)) return STREAM_256x128;
+  if (rows <= 96 && fill(128) >= (long_rows ? 0.95 : 0.85) && (one_round(256, 128) || K >= (swiglu ? 768 : 832))) return STREAM_256x128;
   if (wide && rows <= 96 && long_rows && (one_round(128, 128) || K >= 2048)) return STREAM_128x128;
   if (wide && (big <= 96 || (big <= 128 && rows <= 152)) && tiles(128, 192) <= (K >= 4096 ? 512 : 256)) return STREAM_128x192;
   // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)

@@ -72,13 +72,16 @@ def test_tiles_beyond_one_round_need_long_rows_of_weights():
     """Shapes that measured slower than the grouped GEMM: several rounds of tiles over few values of the contraction index,
     row counts just below a tile edge that uneven routing crosses, two rounds of 128 x 192."""
     first = lambda rows, E, N, K, act="gelu": product_kernel(M.MoEConfig(T=rows * E, d_model=K, d_ff=N, E=E, k=1, act=act), 0)
-    for rows, E, N, K in ((36, 16, 10752, 512), (28, 64, 1792, 512), (27, 16, 9984, 576),                  # 128 x 64
+    for rows, E, N, K in ((36, 16, 10752, 512), (28, 64, 1792, 512), (27, 16, 9984, 576), (34, 32, 3136, 896),   # 128 x 64
                           (62, 128, 7296, 512), (85, 32, 7168, 512), (46, 16, 2560, 512), (66, 64, 576, 1024),   # 256 x 128, 128 x 128
                           (105, 96, 512, 1088), (128, 32, 1536, 2560), (124, 64, 768, 3584),               # over 96 rows
                           (381, 16, 1216, 1408), (384, 32, 640, 768), (209, 16, 1408, 704), (206, 24, 768, 640)):
         assert first(rows, E, N, K) == "grouped 256", (rows, E, N, K)
     # beside them: one round, longer rows, a row count clear of the edge
-    for rows, E, N, K, want in ((30, 64, 1280, 1280, "128x64"), (30, 8, 4096, 512, "128x64"), (60, 8, 3520, 512, "128x128"), (62, 32, 1664, 2560, "128x128"),
+    for rows, E, N, K, want in ((30, 64, 1280, 1280, "128x64"), (35, 64, 1152, 832, "128x64"), (30, 8, 4096, 512, "128x64"), (60, 8, 3520, 512, "128x128"), (62, 32, 1664, 2560, "128x128"),
                                 (38, 128, 1600, 832, "256x128"), (64, 64, 8192, 2048, "256x128"), (330, 16, 1216, 1408, "128x128"),
                                 (170, 16, 1408, 704, "128x192"), (209, 16, 1408, 4096, "128x192")):
         assert first(rows, E, N, K) == "stream " + want, (rows, E, N, K)
+    # two products per tile: shorter rows still pay
+    for rows, E, N, K, want in ((28, 128, 1600, 768, "stream 128x64"), (34, 16, 5952, 512, "grouped 256"), (80, 128, 896, 768, "stream 256x128"), (80, 128, 896, 704, "grouped 256")):
+        assert first(rows, E, N, K, "swiglu") == want, (rows, E, N, K)
