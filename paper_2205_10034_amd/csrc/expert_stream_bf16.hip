@@ -279,11 +279,11 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    768 0.9 (0.74), from 832 1.0 to 1.1 where the big tiles leave a fifth of their rounds empty, where they do not 0.86 to
 //    1.07 up to 1024 and 1.05 and more above; 256x128 up to 704 0.97 to 1.02 (0.86), above 1.04 to 1.14; 128x128 below 2048 1.02
 //    (0.90).
-// Skewed routing costs row tiles that the rule does not see: of 1300 whole expert blocks under even or random routing none
-// is slower than on the grouped GEMM by more than 3 %, of 1300 under Zipf or half-on-one-expert routing 16 are, by up to 9 %.  Over the same shapes under Zipf(1.2) masses the mean gain is
+// Skewed routing costs row tiles that the rule does not see.  Over the same shapes under Zipf(1.2) masses the mean gain is
 // within a tenth of that under even routing, but 128x192 loses 7 to 14 % where the hot expert's extra tiles open a second
 // round (16 experts, f 1600 -> d 1792, 115 rows: even 33 / 22, Zipf 35 / 40), and 64x32 up to 20 % with every row of a
-// step on one expert of 64.
+// step on one expert of 64.  Of 1300 whole expert blocks under even or random routing none is more than 3 % slower than on
+// the grouped GEMM, of 1300 under Zipf or half-on-one-expert routing 16 are, by up to 9 %.
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128 };
 int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
