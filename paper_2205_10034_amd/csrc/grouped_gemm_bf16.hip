@@ -761,6 +761,10 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     if (kt < KT) any_step(kt, s0, s1);
   };
 
+  constexpr bool AUX = EPI == EPI_DGELU || EPI == EPI_DSWIGLU;  // epilogues that read the activations' gradient
+  constexpr int AUX_PER_TB = EPI == EPI_DSWIGLU ? 2 : 2 * FB, AUX_STEPS = TB * AUX_PER_TB;
+  constexpr int AUX_AHEAD = !AUX ? 1 : AUX_STEPS < 8 ? AUX_STEPS : TOK > 256 ? 6 : 8;
+
   // ---- persistent loop over this workgroup's slots ------------------------------------------------
   bool have = walk.next(offsets, E, s_pref, ti);
   if (!have) return;
@@ -822,6 +826,38 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     const TileInfo done = ti;
     ti = nx;
     have = have_nx;
+    const int feat0 = first_feature(done.ntile);
+    const bool idle = idle_wave(done.ntile);
+    // where this lane's four features of member g of pair i0 start inside a 32-feature block (before the trade)
+    auto run_off = [&](int i0, int g) { return MI16 ? 16 * g + 4 * fhalf : 8 * (i0 + g) + 4 * fhalf; };
+    // where the eight features this lane stores for pair i0 start (after the trade)
+    auto store_off = [&](int i0) { return MI16 ? 16 * (fhalf & 1) + 8 * (fhalf >> 1) : 8 * (i0 + fhalf); };
+    // this lane's row of the tile for token block tb and pair i0
+    auto tile_row = [&](int tb, int i0) { return (tb * WT + wt) * 32 + (MI16 ? 16 * (i0 >> 1) : 0) + frow; };
+    // EPI_DGELU, EPI_DSWIGLU: the activations' gradient in the layout of the stores, 16 bytes per lane and step (the 8
+    // features this lane stores; rows past the tile's last re-read the last row).  AUX_AHEAD steps are requested ahead, the
+    // first ones before the next tile's stages (requested behind those and one step ahead of their use, every step waited
+    // for memory).  What bounds the epilogue now is that all CUs read it at once, 160 KB each per tile.  MI355X, us: 8 SwiGLU
+    // experts 2048 x 5632 of 1025 rows 394 -> 377, GELU 16 x 1024 x 4096 of 1024 rows 210 -> 207.  (Six ahead in the
+    // 320-row kernel: eight spill.)
+    auto aux_load = [&](int step) {
+      const int tb = step / AUX_PER_TB, fb = swiglu_tile(EPI) ? 0 : step / 2 % FB, i0 = 2 * (step % 2);
+      const int trow = min(tile_row(tb, i0), done.rows - 1);
+      return *reinterpret_cast<const u32x4*>(residual + (size_t)(done.row0 + trow) * N + feat0 +
+                                             (swiglu_tile(EPI) ? wf * 32 : wf * WFEAT + fb * 32) + store_off(i0));
+    };
+    u32x4 aux[AUX_AHEAD];
+    if constexpr (AUX) {
+#pragma unroll
+      for (int i = 0; i < AUX_AHEAD; ++i) aux[i] = aux_load(i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // step's gradient, its place in the ring going to step + AUX_AHEAD
+    auto take_aux = [&](int step) {
+      const u32x4 v = aux[step % AUX_AHEAD];
+      if (step + AUX_AHEAD < AUX_STEPS) aux[step % AUX_AHEAD] = aux_load(step + AUX_AHEAD);
+      return v;
+    };
     // every fragment read of real data finished before the last barrier; what the last sub-step read
     // afterwards is never used, so the stage buffers may be overwritten now
     const int done_set = bias_set;
@@ -846,14 +882,6 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     // as the feature half: lanes l and l+16 hold features 4m..4m+3 and 4m+4..4m+7 of both feature halves and
     // trade (v_permlane16_swap), after which the even 16-lane row owns 8 features of the first half and the odd
     // row 8 of the second.
-    const int feat0 = first_feature(done.ntile);
-    const bool idle = idle_wave(done.ntile);
-    // where this lane's four features of member g of pair i0 start inside a 32-feature block (before the trade)
-    auto run_off = [&](int i0, int g) { return MI16 ? 16 * g + 4 * fhalf : 8 * (i0 + g) + 4 * fhalf; };
-    // where the eight features this lane stores for pair i0 start (after the trade)
-    auto store_off = [&](int i0) { return MI16 ? 16 * (fhalf & 1) + 8 * (fhalf >> 1) : 8 * (i0 + fhalf); };
-    // this lane's row of the tile for token block tb and pair i0
-    auto tile_row = [&](int tb, int i0) { return (tb * WT + wt) * 32 + (MI16 ? 16 * (i0 >> 1) : 0) + frow; };
     auto trade = [&](uint32_t x, uint32_t y) {
       if constexpr (MI16) return __builtin_amdgcn_permlane16_swap(x, y, false, false);
       else return __builtin_amdgcn_permlane32_swap(x, y, false, false);
@@ -875,16 +903,6 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
           row_gw[tb * RSETS + rs] = gate_w[row_tok[tb * RSETS + rs]];
         }
     }
-    // EPI_DGELU: the activations' gradient for one (token block, feature block, group pair) step, loaded one
-    // step ahead of its use in the layout of the stores: 16 bytes per lane, the 8 features this lane stores
-    // (rows past the tile's last re-read the last row)
-    auto aux_load = [&](int tb, int fb, int i0) {
-      const int trow = min(tile_row(tb, i0), done.rows - 1);
-      return *reinterpret_cast<const u32x4*>(residual + (size_t)(done.row0 + trow) * N + feat0 +
-                                             (swiglu_tile(EPI) ? wf * 32 : wf * WFEAT + fb * 32) + store_off(i0));
-    };
-    u32x4 aux_next = {0u, 0u, 0u, 0u};
-    if constexpr (EPI == EPI_DGELU || EPI == EPI_DSWIGLU) aux_next = aux_load(0, 0, 0);
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
       // 32x32x16: lanes l and l+32 share the row, they stay or leave together; the rows grow with tb, so nothing
@@ -901,10 +919,9 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
         for (int i0 = 0; i0 < 4; i0 += 2) {
           uint16_t* orow2 = out + out_row(i0) * (size_t)(2 * N);  // [d_g | d_u] rows
           // aux in the layout of the stores, the halves traded back (as in EPI_DGELU)
-          const u32x2 sx = trade(aux_next.x, aux_next.z);
-          const u32x2 sy = trade(aux_next.y, aux_next.w);
-          if (i0 + 2 < 4) aux_next = aux_load(tb, 0, i0 + 2);
-          else if (tb + 1 < TB) aux_next = aux_load(tb + 1, 0, 0);
+          const u32x4 av = take_aux(tb * AUX_PER_TB + i0 / 2);
+          const u32x2 sx = trade(av.x, av.z);
+          const u32x2 sy = trade(av.y, av.w);
           float pg[8], pu[8];
 #pragma unroll
           for (int g = 0; g < 2; ++g) {
@@ -966,13 +983,9 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
               float dh[8];
               // the store's trade of halves, backwards: every lane gets its own four features of both members
               // of the pair (element g of sx, sy: this lane's features of member g)
-              const u32x2 sx = trade(aux_next.x, aux_next.z);
-              const u32x2 sy = trade(aux_next.y, aux_next.w);
-              {
-                int ni0 = i0 + 2, nfb = fb, ntb = tb;
-                if (ni0 == 4) { ni0 = 0; if (++nfb == FB) { nfb = 0; ++ntb; } }
-                if (ntb < TB) aux_next = aux_load(ntb, nfb, ni0);
-              }
+              const u32x4 av = take_aux(tb * AUX_PER_TB + fb * 2 + i0 / 2);
+              const u32x2 sx = trade(av.x, av.z);
+              const u32x2 sy = trade(av.y, av.w);
 #pragma unroll
               for (int g = 0; g < 2; ++g) {
                 const u32x2 rv = {g ? sx.y : sx.x, g ? sy.y : sy.x};
