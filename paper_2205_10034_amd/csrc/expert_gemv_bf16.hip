@@ -27,6 +27,15 @@ namespace {
 constexpr int GV_MAX_ROWS = 16;  // rows of one expert, at most (= assignments of the whole step)
 constexpr int GV_WAVES = 4;
 
+// NT: non-temporal (nobody else reads a weight, and the call's weights exceed the last-level cache, weights_exceed_cache)
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <bool NT>
+__device__ __forceinline__ uint4 load_weights(const uint16_t* p) {
+  if constexpr (!NT) return *reinterpret_cast<const uint4*>(p);
+  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return uint4{v.x, v.y, v.z, v.w};
+}
+
 enum GvEpi { GV_GELU = 0, GV_SWIGLU = 1, GV_BIAS = 2, GV_COMBINE = 3 };
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -45,7 +54,7 @@ __device__ __forceinline__ float gelu_exact(float u) { return 0.5f * u * erfcf(-
 // GATHER: act is x[T, K] and row r reads token row_map[r] mod T.
 // KSPLIT: the four wavefronts of a workgroup share one set of GV_FPW weight rows and split the contraction index
 // (their sums meet in LDS, in wavefront order): four times the workgroups, for long rows and few experts.
-template <int EPI, bool GATHER, int GV_ROWS, int GV_FPW, bool KSPLIT>
+template <int EPI, bool GATHER, int GV_ROWS, int GV_FPW, bool KSPLIT, bool NT>
 __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
     const uint16_t* __restrict__ act, const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb,
     const uint16_t* __restrict__ bias, const int32_t* __restrict__ offsets, uint16_t* out,
@@ -101,7 +110,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
     for (int kb = (KSPLIT ? (int)threadIdx.x : lane) * 8; kb < K; kb += (KSPLIT ? GV_WAVES : 1) * 64 * 8) {
       uint4 wv[GV_FPW], xv[GV_ROWS];
   #pragma unroll
-      for (int j = 0; j < GV_FPW; ++j) wv[j] = *reinterpret_cast<const uint4*>(wrow[j] + kb);
+      for (int j = 0; j < GV_FPW; ++j) wv[j] = load_weights<NT>(wrow[j] + kb);
   #pragma unroll
       for (int r = 0; r < GV_ROWS; ++r)
         if (r < rows) xv[r] = *reinterpret_cast<const uint4*>(xrow[r] + kb);
@@ -207,6 +216,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
 // residual + sum_j w_j * yd[row_j] from those rounded values, in float32 and in the order of the combine kernel.
 constexpr int C1_FPW = 8;
 
+template <bool NT>
 __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_combine1_kernel(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w2, const uint16_t* __restrict__ bias,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ a2r, const float* __restrict__ topk_w,
@@ -234,7 +244,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_combine1_kernel(
     for (int kb = (int)threadIdx.x * 8; kb < K; kb += GV_WAVES * 64 * 8) {
       uint4 wv[C1_FPW];
 #pragma unroll
-      for (int f = 0; f < C1_FPW; ++f) wv[f] = *reinterpret_cast<const uint4*>(wbase + (int64_t)f * K + kb);
+      for (int f = 0; f < C1_FPW; ++f) wv[f] = load_weights<NT>(wbase + (int64_t)f * K + kb);
       const uint4 xv = *reinterpret_cast<const uint4*>(xrow + kb);
       const float x0 = lo16(xv.x), x1 = hi16(xv.x), x2 = lo16(xv.y), x3 = hi16(xv.y);
       const float x4 = lo16(xv.z), x5 = hi16(xv.z), x6 = lo16(xv.w), x7 = hi16(xv.w);
@@ -288,8 +298,9 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
   reps = reps < 1 ? 1 : reps > 8 ? 8 : reps;
   while (reps > 1 && (blocks % reps || (int64_t)(blocks / reps) * A < 512)) --reps;
   const dim3 grid(blocks / reps, A), block(GV_WAVES * 64);
+  const bool nt = weights_exceed_cache(cfg);
 #define MOESYS_GEMV(G, S)                                                                                                  \
-  hipLaunchKernelGGL((expert_gemv_kernel<EPI, G, ROWS, FPW, S>), grid, block, 0, s, act, wa, wb, bias, offsets, out, row_map, \
+  hipLaunchKernelGGL((nt ? expert_gemv_kernel<EPI, G, ROWS, FPW, S, true> : expert_gemv_kernel<EPI, G, ROWS, FPW, S, false>), grid, block, 0, s, act, wa, wb, bias, offsets, out, row_map, \
                      gate_w, residual, eoff, cfg->T, cfg->E, N, K, reps)
   if (gather) { if (ksplit) MOESYS_GEMV(true, true); else MOESYS_GEMV(true, false); }
   else { if (ksplit) MOESYS_GEMV(false, true); else MOESYS_GEMV(false, false); }
@@ -326,7 +337,7 @@ int32_t launch_expert_gemv_combine_one_token(const moe_config* cfg, const void* 
                                              const int32_t* offsets, const int32_t* a2r, const float* topk_w,
                                              const void* residual, void* yd, void* out, const int64_t* eoff, hipStream_t s) {
   if (!expert_gemv_combine_one_token_applies(cfg)) return fail(MOE_ERR_UNSUPPORTED, "expert GEMV: not a one-token step");
-  hipLaunchKernelGGL(expert_gemv_combine1_kernel, dim3(cfg->d_model / C1_FPW), dim3(GV_WAVES * 64), 0, s, (const uint16_t*)h,
+  hipLaunchKernelGGL(weights_exceed_cache(cfg) ? expert_gemv_combine1_kernel<true> : expert_gemv_combine1_kernel<false>, dim3(cfg->d_model / C1_FPW), dim3(GV_WAVES * 64), 0, s, (const uint16_t*)h,
                      (const uint16_t*)w2, (const uint16_t*)bias, offsets, a2r, topk_w, (const uint16_t*)residual, (uint16_t*)yd,
                      (uint16_t*)out, eoff, cfg->E, cfg->d_model, cfg->d_ff, cfg->k);
   return check_hip(hipGetLastError(), "expert GEMV launch");

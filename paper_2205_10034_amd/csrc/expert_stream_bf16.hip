@@ -43,6 +43,7 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
 __device__ __forceinline__ float lo16(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi16(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 __device__ __forceinline__ float gelu_exact(float u) { return 0.5f * u * erfcf(-u * 0.70710678118654752f); }
+constexpr int LOAD_NT = 2;  // cache policy of a buffer load: non-temporal
 // s_waitcnt operand: at most n vector memory operations and no LDS operation in flight
 constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
 
@@ -52,7 +53,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t stream_rsrc(const void* base, 
 }
 #endif
 
-template <int EPI, bool GATHER, typename S>
+// NT: the call's weights exceed the last-level cache (weights_exceed_cache)
+template <int EPI, bool GATHER, bool NT, typename S>
 __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     const uint16_t* __restrict__ act, const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb,
     const uint16_t* __restrict__ bias, const int32_t* __restrict__ offsets, uint16_t* out,
@@ -105,8 +107,11 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   }
   const uint16_t* a_ptr = GATHER ? act : act + (int64_t)t.row0 * K;
   const uint32_t a_bytes = (uint32_t)(GATHER ? T : t.rows) * (uint32_t)k2, w_bytes = (uint32_t)OUTF * (uint32_t)k2;
+  // Weights that only this workgroup reads pass the caches by where the call's weights do not fit them (a second row tile
+  // of an expert finds them in the XCD's L2).  MI355X, us, first / second product: 8 tokens top-2 of 64 experts 2048 x 8192
+  // 91 / 86 -> 83 / 76 (5.6 and 6.2 TB/s); 96 tokens top-2 of 8 SwiGLU experts 4096 x 14336 338 / 180 -> 297 / 162 (6.3 and 5.8).
   // (past the last stage the descriptors are empty: nothing is read, and the number of loads in flight is always the same)
-  auto issue = [&](int kt, unsigned char* stage) {
+  auto issue = [&](auto policy, int kt, unsigned char* stage) {
     const bool live = kt < KT;
     const __amdgpu_buffer_rsrc_t ra = stream_rsrc(a_ptr, live ? a_bytes : 0u), rw = stream_rsrc(wa + wbase, live ? w_bytes : 0u);
 #pragma unroll
@@ -114,8 +119,12 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
       const int blk = block(i);
       __amdgpu_buffer_rsrc_t r = i < W_LOADS ? rw : ra;
       if (EPI == ST_SWIGLU && i < W_LOADS) r = stream_rsrc(((blk & 1) ? wb : wa) + wbase, live ? w_bytes : 0u);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(stage + (i < W_LOADS ? 0 : W_BYTES) + blk * 1024),
-                                               16, voff[i], kt * 128, 0, 0);
+      if (i < W_LOADS)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(stage + blk * 1024), 16, voff[i], kt * 128, 0,
+                                                 decltype(policy)::value);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(stage + W_BYTES + blk * 1024), 16, voff[i],
+                                                 kt * 128, 0, 0);
     }
   };
   // ---- fragments: 16 rows x 32 values, lane = row + 16 * (chunk of the four)
@@ -153,28 +162,32 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   // Stage kt is multiplied while stages kt+1 .. kt+STAGES-1 are on their way.  A wavefront waits for its own share of
   // stage kt (loads retire in order) and for its reads of the stage before, then the workgroup meets: stage kt is whole
   // and the buffer of stage kt-1 is free for stage kt+STAGES-1.
-  auto step = [&](auto i, int kt) {
+  auto step = [&](auto policy, auto i, int kt) {
     __builtin_amdgcn_s_waitcnt(wait_vm((STAGES - 2) * LOADS));
     __builtin_amdgcn_s_barrier();
-    issue(kt + STAGES - 1, stage_of(std::integral_constant<int, decltype(i)::value + STAGES - 1>{}));
+    issue(policy, kt + STAGES - 1, stage_of(std::integral_constant<int, decltype(i)::value + STAGES - 1>{}));
     compute(stage_of(i));
   };
-  issue(0, s0);
-  issue(1, s1);
-  if constexpr (STAGES > 3) issue(2, s2);
-  if constexpr (STAGES > 4) issue(3, s3);
-  // (left by breaks: on every way round the loop all stages were requested, which is what lets the compiler see that no
-  // further wait is needed before a stage is read)
-  for (int kt = 0;;) {
-    step(std::integral_constant<int, 0>{}, kt);
-    if (++kt == KT) break;
-    step(std::integral_constant<int, 1>{}, kt);
-    if (++kt == KT) break;
-    step(std::integral_constant<int, 2>{}, kt);
-    if (++kt == KT) break;
-    if constexpr (STAGES > 3) { step(std::integral_constant<int, 3>{}, kt); if (++kt == KT) break; }
-    if constexpr (STAGES > 4) { step(std::integral_constant<int, 4>{}, kt); if (++kt == KT) break; }
-  }
+  auto contract = [&](auto policy) {
+    issue(policy, 0, s0);
+    issue(policy, 1, s1);
+    if constexpr (STAGES > 3) issue(policy, 2, s2);
+    if constexpr (STAGES > 4) issue(policy, 3, s3);
+    // (left by breaks: on every way round the loop all stages were requested, which is what lets the compiler see that no
+    // further wait is needed before a stage is read)
+    for (int kt = 0;;) {
+      step(policy, std::integral_constant<int, 0>{}, kt);
+      if (++kt == KT) break;
+      step(policy, std::integral_constant<int, 1>{}, kt);
+      if (++kt == KT) break;
+      step(policy, std::integral_constant<int, 2>{}, kt);
+      if (++kt == KT) break;
+      if constexpr (STAGES > 3) { step(policy, std::integral_constant<int, 3>{}, kt); if (++kt == KT) break; }
+      if constexpr (STAGES > 4) { step(policy, std::integral_constant<int, 4>{}, kt); if (++kt == KT) break; }
+    }
+  };
+  if (NT && t.tiles == 1) contract(std::integral_constant<int, LOAD_NT>{});
+  else contract(std::integral_constant<int, 0>{});
   __builtin_amdgcn_s_waitcnt(wait_vm(0));  // (the empty loads retire)
 
   // GELU: by the exact function for a few elements per lane, by the table (built in the first stage's buffer) for many
@@ -250,7 +263,8 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
   const int64_t grid = row_tile_grid(cfg, S::TM, n_tiles);
   if (grid > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "expert stream: too many tiles");
   if (max_rows(cfg) == 0) return MOE_OK;
-  hipLaunchKernelGGL((expert_stream_kernel<EPI, GATHER, S>), dim3((unsigned)grid), dim3(S::WAVES * 64), 0, s, act, wa, wb, bias,
+  auto kern = weights_exceed_cache(cfg) ? expert_stream_kernel<EPI, GATHER, true, S> : expert_stream_kernel<EPI, GATHER, false, S>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(S::WAVES * 64), 0, s, act, wa, wb, bias,
                      offsets, out, row_map, gate_w, residual, eoff, clear_ctr, cfg->T, cfg->E, N, K, n_tiles);
   return check_hip(hipGetLastError(), "expert stream launch");
 }

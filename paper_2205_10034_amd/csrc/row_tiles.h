@@ -13,7 +13,7 @@ inline int64_t row_tile_grid(const moe_config* cfg, int tile_rows, int n_tiles) 
   return (mt * n_tiles + 7) / 8 * 8;
 }
 
-struct RowTile { int expert, row0, rows, nt; };  // first dispatched row, valid rows, feature tile
+struct RowTile { int expert, row0, rows, nt, tiles; };  // first dispatched row, valid rows, feature tile, row tiles of the expert
 
 // Tile of workgroup blockIdx.x, false if there is none.  Tiles are numbered expert by expert, feature tile by feature
 // tile, row tiles innermost, and every XCD (workgroup b runs on XCD b mod 8) takes one contiguous eighth: the row tiles
@@ -54,6 +54,7 @@ __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ offset
   t.row0 = offsets[e] + m * TM;
   t.rows = min(TM, offsets[e + 1] - t.row0);
   t.nt = nt;
+  t.tiles = tiles;
   return true;
 }
 
