@@ -30,10 +30,10 @@ enum StreamEpi { ST_GELU = 0, ST_SWIGLU = 1, ST_BIAS = 2, ST_COMBINE = 3 };
 
 constexpr int ST_KS = 64;     // values of the contraction index per stage: LDS rows of 128 bytes, eight 16-byte chunks
 
-// NWF x NWM wavefronts, each FB blocks of 16 weight rows x RB blocks of 16 rows
-template <int NWF_, int NWM_, int FB_, int RB_, int STAGES_>
+// NWF x NWM wavefronts, each FB blocks of 16 weight rows x RB blocks of 16 rows; stages of weights, and of rows if fewer
+template <int NWF_, int NWM_, int FB_, int RB_, int STAGES_, int ROW_STAGES_ = STAGES_>
 struct StreamShape {
-  static constexpr int NWF = NWF_, NWM = NWM_, FB = FB_, RB = RB_, STAGES = STAGES_;
+  static constexpr int NWF = NWF_, NWM = NWM_, FB = FB_, RB = RB_, STAGES = STAGES_, ROW_STAGES = ROW_STAGES_;
   static constexpr int WAVES = NWF * NWM, WROWS = NWF * FB * 16, TM = NWM * RB * 16;
 };
 
@@ -61,19 +61,20 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     const int32_t* __restrict__ row_map, const float* __restrict__ gate_w, const uint16_t* residual,
     const int64_t* __restrict__ eoff, int32_t* __restrict__ clear_ctr, int T, int E, int N, int K, int n_tiles) {
 #if defined(__HIP_DEVICE_COMPILE__)  // (buffer descriptors are device-only types)
-  constexpr int TM = S::TM, STAGES = S::STAGES, ST_WAVES = S::WAVES, FB = S::FB, RB = S::RB;
+  constexpr int TM = S::TM, STAGES = S::STAGES, ROW_STAGES = S::ROW_STAGES, ST_WAVES = S::WAVES, FB = S::FB, RB = S::RB;
   constexpr int OUTF = EPI == ST_SWIGLU ? S::WROWS / 2 : S::WROWS;  // output features per workgroup
-  constexpr int W_BYTES = S::WROWS * 128, STAGE = W_BYTES + TM * 128;
+  constexpr int W_BYTES = S::WROWS * 128, A_BYTES = TM * 128;
+  constexpr bool SPLIT = ROW_STAGES != STAGES;  // the shape for 97 to 160 rows
   constexpr int A_BLKS = TM / 8;  // blocks of eight rows, one load each
   constexpr int W_LOADS = W_BYTES / 1024 / ST_WAVES, A_LOADS = A_BLKS / ST_WAVES, LOADS = W_LOADS + A_LOADS;
   static_assert(W_BYTES % (1024 * ST_WAVES) == 0 && A_BLKS % ST_WAVES == 0, "whole loads of 8 rows per wavefront");
-  static_assert(STAGES >= 3 && STAGES <= 5, "the K loop below");
+  static_assert(STAGES >= 3 && STAGES <= 5 && (ROW_STAGES == STAGES || (STAGES == 3 && ROW_STAGES == 2)), "the K loop below");
   // one array per stage: the compiler can then tell the stages being filled from the one being read
-  __shared__ __attribute__((aligned(1024))) unsigned char s0[STAGE];
-  __shared__ __attribute__((aligned(1024))) unsigned char s1[STAGE];
-  __shared__ __attribute__((aligned(1024))) unsigned char s2[STAGE];
-  __shared__ __attribute__((aligned(1024))) unsigned char s3[STAGES > 3 ? STAGE : 16];
-  __shared__ __attribute__((aligned(1024))) unsigned char s4[STAGES > 4 ? STAGE : 16];
+  __shared__ __attribute__((aligned(1024))) unsigned char w0[W_BYTES], a0[A_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char w1[W_BYTES], a1[A_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char w2[W_BYTES], a2[ROW_STAGES > 2 ? A_BYTES : 16];
+  __shared__ __attribute__((aligned(1024))) unsigned char w3[STAGES > 3 ? W_BYTES : 16], a3[ROW_STAGES > 3 ? A_BYTES : 16];
+  __shared__ __attribute__((aligned(1024))) unsigned char w4[STAGES > 4 ? W_BYTES : 16], a4[ROW_STAGES > 4 ? A_BYTES : 16];
   if (clear_ctr && blockIdx.x == 0 && threadIdx.x < 8) clear_ctr[threadIdx.x] = 0;  // (a grouped GEMM may run next)
   RowTile t;
   if (!find_row_tile<TM>(offsets, E, n_tiles, t)) return;
@@ -104,6 +105,8 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
       }
     }
     voff[i] = r * k2 + chunk * 16;
+    // (a third of this shape's rows may be missing: out of range, they read as zero without going to memory)
+    if (SPLIT && i >= W_LOADS && row >= t.rows) voff[i] = 0x7fffffff;
   }
   const uint16_t* a_ptr = GATHER ? act : act + (int64_t)t.row0 * K;
   const uint32_t a_bytes = (uint32_t)(GATHER ? T : t.rows) * (uint32_t)k2, w_bytes = (uint32_t)OUTF * (uint32_t)k2;
@@ -111,68 +114,96 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   // of an expert finds them in the XCD's L2).  MI355X, us, first / second product: 8 tokens top-2 of 64 experts 2048 x 8192
   // 91 / 86 -> 83 / 76 (5.6 and 6.2 TB/s); 96 tokens top-2 of 8 SwiGLU experts 4096 x 14336 338 / 180 -> 297 / 162 (6.3 and 5.8).
   // (past the last stage the descriptors are empty: nothing is read, and the number of loads in flight is always the same)
-  auto issue = [&](auto policy, int kt, unsigned char* stage) {
+  auto issue_w = [&](auto policy, int kt, unsigned char* stage) {
     const bool live = kt < KT;
-    const __amdgpu_buffer_rsrc_t ra = stream_rsrc(a_ptr, live ? a_bytes : 0u), rw = stream_rsrc(wa + wbase, live ? w_bytes : 0u);
+    const __amdgpu_buffer_rsrc_t rw = stream_rsrc(wa + wbase, live ? w_bytes : 0u);
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
+    for (int i = 0; i < W_LOADS; ++i) {
       const int blk = block(i);
-      __amdgpu_buffer_rsrc_t r = i < W_LOADS ? rw : ra;
-      if (EPI == ST_SWIGLU && i < W_LOADS) r = stream_rsrc(((blk & 1) ? wb : wa) + wbase, live ? w_bytes : 0u);
-      if (i < W_LOADS)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(stage + blk * 1024), 16, voff[i], kt * 128, 0,
-                                                 decltype(policy)::value);
-      else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(stage + W_BYTES + blk * 1024), 16, voff[i],
-                                                 kt * 128, 0, 0);
+      __amdgpu_buffer_rsrc_t r = rw;
+      if (EPI == ST_SWIGLU) r = stream_rsrc(((blk & 1) ? wb : wa) + wbase, live ? w_bytes : 0u);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(stage + blk * 1024), 16, voff[i], kt * 128, 0,
+                                               decltype(policy)::value);
     }
+  };
+  auto issue_a = [&](int kt, unsigned char* stage) {
+    const __amdgpu_buffer_rsrc_t ra = stream_rsrc(a_ptr, kt < KT ? a_bytes : 0u);
+#pragma unroll
+    for (int i = W_LOADS; i < LOADS; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(stage + block(i) * 1024), 16, voff[i], kt * 128, 0, 0);
   };
   // ---- fragments: 16 rows x 32 values, lane = row + 16 * (chunk of the four)
   const int frow = lane & 15, fch = lane >> 4;
   const int wf = wave % S::NWF, wm = wave / S::NWF;  // row block b of row group wm is block b * NWM + wm of the tile
   const int in_row = frow * 128 + ((fch ^ ((frow >> 1) & 7)) << 4);   // (the key repeats every 16 rows) second 32 values: ^ 64
-  const int w_off = wf * FB * 2048 + in_row, a_off = W_BYTES + wm * 2048 + in_row;
+  const int w_off = wf * FB * 2048 + in_row, a_off = wm * 2048 + in_row;
   f32x4 acc[FB][RB];
 #pragma unroll
   for (int f = 0; f < FB; ++f)
 #pragma unroll
     for (int b = 0; b < RB; ++b) acc[f][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](const unsigned char* stage) {
+  auto compute = [&](const unsigned char* ws, const unsigned char* as) {
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       bf16x8 w[FB];
 #pragma unroll
-      for (int f = 0; f < FB; ++f) w[f] = *reinterpret_cast<const bf16x8*>(stage + (w_off ^ (kk << 6)) + f * 2048);
+      for (int f = 0; f < FB; ++f) w[f] = *reinterpret_cast<const bf16x8*>(ws + (w_off ^ (kk << 6)) + f * 2048);
 #pragma unroll
       for (int b = 0; b < RB; ++b) {
-        const bf16x8 r = *reinterpret_cast<const bf16x8*>(stage + (a_off ^ (kk << 6)) + b * S::NWM * 2048);
+        const bf16x8 r = *reinterpret_cast<const bf16x8*>(as + (a_off ^ (kk << 6)) + b * S::NWM * 2048);
 #pragma unroll
         for (int f = 0; f < FB; ++f) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[f], r, acc[f][b], 0, 0, 0);
       }
     }
+    if constexpr (SPLIT) {
+      // the next stages' loads between the multiplications: in one burst ahead of them the wavefronts wait for the queue
+      __builtin_amdgcn_sched_group_barrier(0x100, FB + 1, 0);                         // DS read
+#pragma unroll
+      for (int q = 0; q < 2 * RB; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, FB, 0);                           // MFMA
+        if (q + 2 == RB) __builtin_amdgcn_sched_group_barrier(0x100, FB + 1, 0);
+        else __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (q < LOADS) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);             // VMEM
+      }
+    }
   };
-  auto stage_of = [&](auto i) -> unsigned char* {
+  auto w_of = [&](auto i) -> unsigned char* {
     constexpr int I = decltype(i)::value % STAGES;
-    if constexpr (I == 0) return s0;
-    else if constexpr (I == 1) return s1;
-    else if constexpr (I == 2) return s2;
-    else if constexpr (I == 3) return s3;
-    else return s4;
+    if constexpr (I == 0) return w0;
+    else if constexpr (I == 1) return w1;
+    else if constexpr (I == 2) return w2;
+    else if constexpr (I == 3) return w3;
+    else return w4;
   };
-  // Stage kt is multiplied while stages kt+1 .. kt+STAGES-1 are on their way.  A wavefront waits for its own share of
-  // stage kt (loads retire in order) and for its reads of the stage before, then the workgroup meets: stage kt is whole
-  // and the buffer of stage kt-1 is free for stage kt+STAGES-1.
+  auto a_of = [&](auto i) -> unsigned char* {
+    constexpr int I = decltype(i)::value % ROW_STAGES;
+    if constexpr (I == 0) return a0;
+    else if constexpr (I == 1) return a1;
+    else if constexpr (I == 2) return a2;
+    else if constexpr (I == 3) return a3;
+    else return a4;
+  };
+  // Stage kt is multiplied while the weights of stages kt+1 .. kt+STAGES-1 (and the rows of kt+1 .. kt+ROW_STAGES-1) are on
+  // their way.  A wavefront waits for its own share of stage kt (loads retire in order; a step requests rows before
+  // weights) and for its reads of the stage before, then the workgroup meets: stage kt is whole and the buffers of stage
+  // kt-1 are free.
+  constexpr int AHEAD = ROW_STAGES == STAGES ? (STAGES - 2) * LOADS : (ROW_STAGES - 2) * LOADS + W_LOADS;
   auto step = [&](auto policy, auto i, int kt) {
-    __builtin_amdgcn_s_waitcnt(wait_vm((STAGES - 2) * LOADS));
+    constexpr int I = decltype(i)::value;
+    __builtin_amdgcn_s_waitcnt(wait_vm(AHEAD));
     __builtin_amdgcn_s_barrier();
-    issue(policy, kt + STAGES - 1, stage_of(std::integral_constant<int, decltype(i)::value + STAGES - 1>{}));
-    compute(stage_of(i));
+    issue_a(kt + ROW_STAGES - 1, a_of(std::integral_constant<int, I + ROW_STAGES - 1>{}));
+    issue_w(policy, kt + STAGES - 1, w_of(std::integral_constant<int, I + STAGES - 1>{}));
+    compute(w_of(i), a_of(i));
   };
   auto contract = [&](auto policy) {
-    issue(policy, 0, s0);
-    issue(policy, 1, s1);
-    if constexpr (STAGES > 3) issue(policy, 2, s2);
-    if constexpr (STAGES > 4) issue(policy, 3, s3);
+    if constexpr (ROW_STAGES == STAGES) issue_a(0, a0);
+    issue_w(policy, 0, w0);
+    if constexpr (ROW_STAGES == STAGES) issue_a(1, a1);
+    else issue_a(0, a0);
+    issue_w(policy, 1, w1);
+    if constexpr (STAGES > 3) { issue_a(2, a2); issue_w(policy, 2, w2); }
+    if constexpr (STAGES > 4) { issue_a(3, a3); issue_w(policy, 3, w3); }
     // (left by breaks: on every way round the loop all stages were requested, which is what lets the compiler see that no
     // further wait is needed before a stage is read)
     for (int kt = 0;;) {
@@ -182,8 +213,9 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
       if (++kt == KT) break;
       step(policy, std::integral_constant<int, 2>{}, kt);
       if (++kt == KT) break;
-      if constexpr (STAGES > 3) { step(policy, std::integral_constant<int, 3>{}, kt); if (++kt == KT) break; }
-      if constexpr (STAGES > 4) { step(policy, std::integral_constant<int, 4>{}, kt); if (++kt == KT) break; }
+      if constexpr (STAGES > 3 || ROW_STAGES == 2) { step(policy, std::integral_constant<int, 3>{}, kt); if (++kt == KT) break; }
+      if constexpr (STAGES > 4 || ROW_STAGES == 2) { step(policy, std::integral_constant<int, 4>{}, kt); if (++kt == KT) break; }
+      if constexpr (ROW_STAGES == 2) { step(policy, std::integral_constant<int, 5>{}, kt); if (++kt == KT) break; }
     }
   };
   if (NT && t.tiles == 1) contract(std::integral_constant<int, LOAD_NT>{});
@@ -192,8 +224,8 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
 
   // GELU: by the exact function for a few elements per lane, by the table (built in the first stage's buffer) for many
   constexpr bool TABLE = EPI == ST_GELU && FB * RB >= 8;
-  static_assert(PHI_N * 8 <= STAGE, "the table fits a stage");
-  phi_f32x2* const phi = reinterpret_cast<phi_f32x2*>(s0);
+  static_assert(PHI_N * 8 <= W_BYTES, "the table fits a stage of weights");
+  phi_f32x2* const phi = reinterpret_cast<phi_f32x2*>(w0);
   const float phi_add = phi_addend(phi);
   if constexpr (TABLE) {
     __syncthreads();
@@ -298,7 +330,15 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 // round (16 experts, f 1600 -> d 1792, 115 rows: even 33 / 22, Zipf 35 / 40), and 64x32 up to 20 % with every row of a
 // step on one expert of 64.  Of 1300 whole expert blocks under even or random routing none is more than 3 % slower than on
 // the grouped GEMM, of 1300 under Zipf or half-on-one-expert routing 16 are, by up to 9 %.
-enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128 };
+//  - 97 to 160 rows otherwise: 256x192, three stages of weights and two of rows in the LDS; the grouped GEMM has one stage of
+//    weights on its way and waits for it.  Over 126 random products of 97 to 180 rows 1.12 on average (grouped / here): 64
+//    experts, 131 rows, f 3456 -> d 3264 366 / 314; 16 SwiGLU, 112 rows, 3008 -> 8704 467 / 398; 64 SwiGLU, 128 rows, 2048 -> 4096
+//    523 / 466 and 283 / 210; few tiles 1.2 to 1.3.  Not beyond 160 rows, where experts need a second tile (32 experts, 169
+//    rows, 5248 -> 3904 326 / 350), nor for short rows, where the start and end of these tiles weigh: below 832 values (128, 147
+//    rows, 576 -> 4416 212 / 226), from 137 rows below 1408 (64, 143 rows, 1280 -> 3392 189 / 204), first products, with an activation in their end, below 1152 (32, 113 rows, 896 -> 9152 148 / 154) and
+//    in more than six rounds below 2240 (64, 128 rows, 2048 -> 8192 469 / 479).  First products of at most a round stay with the
+//    grouped GEMM too, where the line below 128x192 has them; they would gain 1.05 to 1.2.
+enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128, STREAM_256x192 };
 int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
   // Buffer sizes and offsets of a tile are 32-bit.  The line is that of the grouped GEMM's largest row tile, so that what
@@ -334,6 +374,10 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (wide && (big <= 96 || (big <= 128 && rows <= 152)) && tiles(128, 192) <= (K >= 4096 ? 512 : 256)) return STREAM_128x192;
   // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)
   if (wide && rows > 192 && big > 128 && big <= 192 && tiles_of(128, 128, rows + (rows * 2 + 24) / 25) <= 512) return STREAM_128x128;
+  if (N >= (swiglu ? 128 : 256) && rows > 96 && rows <= 160) {
+    const bool first = N == cfg->d_ff && K == cfg->d_model;
+    if (!first ? K >= (rows > 136 ? 1408 : 832) : !one_round(256, 192) && K >= (tiles(256, 192) > 6 * 256 ? 2240 : 1152)) return STREAM_256x192;
+  }
   return STREAM_NONE;
 }
 
@@ -350,6 +394,7 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
     case STREAM_128x192: MOE_STREAM(4, 2, 2, 6, 4);
     case STREAM_256x64: MOE_STREAM(4, 2, 4, 2, 4);
     case STREAM_256x128: MOE_STREAM(4, 2, 4, 4, 3);
+    case STREAM_256x192: MOE_STREAM(4, 2, 4, 6, 3, 2);
   }
 #undef MOE_STREAM
   return fail(MOE_ERR_UNSUPPORTED, "expert stream: shape outside its range");
@@ -361,7 +406,7 @@ bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu) { r
 
 // name of the shape (weight rows x rows), for tests
 const char* expert_stream_shape(const moe_config* cfg, int N, int K, bool swiglu) {
-  static const char* const names[] = {"", "stream 64x32", "stream 64x64", "stream 128x64", "stream 128x128", "stream 128x192", "stream 256x64", "stream 256x128"};
+  static const char* const names[] = {"", "stream 64x32", "stream 64x64", "stream 128x64", "stream 128x128", "stream 128x192", "stream 256x64", "stream 256x128", "stream 256x192"};
   return names[pick_stream(cfg, N, K, swiglu)];
 }
 
