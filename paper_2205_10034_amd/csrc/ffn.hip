@@ -3,6 +3,8 @@
 //
 // The bf16 MFMA grouped GEMM lives in grouped_gemm_bf16.hip; the float32 path
 // below multiplies on the float32 matrix instructions.
+#include <cmath>
+#include <type_traits>
 #include "moesys_internal.h"
 #include "row_tiles.h"
 
@@ -149,6 +151,167 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
   }
 }
 
+// Up to 16 BU rows x 64 FBW weight rows per workgroup, four wavefronts of 16 FBW weight rows each on v_mfma_f32_16x16x4_f32,
+// weights as the first operand: a lane ends up with four consecutive features of one row.  An expert's rows are dealt out
+// evenly over the fewest tiles in units of 16, and the K loop is compiled once per number of units, so a tile multiplies what
+// it holds.  A step is 32 values of the contraction index: operands go through registers into one of two LDS stages (16-byte
+// chunks XORed with half the row) while the other is multiplied; the loads of the step after next stay in flight across the
+// barrier, and a unit's rows of the second half of a step are read as soon as those of the first have been multiplied.
+// Two shapes, by pick_f32: 80 rows, three workgroups per CU (SwiGLU: 128 weight rows, two products), and 160 rows x 128 weight
+// rows, two per CU.  Bound by the float32 MFMAs (busy 75 % with even rows) and by whole rounds of tiles.  Measured on MI355X
+// against the 64 x 64 kernel (us): 80 rows, 140 random products 1.07 on average where the rule below picks it, 1.10 each
+// (4 experts of 1538 rows, 3712 -> 192 149 / 106; 8 of 268, 3648 -> 960 206 / 164; 16 of 69, 768 -> 3584 114 / 82); 160 rows, 16
+// experts of 256, 1024 -> 4096 -> 1024: 354 / 322 and 375 / 334 (107 and 103 TFLOP/s).
+// Workgroup barrier for data exchanged through LDS: waits for this wavefront's LDS operations only, the loads of the step after
+// the next stay in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+template <int EPI, bool IM, int FBW, int BU>
+__global__ __launch_bounds__(256, BU > 5 ? 2 : 3) void ffn_f32_units_kernel(const float* __restrict__ act, const float* __restrict__ wa,
+                                                                          const float* __restrict__ wb, const float* __restrict__ bias,
+                                                                          const int32_t* __restrict__ offsets, float* __restrict__ out,
+                                                                          int E, int N, int K, int n_tiles) {
+  constexpr int BM = 16 * BU;
+  static_assert(EPI != F_SWIGLU || FBW == 2, "a wavefront has a gate block and the up block of the same features");
+  constexpr int TN = 64 * FBW, OUTF = EPI == F_SWIGLU ? TN / 2 : TN;  // weight rows, output features
+  constexpr int AQ = (BM * 8 + 255) / 256, BQ = TN * 8 / 256;                 // 16-byte pieces of a stage per thread
+  constexpr int BP = TN + 4;                                          // IM: LDS pitch of a row of weights, in floats
+  __shared__ __attribute__((aligned(16))) float sa[2][BM * FKS];
+  __shared__ __attribute__((aligned(16))) float sb[2][IM ? FKS * BP : TN * FKS];
+  RowTile t;
+  if (!find_row_tile<BM, 16>(offsets, E, n_tiles, t)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q16 = lane & 15, g = lane >> 4;
+  const int n0 = min(t.nt * OUTF, N - OUTF);  // (the last tile of a feature count that is no multiple leaves to the one before what is its)
+  const size_t we = (size_t)t.expert * N * K;
+  const int units = (t.rows + 15) / 16;
+  // weight row r of the tile: matrix and feature (SwiGLU: 16 gate rows and 16 up rows of the same features per wavefront)
+  auto feature = [&](int r) { return EPI == F_SWIGLU ? n0 + (r >> 5) * 16 + (r & 15) : n0 + r; };
+  auto matrix = [&](int r) { return EPI == F_SWIGLU && (r & 16) ? wb : wa; };
+
+  const float* pa[AQ];
+  const float* pb[BQ];
+  int la[AQ], lb[BQ];
+#pragma unroll
+  for (int q = 0; q < AQ; ++q) {
+    const int i = q * 256 + tid, r = i / 8, c = i % 8;
+    pa[q] = act + (size_t)(t.row0 + min(r, t.rows - 1)) * K + 4 * c;
+    la[q] = r * FKS + 4 * (c ^ ((r >> 1) & 7));
+  }
+#pragma unroll
+  for (int q = 0; q < BQ; ++q) {
+    const int i = q * 256 + tid;
+    if (IM) {
+      const int kr = i / (TN / 4), r = 4 * (i % (TN / 4));  // contraction row, first of four weight rows
+      pb[q] = matrix(r) + we + (size_t)kr * N + feature(r);
+      lb[q] = kr * BP + r;
+    } else {
+      const int r = i / 8, c = i % 8;
+      pb[q] = matrix(r) + we + (size_t)feature(r) * K + 4 * c;
+      lb[q] = r * FKS + 4 * (c ^ ((r >> 1) & 7));
+    }
+  }
+  const size_t b_step = IM ? (size_t)FKS * N : FKS;
+  const int w0 = wave * 16 * FBW, key = (q16 >> 1) & 7;  // (the key of a row repeats every 16)
+  const int KT = K / FKS;
+  f32x4 acc[BU][FBW];
+#pragma unroll
+  for (int u = 0; u < BU; ++u)
+#pragma unroll
+    for (int f = 0; f < FBW; ++f) acc[u][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // the K loop of a tile of U units: 16 values at a time, of which lane group g has the four of chunk 4 h + g, one per MFMA
+  auto contract = [&](auto u_tag) {
+    constexpr int U = decltype(u_tag)::value, AU = (U + 1) / 2;
+    f32x4 ra[AU], rb[BQ], x[U], w[2][FBW];
+    auto load = [&](int kt) {
+#pragma unroll
+      for (int q = 0; q < AU; ++q) ra[q] = load4(pa[q] + (size_t)kt * FKS);
+#pragma unroll
+      for (int q = 0; q < BQ; ++q) rb[q] = load4(pb[q] + kt * b_step);
+    };
+    auto store = [&](int s) {
+#pragma unroll
+      for (int q = 0; q < AU; ++q)
+        if (32 * q + 32 <= BM || tid < (BM - 32 * q) * 8)  // (BM is a multiple of 16)
+          *reinterpret_cast<f32x4*>(&sa[s][la[q]]) = ra[q];
+#pragma unroll
+      for (int q = 0; q < BQ; ++q) *reinterpret_cast<f32x4*>(&sb[s][lb[q]]) = rb[q];
+    };
+    auto read_w = [&](int s, int h, f32x4 (&v)[FBW]) {
+#pragma unroll
+      for (int f = 0; f < FBW; ++f) {
+        if (IM) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[f][i] = sb[s][(16 * h + 4 * g + i) * BP + w0 + 16 * f + q16];
+        } else {
+          v[f] = *reinterpret_cast<const f32x4*>(&sb[s][(w0 + 16 * f + q16) * FKS + 4 * ((4 * h + g) ^ key)]);
+        }
+      }
+    };
+    auto read_x = [&](int s, int h, int u) { return *reinterpret_cast<const f32x4*>(&sa[s][(16 * u + q16) * FKS + 4 * ((4 * h + g) ^ key)]); };
+    auto multiply = [&](int u, const f32x4 (&v)[FBW]) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int f = 0; f < FBW; ++f) acc[u][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[f][i], x[u][i], acc[u][f], 0, 0, 0);
+    };
+    load(0);
+    store(0);
+    load(1);  // (K is a multiple of 64)
+    __syncthreads();
+    for (int kt = 0; kt < KT; ++kt) {
+      const int s = kt & 1;
+      read_w(s, 0, w[0]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = read_x(s, 0, u);
+      if (kt + 1 < KT) store(s ^ 1);  // (nobody has read that stage since the last barrier)
+      if (kt + 2 < KT) load(kt + 2);
+      read_w(s, 1, w[1]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        multiply(u, w[0]);
+        x[u] = read_x(s, 1, u);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) multiply(u, w[1]);
+      lds_barrier();
+    }
+  };
+  switch (units) {
+    case 1: contract(std::integral_constant<int, (1 < BU ? 1 : BU)>{}); break;
+    case 2: contract(std::integral_constant<int, (2 < BU ? 2 : BU)>{}); break;
+    case 3: contract(std::integral_constant<int, (3 < BU ? 3 : BU)>{}); break;
+    case 4: contract(std::integral_constant<int, (4 < BU ? 4 : BU)>{}); break;
+    case 5: contract(std::integral_constant<int, (5 < BU ? 5 : BU)>{}); break;
+    case 6: contract(std::integral_constant<int, (6 < BU ? 6 : BU)>{}); break;
+    case 7: contract(std::integral_constant<int, (7 < BU ? 7 : BU)>{}); break;
+    case 8: contract(std::integral_constant<int, (8 < BU ? 8 : BU)>{}); break;
+    case 9: contract(std::integral_constant<int, (9 < BU ? 9 : BU)>{}); break;
+    default: contract(std::integral_constant<int, BU>{}); break;
+  }
+  // lane (q16, g): row q16 of every unit, weight rows 4 g .. 4 g + 3 of every block
+#pragma unroll
+  for (int f = 0; f < (EPI == F_SWIGLU ? 1 : FBW); ++f) {
+    const int nb = EPI == F_SWIGLU ? n0 + wave * 16 : n0 + w0 + 16 * f;
+    if (nb < t.nt * OUTF) continue;
+    const int n = nb + 4 * g;
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+    if (EPI != F_SWIGLU && bias) b = load4(bias + (size_t)t.expert * N + n);
+#pragma unroll
+    for (int u = 0; u < BU; ++u) {
+      const int r = 16 * u + q16;
+      if (r >= t.rows) continue;
+      f32x4a4 y;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if constexpr (EPI == F_SWIGLU) y[v] = silu_exact(acc[u][0][v]) * acc[u][FBW - 1][v];
+        else if (EPI == F_GELU) y[v] = gelu_exact(acc[u][f][v] + b[v]);
+        else y[v] = acc[u][f][v] + b[v];
+      }
+      *reinterpret_cast<f32x4a4*>(out + (size_t)(t.row0 + r) * N + n) = y;
+    }
+  }
+}
+
 // Few tiles: 32 rows x 32 features per workgroup, whose eight wavefronts split the contraction index (runs of 32 values,
 // one 128-byte line per row, straight from global memory into MFMA operands); their sums meet in LDS in wavefront
 // order.  Bound by latency: a quarter of the tile, an eighth of the chain.
@@ -241,26 +404,54 @@ __global__ __launch_bounds__(SPLIT_WAVES * 64) void ffn_f32_split_kernel(
   }
 }
 
+// Which kernel: for evenly loaded experts, +- their spread under random routing (row tiles of an expert: the mean over 1.2
+// standard deviations below, at and above the mean row count).
+//  - the kernel that splits the contraction index up to 256 tiles of 64 rows (one for every CU).  Measured (us, 64 rows / split):
+//    112 tiles, K 2624: 60 / 50; 144 tiles, K 640: 21 / 18; 256 tiles of 16 rows, K 4096: 99 / 78; 288 tiles, K 2048: 85 / 92;
+//    656 tiles, K 448: 38 / 67; 1280 tiles, K 4096: 380 / 548;
+//  - 160 rows where long rows meet whole rounds of such tiles (one per CU, or two) that no expert overflows (three deviations):
+//    a round more costs more than the shape gains (8 experts of 599 rows, 3264 -> 960, one round and a few tiles: 307 / 493);
+//  - 80 rows from 256 values on where the tiles come to at least 0.8 of their rounds of 256 and to a tenth fewer than those of 64 (us, 64 / 80
+//    rows: 0.94 of a round against 1.2 114 / 87; 1.9 against 2.3 229 / 184; 2.6 against 3.3 171 / 155; but 1.5 against 1.8 78 / 88; 2.3
+//    against 2.9 131 / 149; 4 experts' worth of equal tiles, 16 of 93 rows, 52 / 56).  Of 140 random products 91 are within this
+//    line, 14 of them slower, by up to 14 % (7 experts of 805 rows, 1472 -> 1024 169 / 197).
+enum { F32_SPLIT, F32_64, F32_80, F32_160 };
+int pick_f32(const moe_config* cfg, int N, int K, bool swiglu) {
+  const int64_t rows = (max_rows(cfg) + cfg->E - 1) / cfg->E, E = cfg->E;
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  if (E * up(rows, FM) * up(N, FN) <= 256) return F32_SPLIT;
+  const double sd = std::sqrt((double)rows);
+  const int64_t low = rows - 1.2 * sd < 1 ? 1 : (int64_t)(rows - 1.2 * sd), high = (int64_t)(rows + 1.2 * sd);
+  auto rounds = [&](int tm, int outf) { return E * ((up(low, tm) + up(rows, tm) + up(high, tm)) / 3.0) * up(N, outf) / 256.0; };
+  const int outf160 = swiglu ? 64 : 128;
+  if (K >= 1024 && N >= outf160 && up(rows, 160) == up((int64_t)(rows + 3 * sd), 160)) {
+    const double r = E * up(rows, 160) * up(N, outf160) / 256.0, pairs = std::ceil(r / 2) * 2;
+    if ((r <= 1 && r >= 0.94) || (r > 1 && r >= 0.94 * pairs)) return F32_160;
+  }
+  const double r80 = rounds(80, 64);
+  if (K >= 256 && r80 >= 0.8 * std::ceil(r80) && r80 <= 0.9 * rounds(FM, FN)) return F32_80;
+  return F32_64;
+}
+
 template <int EPI, bool IM>
 int32_t launch_f32_layout(const moe_config* cfg, const float* act, const float* wa, const float* wb, const float* bias,
                           const int32_t* offsets, float* out, int N, int K, hipStream_t s) {
-  const int64_t rmax = max_rows(cfg);
-  if (rmax == 0) return MOE_OK;
-  // The 64-row kernel from 257 tiles on (one for every CU), for evenly loaded experts; below, the kernel that splits the
-  // contraction index.  Measured (us, 64 rows / split): 112 tiles, K 2624: 60 / 50; 144 tiles, K 640: 21 / 18; 256 tiles of
-  // 16 rows, K 4096: 99 / 78; 288 tiles, K 2048: 85 / 92; 656 tiles, K 448: 38 / 67; 1280 tiles, K 4096: 380 / 548.
-  const int64_t rows_each = (rmax + cfg->E - 1) / cfg->E;
-  const bool split = cfg->E * ((rows_each + FM - 1) / FM) * ((N + FN - 1) / FN) <= 256;
-  const int tm = split ? 32 : FM, tn = split ? 32 : FN;
-  const int64_t grid = row_tile_grid(cfg, tm, (N + tn - 1) / tn);
-  if (grid > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "float32 FFN: too many tiles");
-  const dim3 g((unsigned)grid);
-  const int n_tiles = (N + tn - 1) / tn;
-  if (split)
-    hipLaunchKernelGGL((ffn_f32_split_kernel<EPI, IM>), g, dim3(SPLIT_WAVES * 64), 0, s, act, wa, wb, bias, offsets, out, cfg->E, N, K, n_tiles);
-  else
-    hipLaunchKernelGGL((ffn_f32_kernel<EPI, IM>), g, dim3(256), 0, s, act, wa, wb, bias, offsets, out, cfg->E, N, K, n_tiles);
-  return check_hip(hipGetLastError(), "float32 FFN launch");
+  if (max_rows(cfg) == 0) return MOE_OK;
+  constexpr bool SW = EPI == F_SWIGLU;
+  const int which = pick_f32(cfg, N, K, SW);
+  auto run = [&](auto kern, int tm, int tn, int threads) {
+    const int n_tiles = (N + tn - 1) / tn;
+    const int64_t grid = row_tile_grid(cfg, tm, n_tiles);
+    if (grid > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "float32 FFN: too many tiles");
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, s, act, wa, wb, bias, offsets, out, cfg->E, N, K, n_tiles);
+    return check_hip(hipGetLastError(), "float32 FFN launch");
+  };
+  switch (which) {
+    case F32_SPLIT: return run(ffn_f32_split_kernel<EPI, IM>, 32, 32, SPLIT_WAVES * 64);
+    case F32_80: return run(ffn_f32_units_kernel<EPI, IM, SW ? 2 : 1, 5>, 80, 64, 256);
+    case F32_160: return run(ffn_f32_units_kernel<EPI, IM, 2, 10>, 160, SW ? 64 : 128, 256);
+  }
+  return run(ffn_f32_kernel<EPI, IM>, FM, FN, 256);
 }
 
 int32_t launch_f32(const moe_config* cfg, int epi, const float* act, const float* wa, const float* wb,
@@ -411,4 +602,14 @@ extern "C" int32_t moe_transpose_expert_weights(const void* src, void* dst, int3
   if (dtype == MOE_BF16) launch_transpose<uint16_t>(src, dst, E, rows, cols, (hipStream_t)stream);
   else launch_transpose<float>(src, dst, E, rows, cols, (hipStream_t)stream);
   return check_hip(hipGetLastError(), "transpose launch");
+}
+
+// Rows per tile of the kernel that serves the float32 experts' first (second = 0) or second product; 32: the one that splits the
+// contraction index.  For the tests of the rule above; host only, not part of the interface in moesys.h.
+extern "C" int32_t moe_test_f32_tile_rows(const moe_config* cfg, int32_t second) {
+  using namespace moesys;
+  if (moe_config_check(cfg) != MOE_OK || cfg->dtype != MOE_F32) return 0;
+  const int N = second ? cfg->d_model : cfg->d_ff, K = second ? cfg->d_ff : cfg->d_model;
+  const int rows[] = {32, FM, 80, 160};
+  return rows[pick_f32(cfg, N, K, !second && cfg->act == MOE_ACT_SWIGLU)];
 }

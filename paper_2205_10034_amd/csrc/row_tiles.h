@@ -18,8 +18,8 @@ struct RowTile { int expert, row0, rows, nt, tiles; };  // first dispatched row,
 // Tile of workgroup blockIdx.x, false if there is none.  Tiles are numbered expert by expert, feature tile by feature
 // tile, row tiles innermost, and every XCD (workgroup b runs on XCD b mod 8) takes one contiguous eighth: the row tiles
 // that share a weight tile, and the feature tiles that share the rows, meet in one L2.  Every wavefront finds its tile
-// by itself (lane l looks at the experts 4l .. 4l+3), so no barrier is spent on it.
-template <int TM>
+// by itself (lane l looks at the experts 4l .. 4l+3), so no barrier is spent on it.  An expert has the fewest tiles of at most TM rows.
+template <int TM, int UNIT = 0>
 __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ offsets, int E, int n_tiles, RowTile& t) {
   const int lane = threadIdx.x & 63;
   static_assert(MOE_MAX_EXPERTS == 256, "four experts per lane");
@@ -51,8 +51,11 @@ __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ offset
   tiles = __builtin_amdgcn_readlane(tiles, src);
   const int r = id - base * n_tiles, nt = r / tiles, m = r - nt * tiles;
   t.expert = e;
-  t.row0 = offsets[e] + m * TM;
-  t.rows = min(TM, offsets[e + 1] - t.row0);
+  const int n = offsets[e + 1] - offsets[e];
+  // (UNIT: the rows dealt out evenly in whole units; TM is a multiple, so no tile comes out larger and none empty)
+  const int per = UNIT ? ((n + tiles - 1) / tiles + UNIT - 1) / (UNIT ? UNIT : 1) * UNIT : TM;
+  t.row0 = offsets[e] + m * per;
+  t.rows = min(per, n - m * per);
   t.nt = nt;
   t.tiles = tiles;
   return true;
