@@ -212,6 +212,139 @@ int32_t launch_few(const moe_config* cfg, const void* x, const float* w_router, 
   return check_hip(hipGetLastError(), "gate launch");
 }
 
+// Up to eight of those tokens inside a layer whose router is half a megabyte or more: one compute unit takes 10 to 16 us to
+// read it.  Its rows are spread over up to GS_SLICES workgroups, each of which multiplies its slice by all tokens in float64
+// (exact products) and stores the partial logits; one workgroup then adds them in slice order, ranks every token in a
+// wavefront of its own and writes the dispatch tables of the at most 64 assignments, which saves their kernel.  Four or
+// more tokens are dealt out to the wavefronts; fewer: the wavefronts split the rows.  Bound by the latency of two launches
+// and of the ranking.  Measured on MI355X: routing alone with everything cached (us, one workgroup per token / slices), d 2048,
+// 64 experts: T 1 10.0 / 9.5, T 4 12.8 / 11.5, T 8 12.9 / 13.6, T 16 14.4 / 20.2; d 4096, 64: T 1 14.8 / 10.1, T 8 17.9 / 17.1; d 4096,
+// 32: T 2 13.0 / 11.1; smaller routers lose (d 2048, 32: T 1 8.0 / 9.5).  In the layer, where the experts' weights have driven
+// the router out of the caches: d 2048, 64 experts, T 1 47.4 / 41.3 us per layer, T 8 184.1 / 179.9.
+constexpr int GS_SLICES = 32, GS_MAX_T = 8, GS_TT = 3;
+template <bool SPLIT_ROWS>
+__global__ __launch_bounds__(256) void gate_slice_kernel(const uint16_t* __restrict__ x, const float* __restrict__ wr, int T, int d, int E,
+                                                         int rows_per, double* __restrict__ part) {
+  __shared__ double red[SPLIT_ROWS ? 4 : 1][GS_TT][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int cpr = E >> 2, rpi = 64 / cpr;  // chunks per row, rows per wave-wide load
+  const int r = lane / cpr, c = lane % cpr;
+  const int r0 = blockIdx.x * rows_per, r1 = min(d, r0 + rows_per);
+  const int step = SPLIT_ROWS ? 4 * rpi : rpi;
+  double acc[GS_TT][4];
+#pragma unroll
+  for (int u = 0; u < GS_TT; ++u)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[u][i] = 0.0;
+  const uint16_t* xt[GS_TT];  // (tokens past the last redo it; their sums are not stored)
+#pragma unroll
+  for (int u = 0; u < GS_TT; ++u) xt[u] = x + (size_t)min(SPLIT_ROWS ? u : wave + 4 * u, T - 1) * d;
+#pragma unroll 8
+  for (int row = r0 + (SPLIT_ROWS ? wave * rpi : 0) + r; row < r1; row += step) {
+    const float4 w4 = *reinterpret_cast<const float4*>(wr + (size_t)row * E + 4 * c);
+#pragma unroll
+    for (int u = 0; u < GS_TT; ++u) {
+      if ((SPLIT_ROWS ? u : 4 * u) >= T) break;  // (uniform)
+      const double xd = (double)bf16_to_f32(xt[u][row]);
+      acc[u][0] = fma(xd, (double)w4.x, acc[u][0]);
+      acc[u][1] = fma(xd, (double)w4.y, acc[u][1]);
+      acc[u][2] = fma(xd, (double)w4.z, acc[u][2]);
+      acc[u][3] = fma(xd, (double)w4.w, acc[u][3]);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < GS_TT; ++u) {
+    if ((SPLIT_ROWS ? u : 4 * u) >= T) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      for (int m = cpr; m < 64; m <<= 1) acc[u][i] += shfl_xor_f64(acc[u][i], m);
+    const int t = SPLIT_ROWS ? u : wave + 4 * u;
+    if (SPLIT_ROWS) {
+      if (lane < cpr)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[wave][u][4 * c + i] = acc[u][i];
+    } else if (t < T && lane < cpr) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) part[((size_t)blockIdx.x * T + t) * E + 4 * c + i] = acc[u][i];
+    }
+  }
+  if (SPLIT_ROWS) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < T * E; i += 256) {
+      const int u = i / E, e = i - u * E;
+      part[((size_t)blockIdx.x * T + u) * E + e] = ((red[0][u][e] + red[1][u][e]) + red[2][u][e]) + red[3][u][e];
+    }
+  }
+}
+
+__global__ __launch_bounds__(GS_MAX_T * 64) void gate_finish_kernel(const double* __restrict__ part, const float* __restrict__ br, int T, int E,
+                                                                     int k, int C, int renorm, int slices, int32_t* __restrict__ topk_idx,
+                                                                     float* __restrict__ topk_w, int32_t* __restrict__ counts,
+                                                                     int32_t* __restrict__ offsets, int32_t* __restrict__ a2r,
+                                                                     int32_t* __restrict__ r2a, int32_t* __restrict__ clear8) {
+  __shared__ double zrow[GS_MAX_T][64];
+  __shared__ int sel_s[GS_MAX_T * MOE_MAX_TOPK];
+  __shared__ int cnt[64], off_s[64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (clear8 && threadIdx.x < 8) clear8[threadIdx.x] = 0;
+  if (wave < T) {
+    double z = 0.0;
+    const double* p = part + (size_t)wave * E + min(lane, E - 1);
+#pragma unroll 8
+    for (int q = 0; q < slices; ++q) z += p[(size_t)q * T * E];
+    zrow[wave][lane] = z + (br && lane < E ? (double)br[lane] : 0.0);
+    asm volatile("" ::: "memory");  // (a wavefront's LDS operations execute in order)
+    const int sel = rank_token(zrow[wave], lane, E, k, renorm, wave, topk_idx, topk_w, nullptr);
+    if (lane < k) sel_s[lane * T + wave] = sel;  // assignment j * T + t
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  // the tables: 64 assignments at a time, ranked per expert in order (E <= 64)
+  cnt[lane] = 0;
+  asm volatile("" ::: "memory");
+  constexpr int R = GS_MAX_T * MOE_MAX_TOPK / 64;
+  int e_of[R], slot[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int a = q * 64 + lane, e = a < T * k ? sel_s[a] : -1;
+    unsigned long long same = __ballot(e >= 0);
+    for (int bit = 1; bit < E; bit <<= 1) {
+      const bool one = (e & bit) != 0;
+      const unsigned long long with = __ballot(one);
+      same &= one ? with : ~with;
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    const int before = e >= 0 ? cnt[e] : 0;
+    asm volatile("" ::: "memory");
+    if (e >= 0 && rank == 0) cnt[e] = before + __popcll(same);
+    asm volatile("" ::: "memory");
+    e_of[q] = e;
+    slot[q] = before + rank;
+  }
+  const int n = lane < E ? cnt[lane] : 0, kept = min(n, C);
+  int incl = kept;
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    const int up = __shfl_up(incl, m, 64);
+    incl += lane >= m ? up : 0;
+  }
+  off_s[lane] = incl - kept;
+  asm volatile("" ::: "memory");
+  if (lane < E) {
+    counts[lane] = n;
+    offsets[lane] = incl - kept;
+    if (lane == E - 1) offsets[E] = incl;
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int a = q * 64 + lane;
+    if (a >= T * k) continue;
+    const int row = slot[q] < C ? off_s[e_of[q]] + slot[q] : -1;
+    a2r[a] = row;
+    if (row >= 0) r2a[row] = a;
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // Fast path.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -1102,6 +1235,30 @@ int32_t launch_packed(const moe_config* cfg, const void* x, const void* packed, 
 bool gate_dispatch_one_token_applies(const moe_config* cfg, const float* w_router) {
   return cfg->T == 1 && cfg->dtype == MOE_BF16 && gate_few_applies(cfg, w_router);
 }
+// Gate and dispatch tables of a step of few tokens through slices of the router; scratch: bytes for the partial logits
+// (eight slices at least).
+static int gate_slices(const moe_config* cfg, size_t scratch_bytes) {
+  int64_t s = (int64_t)(scratch_bytes / ((size_t)cfg->T * cfg->E * sizeof(double)));
+  if (s > GS_SLICES) s = GS_SLICES;
+  return (int)s;
+}
+bool gate_dispatch_slices_applies(const moe_config* cfg, const float* w_router, size_t scratch_bytes) {
+  return cfg->T >= 1 && cfg->T <= GS_MAX_T && cfg->dtype == MOE_BF16 && gate_few_applies(cfg, w_router) &&
+         (int64_t)cfg->d_model * cfg->E >= 131072 &&
+         gate_slices(cfg, scratch_bytes) >= 8;
+}
+int32_t launch_gate_dispatch_slices(const moe_config* cfg, const void* x, const float* w_router, const float* b_router, int32_t* topk_idx,
+                                    float* topk_w, int32_t* counts, int32_t* offsets, int32_t* a2r, int32_t* r2a, int32_t* clear8,
+                                    void* scratch, size_t scratch_bytes, hipStream_t s) {
+  const int T = cfg->T, d = cfg->d_model, E = cfg->E, most = gate_slices(cfg, scratch_bytes);
+  const int rows_per = (d + most - 1) / most, slices = (d + rows_per - 1) / rows_per;
+  hipLaunchKernelGGL(T < 4 ? gate_slice_kernel<true> : gate_slice_kernel<false>, dim3(slices), dim3(256), 0, s, (const uint16_t*)x, w_router, T, d, E,
+                     rows_per, (double*)scratch);
+  hipLaunchKernelGGL(gate_finish_kernel, dim3(1), dim3(GS_MAX_T * 64), 0, s, (const double*)scratch, b_router, T, E, cfg->k, moe_capacity(cfg),
+                     cfg->renormalize, slices, topk_idx, topk_w, counts, offsets, a2r, r2a, clear8);
+  return check_hip(hipGetLastError(), "gate launch");
+}
+
 int32_t launch_gate_dispatch_one_token(const moe_config* cfg, const void* x, const float* w_router, const float* b_router,
                                        int32_t* topk_idx, float* topk_w, int32_t* counts, int32_t* offsets, int32_t* a2r,
                                        int32_t* r2a, int32_t* clear8, hipStream_t s) {

@@ -57,6 +57,16 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   if (!w->w_router) return fail(MOE_ERR_INVALID_ARG, "%s: w_router is NULL", who);
   if ((st = mark(timer, 0, s)) != MOE_OK) return st;
   const bool gather = gemm1_can_gather(cfg);
+  // few tokens, a large router: the gate runs on many compute units and writes the dispatch tables as well (the partial logits go
+  // where the first product will write)
+  const size_t h_bytes = (size_t)max_rows(cfg) * cfg->d_ff * elem_size(cfg->dtype);
+  if (gather && gate_dispatch_slices_applies(cfg, w->w_router, h_bytes)) {
+    if ((st = launch_gate_dispatch_slices(cfg, x, w->w_router, w->b_router, sg.topk_idx, sg.topk_w, sg.counts, sg.offsets, sg.a2r,
+                                          sg.r2a, sg.tile_ctr, sg.h, h_bytes, s)) != MOE_OK)
+      return st;
+    if ((st = mark(timer, 1, s)) != MOE_OK) return st;
+    return mark(timer, 2, s);
+  }
   if (gather && gate_dispatch_one_token_applies(cfg, w->w_router)) {
     // a step of one token: the gate's kernel writes the dispatch tables as well
     if ((st = launch_gate_dispatch_one_token(cfg, x, w->w_router, w->b_router, sg.topk_idx, sg.topk_w, sg.counts, sg.offsets,

@@ -56,6 +56,10 @@ bool gate_dispatch_one_token_applies(const moe_config* cfg, const float* w_route
 int32_t launch_gate_dispatch_one_token(const moe_config* cfg, const void* x, const float* w_router, const float* b_router,
                                        int32_t* topk_idx, float* topk_w, int32_t* counts, int32_t* offsets, int32_t* a2r,
                                        int32_t* r2a, int32_t* clear8, hipStream_t s);
+bool gate_dispatch_slices_applies(const moe_config* cfg, const float* w_router, size_t scratch_bytes);
+int32_t launch_gate_dispatch_slices(const moe_config* cfg, const void* x, const float* w_router, const float* b_router, int32_t* topk_idx,
+                                    float* topk_w, int32_t* counts, int32_t* offsets, int32_t* a2r, int32_t* r2a, int32_t* clear8,
+                                    void* scratch, size_t scratch_bytes, hipStream_t s);
 int32_t launch_gate(const moe_config* cfg, const void* x, const float* w_router, const float* b_router,
                     int32_t* topk_idx, float* topk_w, float* probs, hipStream_t s);
 // the same on the pre-split router when w carries one (moe_weights.w_router_packed) and it applies

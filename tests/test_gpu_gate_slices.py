@@ -1,0 +1,51 @@
+"""Routing of a few tokens through slices of a large router: routing and tables exact against float64 at every token count the
+slices serve and the first beyond, experts preferred by all tokens, capacities that drop, exact ties (lower expert first),
+widths that leave the last slice short."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2205_10034_amd as M
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,E", [(2048, 64), (2112, 64), (4096, 32), (4160, 32), (16384, 8)])
+@pytest.mark.parametrize("T,k,cf", [(1, 1, 0.0), (1, 2, 0.0), (2, 8, 0.0), (3, 2, 0.5), (4, 2, 0.0), (5, 3, 0.0), (7, 2, 0.5), (8, 8, 0.0), (8, 1, 0.5), (9, 2, 0.0)])
+def test_gate_slices(d, E, T, k, cf):
+    cfg = M.MoEConfig(T=T, d_model=d, d_ff=4096, E=E, k=k, capacity_factor=cf, renormalize=bool(T & 1))
+    g = torch.Generator(device="cuda").manual_seed(d + E + T)
+    x = torch.randn(T, d, generator=g, device="cuda").bfloat16()
+    router = torch.randn(d, E, generator=g, device="cuda") * d ** -0.5
+    router[:, 3] = router[:, 1]                            # exact ties
+    bias = torch.randn(E, generator=g, device="cuda")
+    bias[3] = bias[1] = 2.5
+    one = torch.zeros(1, dtype=torch.bfloat16, device="cuda")
+    W = M.Weights({"w1": one, "w2": one, "w_router": router, "b_router": bias}, "output_major")
+    W.need = lambda c: None                                # (routing reads no expert)
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda").fill_(0xAB)
+    lay = M.moe_workspace_layout(cfg)
+    read = lambda n, c, dt=torch.int32: ws[lay[n]:lay[n] + 4 * c].view(dt).cpu().numpy()
+    z = (x.double() @ router.double() + bias.double()).cpu()
+    idx = torch.sort(z, dim=1, descending=True, stable=True).indices[:, :k].numpy()
+    p = np.take_along_axis(torch.softmax(z, 1).numpy(), idx, 1)
+    if cfg.renormalize:
+        p = p / p.sum(1, keepdims=True)
+    cap = max(1, int(np.ceil(k * T * cf / E))) if cf else k * T
+    counts, a2r = np.bincount(idx.reshape(-1), minlength=E), np.full(T * k, -1)
+    offsets = np.concatenate([[0], np.cumsum(np.minimum(counts, cap))])
+    seen, r2a = np.zeros(E, int), np.zeros(offsets[-1], int)
+    for a, e in enumerate(idx.T.reshape(-1)):
+        if seen[e] < cap:
+            a2r[a] = offsets[e] + seen[e]
+            r2a[a2r[a]] = a
+        seen[e] += 1
+    for _ in range(2):
+        M.moe_layer_route(cfg, W, x, ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(read("topk_idx", T * k).reshape(T, k), idx)
+        # float32 exponentials and one division: a few units in the last place
+        assert np.abs(read("topk_w", T * k, torch.float32).reshape(T, k) - p).max() < 16 * 2.0 ** -24
+        assert np.array_equal(read("expert_counts", E), counts) and np.array_equal(read("expert_offsets", E + 1), offsets)
+        assert np.array_equal(read("assign_to_row", T * k), a2r) and np.array_equal(read("row_to_assign", offsets[-1]), r2a)
+        assert not read("tile_counters", 8).any()
