@@ -334,10 +334,11 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    weights on its way and waits for it.  Over 126 random products of 97 to 180 rows 1.12 on average (grouped / here): 64
 //    experts, 131 rows, f 3456 -> d 3264 366 / 314; 16 SwiGLU, 112 rows, 3008 -> 8704 467 / 398; 64 SwiGLU, 128 rows, 2048 -> 4096
 //    523 / 466 and 283 / 210; few tiles 1.2 to 1.3.  Not beyond 160 rows, where experts need a second tile (32 experts, 169
-//    rows, 5248 -> 3904 326 / 350), nor for short rows, where the start and end of these tiles weigh: below 832 values (128, 147
-//    rows, 576 -> 4416 212 / 226), from 137 rows below 1408 (64, 143 rows, 1280 -> 3392 189 / 204), first products, with an activation in their end, below 1152 (32, 113 rows, 896 -> 9152 148 / 154) and
-//    in more than six rounds below 2240 (64, 128 rows, 2048 -> 8192 469 / 479).  First products of at most a round stay with the
-//    grouped GEMM too, where the line below 128x192 has them; they would gain 1.05 to 1.2.
+//    rows, 5248 -> 3904 326 / 350), nor for short rows, where the start and end of these tiles weigh: below 1152 values (128, 132
+//    rows, 896 -> 3840 299 / 352), from 137 rows below 1408 (128, 148 rows, 832 -> 1920 151 / 204; 45 products 0.97 on average),
+//    first products, with an activation in their end, below 1152 (32, 113 rows, 896 -> 9152 148 / 154) and in more than six rounds
+//    below 2240 (64, 128 rows, 2048 -> 8192 469 / 479).  First products of at most a round stay with the grouped GEMM too, where the
+//    line below 128x192 has them; they would gain 1.05 to 1.2.
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128, STREAM_256x192 };
 int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
@@ -376,7 +377,7 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   if (wide && rows > 192 && big > 128 && big <= 192 && tiles_of(128, 128, rows + (rows * 2 + 24) / 25) <= 512) return STREAM_128x128;
   if (N >= (swiglu ? 128 : 256) && rows > 96 && rows <= 160) {
     const bool first = N == cfg->d_ff && K == cfg->d_model;
-    if (!first ? K >= (rows > 136 ? 1408 : 832) : !one_round(256, 192) && K >= (tiles(256, 192) > 6 * 256 ? 2240 : 1152)) return STREAM_256x192;
+    if (!first ? K >= (rows > 136 ? 1408 : 1152) : !one_round(256, 192) && K >= (tiles(256, 192) > 6 * 256 ? 2240 : 1152)) return STREAM_256x192;
   }
   return STREAM_NONE;
 }
