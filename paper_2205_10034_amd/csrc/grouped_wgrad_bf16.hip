@@ -29,8 +29,9 @@
 // Tile order.  The 8 XCDs have an L2 each, and the hardware deals workgroups out to them round robin.  A tile
 // streams a slab of A and one of B; tiles of one expert with the same n1 (n2) tile share the A (B) slab.  The tiles of
 // an expert are numbered in blocks of BY x BX, the experts one after the other, and units of `unit` consecutive tiles are
-// dealt out to the XCDs in turn: as many as fill an XCD, or evenly fewer, so that no XCD gets more than a unit's rounding
-// more than another.  (Blocks dealt out whole, partial ones too, met on the same XCDs where their number per expert
+// dealt out to the XCDs in turn: 32, or evenly fewer, so that no XCD gets more than a unit's rounding more than another.
+// (Units of what an XCD runs at once, 64 or 96 tiles, are no faster with even routing and put a hot expert of 64 tiles on one XCD: 8
+// experts, 2048 x 512, half of 5600 rows on one: 38.7 us.)  (Blocks dealt out whole, partial ones too, met on the same XCDs where their number per expert
 // has a factor in common with eight: 64 experts of 81 rows, 768 x 2560 bf16, 96 against 70 us; over 150 random shapes the
 // units gain 4.5 %.)
 // Column sums of A per expert (the bias gradients: db2_e = sum_r d_y[r, :], db1_e = sum_r d_u[r, :]) come from
@@ -344,9 +345,9 @@ int32_t launch_wgrad_bf16(const uint16_t* a, const uint16_t* b, const int32_t* o
   const bool h = c_dtype == MOE_BF16;
   const WgTiles t = wgrad_tiles(E, N1, N2, c_dtype, rows_per_expert);
   const int BX = t.BX, n1t = N1 / t.TN1, n2t = N2 / t.TN;
-  // workgroups that fill an XCD at once (three, two or one per CU) share a block of BY x BX tiles as far as it goes
-  const int at_once = CU_PER_XCD * (t.TN == 128 ? 3 : t.TN1 == 128 ? 2 : 1), BY = at_once / BX;
-  const int64_t tiles = (int64_t)E * n1t * n2t, units = (tiles + 8 * at_once - 1) / (8 * at_once);  // (of one XCD)
+  // blocks of 32 tiles, units of at most as many
+  const int BY = CU_PER_XCD / BX;
+  const int64_t tiles = (int64_t)E * n1t * n2t, units = (tiles + 8 * CU_PER_XCD - 1) / (8 * CU_PER_XCD);  // (of one XCD)
   const int unit = (int)((tiles + 8 * units - 1) / (8 * units));
   const int64_t wgs = 8 * units * unit;
   if (wgs > INT32_MAX) return fail(MOE_ERR_UNSUPPORTED, "weight gradient: too many tiles");
