@@ -24,6 +24,7 @@
 // histogram atomics only add).
 #include <atomic>
 #include "moesys_internal.h"
+#include "wave_util.h"
 
 // Bookkeeping scratch of moe_dispatch_static, the variant of moe_dispatch for callers that cannot allocate:
 // one array per GPU, held from the moment the library's code is loaded on that GPU until the process ends.
@@ -227,27 +228,12 @@ __global__ __launch_bounds__(ONE_WAVES * 64) void dispatch_one_kernel(const int3
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int a = (wave * R + r) * 64 + lane;
-    e_of[r] = a < T * k ? expert_of(topk_idx, a, T, k) : -1;
-    if ((unsigned)e_of[r] >= (unsigned)E) e_of[r] = -1;  // (an index outside 0..E-1 is ignored: dropped)
+    e_of[r] = a < T * k ? valid_expert(expert_of(topk_idx, a, T, k), E) : -1;
   }
   for (int e = lane; e < E; e += 64) cnt[wave][e] = 0;
   asm volatile("" ::: "memory");  // (a wavefront's LDS operations execute in order)
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int e = e_of[r];
-    unsigned long long same = __ballot(e >= 0);
-    for (int bit = 1; bit < E; bit <<= 1) {
-      const bool one = (e & bit) != 0;
-      const unsigned long long with = __ballot(one);
-      same &= one ? with : ~with;
-    }
-    const int rank = __popcll(same & ((1ull << lane) - 1ull));
-    const int before = e >= 0 ? cnt[wave][e] : 0;
-    asm volatile("" ::: "memory");
-    if (e >= 0 && rank == 0) cnt[wave][e] = before + __popcll(same);
-    asm volatile("" ::: "memory");
-    slot[r] = before + rank;
-  }
+  for (int r = 0; r < R; ++r) slot[r] = place_in_expert(e_of[r], E, cnt[wave], lane);
   __syncthreads();
   if (tid < E) {
     int run = 0;

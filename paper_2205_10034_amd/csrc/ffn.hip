@@ -7,6 +7,7 @@
 #include <type_traits>
 #include "moesys_internal.h"
 #include "row_tiles.h"
+#include "wave_util.h"
 
 namespace moesys {
 
@@ -162,9 +163,6 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
 // against the 64 x 64 kernel (us): 80 rows, 140 random products 1.07 on average where the rule below picks it, 1.10 each
 // (4 experts of 1538 rows, 3712 -> 192 149 / 106; 8 of 268, 3648 -> 960 206 / 164; 16 of 69, 768 -> 3584 114 / 82); 160 rows, 16
 // experts of 256, 1024 -> 4096 -> 1024: 354 / 322 and 375 / 334 (107 and 103 TFLOP/s).
-// Workgroup barrier for data exchanged through LDS: waits for this wavefront's LDS operations only, the loads of the step after
-// the next stay in flight.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 template <int EPI, bool IM, int FBW, int BU>
 __global__ __launch_bounds__(256, BU > 5 ? 2 : 3) void ffn_f32_units_kernel(const float* __restrict__ act, const float* __restrict__ wa,
                                                                           const float* __restrict__ wb, const float* __restrict__ bias,

@@ -14,6 +14,7 @@
 // recomputed; see gate_f64_kernel.
 #include <type_traits>
 #include "moesys_internal.h"
+#include "wave_util.h"
 
 namespace moesys {
 namespace {
@@ -49,11 +50,6 @@ __device__ __forceinline__ void group8_steps(F&& f) {
   f(std::integral_constant<int, 1>{});
   f(std::integral_constant<int, 2>{});
 }
-
-// Workgroup barrier for data exchanged through LDS: waits for this wavefront's LDS operations only.  (__syncthreads
-// also waits for every global load and store in flight: for the results just stored, a microsecond at the end of a
-// kernel that lasts ten, and for refill loads that nobody will use.)
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // One wavefront ranks one token from its float64 logits z[0..E): softmax in float32 (row maximum subtracted),
 // k rounds of arg-max on the float64 logits (ties -> lower expert index), weights p or p / sum of the selected.
@@ -295,7 +291,7 @@ __global__ __launch_bounds__(GS_MAX_T * 64) void gate_finish_kernel(const double
     zrow[wave][lane] = z + (br && lane < E ? (double)br[lane] : 0.0);
     asm volatile("" ::: "memory");  // (a wavefront's LDS operations execute in order)
     const int sel = rank_token(zrow[wave], lane, E, k, renorm, wave, topk_idx, topk_w, nullptr);
-    if (lane < k) sel_s[lane * T + wave] = sel;  // assignment j * T + t
+    if (lane < k) sel_s[lane * T + wave] = valid_expert(sel, E);  // assignment j * T + t
   }
   __syncthreads();
   if (wave != 0) return;
@@ -306,20 +302,9 @@ __global__ __launch_bounds__(GS_MAX_T * 64) void gate_finish_kernel(const double
   int e_of[R], slot[R];
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    const int a = q * 64 + lane, e = a < T * k ? sel_s[a] : -1;
-    unsigned long long same = __ballot(e >= 0);
-    for (int bit = 1; bit < E; bit <<= 1) {
-      const bool one = (e & bit) != 0;
-      const unsigned long long with = __ballot(one);
-      same &= one ? with : ~with;
-    }
-    const int rank = __popcll(same & ((1ull << lane) - 1ull));
-    const int before = e >= 0 ? cnt[e] : 0;
-    asm volatile("" ::: "memory");
-    if (e >= 0 && rank == 0) cnt[e] = before + __popcll(same);
-    asm volatile("" ::: "memory");
-    e_of[q] = e;
-    slot[q] = before + rank;
+    const int a = q * 64 + lane;
+    e_of[q] = a < T * k ? sel_s[a] : -1;
+    slot[q] = place_in_expert(e_of[q], E, cnt, lane);
   }
   const int n = lane < E ? cnt[lane] : 0, kept = min(n, C);
   int incl = kept;
@@ -339,7 +324,7 @@ __global__ __launch_bounds__(GS_MAX_T * 64) void gate_finish_kernel(const double
   for (int q = 0; q < R; ++q) {
     const int a = q * 64 + lane;
     if (a >= T * k) continue;
-    const int row = slot[q] < C ? off_s[e_of[q]] + slot[q] : -1;
+    const int row = e_of[q] >= 0 && slot[q] < C ? off_s[e_of[q]] + slot[q] : -1;
     a2r[a] = row;
     if (row >= 0) r2a[row] = a;
   }
