@@ -222,7 +222,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_combine1_kernel(
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ a2r, const float* __restrict__ topk_w,
     const uint16_t* residual, uint16_t* __restrict__ yd, uint16_t* out, const int64_t* __restrict__ eoff, int E, int N,
     int K, int k) {
-  __shared__ int s_e[MOE_MAX_TOPK];  // expert of dispatched row r (T = 1: there are exactly k rows)
+  __shared__ int s_e[MOE_MAX_TOPK];  // expert of dispatched row r (T = 1: at most k rows)
   __shared__ float red[GV_WAVES][C1_FPW];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int e = threadIdx.x; e < E; e += GV_WAVES * 64)
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_combine1_kernel(
   if (wave == 0 && lane < C1_FPW && residual) o = lo16((uint32_t)residual[n0 + lane]);
   for (int j = 0; j < k; ++j) {
     const int row = a2r[j];
-    if (row < 0) continue;  // (cannot happen with one token: the capacity is at least one; uniform anyway)
+    if (row < 0) continue;  // (a selection that is no expert: NaN logits; uniform)
     const int e = s_e[row];
     const uint16_t* wbase = w2 + (eoff ? eoff[e] : (int64_t)e * N * K) + (int64_t)n0 * K;
     const uint16_t* xrow = h + (int64_t)row * K;

@@ -173,20 +173,24 @@ __global__ __launch_bounds__(FEW_THREADS) void gate_few_kernel(
   if (wave != 0) return;
   const int sel = rank_token(zrow, lane, E, k, renorm, t, topk_idx, topk_w, probs);
   // A step of ONE token (counts != NULL; T == 1): its dispatch tables follow from the selection at once.  The k
-  // experts are distinct and get one row each (the capacity is at least one, so nothing is dropped); rows are
-  // ordered by expert; assignment j (= j*T + t with T = 1) is the j-th choice.
+  // experts are distinct and get one row each (the capacity is at least one; only a selection that is no expert is
+  // dropped); rows are ordered by expert; assignment j (= j*T + t with T = 1) is the j-th choice.
   if (counts) {
+    const int mine = valid_expert(sel, E);
     unsigned long long chosen = 0;  // bit e: expert e selected (E <= 64)
-    for (int j = 0; j < k; ++j) chosen |= 1ull << __shfl(sel, j, 64);
+    for (int j = 0; j < k; ++j) {
+      const int e = __shfl(mine, j, 64);
+      if (e >= 0) chosen |= 1ull << e;
+    }
     if (lane < E) {
       counts[lane] = (int)((chosen >> lane) & 1ull);
       offsets[lane] = __popcll(chosen & ((1ull << lane) - 1ull));
     }
-    if (lane == 0) offsets[E] = k;
+    if (lane == 0) offsets[E] = __popcll(chosen);
     if (lane < k) {
-      const int row = __popcll(chosen & ((1ull << sel) - 1ull));
+      const int row = mine >= 0 ? __popcll(chosen & ((1ull << mine) - 1ull)) : -1;
       a2r[lane] = row;
-      r2a[row] = lane;
+      if (row >= 0) r2a[row] = lane;
     }
     if (clear8 && lane < 8) clear8[lane] = 0;
   }

@@ -81,3 +81,18 @@ def test_sliced_gate(d, f, E, k, T, cf):
     for bad in place(T):
         print(d, E, T, k, cf, bad, flush=True)
         check(cfg, W, x, bad, residual=True)
+
+
+@pytest.mark.parametrize("d,f,E", [(1024, 512, 64), (2048, 512, 8), (512, 256, 4), (2048, 1024, 64)])   # (the last: slices)
+@pytest.mark.parametrize("k", [2, 4])
+@pytest.mark.parametrize("residual", [False, True])
+def test_one_token(d, f, E, k, residual):
+    print(d, E, k, residual, flush=True)
+    cfg, W, x = layer(d, f, E, 1, k)
+    check(cfg, W, x, [0], residual)
+    xn = torch.full_like(x, float("nan"))
+    out, (counts, offsets, a2r, _), ws = forward(cfg, W, xn, xn if residual else None, fill=3.0)
+    assert not counts.any() and not offsets.any() and (a2r == -1).all()
+    assert bool(out.isnan().all() if residual else (out == 0).all())     # (its residual; no expert added anything)
+    ref = forward(cfg, W, x, x)[0]
+    assert torch.equal(forward(cfg, W, x, x, ws=ws)[0], ref)             # the workspace serves the next step
