@@ -69,7 +69,8 @@ __global__ void aux_loss_kernel(const float* __restrict__ f, const float* __rest
 // d_z[t, e] = p[t,e] * (d_p[t,e] - sum_e' d_p[t,e'] p[t,e']).  d_p is, on the k selected experts,
 // (d_w_j - sum_i d_w_i w_i) / S with S = sum of the selected probabilities if the weights are renormalised and
 // d_w_j otherwise, zero elsewhere; plus, on every expert, aux_scale * f[e] (the auxiliary loss's gradient,
-// aux_scale = coef * E / T; f NULL: none).  One wavefront per token, lanes over the experts.
+// aux_scale = coef * E / T; f NULL: none).  One wavefront per token, lanes over the experts.  A selection that is no expert
+// (NaN logits, whose probabilities are all NaN) reads another probability of its token: the row of d_z comes out NaN.
 __global__ __launch_bounds__(256) void gate_dlogits_kernel(const float* __restrict__ probs, const int32_t* __restrict__ topk_idx,
                                                            const float* __restrict__ topk_w, const float* __restrict__ d_topk_w,
                                                            float* __restrict__ d_z, int T, int E, int k, int renorm,
@@ -77,15 +78,16 @@ __global__ __launch_bounds__(256) void gate_dlogits_kernel(const float* __restri
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
+  auto selected = [&](int j) { return probs[(size_t)t * E + min((unsigned)topk_idx[(size_t)t * k + j], (unsigned)E - 1u)]; };
   float S = 0.f, common = 0.f;
   for (int j = 0; j < k; ++j) {
-    S += probs[(size_t)t * E + topk_idx[(size_t)t * k + j]];
+    S += selected(j);
     common += d_topk_w[(size_t)t * k + j] * topk_w[(size_t)t * k + j];
   }
   float s = 0.f;  // sum over the experts of d_p * p: the selected ones ...
   for (int j = 0; j < k; ++j) {
     const float dp = renorm ? (d_topk_w[(size_t)t * k + j] - common) / S : d_topk_w[(size_t)t * k + j];
-    s += dp * probs[(size_t)t * E + topk_idx[(size_t)t * k + j]];
+    s += dp * selected(j);
   }
   if (f) {  // ... and the auxiliary term on all of them (lanes in a fixed butterfly order)
     float a = 0.f;

@@ -96,3 +96,38 @@ def test_one_token(d, f, E, k, residual):
     assert bool(out.isnan().all() if residual else (out == 0).all())     # (its residual; no expert added anything)
     ref = forward(cfg, W, x, x)[0]
     assert torch.equal(forward(cfg, W, x, x, ws=ws)[0], ref)             # the workspace serves the next step
+
+
+@pytest.mark.parametrize("T,E,k,act,renorm", [(300, 8, 2, "gelu", False), (300, 8, 2, "swiglu", True), (131, 20, 1, "gelu", True), (8, 64, 2, "gelu", False)])
+def test_backward(T, E, k, act, renorm):
+    """Gradients of a layer with NaN tokens against those with ordinary tokens in their place whose upstream gradient is
+    zero: alike for the experts and the other tokens, NaN for the router and the NaN tokens."""
+    print(T, E, k, act, renorm, flush=True)
+    d, f = (2048, 512) if E == 64 else (512, 512)
+    cfg, W, x = layer(d, f, E, T, k, act=act, renorm=renorm)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    G = torch.randn(T, d, generator=g, device="cuda").bfloat16()
+    bad = [0, T // 2, T - 1]
+    good = [t for t in range(T) if t not in bad]
+    G[bad] = 0
+    im = lambda n: W.tensors[n].transpose(1, 2).contiguous()
+    w1, w2 = (torch.cat([im("w_gate_proj"), im("w_up")], 2), im("w_down")) if act == "swiglu" else (im("w1"), im("w2"))
+    f1 = 2 * f if act == "swiglu" else f
+
+    def step(xs):
+        nan = lambda *shape: torch.full(shape, float("nan"), device="cuda")
+        d_x, d_wr, d_br, d_w1, d_w2 = torch.full_like(x, float("nan")), nan(d, E), nan(E), nan(E, f1, d), nan(E, d, f)
+        ws = forward(cfg, W, xs, xs)[2]
+        bws = torch.empty(M.moe_layer_backward_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+        M.moe_layer_backward(cfg, W, w1, w2, xs, G, None, ws, d_x, d_wr, d_br, d_w1, None, d_w2, None, bws)
+        torch.cuda.synchronize()
+        return d_x, d_wr, d_br, d_w1, d_w2
+
+    xn = x.clone()
+    xn[bad, ::7] = float("nan")
+    want, got = step(x), step(xn)
+    assert torch.equal(got[0][good], want[0][good]) and bool(got[0][bad].isnan().all())
+    assert bool(got[1].isnan().all()) and bool(got[2].isnan().all())
+    for a, b in zip(got[3:], want[3:]):
+        # the same float32 sums without a few terms that are zero: up to T roundings of 2^-24 in other places
+        assert float((a - b).norm() / b.norm()) < 4 * T ** 0.5 * 2.0 ** -24
