@@ -183,6 +183,9 @@ int32_t moe_get_tuning(int32_t key, int32_t* value);
  * Logits that decide the ranking are accumulated so that the selection equals
  * the one made on exactly computed logits (products of the stored values are
  * exact in float64; see the kernel for the fast path / exact path split).
+ * A token with fewer than k logits that compare (NaN) gets an index outside
+ * 0..E-1 for the choices that are missing; the dispatch drops those, so such a
+ * token takes no row from another and its output is its residual, or zero.
  * x device [T,d_model] (cfg.dtype); w_router device [d_model,E] f32; b_router
  * device [E] f32 or NULL; topk_idx device int32 [T,k]; topk_w device f32
  * [T,k]; probs device f32 [T,E] or NULL. */

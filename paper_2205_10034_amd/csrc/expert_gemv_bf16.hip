@@ -17,6 +17,7 @@
 // 2048 x 8192 118 + 111 us here, 99 + 95 there; with 8 assignments 56 + 52 here, 58 + 57 there.  The 4 x 16 shape serves
 // what those kernels leave: contraction lengths beyond their 32-bit offsets, and calls whose tuning keys keep them out.
 #include "moesys_internal.h"
+#include "wave_util.h"
 
 namespace moesys {
 
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
     const uint16_t* __restrict__ act, const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb,
     const uint16_t* __restrict__ bias, const int32_t* __restrict__ offsets, uint16_t* out,
     const int32_t* __restrict__ row_map, const float* __restrict__ gate_w, const uint16_t* residual,
-    const int64_t* __restrict__ eoff, int T, int E, int N, int K, int reps) {
+    const int32_t* __restrict__ a2r, const int64_t* __restrict__ eoff, int T, int E, int N, int K, int reps) {
   constexpr int OUTF = EPI == GV_SWIGLU ? GV_FPW / 2 : GV_FPW;  // output features per wavefront
   __shared__ int s_e;
   __shared__ float red[KSPLIT ? GV_WAVES : 1][GV_ROWS][GV_FPW];
@@ -70,6 +71,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
     if (offsets[e] == r0 && offsets[e + 1] > r0) s_e = e;  // at most one expert starts at row r0
   __syncthreads();
   const int e = s_e;
+  if constexpr (EPI == GV_COMBINE) fill_rowless_tokens<GV_WAVES>(a2r, offsets[E], T, N, residual, out);
   if (e < 0) return;
   const int rows = min(offsets[e + 1] - r0, GV_ROWS);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -285,7 +287,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_combine1_kernel(
 template <int EPI, int ROWS, int FPW>
 int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                      const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
-                     const int64_t* eoff, int N, int K, bool gather, hipStream_t s) {
+                     const int32_t* a2r, const int64_t* eoff, int N, int K, bool gather, hipStream_t s) {
   constexpr int OUTF = EPI == GV_SWIGLU ? FPW / 2 : FPW;
   // About 256 KB of weights per workgroup, in whole blocks of output features, as long as that leaves about two
   // workgroups per CU (the experts with rows are at most k*T).  Long rows and too few workgroups even so: the
@@ -301,7 +303,7 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
   const bool nt = weights_exceed_cache(cfg);
 #define MOESYS_GEMV(G, S)                                                                                                  \
   hipLaunchKernelGGL((nt ? expert_gemv_kernel<EPI, G, ROWS, FPW, S, true> : expert_gemv_kernel<EPI, G, ROWS, FPW, S, false>), grid, block, 0, s, act, wa, wb, bias, offsets, out, row_map, \
-                     gate_w, residual, eoff, cfg->T, cfg->E, N, K, reps)
+                     gate_w, residual, a2r, eoff, cfg->T, cfg->E, N, K, reps)
   if (gather) { if (ksplit) MOESYS_GEMV(true, true); else MOESYS_GEMV(true, false); }
   else { if (ksplit) MOESYS_GEMV(false, true); else MOESYS_GEMV(false, false); }
 #undef MOESYS_GEMV
@@ -311,11 +313,11 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 template <int EPI>
 int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
-               const int64_t* eoff, int N, int K, bool gather, hipStream_t s) {
+               const int32_t* a2r, const int64_t* eoff, int N, int K, bool gather, hipStream_t s) {
   const int A = cfg->k * cfg->T;
   if (A == 0) return MOE_OK;
-  if (A <= 8) return launch_shape<EPI, 8, 8>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, eoff, N, K, gather, s);
-  return launch_shape<EPI, 16, 4>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, eoff, N, K, gather, s);
+  if (A <= 8) return launch_shape<EPI, 8, 8>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, a2r, eoff, N, K, gather, s);
+  return launch_shape<EPI, 16, 4>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, a2r, eoff, N, K, gather, s);
 }
 
 }  // namespace
@@ -344,20 +346,20 @@ int32_t launch_expert_gemv_combine_one_token(const moe_config* cfg, const void* 
 }
 
 // epi: 0 GELU (+bias), 1 SwiGLU (wa = gate, wb = up), 2 plain (+bias), 3 combine for k = 1 (row_map = row_to_assign,
-// gate_w, residual).  row_map with epi 0/1: gather the rows from x[T, K].  eoff: per-expert element offsets or NULL.
+// gate_w, residual; a2r or NULL: fill_rowless_tokens).  row_map with epi 0/1: gather the rows from x[T, K].  eoff: per-expert element offsets or NULL.
 int32_t launch_expert_gemv_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
                                 const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
-                                const void* residual, const int64_t* eoff, int N, int K, hipStream_t s) {
+                                const void* residual, const int32_t* a2r, const int64_t* eoff, int N, int K, hipStream_t s) {
   if (!expert_gemv_applies(cfg, N, K)) return fail(MOE_ERR_UNSUPPORTED, "expert GEMV: shape outside the few-row path");
   const uint16_t *a = (const uint16_t*)act, *w0 = (const uint16_t*)wa, *w1 = (const uint16_t*)wb, *b = (const uint16_t*)bias;
   const uint16_t* res = (const uint16_t*)residual;
   switch (epi) {
-    case GV_GELU: return launch<GV_GELU>(cfg, a, w0, w1, b, offsets, (uint16_t*)out, row_map, gate_w, res, eoff, N, K, row_map != nullptr, s);
-    case GV_SWIGLU: return launch<GV_SWIGLU>(cfg, a, w0, w1, nullptr, offsets, (uint16_t*)out, row_map, gate_w, res, eoff, N, K, row_map != nullptr, s);
-    case GV_BIAS: return launch<GV_BIAS>(cfg, a, w0, w1, b, offsets, (uint16_t*)out, nullptr, gate_w, res, eoff, N, K, false, s);
+    case GV_GELU: return launch<GV_GELU>(cfg, a, w0, w1, b, offsets, (uint16_t*)out, row_map, gate_w, res, a2r, eoff, N, K, row_map != nullptr, s);
+    case GV_SWIGLU: return launch<GV_SWIGLU>(cfg, a, w0, w1, nullptr, offsets, (uint16_t*)out, row_map, gate_w, res, a2r, eoff, N, K, row_map != nullptr, s);
+    case GV_BIAS: return launch<GV_BIAS>(cfg, a, w0, w1, b, offsets, (uint16_t*)out, nullptr, gate_w, res, a2r, eoff, N, K, false, s);
     case GV_COMBINE:
       if (!row_map || !gate_w || cfg->k != 1) return fail(MOE_ERR_INVALID_ARG, "expert GEMV: combine epilogue needs k = 1, row map and gate weights");
-      return launch<GV_COMBINE>(cfg, a, w0, w1, b, offsets, (uint16_t*)out, row_map, gate_w, res, eoff, N, K, false, s);
+      return launch<GV_COMBINE>(cfg, a, w0, w1, b, offsets, (uint16_t*)out, row_map, gate_w, res, a2r, eoff, N, K, false, s);
   }
   return fail(MOE_ERR_INVALID_ARG, "expert GEMV: unknown epilogue");
 }

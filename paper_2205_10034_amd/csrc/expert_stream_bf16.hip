@@ -16,6 +16,7 @@
 #include "moesys_internal.h"
 #include "phi_table.h"
 #include "row_tiles.h"
+#include "wave_util.h"
 
 namespace moesys {
 namespace {
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     const uint16_t* __restrict__ act, const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb,
     const uint16_t* __restrict__ bias, const int32_t* __restrict__ offsets, uint16_t* out,
     const int32_t* __restrict__ row_map, const float* __restrict__ gate_w, const uint16_t* residual,
-    const int64_t* __restrict__ eoff, int32_t* __restrict__ clear_ctr, int T, int E, int N, int K, int n_tiles) {
+    const int32_t* __restrict__ a2r, const int64_t* __restrict__ eoff, int32_t* __restrict__ clear_ctr, int T, int E, int N, int K, int n_tiles) {
 #if defined(__HIP_DEVICE_COMPILE__)  // (buffer descriptors are device-only types)
   constexpr int TM = S::TM, STAGES = S::STAGES, ROW_STAGES = S::ROW_STAGES, ST_WAVES = S::WAVES, FB = S::FB, RB = S::RB;
   constexpr int OUTF = EPI == ST_SWIGLU ? S::WROWS / 2 : S::WROWS;  // output features per workgroup
@@ -77,7 +78,10 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned char w4[STAGES > 4 ? W_BYTES : 16], a4[ROW_STAGES > 4 ? A_BYTES : 16];
   if (clear_ctr && blockIdx.x == 0 && threadIdx.x < 8) clear_ctr[threadIdx.x] = 0;  // (a grouped GEMM may run next)
   RowTile t;
-  if (!find_row_tile<TM>(offsets, E, n_tiles, t)) return;
+  const int kept = EPI == ST_COMBINE ? offsets[E] : 0;
+  const bool have = find_row_tile<TM>(offsets, E, n_tiles, t);
+  if constexpr (EPI == ST_COMBINE) fill_rowless_tokens<ST_WAVES>(a2r, kept, T, N, residual, out);
+  if (!have) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // a feature count that is no multiple of the tile: the last tile starts at N - OUTF and leaves to the one before what is its
   const int n0 = min(t.nt * OUTF, N - OUTF);
@@ -289,7 +293,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
 template <int EPI, bool GATHER, typename S>
 int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                      const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
-                     const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
+                     const int32_t* a2r, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
   constexpr int OUTF = EPI == ST_SWIGLU ? S::WROWS / 2 : S::WROWS;
   const int n_tiles = (N + OUTF - 1) / OUTF;
   const int64_t grid = row_tile_grid(cfg, S::TM, n_tiles);
@@ -297,7 +301,7 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
   if (max_rows(cfg) == 0) return MOE_OK;
   auto kern = weights_exceed_cache(cfg) ? expert_stream_kernel<EPI, GATHER, true, S> : expert_stream_kernel<EPI, GATHER, false, S>;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(S::WAVES * 64), 0, s, act, wa, wb, bias,
-                     offsets, out, row_map, gate_w, residual, eoff, clear_ctr, cfg->T, cfg->E, N, K, n_tiles);
+                     offsets, out, row_map, gate_w, residual, a2r, eoff, clear_ctr, cfg->T, cfg->E, N, K, n_tiles);
   return check_hip(hipGetLastError(), "expert stream launch");
 }
 
@@ -385,8 +389,8 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
 template <int EPI, bool GATHER>
 int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
-               const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
-#define MOE_STREAM(...) return launch_shape<EPI, GATHER, StreamShape<__VA_ARGS__>>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, eoff, clear_ctr, N, K, s)
+               const int32_t* a2r, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
+#define MOE_STREAM(...) return launch_shape<EPI, GATHER, StreamShape<__VA_ARGS__>>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, a2r, eoff, clear_ctr, N, K, s)
   switch (pick_stream(cfg, N, K, EPI == ST_SWIGLU)) {
     case STREAM_64x32: MOE_STREAM(4, 1, 1, 2, 4);
     case STREAM_64x64: MOE_STREAM(4, 1, 1, 4, 4);
@@ -412,25 +416,25 @@ const char* expert_stream_shape(const moe_config* cfg, int N, int K, bool swiglu
 }
 
 // epi: 0 GELU (+bias), 1 SwiGLU (wa = gate, wb = up), 2 plain (+bias), 3 combine for k = 1 (row_map = row_to_assign,
-// gate_w, residual).  row_map with epi 0/1: gather the rows from x[T, K].  eoff: per-expert element offsets or NULL.
+// gate_w, residual; a2r or NULL: fill_rowless_tokens).  row_map with epi 0/1: gather the rows from x[T, K].  eoff: per-expert element offsets or NULL.
 // clear_ctr (nullable): eight ints cleared on the way, the tile counters that the grouped GEMM in this place would clear.
 int32_t launch_expert_stream_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
                                   const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
-                                  const void* residual, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
+                                  const void* residual, const int32_t* a2r, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
   const uint16_t *a = (const uint16_t*)act, *w0 = (const uint16_t*)wa, *w1 = (const uint16_t*)wb, *b = (const uint16_t*)bias;
   const uint16_t* res = (const uint16_t*)residual;
   uint16_t* o = (uint16_t*)out;
   switch (epi) {
     case ST_GELU:
-      return row_map ? launch<ST_GELU, true>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s)
-                     : launch<ST_GELU, false>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s);
+      return row_map ? launch<ST_GELU, true>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, a2r, eoff, clear_ctr, N, K, s)
+                     : launch<ST_GELU, false>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, a2r, eoff, clear_ctr, N, K, s);
     case ST_SWIGLU:
-      return row_map ? launch<ST_SWIGLU, true>(cfg, a, w0, w1, nullptr, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s)
-                     : launch<ST_SWIGLU, false>(cfg, a, w0, w1, nullptr, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s);
-    case ST_BIAS: return launch<ST_BIAS, false>(cfg, a, w0, w1, b, offsets, o, nullptr, gate_w, res, eoff, clear_ctr, N, K, s);
+      return row_map ? launch<ST_SWIGLU, true>(cfg, a, w0, w1, nullptr, offsets, o, row_map, gate_w, res, a2r, eoff, clear_ctr, N, K, s)
+                     : launch<ST_SWIGLU, false>(cfg, a, w0, w1, nullptr, offsets, o, row_map, gate_w, res, a2r, eoff, clear_ctr, N, K, s);
+    case ST_BIAS: return launch<ST_BIAS, false>(cfg, a, w0, w1, b, offsets, o, nullptr, gate_w, res, a2r, eoff, clear_ctr, N, K, s);
     case ST_COMBINE:
       if (!row_map || !gate_w || cfg->k != 1) return fail(MOE_ERR_INVALID_ARG, "expert stream: combine epilogue needs k = 1, row map and gate weights");
-      return launch<ST_COMBINE, false>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, eoff, clear_ctr, N, K, s);
+      return launch<ST_COMBINE, false>(cfg, a, w0, w1, b, offsets, o, row_map, gate_w, res, a2r, eoff, clear_ctr, N, K, s);
   }
   return fail(MOE_ERR_INVALID_ARG, "expert stream: unknown epilogue");
 }

@@ -15,7 +15,7 @@ int32_t launch_gemm1_bf16(const moe_config*, const moe_weights*, const void*, co
                           hipStream_t);
 int32_t launch_gemm2_bf16(const moe_config*, const moe_weights*, const void*, const int32_t*, void*, int32_t*, hipStream_t);
 int32_t launch_gemm2_combine_bf16(const moe_config*, const moe_weights*, const void*, const int32_t*, const int32_t*,
-                                  const float*, const void*, void*, int32_t*, hipStream_t);
+                                  const float*, const void*, void*, const int32_t*, int32_t*, hipStream_t);
 
 namespace {
 
@@ -560,9 +560,9 @@ bool gemm2_can_combine(const moe_config* cfg) { return cfg->dtype == MOE_BF16 &&
 
 int32_t launch_gemm2_combine(const moe_config* cfg, const moe_weights* w, const void* h, const int32_t* offsets,
                              const int32_t* r2a, const float* topk_w, const void* residual, void* out,
-                             int32_t* tile_counters, hipStream_t s) {
+                             const int32_t* a2r, int32_t* tile_counters, hipStream_t s) {
   if (!gemm2_can_combine(cfg)) return fail(MOE_ERR_UNSUPPORTED, "combine in the second GEMM needs bf16 and k = 1");
-  return launch_gemm2_combine_bf16(cfg, w, h, offsets, r2a, topk_w, residual, out, tile_counters, s);
+  return launch_gemm2_combine_bf16(cfg, w, h, offsets, r2a, topk_w, residual, out, a2r, tile_counters, s);
 }
 
 }  // namespace moesys

@@ -47,6 +47,7 @@
 #include <cstdlib>
 #include <type_traits>
 #include "moesys_internal.h"
+#include "wave_util.h"
 #include "phi_table.h"
 
 // Optional phase timing, compiled in with -DMOESYS_GEMM_PROFILE (a separate library, never the product
@@ -311,6 +312,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
                                           // EPI_COMBINE: row_to_assign with k = 1, i.e. the token of every row
     const float* __restrict__ gate_w,     // EPI_COMBINE: [T] gate weight of every token
     const uint16_t* residual,             // EPI_COMBINE: [T, N] or NULL
+    const int32_t* __restrict__ a2r,      // EPI_COMBINE: fill_rowless_tokens; NULL otherwise
     const int64_t* __restrict__ eoff,     // [E] or NULL: expert e's weights (and bias) start eoff[e] elements after
                                           // wa/wb (bias) instead of e*N*K (e*N)
     int32_t* __restrict__ tile_ctr,       // [NUM_XCD] zero at launch: tiles handed out beyond each workgroup's first
@@ -382,7 +384,9 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
   if (EPI == EPI_GELU) fill_phi_table(s_phi);
   if (EPI == EPI_DGELU) fill_gelu_prime_table(s_phi);
   const float phi_add = phi_addend(s_phi);
+  const int kept = EPI == EPI_COMBINE ? offsets[E] : 0;
   count_token_tiles(offsets, E, TOK, s_pref);  // ends with a barrier: s_pref and the table are visible
+  if constexpr (EPI == EPI_COMBINE) fill_rowless_tokens<NW>(a2r, kept, T, N, residual, out);
   TileWalker<TOK, 32 * WT> walk;
   walk.init(s_pref[E], n_tiles);
 
@@ -1048,7 +1052,7 @@ template <int TOK, int FEAT, int WT, int WF, int KS, int WPE, int EPI, bool MI16
 int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb,
                const uint16_t* bias, const int32_t* offsets, uint16_t* out, const int32_t* row_map,
                int32_t* tile_ctr, int32_t* clear_ctr, int N, int K, hipStream_t s, const int64_t* eoff,
-               const float* gate_w = nullptr, const uint16_t* residual = nullptr) {
+               const float* gate_w = nullptr, const uint16_t* residual = nullptr, const int32_t* a2r = nullptr) {
   constexpr int OUT_FEAT = swiglu_tile(EPI) ? FEAT / 2 : FEAT;
   if (N < OUT_FEAT || N % (RAGGED_N ? 64 : OUT_FEAT)) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: N=%d does not fit tiles of %d features", N, OUT_FEAT);
   if (K % KS) return fail(MOE_ERR_UNSUPPORTED, "grouped GEMM: K=%d is not a multiple of %d", K, KS);
@@ -1089,7 +1093,7 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
     if (!row_map || !gate_w || cfg->k != 1) return fail(MOE_ERR_INVALID_ARG, "grouped GEMM: combine epilogue needs k = 1, row map and gate weights");
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WT * WF * 64), 0, s, act, wa, wb, bias, offsets, out, row_map,
-                     gate_w, residual, eoff, tile_ctr, clear_ctr, cfg->T, cfg->E, N, K);
+                     gate_w, residual, a2r, eoff, tile_ctr, clear_ctr, cfg->T, cfg->E, N, K);
   return check_hip(hipGetLastError(), "grouped GEMM launch");
 }
 
@@ -1153,25 +1157,25 @@ template <int EPI>
 int32_t gemm_any(const moe_config* cfg, const uint16_t* a, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                  const int32_t* offsets, uint16_t* o, const int32_t* row_map, int32_t* tile_ctr, int32_t* clear_ctr, int N,
                  int K, hipStream_t s, const int64_t* eoff, const float* gate_w = nullptr,
-                 const uint16_t* residual = nullptr) {
+                 const uint16_t* residual = nullptr, const int32_t* a2r = nullptr) {
   constexpr int BF = swiglu_tile(EPI) ? 128 : 256;  // output features of the big tile
   const int rows = grouped_tile_rows(cfg, N, K, BF);
   if (rows != 128) {
     if (rows == 320)
-      return launch<320, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
+      return launch<320, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual, a2r);
     const bool mi16 = use_mi16(256, 2, EPI) && prefer_mi16(cfg);
     if constexpr (EPI != EPI_DGELU && EPI != EPI_DSWIGLU) {  // (the weight gradients beside these want multiples of 256 anyway)
       if (N % BF)
-        return mi16 ? launch<256, 256, 2, 4, 64, 2, EPI, true, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual)
-                    : launch<256, 256, 2, 4, 64, 2, EPI, false, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
+        return mi16 ? launch<256, 256, 2, 4, 64, 2, EPI, true, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual, a2r)
+                    : launch<256, 256, 2, 4, 64, 2, EPI, false, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual, a2r);
     }
-    return mi16 ? launch<256, 256, 2, 4, 64, 2, EPI, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual)
-                : launch<256, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
+    return mi16 ? launch<256, 256, 2, 4, 64, 2, EPI, true>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual, a2r)
+                : launch<256, 256, 2, 4, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual, a2r);
   }
   if constexpr (swiglu_tile(EPI))
-    return launch<128, 128, 2, 2, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
+    return launch<128, 128, 2, 2, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual, a2r);
   else
-    return launch<128, 64, 4, 1, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual);
+    return launch<128, 64, 4, 1, 64, 2, EPI>(cfg, a, wa, wb, bias, offsets, o, row_map, tile_ctr, clear_ctr, N, K, s, eoff, gate_w, residual, a2r);
 }
 
 }  // namespace
@@ -1180,13 +1184,13 @@ int32_t gemm_any(const moe_config* cfg, const uint16_t* a, const uint16_t* wa, c
 bool expert_gemv_applies(const moe_config* cfg, int N, int K);
 int32_t launch_expert_gemv_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
                                 const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
-                                const void* residual, const int64_t* eoff, int N, int K, hipStream_t s);
+                                const void* residual, const int32_t* a2r, const int64_t* eoff, int N, int K, hipStream_t s);
 // steps of few rows per expert take the weight-streaming kernels
 bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu);
 const char* expert_stream_shape(const moe_config* cfg, int N, int K, bool swiglu);
 int32_t launch_expert_stream_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
                                   const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
-                                  const void* residual, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s);
+                                  const void* residual, const int32_t* a2r, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s);
 
 // row_map (nullable): row_to_assign; the token rows are then gathered from x[T, d_model] instead of read
 // from a dispatched copy.
@@ -1194,16 +1198,16 @@ int32_t launch_gemm1_bf16(const moe_config* cfg, const moe_weights* w, const voi
                           void* h, const int32_t* row_map, int32_t* tile_counters, hipStream_t s) {
   if (expert_gemv_applies(cfg, cfg->d_ff, cfg->d_model)) {
     if (cfg->act == MOE_ACT_SWIGLU)
-      return launch_expert_gemv_bf16(EPI_SWIGLU, cfg, xd, w->w_gate_proj, w->w_up, nullptr, offsets, h, row_map, nullptr, nullptr,
+      return launch_expert_gemv_bf16(EPI_SWIGLU, cfg, xd, w->w_gate_proj, w->w_up, nullptr, offsets, h, row_map, nullptr, nullptr, nullptr,
                                      w->expert_elem_offset, cfg->d_ff, cfg->d_model, s);
-    return launch_expert_gemv_bf16(EPI_GELU, cfg, xd, w->w1, nullptr, w->b1, offsets, h, row_map, nullptr, nullptr,
+    return launch_expert_gemv_bf16(EPI_GELU, cfg, xd, w->w1, nullptr, w->b1, offsets, h, row_map, nullptr, nullptr, nullptr,
                                    w->expert_elem_offset, cfg->d_ff, cfg->d_model, s);
   }
   if (expert_stream_applies(cfg, cfg->d_ff, cfg->d_model, cfg->act == MOE_ACT_SWIGLU)) {
     if (cfg->act == MOE_ACT_SWIGLU)
-      return launch_expert_stream_bf16(EPI_SWIGLU, cfg, xd, w->w_gate_proj, w->w_up, nullptr, offsets, h, row_map, nullptr, nullptr,
+      return launch_expert_stream_bf16(EPI_SWIGLU, cfg, xd, w->w_gate_proj, w->w_up, nullptr, offsets, h, row_map, nullptr, nullptr, nullptr,
                                        w->expert_elem_offset, tile_counters + NUM_XCD, cfg->d_ff, cfg->d_model, s);
-    return launch_expert_stream_bf16(EPI_GELU, cfg, xd, w->w1, nullptr, w->b1, offsets, h, row_map, nullptr, nullptr,
+    return launch_expert_stream_bf16(EPI_GELU, cfg, xd, w->w1, nullptr, w->b1, offsets, h, row_map, nullptr, nullptr, nullptr,
                                      w->expert_elem_offset, tile_counters + NUM_XCD, cfg->d_ff, cfg->d_model, s);
   }
   // the first GEMM draws from counters [0,8) and clears [8,16) for the second, which in turn clears [0,8): after
@@ -1223,10 +1227,10 @@ int32_t launch_gemm2_bf16(const moe_config* cfg, const moe_weights* w, const voi
   const bool sw = cfg->act == MOE_ACT_SWIGLU;
   if (expert_gemv_applies(cfg, cfg->d_model, cfg->d_ff))
     return launch_expert_gemv_bf16(EPI_BIAS, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, yd, nullptr,
-                                   nullptr, nullptr, w->expert_elem_offset, cfg->d_model, cfg->d_ff, s);
+                                   nullptr, nullptr, nullptr, w->expert_elem_offset, cfg->d_model, cfg->d_ff, s);
   if (expert_stream_applies(cfg, cfg->d_model, cfg->d_ff, false))
     return launch_expert_stream_bf16(EPI_BIAS, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, yd, nullptr,
-                                     nullptr, nullptr, w->expert_elem_offset, tile_counters, cfg->d_model, cfg->d_ff, s);
+                                     nullptr, nullptr, nullptr, w->expert_elem_offset, tile_counters, cfg->d_model, cfg->d_ff, s);
   return gemm_any<EPI_BIAS>(
       cfg, (const uint16_t*)h, (const uint16_t*)(sw ? w->w_down : w->w2), nullptr,
       (const uint16_t*)(sw ? nullptr : w->b2), offsets, (uint16_t*)yd, nullptr, tile_counters + NUM_XCD, tile_counters,
@@ -1234,21 +1238,21 @@ int32_t launch_gemm2_bf16(const moe_config* cfg, const moe_weights* w, const voi
 }
 
 // The second GEMM with the top-1 combine in its epilogue: out[T, d_model] rows of the tokens that kept their
-// expert are written here, the others by the caller.
+// expert are written here, the others too if a2r (assign_to_row) is given and by the caller if it is NULL.
 int32_t launch_gemm2_combine_bf16(const moe_config* cfg, const moe_weights* w, const void* h, const int32_t* offsets,
                                   const int32_t* row_to_assign, const float* topk_w, const void* residual, void* out,
-                                  int32_t* tile_counters, hipStream_t s) {
+                                  const int32_t* a2r, int32_t* tile_counters, hipStream_t s) {
   const bool sw = cfg->act == MOE_ACT_SWIGLU;
   if (expert_gemv_applies(cfg, cfg->d_model, cfg->d_ff))
     return launch_expert_gemv_bf16(EPI_COMBINE, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, out,
-                                   row_to_assign, topk_w, residual, w->expert_elem_offset, cfg->d_model, cfg->d_ff, s);
+                                   row_to_assign, topk_w, residual, a2r, w->expert_elem_offset, cfg->d_model, cfg->d_ff, s);
   if (expert_stream_applies(cfg, cfg->d_model, cfg->d_ff, false))
     return launch_expert_stream_bf16(EPI_COMBINE, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, out,
-                                     row_to_assign, topk_w, residual, w->expert_elem_offset, tile_counters, cfg->d_model, cfg->d_ff, s);
+                                     row_to_assign, topk_w, residual, a2r, w->expert_elem_offset, tile_counters, cfg->d_model, cfg->d_ff, s);
   return gemm_any<EPI_COMBINE>(
       cfg, (const uint16_t*)h, (const uint16_t*)(sw ? w->w_down : w->w2), nullptr,
       (const uint16_t*)(sw ? nullptr : w->b2), offsets, (uint16_t*)out, row_to_assign, tile_counters + NUM_XCD, tile_counters,
-      cfg->d_model, cfg->d_ff, s, w->expert_elem_offset, topk_w, (const uint16_t*)residual);
+      cfg->d_model, cfg->d_ff, s, w->expert_elem_offset, topk_w, (const uint16_t*)residual, a2r);
 }
 
 // A plain grouped product out[r, n] = sum_k act[r, k] * w_e[n, k] (+ bias_e[n]) with the second GEMM's kernel:
@@ -1257,7 +1261,7 @@ int32_t launch_gemm2_combine_bf16(const moe_config* cfg, const moe_weights* w, c
 int32_t launch_grouped_matmul_bf16(const moe_config* cfg, const void* act, const void* w, const void* bias,
                                    const int32_t* offsets, void* out, int N, int K, int32_t* counters8, hipStream_t s) {
   if (expert_stream_applies(cfg, N, K, false))
-    return launch_expert_stream_bf16(EPI_BIAS, cfg, act, w, nullptr, bias, offsets, out, nullptr, nullptr, nullptr, nullptr, nullptr, N, K, s);
+    return launch_expert_stream_bf16(EPI_BIAS, cfg, act, w, nullptr, bias, offsets, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, N, K, s);
   return gemm_any<EPI_BIAS>(cfg, (const uint16_t*)act, (const uint16_t*)w, nullptr, (const uint16_t*)bias, offsets,
                             (uint16_t*)out, nullptr, counters8, nullptr, N, K, s, nullptr);
 }

@@ -99,12 +99,14 @@ int32_t experts_impl(const char* who, const moe_config* cfg, const moe_weights* 
   if ((st = mark(timer, 3, s)) != MOE_OK) return st;
   if (gemm2_can_combine(cfg)) {
     // one expert per token: the second GEMM scales each row by its gate weight, adds the residual and writes
-    // it to its token's place; what is left of the combine stage are the rows of dropped tokens
-    if ((st = launch_gemm2_combine(cfg, w, sg.h, sg.offsets, sg.r2a, sg.topk_w, residual, out, sg.tile_ctr, s)) != MOE_OK)
+    // it to its token's place; what is left of the combine stage are the rows of dropped tokens.  An expert gets at most T
+    // rows: unless C is smaller only tokens with NaN logits have none, and the second GEMM writes those as well
+    const int64_t C = moe_capacity(cfg);
+    const bool drops = C != MOE_DROPLESS && C < cfg->T;
+    if ((st = launch_gemm2_combine(cfg, w, sg.h, sg.offsets, sg.r2a, sg.topk_w, residual, out, drops ? nullptr : sg.a2r, sg.tile_ctr, s)) != MOE_OK)
       return st;
     if ((st = mark(timer, 4, s)) != MOE_OK) return st;
-    const int64_t C = moe_capacity(cfg);  // an expert gets at most T rows: no drops unless C is smaller
-    if (C != MOE_DROPLESS && C < cfg->T)
+    if (drops)
       if ((st = launch_fill_dropped(cfg, sg.a2r, residual, out, s)) != MOE_OK) return st;
   } else if (expert_gemv_combine_one_token_applies(cfg)) {
     // a step of one token with several experts: the second product and the combine in one kernel (same yd, same out)

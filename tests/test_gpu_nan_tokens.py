@@ -131,3 +131,29 @@ def test_backward(T, E, k, act, renorm):
     for a, b in zip(got[3:], want[3:]):
         # the same float32 sums without a few terms that are zero: up to T roundings of 2^-24 in other places
         assert float((a - b).norm() / b.norm()) < 4 * T ** 0.5 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("T,E,d,f,kernel", [
+    (1, 4, 512, 512, "gemv 8"), (7, 8, 1024, 512, "gemv 8"), (12, 8, 512, 512, "stream 64x32"), (40, 4, 512, 512, "stream 64x32"),
+    (300, 2, 64, 256, "stream 64x64"), (2000, 3, 1024, 256, "stream 128x192"), (4000, 32, 2048, 1152, "stream 256x192"),
+    (20000, 64, 128, 256, "grouped 128"), (2500, 6, 2048, 256, "grouped 256"), (24000, 24, 320, 256, "grouped 256"), (8000, 2, 2048, 256, "grouped 320")])
+@pytest.mark.parametrize("residual", [False, True, "in place"])
+def test_one_expert_per_token(T, E, d, f, kernel, residual):
+    """k = 1: the second product's kernel writes `out` itself, also the rows that no tile holds."""
+    from gpu_util import product_kernel
+    cfg, W, x = layer(d, f, E, T, 1)
+    print(T, E, d, f, residual, product_kernel(cfg, 1), flush=True)
+    assert product_kernel(cfg, 1) == kernel
+    ref = forward(cfg, W, x, x if residual else None)[0]
+    for bad in place(T) + [list(range(T))]:
+        good = [t for t in range(T) if t not in bad]
+        xn = x.clone()
+        xn[bad, 3] = float("nan")
+        res = xn if residual else None
+        ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda").fill_(0xAB)
+        out = xn if residual == "in place" else torch.full_like(x, 3.0)
+        want = torch.zeros_like(x[bad]) if res is None else xn[bad].clone()
+        M.moe_layer_forward(cfg, W, xn, res, out, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out[good], ref[good])
+        assert torch.equal(out[bad].view(torch.int16), want.view(torch.int16))
