@@ -103,10 +103,10 @@ __device__ __forceinline__ int rank_token(const double* z, int lane, int E, int 
       float op = __shfl_xor(bp, m, 64);
       if (oz > bz || (oz == bz && oe < be)) { bz = oz; be = oe; bp = op; }
     }
-    // retire the winner (all lanes agree on be)
+    // retire the winner (all lanes agree on be): as NaN, which no comparison picks again, also where what is left is -inf
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      if (lane + 64 * s == be) zd[s] = -INFINITY;
+      if (lane + 64 * s == be) zd[s] = NAN;
     if (lane == j) { isel = be; wsel = bp; }
     wsum += bp;
   }
@@ -398,7 +398,7 @@ __device__ __forceinline__ bool finalize_group(double (&z)[NPL], int sub, int E,
     });
 #pragma unroll
     for (int i = 0; i < NPL; ++i)
-      if (sub + 8 * i == be) z[i] = -INFINITY;  // retire the winner (every lane of the group agrees on be)
+      if (sub + 8 * i == be) z[i] = NAN;  // retire the winner (every lane of the group agrees on be): no comparison picks it again
     if (r < k) {
       if (sub == r) { my_idx = be; my_w = bp; }
       wsum += bp;
