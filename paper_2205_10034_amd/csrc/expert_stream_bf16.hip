@@ -197,6 +197,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     __builtin_amdgcn_s_waitcnt(wait_vm(AHEAD));
     __builtin_amdgcn_s_barrier();
     issue_a(kt + ROW_STAGES - 1, a_of(std::integral_constant<int, I + ROW_STAGES - 1>{}));
+    if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0x0301);  // no load crosses: AHEAD counts on the weights being the younger ones
     issue_w(policy, kt + STAGES - 1, w_of(std::integral_constant<int, I + STAGES - 1>{}));
     compute(w_of(i), a_of(i));
   };
