@@ -656,6 +656,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     auto step = [&](int kt, unsigned char* cur, unsigned char* nxt) {
       __builtin_amdgcn_s_setprio(2);
       issue_weights(kt + 1, kt + 1 < KT, nxt);
+      __builtin_amdgcn_sched_barrier(0x0301);  // no load crosses: the wait below counts on the prefetch being the youngest
       issue_prefetch(kt + 1 + PF_LEAD);
       substep(cur, cur + A_BYTES, 1, 0, std::integral_constant<int, W_LOADS + 1>{});
       __builtin_amdgcn_s_setprio(1);
@@ -735,6 +736,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     auto step16 = [&](int kt, unsigned char* cur, unsigned char* nxt) {
       __builtin_amdgcn_s_setprio(2);
       issue_weights(kt + 1, kt + 1 < KT, nxt);
+      __builtin_amdgcn_sched_barrier(0x0301);  // as in `step`
       issue_prefetch(kt + 1 + PF_LEAD);
       phase16(cur, cur + A_BYTES, std::integral_constant<int, 0>{}, std::integral_constant<int, W_LOADS + 1>{});
       __builtin_amdgcn_s_setprio(1);
