@@ -340,7 +340,7 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
   constexpr int FBH = swiglu_tile(EPI) ? FB / 2 : FB;
   static_assert(!swiglu_tile(EPI) || FB % 2 == 0, "SwiGLU wave tile is gate blocks + as many up blocks");
   static_assert(EPI != EPI_DSWIGLU || FB == 2, "the SwiGLU-gradient epilogue is written for one gate and one up block");
-  static_assert(NSUB == 2 || NSUB == 4, "K-step is 32 or 64");  // (an even count: the fragment sets alternate)
+  static_assert(NSUB == 4, "the K loops are written out for four sub-steps");
   constexpr int ABUF = TOK > 256 ? 1 : 2;  // sets of token fragments, see `substep`
   constexpr bool MI16 = MI16_ && use_mi16(TOK, WT, EPI);  // 16x16x32 MFMAs, see `phase16`
   constexpr int PF_LEAD = 1;               // K-steps between a line's prefetch and the request of its stage (2 and 3
