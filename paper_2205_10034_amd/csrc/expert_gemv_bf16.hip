@@ -21,7 +21,7 @@
 
 namespace moesys {
 
-bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu);
+bool expert_stream_applies(const moe_config* cfg, int N, int K, int epi);
 
 namespace {
 
@@ -328,7 +328,7 @@ bool expert_gemv_applies(const moe_config* cfg, int N, int K) {
   const int64_t A = (int64_t)cfg->k * cfg->T;
   if (!tuning(MOE_TUNE_FEW_TOKEN_KERNELS) || cfg->dtype != MOE_BF16 || N % (GV_WAVES * 8) || K % 8) return false;
   // (with so few rows per expert the choice of the weight-streaming kernels does not depend on the activation)
-  return A <= 8 || (A <= GV_MAX_ROWS && !expert_stream_applies(cfg, N, K, false));
+  return A <= 8 || (A <= GV_MAX_ROWS && !expert_stream_applies(cfg, N, K, GV_BIAS));
 }
 
 // Second product + combine of a one-token step (k >= 2); see the kernel.  residual nullable; out may be residual.

@@ -341,11 +341,12 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    523 / 466 and 283 / 210; few tiles 1.2 to 1.3.  Not beyond 160 rows, where experts need a second tile (32 experts, 169
 //    rows, 5248 -> 3904 326 / 350), nor for short rows, where the start and end of these tiles weigh: below 1152 values (128, 132
 //    rows, 896 -> 3840 299 / 352), from 137 rows below 1408 (128, 148 rows, 832 -> 1920 151 / 204; 45 products 0.97 on average),
-//    first products, with an activation in their end, below 1152 (32, 113 rows, 896 -> 9152 148 / 154) and in more than six rounds
-//    below 2240 (64, 128 rows, 2048 -> 8192 469 / 479).  First products of at most a round stay with the grouped GEMM too, where the
+//    products with an activation in their end below 1152 (32, 113 rows, 896 -> 9152 148 / 154) and in more than six rounds
+//    below 2240 (64, 128 rows, 2048 -> 8192 469 / 479).  Those of at most a round stay with the grouped GEMM too, where the
 //    line below 128x192 has them; they would gain 1.05 to 1.2.
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128, STREAM_256x192 };
-int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
+int pick_stream(const moe_config* cfg, int N, int K, int epi) {
+  const bool swiglu = epi == ST_SWIGLU, activation = epi == ST_GELU || swiglu;
   if (cfg->dtype != MOE_BF16 || N % 64 || K % ST_KS) return STREAM_NONE;
   // Buffer sizes and offsets of a tile are 32-bit.  The line is that of the grouped GEMM's largest row tile, so that what
   // that kernel refuses stays refused whichever of the two would serve the row count.
@@ -381,8 +382,7 @@ int pick_stream(const moe_config* cfg, int N, int K, bool swiglu) {
   // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)
   if (wide && rows > 192 && big > 128 && big <= 192 && tiles_of(128, 128, rows + (rows * 2 + 24) / 25) <= 512) return STREAM_128x128;
   if (N >= (swiglu ? 128 : 256) && rows > 96 && rows <= 160) {
-    const bool first = N == cfg->d_ff && K == cfg->d_model;
-    if (!first ? K >= (rows > 136 ? 1408 : 1152) : !one_round(256, 192) && K >= (tiles(256, 192) > 6 * 256 ? 2240 : 1152)) return STREAM_256x192;
+    if (!activation ? K >= (rows > 136 ? 1408 : 1152) : !one_round(256, 192) && K >= (tiles(256, 192) > 6 * 256 ? 2240 : 1152)) return STREAM_256x192;
   }
   return STREAM_NONE;
 }
@@ -392,7 +392,7 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
                const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
                const int32_t* a2r, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s) {
 #define MOE_STREAM(...) return launch_shape<EPI, GATHER, StreamShape<__VA_ARGS__>>(cfg, act, wa, wb, bias, offsets, out, row_map, gate_w, residual, a2r, eoff, clear_ctr, N, K, s)
-  switch (pick_stream(cfg, N, K, EPI == ST_SWIGLU)) {
+  switch (pick_stream(cfg, N, K, EPI)) {
     case STREAM_64x32: MOE_STREAM(4, 1, 1, 2, 4);
     case STREAM_64x64: MOE_STREAM(4, 1, 1, 4, 4);
     case STREAM_128x64: MOE_STREAM(4, 2, 2, 2, 5);
@@ -408,12 +408,12 @@ int32_t launch(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, c
 
 }  // namespace
 
-bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu) { return pick_stream(cfg, N, K, swiglu) != STREAM_NONE; }
+bool expert_stream_applies(const moe_config* cfg, int N, int K, int epi) { return pick_stream(cfg, N, K, epi) != STREAM_NONE; }
 
 // name of the shape (weight rows x rows), for tests
-const char* expert_stream_shape(const moe_config* cfg, int N, int K, bool swiglu) {
+const char* expert_stream_shape(const moe_config* cfg, int N, int K, int epi) {
   static const char* const names[] = {"", "stream 64x32", "stream 64x64", "stream 128x64", "stream 128x128", "stream 128x192", "stream 256x64", "stream 256x128", "stream 256x192"};
-  return names[pick_stream(cfg, N, K, swiglu)];
+  return names[pick_stream(cfg, N, K, epi)];
 }
 
 // epi: 0 GELU (+bias), 1 SwiGLU (wa = gate, wb = up), 2 plain (+bias), 3 combine for k = 1 (row_map = row_to_assign,

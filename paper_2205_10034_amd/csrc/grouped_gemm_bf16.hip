@@ -1188,8 +1188,8 @@ int32_t launch_expert_gemv_bf16(int epi, const moe_config* cfg, const void* act,
                                 const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
                                 const void* residual, const int32_t* a2r, const int64_t* eoff, int N, int K, hipStream_t s);
 // steps of few rows per expert take the weight-streaming kernels
-bool expert_stream_applies(const moe_config* cfg, int N, int K, bool swiglu);
-const char* expert_stream_shape(const moe_config* cfg, int N, int K, bool swiglu);
+bool expert_stream_applies(const moe_config* cfg, int N, int K, int epi);
+const char* expert_stream_shape(const moe_config* cfg, int N, int K, int epi);
 int32_t launch_expert_stream_bf16(int epi, const moe_config* cfg, const void* act, const void* wa, const void* wb, const void* bias,
                                   const int32_t* offsets, void* out, const int32_t* row_map, const float* gate_w,
                                   const void* residual, const int32_t* a2r, const int64_t* eoff, int32_t* clear_ctr, int N, int K, hipStream_t s);
@@ -1205,7 +1205,7 @@ int32_t launch_gemm1_bf16(const moe_config* cfg, const moe_weights* w, const voi
     return launch_expert_gemv_bf16(EPI_GELU, cfg, xd, w->w1, nullptr, w->b1, offsets, h, row_map, nullptr, nullptr, nullptr,
                                    w->expert_elem_offset, cfg->d_ff, cfg->d_model, s);
   }
-  if (expert_stream_applies(cfg, cfg->d_ff, cfg->d_model, cfg->act == MOE_ACT_SWIGLU)) {
+  if (expert_stream_applies(cfg, cfg->d_ff, cfg->d_model, cfg->act == MOE_ACT_SWIGLU ? EPI_SWIGLU : EPI_GELU)) {
     if (cfg->act == MOE_ACT_SWIGLU)
       return launch_expert_stream_bf16(EPI_SWIGLU, cfg, xd, w->w_gate_proj, w->w_up, nullptr, offsets, h, row_map, nullptr, nullptr, nullptr,
                                        w->expert_elem_offset, tile_counters + NUM_XCD, cfg->d_ff, cfg->d_model, s);
@@ -1230,7 +1230,7 @@ int32_t launch_gemm2_bf16(const moe_config* cfg, const moe_weights* w, const voi
   if (expert_gemv_applies(cfg, cfg->d_model, cfg->d_ff))
     return launch_expert_gemv_bf16(EPI_BIAS, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, yd, nullptr,
                                    nullptr, nullptr, nullptr, w->expert_elem_offset, cfg->d_model, cfg->d_ff, s);
-  if (expert_stream_applies(cfg, cfg->d_model, cfg->d_ff, false))
+  if (expert_stream_applies(cfg, cfg->d_model, cfg->d_ff, EPI_BIAS))
     return launch_expert_stream_bf16(EPI_BIAS, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, yd, nullptr,
                                      nullptr, nullptr, nullptr, w->expert_elem_offset, tile_counters, cfg->d_model, cfg->d_ff, s);
   return gemm_any<EPI_BIAS>(
@@ -1248,7 +1248,7 @@ int32_t launch_gemm2_combine_bf16(const moe_config* cfg, const moe_weights* w, c
   if (expert_gemv_applies(cfg, cfg->d_model, cfg->d_ff))
     return launch_expert_gemv_bf16(EPI_COMBINE, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, out,
                                    row_to_assign, topk_w, residual, a2r, w->expert_elem_offset, cfg->d_model, cfg->d_ff, s);
-  if (expert_stream_applies(cfg, cfg->d_model, cfg->d_ff, false))
+  if (expert_stream_applies(cfg, cfg->d_model, cfg->d_ff, EPI_COMBINE))
     return launch_expert_stream_bf16(EPI_COMBINE, cfg, h, sw ? w->w_down : w->w2, nullptr, sw ? nullptr : w->b2, offsets, out,
                                      row_to_assign, topk_w, residual, a2r, w->expert_elem_offset, tile_counters, cfg->d_model, cfg->d_ff, s);
   return gemm_any<EPI_COMBINE>(
@@ -1262,7 +1262,7 @@ int32_t launch_gemm2_combine_bf16(const moe_config* cfg, const moe_weights* w, c
 // recomputing the pre-activations.  counters8: eight zeroed ints.
 int32_t launch_grouped_matmul_bf16(const moe_config* cfg, const void* act, const void* w, const void* bias,
                                    const int32_t* offsets, void* out, int N, int K, int32_t* counters8, hipStream_t s) {
-  if (expert_stream_applies(cfg, N, K, false))
+  if (expert_stream_applies(cfg, N, K, EPI_BIAS))
     return launch_expert_stream_bf16(EPI_BIAS, cfg, act, w, nullptr, bias, offsets, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, N, K, s);
   return gemm_any<EPI_BIAS>(cfg, (const uint16_t*)act, (const uint16_t*)w, nullptr, (const uint16_t*)bias, offsets,
                             (uint16_t*)out, nullptr, counters8, nullptr, N, K, s, nullptr);
@@ -1300,8 +1300,9 @@ extern "C" const char* moe_test_product_kernel(const moe_config* cfg, int32_t se
   if (moe_config_check(cfg) != MOE_OK || cfg->dtype != MOE_BF16) return "";
   const int N = second ? cfg->d_model : cfg->d_ff, K = second ? cfg->d_ff : cfg->d_model;
   const bool swiglu = !second && cfg->act == MOE_ACT_SWIGLU;
+  const int epi = second ? EPI_BIAS : swiglu ? EPI_SWIGLU : EPI_GELU;
   if (expert_gemv_applies(cfg, N, K)) return (int64_t)cfg->k * cfg->T <= 8 ? "gemv 8" : "gemv 16";
-  if (expert_stream_applies(cfg, N, K, swiglu)) return expert_stream_shape(cfg, N, K, swiglu);
+  if (expert_stream_applies(cfg, N, K, epi)) return expert_stream_shape(cfg, N, K, epi);
   const int rows = grouped_tile_rows(cfg, N, K, swiglu ? 128 : 256);
   if (!tile_offsets_fit(rows, K)) return "refused";
   return rows == 320 ? "grouped 320" : rows == 256 ? "grouped 256" : "grouped 128";

@@ -85,3 +85,15 @@ def test_tiles_beyond_one_round_need_long_rows_of_weights():
     # two products per tile: shorter rows still pay
     for rows, E, N, K, want in ((28, 128, 1600, 768, "stream 128x64"), (34, 16, 5952, 512, "grouped 256"), (80, 128, 896, 768, "stream 256x128"), (80, 128, 896, 704, "grouped 256")):
         assert first(rows, E, N, K, "swiglu") == want, (rows, E, N, K)
+
+
+def test_the_rule_follows_the_products_place_and_not_its_sizes():
+    """d_ff == d_model: each product keeps its own lines (one round of 256 x 192 tiles: not with an activation in the end)."""
+    for rows, E, d, first, second in ((112, 16, 2112, "grouped 256", "stream 256x192"), (112, 16, 2176, "grouped 256", "stream 256x192"),
+                                      (120, 128, 4096, "stream 256x192", "stream 256x192"), (120, 128, 1920, "stream 256x192", "stream 256x192"),
+                                      (120, 128, 1216, "stream 256x192", "stream 256x192"), (130, 128, 4096, "stream 256x192", "stream 256x192")):
+        for k in (2, 4):
+            cfg = M.MoEConfig(T=rows * E // k, d_model=d, d_ff=d, E=E, k=k)
+            assert product_kernel(cfg, 0) == first and product_kernel(cfg, 1) == second, (rows, E, d)
+        beside = M.MoEConfig(T=rows * E // 2, d_model=d, d_ff=d + 64, E=E, k=2)
+        assert product_kernel(beside, 1) == second
