@@ -343,7 +343,13 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    rows, 896 -> 3840 299 / 352), from 137 rows below 1408 (128, 148 rows, 832 -> 1920 151 / 204; 45 products 0.97 on average),
 //    products with an activation in their end below 1152 (32, 113 rows, 896 -> 9152 148 / 154) and in more than six rounds
 //    below 2240 (64, 128 rows, 2048 -> 8192 469 / 479).  Those of at most a round stay with the grouped GEMM too, where the
-//    line below 128x192 has them; they would gain 1.05 to 1.2.
+//    line below 128x192 has them; they would gain 1.05 to 1.2.  Nor where an expert is likely to need a second tile (from 135 rows
+//    on: random routing spreads rows by a tenth to an eighth) and the tiles leave no room for it in their last round (64 experts, 142
+//    rows, 2752 -> 896 94 / 128; 238 products 1.03, a fifth of them slower), nor for combines below 2560 values, whose ends
+//    wait for row numbers, gate weights and residual rows in turn (32 experts, 134 rows, 1984 -> 4032 142 / 156; 161 products 1.00).
+//    Of 3266 random products of 97 to 160 rows in whole layers, three sets of weights in turn, the 2867 that remain gain 1.14, six of
+//    them lose more than 3 %, by up to 6 %; 290 with a capacity 1.14, three; 278 under Zipf routing without one 1.14, but 31, by up to
+//    29 %, where a hot expert's tiles open a further round.
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128, STREAM_256x192 };
 int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   const bool swiglu = epi == ST_SWIGLU, activation = epi == ST_GELU || swiglu;
@@ -382,7 +388,10 @@ int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)
   if (wide && rows > 192 && big > 128 && big <= 192 && tiles_of(128, 128, rows + (rows * 2 + 24) / 25) <= 512) return STREAM_128x128;
   if (N >= (swiglu ? 128 : 256) && rows > 96 && rows <= 160) {
-    if (!activation ? K >= (rows > 136 ? 1408 : 1152) : !one_round(256, 192) && K >= (tiles(256, 192) > 6 * 256 ? 2240 : 1152)) return STREAM_256x192;
+    const int64_t t = tiles(256, 192), rounds = (t + 255) / 256;
+    if (rows > 134 && C > 192 && 100 * t > 97 * 256 * rounds) return STREAM_NONE;
+    if (epi == ST_COMBINE) return K >= 2560 ? STREAM_256x192 : STREAM_NONE;
+    if (!activation ? K >= (rows > 136 ? 1408 : 1152) : !one_round(256, 192) && K >= (t > 6 * 256 ? 2240 : 1152)) return STREAM_256x192;
   }
   return STREAM_NONE;
 }

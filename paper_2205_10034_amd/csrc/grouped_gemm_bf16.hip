@@ -1300,7 +1300,7 @@ extern "C" const char* moe_test_product_kernel(const moe_config* cfg, int32_t se
   if (moe_config_check(cfg) != MOE_OK || cfg->dtype != MOE_BF16) return "";
   const int N = second ? cfg->d_model : cfg->d_ff, K = second ? cfg->d_ff : cfg->d_model;
   const bool swiglu = !second && cfg->act == MOE_ACT_SWIGLU;
-  const int epi = second ? EPI_BIAS : swiglu ? EPI_SWIGLU : EPI_GELU;
+  const int epi = second ? (cfg->k == 1 ? EPI_COMBINE : EPI_BIAS) : swiglu ? EPI_SWIGLU : EPI_GELU;
   if (expert_gemv_applies(cfg, N, K)) return (int64_t)cfg->k * cfg->T <= 8 ? "gemv 8" : "gemv 16";
   if (expert_stream_applies(cfg, N, K, epi)) return expert_stream_shape(cfg, N, K, epi);
   const int rows = grouped_tile_rows(cfg, N, K, swiglu ? 128 : 256);

@@ -135,7 +135,7 @@ def test_backward(T, E, k, act, renorm):
 
 @pytest.mark.parametrize("T,E,d,f,kernel", [
     (1, 4, 512, 512, "gemv 8"), (7, 8, 1024, 512, "gemv 8"), (12, 8, 512, 512, "stream 64x32"), (40, 4, 512, 512, "stream 64x32"),
-    (300, 2, 64, 256, "stream 64x64"), (2000, 3, 1024, 256, "stream 128x192"), (4000, 32, 2048, 1152, "stream 256x192"),
+    (300, 2, 64, 256, "stream 64x64"), (2000, 3, 1024, 256, "stream 128x192"), (4000, 32, 1088, 2560, "stream 256x192"),
     (20000, 64, 128, 256, "grouped 128"), (2500, 6, 2048, 256, "grouped 256"), (24000, 24, 320, 256, "grouped 256"), (8000, 2, 2048, 256, "grouped 320")])
 @pytest.mark.parametrize("residual", [False, True, "in place"])
 def test_one_expert_per_token(T, E, d, f, kernel, residual):

@@ -97,3 +97,15 @@ def test_the_rule_follows_the_products_place_and_not_its_sizes():
             assert product_kernel(cfg, 0) == first and product_kernel(cfg, 1) == second, (rows, E, d)
         beside = M.MoEConfig(T=rows * E // 2, d_model=d, d_ff=d + 64, E=E, k=2)
         assert product_kernel(beside, 1) == second
+
+
+def test_products_of_97_to_160_rows_that_stay_with_the_grouped_kernel():
+    """Shapes that measured slower on the streaming kernel: tiles that fill their rounds where an expert's rows are likely to spill
+    into a second tile, and combines (one choice per token) of short rows.  A capacity that rules a second tile out lifts the first."""
+    kernel = lambda rows, E, N, K, k, cf=0.0: product_kernel(M.MoEConfig(T=rows * E // k, d_model=N, d_ff=K, E=E, k=k, capacity_factor=cf), 1)
+    for rows, E, N, K, k in ((155, 64, 896, 5056, 2), (142, 64, 896, 2752, 2), (148, 128, 896, 1792, 2), (135, 16, 4096, 4096, 2),
+                             (134, 32, 4032, 1984, 1), (121, 64, 3584, 1152, 1), (123, 96, 1280, 2496, 1)):
+        assert kernel(rows, E, N, K, k) == "grouped 256", (rows, E, N, K, k)
+    for rows, E, N, K, k, cf in ((142, 64, 1088, 2752, 2, 0.0), (134, 64, 896, 2752, 2, 0.0), (142, 64, 896, 2752, 2, 1.25), (123, 96, 1280, 2560, 1, 0.0),
+                                 (155, 64, 896, 5056, 2, 1.0), (148, 128, 1088, 1792, 2, 0.0)):
+        assert kernel(rows, E, N, K, k, cf) == "stream 256x192", (rows, E, N, K, k, cf)
