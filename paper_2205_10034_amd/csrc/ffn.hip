@@ -158,8 +158,8 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_kernel(const float* __restrict
 // it holds.  A step is 32 values of the contraction index: operands go through registers into one of two LDS stages (16-byte
 // chunks XORed with half the row) while the other is multiplied; the loads of the step after next stay in flight across the
 // barrier, and a unit's rows of the second half of a step are read as soon as those of the first have been multiplied.
-// Two shapes, by pick_f32: 80 rows, three workgroups per CU (SwiGLU: 128 weight rows, two products), and 160 rows x 128 weight
-// rows, two per CU.  Bound by the float32 MFMAs (busy 75 % with even rows) and by whole rounds of tiles.  Measured on MI355X
+// Two shapes, by pick_f32: 80 rows, three workgroups per CU (SwiGLU: 128 weight rows, two products; two per CU if input-major), and
+// 160 rows x 128 weight rows, two per CU.  Bound by the float32 MFMAs (busy 75 % with even rows) and by whole rounds of tiles.  Measured on MI355X
 // against the 64 x 64 kernel (us): 80 rows, 140 random products 1.07 on average where the rule below picks it, 1.10 each
 // (4 experts of 1538 rows, 3712 -> 192 149 / 106; 8 of 268, 3648 -> 960 206 / 164; 16 of 69, 768 -> 3584 114 / 82); 160 rows, 16
 // experts of 256, 1024 -> 4096 -> 1024: 354 / 322 and 375 / 334 (107 and 103 TFLOP/s).
@@ -402,32 +402,51 @@ __global__ __launch_bounds__(SPLIT_WAVES * 64) void ffn_f32_split_kernel(
   }
 }
 
-// Which kernel: for evenly loaded experts, +- their spread under random routing (row tiles of an expert: the mean over 1.2
-// standard deviations below, at and above the mean row count).
+// Spread of an expert's rows under random routing: Poisson, and routers that like one expert a little more than another
+// (random router columns of d values: by about four over the root of 2 d).
+double row_sd(double rows) { return std::sqrt(rows + 0.0064 * rows * rows); }
+// Row tiles of tm rows that E experts of `rows` rows, at most C each, are expected to have together.
+double expected_tiles(int64_t E, int64_t rows, int64_t C, int tm) {
+  const double sd = row_sd((double)rows);
+  if (sd > tm) return E * (rows / (double)tm + 0.5);
+  double t = 1.0;
+  for (int64_t i = 1; i * tm < C && i * tm < rows + 5 * sd; ++i) t += 0.5 * std::erfc((i * tm + 0.5 - rows) / (sd * 1.4142135623730951));
+  return E * t;
+}
+
+// Which kernel (rounds: of 256 CUs):
 //  - the kernel that splits the contraction index up to 256 tiles of 64 rows (one for every CU).  Measured (us, 64 rows / split):
 //    112 tiles, K 2624: 60 / 50; 144 tiles, K 640: 21 / 18; 256 tiles of 16 rows, K 4096: 99 / 78; 288 tiles, K 2048: 85 / 92;
 //    656 tiles, K 448: 38 / 67; 1280 tiles, K 4096: 380 / 548;
-//  - 160 rows where long rows meet whole rounds of such tiles (one per CU, or two) that no expert overflows (three deviations):
-//    a round more costs more than the shape gains (8 experts of 599 rows, 3264 -> 960, one round and a few tiles: 307 / 493);
-//  - 80 rows from 256 values on where the tiles come to at least 0.8 of their rounds of 256 and to a tenth fewer than those of 64 (us, 64 / 80
-//    rows: 0.94 of a round against 1.2 114 / 87; 1.9 against 2.3 229 / 184; 2.6 against 3.3 171 / 155; but 1.5 against 1.8 78 / 88; 2.3
-//    against 2.9 131 / 149; 4 experts' worth of equal tiles, 16 of 93 rows, 52 / 56).  Of 140 random products 91 are within this
-//    line, 14 of them slower, by up to 14 % (7 experts of 805 rows, 1472 -> 1024 169 / 197).
+//  - 160 rows where long rows meet whole rounds of such tiles (one per CU, or two) that no expert is likely to overflow, since that
+//    opens a further round (64 experts of 256 rows, 4096 -> 256, one round: 377 / 580), the features fill their tiles (7 of 339, 5696 ->
+//    1472: 413 / 496), and an expert's rows leave its tiles of 64 rows unfilled, or are so many that those do not matter: at 80 to
+//    128 rows per tile both multiply the same (32 of 172, 3648 -> 512: 267 / 321);
+//  - 80 rows from 256 values on where the tiles come to less than 0.85 of those of 64 rows, in up to four rounds where they fill 0.84
+//    of these (16 of 140 rows, 1088 -> 512: one round overflown 49 / 55; 8 of 1016, 1024 -> 704, 4.5 rounds 120 / 131), or in more
+//    than seven, where no single round matters.  SwiGLU on input-major weights, of which two workgroups fit the LDS of a CU and not
+//    three: up to two rounds and the fourth (2 to 3 rounds 0.94 over 17 products, more than seven 1.01).
+// Over whole layers of random sizes and routing, d_model to 4096, d_ff to 14336, 64 to 16384 tokens, three sets of weights in turn, the
+// 203 products that 160 rows serve gain 1.15 over the kernels of 64 rows and the split (three of them lose more than 3 %, by up to 6 %),
+// the 1219 that 80 rows serve 1.14 (21, by up to 15 %).
 enum { F32_SPLIT, F32_64, F32_80, F32_160 };
-int pick_f32(const moe_config* cfg, int N, int K, bool swiglu) {
-  const int64_t rows = (max_rows(cfg) + cfg->E - 1) / cfg->E, E = cfg->E;
+int pick_f32(const moe_config* cfg, int N, int K, bool swiglu, bool input_major) {
+  const int64_t rows = (max_rows(cfg) + cfg->E - 1) / cfg->E, E = cfg->E, C = moe_capacity(cfg);
   auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   if (E * up(rows, FM) * up(N, FN) <= 256) return F32_SPLIT;
-  const double sd = std::sqrt((double)rows);
-  const int64_t low = rows - 1.2 * sd < 1 ? 1 : (int64_t)(rows - 1.2 * sd), high = (int64_t)(rows + 1.2 * sd);
-  auto rounds = [&](int tm, int outf) { return E * ((up(low, tm) + up(rows, tm) + up(high, tm)) / 3.0) * up(N, outf) / 256.0; };
   const int outf160 = swiglu ? 64 : 128;
-  if (K >= 1024 && N >= outf160 && up(rows, 160) == up((int64_t)(rows + 3 * sd), 160)) {
-    const double r = E * up(rows, 160) * up(N, outf160) / 256.0, pairs = std::ceil(r / 2) * 2;
+  const double most = rows + std::sqrt(2.0 * std::log((double)E)) * row_sd((double)rows);  // of the fullest of E experts
+  const int64_t each = up(rows, 160);
+  if (K >= 1024 && N >= outf160 && each == up(most < C ? (int64_t)most : C, 160) && up(N, outf160) * outf160 * 20 <= (int64_t)N * 21 &&
+      (rows <= 80 * each || rows >= 128 * each)) {
+    const double r = E * each * up(N, outf160) / 256.0, pairs = std::ceil(r / 2) * 2;
     if ((r <= 1 && r >= 0.94) || (r > 1 && r >= 0.94 * pairs)) return F32_160;
   }
-  const double r80 = rounds(80, 64);
-  if (K >= 256 && r80 >= 0.8 * std::ceil(r80) && r80 <= 0.9 * rounds(FM, FN)) return F32_80;
+  const double r80 = expected_tiles(E, rows, C, 80) * up(N, 64) / 256.0, r64 = expected_tiles(E, rows, C, FM) * up(N, FN) / 256.0;
+  const bool two_per_cu = swiglu && input_major;
+  if (K >= 256 && r80 <= 0.85 * r64 &&
+      ((r80 > 7 && !two_per_cu) || (r80 <= 4 && r80 >= 0.84 * std::ceil(r80) && !(two_per_cu && r80 > 2 && r80 <= 3))))
+    return F32_80;
   return F32_64;
 }
 
@@ -436,7 +455,7 @@ int32_t launch_f32_layout(const moe_config* cfg, const float* act, const float* 
                           const int32_t* offsets, float* out, int N, int K, hipStream_t s) {
   if (max_rows(cfg) == 0) return MOE_OK;
   constexpr bool SW = EPI == F_SWIGLU;
-  const int which = pick_f32(cfg, N, K, SW);
+  const int which = pick_f32(cfg, N, K, SW, IM);
   auto run = [&](auto kern, int tm, int tn, int threads) {
     const int n_tiles = (N + tn - 1) / tn;
     const int64_t grid = row_tile_grid(cfg, tm, n_tiles);
@@ -602,12 +621,13 @@ extern "C" int32_t moe_transpose_expert_weights(const void* src, void* dst, int3
   return check_hip(hipGetLastError(), "transpose launch");
 }
 
-// Rows per tile of the kernel that serves the float32 experts' first (second = 0) or second product; 32: the one that splits the
-// contraction index.  For the tests of the rule above; host only, not part of the interface in moesys.h.
-extern "C" int32_t moe_test_f32_tile_rows(const moe_config* cfg, int32_t second) {
+// Rows per tile of the kernel that serves the float32 experts' first (which = 0) or second (1) product, + 2 for input-major weights;
+// 32: the one that splits the contraction index.  For the tests of the rule above; host only, not part of the interface in moesys.h.
+extern "C" int32_t moe_test_f32_tile_rows(const moe_config* cfg, int32_t which) {
   using namespace moesys;
   if (moe_config_check(cfg) != MOE_OK || cfg->dtype != MOE_F32) return 0;
+  const bool second = which & 1;
   const int N = second ? cfg->d_model : cfg->d_ff, K = second ? cfg->d_ff : cfg->d_model;
   const int rows[] = {32, FM, 80, 160};
-  return rows[pick_f32(cfg, N, K, !second && cfg->act == MOE_ACT_SWIGLU)];
+  return rows[pick_f32(cfg, N, K, !second && cfg->act == MOE_ACT_SWIGLU, which & 2)];
 }

@@ -14,10 +14,10 @@ from gpu_util import alloc_ws
 pytestmark = pytest.mark.gpu
 
 
-def tile_rows(cfg, second):
+def tile_rows(cfg, second, layout="output_major"):
     f = M.lib().moe_test_f32_tile_rows
     f.restype = C.c_int32
-    return f(C.byref(cfg.c()), second)
+    return f(C.byref(cfg.c()), second + 2 * (layout == "input_major"))
 
 
 UNITS = [0, 1, 15, 16, 17, 32, 33, 48, 50, 64, 79, 80, 81, 160, 161, 128]      # 80-row tiles of one to five units
@@ -26,8 +26,8 @@ LARGE = [161, 160, 159, 144, 130, 128, 112, 99, 96, 80, 65, 64, 33, 0, 170, 177]
 
 # T is what an evenly loaded expert would hold, which picks the kernel; the rows themselves are RAGGED
 @pytest.mark.parametrize("act,T,rows,d,f,shift,first,second", [
-    ("gelu", 70 * 16, UNITS, 896, 1792, 0, 80, 80), ("swiglu", 70 * 16, UNITS, 896, 1792, 1, 80, 80),
-    ("gelu", 120 * 16, LARGE, 1024, 4032, 0, 160, 80), ("swiglu", 120 * 16, LARGE, 1024, 1984, 1, 160, 80)])
+    ("gelu", 66 * 16, UNITS, 896, 1792, 0, 80, 80), ("swiglu", 66 * 16, UNITS, 896, 1792, 1, 80, 80),
+    ("gelu", 256 * 16, LARGE, 1024, 4032, 0, 160, 160), ("swiglu", 256 * 16, LARGE, 1024, 1984, 1, 160, 160)])
 @pytest.mark.parametrize("layout", ["output_major", "input_major"])
 def test_f32_units(act, T, rows, d, f, shift, first, second, layout):
     print(act, T, d, f, shift, layout, flush=True)
@@ -49,7 +49,7 @@ def test_f32_units(act, T, rows, d, f, shift, first, second, layout):
         {"w_gate_proj": mat(d, f), "w_up": mat(d, f), "w_down": mat(f, d)}
     xd = rand(R, d)
     cfg = M.MoEConfig(T=T, d_model=d, d_ff=f, E=E, k=1, act=act, dtype="f32")
-    assert tile_rows(cfg, 0) == first and tile_rows(cfg, 1) == second
+    assert tile_rows(cfg, 0, layout) == first and tile_rows(cfg, 1, layout) == second
     guard = torch.full((R + 1, d), 7.0, device="cuda")
     W = M.Weights({**t, "w_router": torch.zeros(d, E, device="cuda")}, layout)
     M.moe_expert_ffn(cfg, W, xd, torch.from_numpy(off).cuda(), guard[:R], alloc_ws(cfg, 2))
@@ -73,7 +73,7 @@ def test_f32_units(act, T, rows, d, f, shift, first, second, layout):
 
 
 @pytest.mark.parametrize("rows,E,N,K,want", [
-    (262, 16, 448, 512, 80), (787, 8, 192, 2944, 80), (435, 8, 512, 1856, 64), (512, 8, 704, 2944, 80),
+    (262, 16, 448, 512, 64), (787, 8, 192, 2944, 80), (435, 8, 512, 1856, 64), (512, 8, 704, 2944, 64),
     (256, 16, 1024, 4096, 160), (599, 8, 960, 3264, 80), (16, 16, 1024, 4096, 32)])
 def test_f32_rule(rows, E, N, K, want):
     assert tile_rows(M.MoEConfig(T=rows * E, d_model=N, d_ff=K, E=E, k=1, dtype="f32"), 1) == want

@@ -1,5 +1,7 @@
 """The rules that choose the kernel of an expert product, on the host: what each range of sizes is served by, and that long
 contraction indices reach only kernels whose offsets hold them."""
+import ctypes as C
+
 import pytest
 
 import paper_2205_10034_amd as M
@@ -109,3 +111,36 @@ def test_products_of_97_to_160_rows_that_stay_with_the_grouped_kernel():
     for rows, E, N, K, k, cf in ((142, 64, 1088, 2752, 2, 0.0), (134, 64, 896, 2752, 2, 0.0), (142, 64, 896, 2752, 2, 1.25), (123, 96, 1280, 2560, 1, 0.0),
                                  (155, 64, 896, 5056, 2, 1.0), (148, 128, 1088, 1792, 2, 0.0)):
         assert kernel(rows, E, N, K, k, cf) == "stream 256x192", (rows, E, N, K, k, cf)
+
+
+def f32_rows(rows, E, N, K, cf=0.0, act="gelu", layout="output_major", second=1):
+    """Tile rows of a float32 product [rows E, K] -> N."""
+    f = M.lib().moe_test_f32_tile_rows
+    f.restype = C.c_int32
+    d, h = (N, K) if second else (K, N)
+    cfg = M.MoEConfig(T=rows * E, d_model=d, d_ff=h, E=E, k=1, act=act, dtype="f32", capacity_factor=cf)
+    return f(C.byref(cfg.c()), second + 2 * (layout == "input_major"))
+
+
+def test_float32_tiles_of_160_rows():
+    """Not where an expert is likely to overflow them and open a further round, where features or rows leave them half empty, or
+    where tiles of 64 rows are as full; a capacity rules the overflow out."""
+    for rows, E, N, K, cf in ((256, 64, 256, 4096, 0.0), (271, 32, 512, 7040, 0.0), (241, 64, 192, 11136, 1.25), (339, 7, 1472, 5696, 1.25),
+                              (172, 32, 512, 3648, 0.0), (170, 16, 1024, 2048, 0.0), (491, 64, 128, 2432, 1.25)):
+        assert f32_rows(rows, E, N, K, cf) != 160, (rows, E, N, K, cf)
+    for rows, E, N, K, cf in ((256, 16, 1024, 4096, 0.0), (256, 16, 4096, 1024, 1.25), (256, 64, 256, 4096, 1.25), (64, 32, 1024, 2048, 0.0),
+                              (512, 16, 2048, 2048, 1.25), (17, 64, 512, 2048, 0.0)):
+        assert f32_rows(rows, E, N, K, cf) == 160, (rows, E, N, K, cf)
+
+
+def test_float32_tiles_of_80_rows():
+    """Not where random routing opens a further round of the first four, nor in four to seven, nor for two to three rounds of SwiGLU on
+    input-major weights."""
+    for rows, E, N, K, cf in ((140, 16, 512, 1088, 1.25), (1016, 8, 704, 1024, 1.25), (453, 16, 512, 1536, 1.25), (260, 16, 1344, 1280, 0.0)):
+        assert f32_rows(rows, E, N, K, cf) == 64, (rows, E, N, K, cf)
+    for rows, E, N, K in ((787, 8, 192, 2944), (599, 8, 960, 3264), (66, 16, 896, 1792)):
+        assert f32_rows(rows, E, N, K) == 80, (rows, E, N, K)
+    for rows, N, first in ((375, 1024, 64), (66, 1792, 80)):
+        E = 8 if rows == 375 else 16
+        assert f32_rows(rows, E, N, 512, 1.25, "swiglu", "output_major", 0) == 80
+        assert f32_rows(rows, E, N, 512, 1.25, "swiglu", "input_major", 0) == first
