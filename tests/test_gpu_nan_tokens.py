@@ -157,3 +157,69 @@ def test_one_expert_per_token(T, E, d, f, kernel, residual):
         torch.cuda.synchronize()
         assert torch.equal(out[good], ref[good])
         assert torch.equal(out[bad].view(torch.int16), want.view(torch.int16))
+
+
+def product_name(cfg, second):
+    if cfg.dtype == "f32":
+        import ctypes as C
+        f = M.lib().moe_test_f32_tile_rows
+        f.restype = C.c_int32
+        return f"{f(C.byref(cfg.c()), second)} rows"
+    from gpu_util import product_kernel
+    return product_kernel(cfg, second)
+
+
+@pytest.mark.parametrize("dtype,act,rows,E,d,f,k,kernels", [
+    ("bf16", "gelu", 120, 16, 1280, 4416, 2, ("stream 256x192", "stream 128x192")), ("bf16", "swiglu", 110, 32, 1600, 2624, 2, ("stream 256x192",) * 2),
+    ("bf16", "gelu", 2, 4, 512, 512, 1, ("gemv 8",) * 2), ("bf16", "gelu", 20, 8, 512, 512, 2, ("stream 64x32",) * 2),
+    ("bf16", "swiglu", 700, 8, 1024, 1024, 2, ("grouped 256", "stream 128x192")), ("f32", "gelu", 66, 16, 896, 1792, 2, ("80 rows",) * 2),
+    ("f32", "swiglu", 256, 16, 1024, 1984, 2, ("160 rows",) * 2), ("f32", "gelu", 40, 8, 256, 512, 1, ("32 rows",) * 2), ("f32", "gelu", 435, 8, 512, 1856, 1, ("64 rows",) * 2)])
+def test_rows_of_an_expert_stay_apart(dtype, act, rows, E, d, f, k, kernels):
+    """Rows with NaN or infinite activations (an expert's first, last and one inside, beside experts without any) leave every
+    other row as it is, bit for bit."""
+    print(dtype, act, rows, E, d, f, flush=True)
+    n = [max(1, rows + (i % 3 - 1) * (rows // 4)) for i in range(E)]
+    cfg, W, _ = layer(d, f, E, rows * E // k, k, act=act, dtype=dtype)
+    assert (product_name(cfg, 0), product_name(cfg, 1)) == kernels
+    n[-1] = rows * E - sum(n[:-1])
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = torch.randn(int(off[-1]), d, generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    bad = sorted({int(r) for e in range(0, E, 2) for r in (off[e], off[e] + n[e] // 2, off[e + 1] - 1)})
+    good = sorted(set(range(int(off[-1]))) - set(bad))
+    xn = x.clone()
+    xn[bad, ::5] = float("nan")
+    xn[bad[::2]] = float("inf")
+    ws = torch.empty(M.moe_workspace_bytes(cfg, 2), dtype=torch.uint8, device="cuda")
+    outs = []
+    for a in (x, xn):
+        y = torch.full_like(x, 7.0)
+        ws.fill_(0xAB)
+        M.moe_expert_ffn(cfg, W, a, torch.from_numpy(off).cuda(), y, ws)
+        torch.cuda.synchronize()
+        outs.append(y)
+    assert torch.equal(outs[0][good], outs[1][good]) and bool(outs[0].isfinite().all())
+    assert not bool(outs[1][bad].isfinite().any())
+
+
+@pytest.mark.parametrize("E,rows,N1,N2", [(9, [70, 33, 0, 64, 1], 512, 768), (8, [1500, 1403], 512, 512), (3, [130, 65], 512, 512)])
+def test_weight_gradients_of_experts_stay_apart(E, rows, N1, N2):
+    """An expert whose rows hold NaN and infinities beside one that ends in the middle of a step: its own gradient only."""
+    print(E, rows, N1, N2, flush=True)
+    n = [rows[i % len(rows)] for i in range(E)]
+    off = np.concatenate([[0], np.cumsum(n)])
+    g = torch.Generator(device="cuda").manual_seed(E)
+    a, b = (torch.randn(int(off[-1]), w, generator=g, device="cuda").bfloat16() for w in (N1, N2))
+    offsets = torch.tensor(off, dtype=torch.int32, device="cuda")
+    an, bn = a.clone(), b.clone()
+    for e in range(1, E, 2):
+        an[off[e]:off[e + 1]] = float("nan")
+        bn[off[e]:off[e + 1], ::3] = float("inf")
+    for dt in (torch.float32, torch.bfloat16):
+        c = [torch.full((E, N1, N2), 7.0, dtype=dt, device="cuda") for _ in range(2)]
+        s = [torch.full((E, N1), 7.0, device="cuda") for _ in range(2)]
+        M.moe_expert_wgrad(a, b, offsets, c[0], max(n), a_column_sums=s[0])
+        M.moe_expert_wgrad(an, bn, offsets, c[1], max(n), a_column_sums=s[1])
+        torch.cuda.synchronize()
+        assert torch.equal(c[0][::2], c[1][::2]) and torch.equal(s[0][::2], s[1][::2])
+        assert all(bool(c[1][e].isnan().all()) for e in range(1, E, 2) if n[e])
