@@ -422,13 +422,15 @@ double expected_tiles(int64_t E, int64_t rows, int64_t C, int tm) {
 //    opens a further round (64 experts of 256 rows, 4096 -> 256, one round: 377 / 580), the features fill their tiles (7 of 339, 5696 ->
 //    1472: 413 / 496), and an expert's rows leave its tiles of 64 rows unfilled, or are so many that those do not matter: at 80 to
 //    128 rows per tile both multiply the same (32 of 172, 3648 -> 512: 267 / 321);
-//  - 80 rows from 256 values on where the tiles come to less than 0.85 of those of 64 rows, in up to four rounds where they fill 0.84
-//    of these (16 of 140 rows, 1088 -> 512: one round overflown 49 / 55; 8 of 1016, 1024 -> 704, 4.5 rounds 120 / 131), or in more
-//    than seven, where no single round matters.  SwiGLU on input-major weights, of which two workgroups fit the LDS of a CU and not
-//    three: up to two rounds and the fourth (2 to 3 rounds 0.94 over 17 products, more than seven 1.01).
+//  - 80 rows from 256 values on where the tiles come to at most 0.9 of those of 64 rows and fill 0.82 of their rounds, up to the first
+//    tiles of the fifth (beyond, up to six, 1.01 on average and a quarter slower), or are more than six rounds, where no single round
+//    matters.  One round overflown: 16 experts of 140 rows, 1088 -> 512, 49 / 55; 4.5 rounds: 8 of 1016, 1024 -> 704, 120 / 131.
+//    SwiGLU on output-major weights, where the 64-row kernel has two products' weights for half the rows, always but for
+//    the start of a second round (1.14); on input-major ones two workgroups fit the LDS of a CU and not three: not in two to three
+//    rounds (0.96) nor in four to 5.5 (0.98).
 // Over whole layers of random sizes and routing, d_model to 4096, d_ff to 14336, 64 to 16384 tokens, three sets of weights in turn, the
-// 203 products that 160 rows serve gain 1.15 over the kernels of 64 rows and the split (three of them lose more than 3 %, by up to 6 %),
-// the 1219 that 80 rows serve 1.14 (21, by up to 15 %).
+// 362 products that 160 rows serve gain 1.15 over the kernels of 64 rows and the split (five of them lose more than 3 %, by up to 6 %),
+// the 1643 that 80 rows serve 1.12 (75, by up to 11 %, mostly where routing takes one tile more than expected).
 enum { F32_SPLIT, F32_64, F32_80, F32_160 };
 int pick_f32(const moe_config* cfg, int N, int K, bool swiglu, bool input_major) {
   const int64_t rows = (max_rows(cfg) + cfg->E - 1) / cfg->E, E = cfg->E, C = moe_capacity(cfg);
@@ -443,10 +445,11 @@ int pick_f32(const moe_config* cfg, int N, int K, bool swiglu, bool input_major)
     if ((r <= 1 && r >= 0.94) || (r > 1 && r >= 0.94 * pairs)) return F32_160;
   }
   const double r80 = expected_tiles(E, rows, C, 80) * up(N, 64) / 256.0, r64 = expected_tiles(E, rows, C, FM) * up(N, FN) / 256.0;
-  const bool two_per_cu = swiglu && input_major;
-  if (K >= 256 && r80 <= 0.85 * r64 &&
-      ((r80 > 7 && !two_per_cu) || (r80 <= 4 && r80 >= 0.84 * std::ceil(r80) && !(two_per_cu && r80 > 2 && r80 <= 3))))
-    return F32_80;
+  const bool whole = r80 <= 4.3 && (r80 > 4 || r80 >= 0.82 * std::ceil(r80));
+  const bool pays = !swiglu      ? whole || r80 > 6
+                    : input_major ? (whole && r80 <= 4 && !(r80 > 2 && r80 <= 3)) || r80 > 5.5
+                                  : r80 > 1.65 || (r80 <= 1 && r80 >= 0.8);
+  if (K >= 256 && r80 <= 0.9 * r64 && pays) return F32_80;
   return F32_64;
 }
 

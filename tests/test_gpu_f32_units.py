@@ -73,7 +73,7 @@ def test_f32_units(act, T, rows, d, f, shift, first, second, layout):
 
 
 @pytest.mark.parametrize("rows,E,N,K,want", [
-    (262, 16, 448, 512, 64), (787, 8, 192, 2944, 80), (435, 8, 512, 1856, 64), (512, 8, 704, 2944, 64),
+    (262, 16, 448, 512, 80), (787, 8, 192, 2944, 80), (435, 8, 512, 1856, 64), (512, 8, 704, 2944, 64),
     (256, 16, 1024, 4096, 160), (599, 8, 960, 3264, 80), (16, 16, 1024, 4096, 32)])
 def test_f32_rule(rows, E, N, K, want):
     assert tile_rows(M.MoEConfig(T=rows * E, d_model=N, d_ff=K, E=E, k=1, dtype="f32"), 1) == want

@@ -134,8 +134,8 @@ def test_float32_tiles_of_160_rows():
 
 
 def test_float32_tiles_of_80_rows():
-    """Not where random routing opens a further round of the first four, nor in four to seven, nor for two to three rounds of SwiGLU on
-    input-major weights."""
+    """Not where random routing opens a further round of the first four, nor in the fifth and sixth, nor for two to three rounds of
+    SwiGLU on input-major weights."""
     for rows, E, N, K, cf in ((140, 16, 512, 1088, 1.25), (1016, 8, 704, 1024, 1.25), (453, 16, 512, 1536, 1.25), (260, 16, 1344, 1280, 0.0)):
         assert f32_rows(rows, E, N, K, cf) == 64, (rows, E, N, K, cf)
     for rows, E, N, K in ((787, 8, 192, 2944), (599, 8, 960, 3264), (66, 16, 896, 1792)):
