@@ -480,7 +480,8 @@ extern "C" int32_t moe_layer_backward(const moe_config* cfg, const moe_weights* 
     if (d_b_router) hipLaunchKernelGGL(gate_dbias_kernel, dim3(cfg->E), dim3(256), 0, s, d_z, d_b_router, 0, cfg->E);
     return check_hip(hipGetLastError(), "moe_layer_backward");
   }
-  // the probabilities are not kept by the forward pass: run the gate again (same routing, bit for bit)
+  // the probabilities are not kept by the forward pass: run the gate again (its selection is not used; up to eight tokens the
+  // forward pass may have summed the logits in another order, in float64: the last place of a probability)
   if ((st = launch_gate_of(cfg, w, x, (int32_t*)(b + L.idx), (float*)(b + L.w), probs, s)) != MOE_OK) return st;
   if (gemm2_can_combine(cfg)) {
     // with one expert per token the forward pass wrote `out` directly: recompute the experts' outputs

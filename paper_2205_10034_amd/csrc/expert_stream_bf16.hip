@@ -6,9 +6,9 @@
 // The product's time is the time to stream the activated experts' weights once.  The 256 x 256 tiles of the grouped GEMM
 // have one 64 KB stage in flight per CU, half of it rows that are not there, and their number is too small for the chip
 // when the feature count is: 8 experts x 4096 features are 128 tiles for 256 CUs.  Here a workgroup owns 64 to 256 weight
-// rows and 32 to 192 rows of one expert and keeps all but one of its three to five LDS stages (64 values of the
-// contraction index each) requested ahead: weights and rows go from global memory straight into LDS, swizzled like the
-// grouped GEMM's, one barrier per stage.  A wavefront multiplies blocks of 16 weight rows by blocks of 16 rows
+// rows and 32 to 192 rows of one expert and requests the stages of all but one of its three to five LDS buffers (64 values of the
+// contraction index each) ahead, though the queue drains once per pass through the buffers (see the K loop): weights and
+// rows go from global memory straight into LDS, swizzled like the grouped GEMM's, one barrier per stage.  A wavefront multiplies blocks of 16 weight rows by blocks of 16 rows
 // (v_mfma_f32_16x16x32_bf16, weights as the first operand: a lane ends up with four consecutive features of one row).
 // SwiGLU: half of the weight rows are the gate's and half the up projection's; a block of 16 is eight and eight of the
 // same features.
@@ -209,8 +209,9 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     issue_w(policy, 1, w1);
     if constexpr (STAGES > 3) { issue_a(2, a2); issue_w(policy, 2, w2); }
     if constexpr (STAGES > 4) { issue_a(3, a3); issue_w(policy, 3, w3); }
-    // (left by breaks: on every way round the loop all stages were requested, which is what lets the compiler see that no
-    // further wait is needed before a stage is read)
+    // Left by breaks: on every way round the loop all stages were requested, and inside a pass the compiler adds no wait of
+    // its own.  At the head of the loop, where the passes and the prologue meet, it does: the first step of every pass waits for
+    // all loads (vmcnt(0) behind the barrier), whichever stages they belong to.
     for (int kt = 0;;) {
       step(policy, std::integral_constant<int, 0>{}, kt);
       if (++kt == KT) break;
@@ -333,8 +334,8 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 // Skewed routing costs row tiles that the rule does not see.  Over the same shapes under Zipf(1.2) masses the mean gain is
 // within a tenth of that under even routing, but 128x192 loses 7 to 14 % where the hot expert's extra tiles open a second
 // round (16 experts, f 1600 -> d 1792, 115 rows: even 33 / 22, Zipf 35 / 40), and 64x32 up to 20 % with every row of a
-// step on one expert of 64.  Of 1300 whole expert blocks under even or random routing none is more than 3 % slower than on
-// the grouped GEMM, of 1300 under Zipf or half-on-one-expert routing 16 are, by up to 9 %.
+// step on one expert of 64.  Of 1300 whole expert blocks under even or random routing none was more than 3 % slower than on
+// the grouped GEMM, of 1300 under Zipf or half-on-one-expert routing 16 were, by up to 9 % (before the shape that follows).
 //  - 97 to 160 rows otherwise: 256x192, three stages of weights and two of rows in the LDS; the grouped GEMM has one stage of
 //    weights on its way and waits for it.  Over 126 random products of 97 to 180 rows 1.12 on average (grouped / here): 64
 //    experts, 131 rows, f 3456 -> d 3264 366 / 314; 16 SwiGLU, 112 rows, 3008 -> 8704 467 / 398; 64 SwiGLU, 128 rows, 2048 -> 4096

@@ -651,8 +651,8 @@ __global__ __launch_bounds__(WT * WF * 64, WPE) void grouped_gemm_kernel(
     // sub-step 0 of stage kt+1 is read.
     // The two wavefronts of a SIMD leave the barrier together, and oldest-first issue lets one run ahead through the whole
     // K-step, wait at the next barrier and leave the other's latencies uncovered (860 clocks of barrier wait against 90).  A
-    // wavefront's priority falls from sub-step to sub-step, so that the one behind goes first.  MI355X, us: layer_top1 203 -> 200,
-    // layer_ring 924 -> 913, a SwiGLU training step 2068 -> 2047, a GPT-style layer 312 -> 311; none slower.
+    // wavefront's priority falls from sub-step to sub-step, so that the one behind goes first.  MI355X, whole layers and training
+    // steps: 0 to 1 %, 0.5 on average of seven (a SwiGLU training step 2068 -> 2047 us), which single runs do not resolve.
     auto step = [&](int kt, unsigned char* cur, unsigned char* nxt) {
       __builtin_amdgcn_s_setprio(2);
       issue_weights(kt + 1, kt + 1 < KT, nxt);

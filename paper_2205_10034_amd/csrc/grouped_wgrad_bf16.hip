@@ -26,6 +26,9 @@
 // 1024 float32 (us): 256 x 256 tiles, 16 bytes per lane and row 159; the same as whole lines 153; past the caches too
 // 149; 128 x 256 tiles 135 (1.02 PFLOP/s; without the whole lines 159-172; past the caches without them 185).  At 256 rows
 // 79 -> 60, bf16 58 -> 45; 8 experts of 1024 rows, 11264 x 2048 bf16 375 -> 332; 64 of 128, 2048 x 4096 bf16 366 -> 238.
+// At every size: an optimizer that reads the gradient at once and finds it in no cache pays for it.  Ordinary / non-temporal over 250
+// random products, three sets in turn, alone and with an update p += a g right behind: up to 64 MB of gradient 1.05 and 1.00, 64 to
+// 128 MB 1.08 and 0.95, above 1.15 and 1.02.  In a training step the other gradients come between, more than the caches hold.
 // Tile order.  The 8 XCDs have an L2 each, and the hardware deals workgroups out to them round robin.  A tile
 // streams a slab of A and one of B; tiles of one expert with the same n1 (n2) tile share the A (B) slab.  The tiles of
 // an expert are numbered in blocks of BY x BX, the experts one after the other, and units of `unit` consecutive tiles are
@@ -287,8 +290,9 @@ __global__ __launch_bounds__((WgShape<TN1, TN2, N1B>::WAVES * 64), 2) void group
 #endif
 }
 
-// Tiles of the XCD that gets most of them when blocks of BY x BX tiles are dealt out whole (a measure of how raggedly an
-// expert's tiles divide into blocks).
+// Tiles of the XCD that gets most of them when blocks of BY x BX tiles are dealt out whole.  The kernel deals out even units, so
+// this is no load of its XCDs; it measures how raggedly an expert's tiles divide into blocks, and thus how many slabs of operands
+// the tiles that run together on an XCD share.
 int64_t busiest_xcd(int E, int n1t, int n2t, int BX, int BY) {
   int64_t load[8] = {}, most = 0;
   int x = 0;
@@ -300,8 +304,12 @@ int64_t busiest_xcd(int E, int n1t, int n2t, int BX, int BY) {
 }
 
 // Edge along n2: 256 (3 transposing LDS reads per 2 MFMAs against 4 per 2 for 128 x 128) unless 256 x 256 tiles leave a quarter
-// of their rounds of 256 CUs empty and do not divide more raggedly when they are smaller (whole rounds of 32 large tiles per
-// XCD against 64 small ones in 0.62 of that time).  Measured on MI355X (us, 128 x 256 / 128 x 128): 4 experts of
+// of their rounds of 256 CUs empty and do not divide more raggedly when they are smaller.  The line (62 small tiles of an XCD
+// against its 64 for whole rounds of 32 large ones) was drawn when blocks were dealt out whole and is no model of the present
+// order.  Over 500 random products, a quarter under Zipf routing, the best of the three tiles takes 0.973 of its time, one tile
+// always 0.99 (128 x 128), 1.13 (128 x 256) and 1.31 (256 x 256); most of what it gives away is under Zipf routing, where a hot
+// expert's sums are long (64 experts, 512 x 512, 699 / 365 with 128 x 128).  Of 250 products three are slower than with the tiles and order
+// before these, by up to 10 %.  Measured on MI355X (us, 128 x 256 / 128 x 128): 4 experts of
 // 1840 rows, 2048 x 512 f32 33 / 23; 4 of 708, 1024 x 1536 f32 19 / 17; 4 of 2525, 1792 x 1280 bf16 64 / 57.  Past that line either may
 // win by a tenth: 4 experts of 230 rows, 2048 x 2304 f32 26 / 21; 8 of 1004, 4096 x 1024 74 / 81; 32 of 1653, 1024 x 5376 560 / 646.
 // Edge along n1 beside 256: 128, two workgroups per CU that cover each other's start and stores.  256 where the operands are
