@@ -278,7 +278,8 @@ int32_t moe_layer_forward(const moe_config* cfg, const moe_weights* w, const voi
  * are the only weights read); moe_layer_experts runs expert FFN and combine
  * from what moe_layer_route left in the same workspace.  Same arguments,
  * workspace and rules as moe_layer_forward; calling one after the other is
- * moe_layer_forward.  moe_layer_experts leaves the routing tables as it found
+ * moe_layer_forward.  moe_layer_route may use the h segment as scratch (the
+ * next moe_layer_experts writes it).  moe_layer_experts leaves the routing tables as it found
  * them, so it may run again on the same workspace (e.g. with other expert
  * weights, or after a failed load) without a new moe_layer_route. */
 int32_t moe_layer_route(const moe_config* cfg, const moe_weights* w, const void* x, void* ws,
