@@ -24,6 +24,7 @@
 // histogram atomics only add).
 #include <atomic>
 #include "moesys_internal.h"
+#include "routing_tables.h"
 #include "wave_util.h"
 
 // Bookkeeping scratch of moe_dispatch_static, the variant of moe_dispatch for callers that cannot allocate:
@@ -99,30 +100,6 @@ __global__ __launch_bounds__(SCAN_E * SCAN_S) void dispatch_scan_kernel(int32_t*
       }
   }
   if (seg == SCAN_S - 1) block_hist[(size_t)nblocks * E + e] = run;
-}
-
-// Exclusive prefix of the kept rows per expert by the first wavefront: lane l owns the experts 4l .. 4l + 3.
-__device__ __forceinline__ void prefix_offsets(const int* total_s, int* off_s, int E, int C, int wave, int lane) {
-  if (wave != 0) return;
-  static_assert(MOE_MAX_EXPERTS == 256, "four experts per lane");
-  int own[4], sum = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int e = 4 * lane + j;
-    own[j] = sum;
-    sum += e < E ? min(total_s[e], C) : 0;
-  }
-  int incl = sum;
-  for (int m = 1; 4 * m <= E; m <<= 1) {  // (lanes 0 .. E / 4 meet: the last writes off_s[E])
-    const int up = __shfl_up(incl, m, 64);
-    incl += lane >= m ? up : 0;
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int e = 4 * lane + j;
-    if (e <= E) off_s[e] = incl - sum + own[j];  // (e == E: the experts before it are all there are)
-  }
-  if (E == MOE_MAX_EXPERTS && lane == 63) off_s[E] = incl;
 }
 
 // prefixed = 1: block_hist holds exclusive prefixes and a totals row (scan kernel ran);
@@ -208,62 +185,25 @@ __global__ __launch_bounds__(BT) void dispatch_assign_kernel(const int32_t* __re
   }
 }
 
-// Up to 1024 R assignments in one workgroup: a wavefront ranks its 64 R consecutive assignments 64 at a time against its own
-// running counts, the wavefronts' counts meet in LDS.  Bound by latency: the two kernels it replaces take 4 to 5 us each for
+// Up to 1024 R assignments in one workgroup.  Bound by latency: the two kernels it replaces take 4 to 5 us each for
 // launch, one chain of loads and stores.  Measured on MI355X, calls back to back (us, before / now): 258 assignments over 8
 // experts 12.8 / 10.2, 1024 over 64 12.1 / 9.5, 4092 over 128 12.3 / 9.4, 4096 over 256 14.8 / 9.5; layers of 257 to 1300 assignments
 // 2 to 2.6 us less.
-constexpr int ONE_WAVES = 16;
 template <int R>
 __global__ __launch_bounds__(ONE_WAVES * 64) void dispatch_one_kernel(const int32_t* __restrict__ topk_idx, int T, int k, int E, int C,
                                                                       int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                                                                       int32_t* __restrict__ a2r, int32_t* __restrict__ r2a,
                                                                       int32_t* __restrict__ clear8) {
-  __shared__ int cnt[ONE_WAVES][MOE_MAX_EXPERTS];  // per wavefront: assignments of every expert, then those before the wavefront's
-  __shared__ int total_s[MOE_MAX_EXPERTS];
-  __shared__ int off_s[MOE_MAX_EXPERTS + 1];
+  __shared__ OneTables tables;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (clear8 && tid < 8) clear8[tid] = 0;
-  int e_of[R], slot[R];
+  int e_of[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int a = (wave * R + r) * 64 + lane;
     e_of[r] = a < T * k ? valid_expert(expert_of(topk_idx, a, T, k), E) : -1;
   }
-  for (int e = lane; e < E; e += 64) cnt[wave][e] = 0;
-  asm volatile("" ::: "memory");  // (a wavefront's LDS operations execute in order)
-#pragma unroll
-  for (int r = 0; r < R; ++r) slot[r] = place_in_expert(e_of[r], E, cnt[wave], lane);
-  __syncthreads();
-  if (tid < E) {
-    int run = 0;
-#pragma unroll
-    for (int w = 0; w < ONE_WAVES; ++w) {
-      const int c = cnt[w][tid];
-      cnt[w][tid] = run;
-      run += c;
-    }
-    total_s[tid] = run;
-  }
-  __syncthreads();
-  prefix_offsets(total_s, off_s, E, C, wave, lane);
-  __syncthreads();
-  for (int i = tid; i <= E; i += ONE_WAVES * 64) {
-    offsets[i] = off_s[i];
-    if (i < E) counts[i] = total_s[i];
-  }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int a = (wave * R + r) * 64 + lane, e = e_of[r];
-    if (a >= T * k) continue;
-    int row = -1;
-    if (e >= 0) {
-      const int s = slot[r] + cnt[wave][e];
-      if (s < C) row = off_s[e] + s;
-    }
-    a2r[a] = row;
-    if (row >= 0) r2a[row] = a;
-  }
+  write_tables<R>(e_of, T * k, E, C, tables, counts, offsets, a2r, r2a);
 }
 
 // With no assignment at all the tables still have to say so.

@@ -12,8 +12,9 @@
 // Exact path (float32 activations, E > 64, or many tokens on more than 16 experts by gate_f64_pays): the products of two float32 / bfloat16 values are exact in float64, and
 // v_mfma_f64_16x16x4_f64 accumulates them there, so only the summation rounds, at 2^-53 relative, and nothing has to be
 // recomputed; see gate_f64_kernel.
-#include <type_traits>
+#include "gate_rank.h"
 #include "moesys_internal.h"
+#include "routing_tables.h"
 #include "wave_util.h"
 
 namespace moesys {
@@ -26,29 +27,6 @@ __device__ __forceinline__ double shfl_xor_f64(double v, int m) {
   lo = __shfl_xor(lo, m, 64);
   hi = __shfl_xor(hi, m, 64);
   return __hiloint2double(hi, lo);
-}
-
-// A lane's partner inside its group of eight consecutive lanes, for the three steps of a reduction over the group:
-// steps 0 and 1 swap lanes inside a quad (lane ^ 1, lane ^ 2), step 2 mirrors the eight lanes (lane i with 7 - i,
-// which lies in the other quad).  Data-parallel-primitive moves on the vector ALU: a few clocks each, where a
-// general lane permutation goes through the LDS crossbar (a hundred clocks, and a reduction is a chain of them).
-template <int STEP>
-__device__ __forceinline__ int group8_partner(int v) {
-  constexpr int ctrl = STEP == 0 ? 0xB1 /* quad_perm 1,0,3,2 */ : STEP == 1 ? 0x4E /* quad_perm 2,3,0,1 */ : 0x141 /* row_half_mirror */;
-  return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xF, 0xF, true);
-}
-template <int STEP>
-__device__ __forceinline__ float group8_partner(float v) { return __int_as_float(group8_partner<STEP>(__float_as_int(v))); }
-template <int STEP>
-__device__ __forceinline__ double group8_partner(double v) {
-  return __hiloint2double(group8_partner<STEP>(__double2hiint(v)), group8_partner<STEP>(__double2loint(v)));
-}
-// f(step) for the three steps, unrolled
-template <typename F>
-__device__ __forceinline__ void group8_steps(F&& f) {
-  f(std::integral_constant<int, 0>{});
-  f(std::integral_constant<int, 1>{});
-  f(std::integral_constant<int, 2>{});
 }
 
 // One wavefront ranks one token from its float64 logits z[0..E): softmax in float32 (row maximum subtracted),
@@ -212,128 +190,6 @@ int32_t launch_few(const moe_config* cfg, const void* x, const float* w_router, 
   return check_hip(hipGetLastError(), "gate launch");
 }
 
-// Up to eight of those tokens inside a layer whose router is half a megabyte or more: one compute unit takes 10 to 16 us to
-// read it.  Its rows are spread over up to GS_SLICES workgroups, each of which multiplies its slice by all tokens in float64
-// (exact products) and stores the partial logits; one workgroup then adds them in slice order, ranks every token in a
-// wavefront of its own and writes the dispatch tables of the at most 64 assignments, which saves their kernel.  Four or
-// more tokens are dealt out to the wavefronts; fewer: the wavefronts split the rows.  Bound by the latency of two launches
-// and of the ranking.  Measured on MI355X: routing alone with everything cached (us, one workgroup per token / slices), d 2048,
-// 64 experts: T 1 10.0 / 9.5, T 4 12.8 / 11.5, T 8 12.9 / 13.6, T 16 14.4 / 20.2; d 4096, 64: T 1 14.8 / 10.1, T 8 17.9 / 17.1; d 4096,
-// 32: T 2 13.0 / 11.1; smaller routers lose (d 2048, 32: T 1 8.0 / 9.5).  In the layer, where the experts' weights have driven
-// the router out of the caches: d 2048, 64 experts, T 1 47.4 / 41.3 us per layer, T 8 184.1 / 179.9.
-constexpr int GS_SLICES = 32, GS_MAX_T = 8, GS_TT = 3;
-template <bool SPLIT_ROWS>
-__global__ __launch_bounds__(256) void gate_slice_kernel(const uint16_t* __restrict__ x, const float* __restrict__ wr, int T, int d, int E,
-                                                         int rows_per, double* __restrict__ part) {
-  __shared__ double red[SPLIT_ROWS ? 4 : 1][GS_TT][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cpr = E >> 2, rpi = 64 / cpr;  // chunks per row, rows per wave-wide load
-  const int r = lane / cpr, c = lane % cpr;
-  const int r0 = blockIdx.x * rows_per, r1 = min(d, r0 + rows_per);
-  const int step = SPLIT_ROWS ? 4 * rpi : rpi;
-  double acc[GS_TT][4];
-#pragma unroll
-  for (int u = 0; u < GS_TT; ++u)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[u][i] = 0.0;
-  const uint16_t* xt[GS_TT];  // (tokens past the last redo it; their sums are not stored)
-#pragma unroll
-  for (int u = 0; u < GS_TT; ++u) xt[u] = x + (size_t)min(SPLIT_ROWS ? u : wave + 4 * u, T - 1) * d;
-#pragma unroll 8
-  for (int row = r0 + (SPLIT_ROWS ? wave * rpi : 0) + r; row < r1; row += step) {
-    const float4 w4 = *reinterpret_cast<const float4*>(wr + (size_t)row * E + 4 * c);
-#pragma unroll
-    for (int u = 0; u < GS_TT; ++u) {
-      if ((SPLIT_ROWS ? u : 4 * u) >= T) break;  // (uniform)
-      const double xd = (double)bf16_to_f32(xt[u][row]);
-      acc[u][0] = fma(xd, (double)w4.x, acc[u][0]);
-      acc[u][1] = fma(xd, (double)w4.y, acc[u][1]);
-      acc[u][2] = fma(xd, (double)w4.z, acc[u][2]);
-      acc[u][3] = fma(xd, (double)w4.w, acc[u][3]);
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < GS_TT; ++u) {
-    if ((SPLIT_ROWS ? u : 4 * u) >= T) break;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      for (int m = cpr; m < 64; m <<= 1) acc[u][i] += shfl_xor_f64(acc[u][i], m);
-    const int t = SPLIT_ROWS ? u : wave + 4 * u;
-    if (SPLIT_ROWS) {
-      if (lane < cpr)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) red[wave][u][4 * c + i] = acc[u][i];
-    } else if (t < T && lane < cpr) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) part[((size_t)blockIdx.x * T + t) * E + 4 * c + i] = acc[u][i];
-    }
-  }
-  if (SPLIT_ROWS) {
-    __syncthreads();
-    for (int i = threadIdx.x; i < T * E; i += 256) {
-      const int u = i / E, e = i - u * E;
-      part[((size_t)blockIdx.x * T + u) * E + e] = ((red[0][u][e] + red[1][u][e]) + red[2][u][e]) + red[3][u][e];
-    }
-  }
-}
-
-__global__ __launch_bounds__(GS_MAX_T * 64) void gate_finish_kernel(const double* __restrict__ part, const float* __restrict__ br, int T, int E,
-                                                                     int k, int C, int renorm, int slices, int32_t* __restrict__ topk_idx,
-                                                                     float* __restrict__ topk_w, int32_t* __restrict__ counts,
-                                                                     int32_t* __restrict__ offsets, int32_t* __restrict__ a2r,
-                                                                     int32_t* __restrict__ r2a, int32_t* __restrict__ clear8) {
-  __shared__ double zrow[GS_MAX_T][64];
-  __shared__ int sel_s[GS_MAX_T * MOE_MAX_TOPK];
-  __shared__ int cnt[64], off_s[64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (clear8 && threadIdx.x < 8) clear8[threadIdx.x] = 0;
-  if (wave < T) {
-    double z = 0.0;
-    const double* p = part + (size_t)wave * E + min(lane, E - 1);
-#pragma unroll 8
-    for (int q = 0; q < slices; ++q) z += p[(size_t)q * T * E];
-    zrow[wave][lane] = z + (br && lane < E ? (double)br[lane] : 0.0);
-    asm volatile("" ::: "memory");  // (a wavefront's LDS operations execute in order)
-    const int sel = rank_token(zrow[wave], lane, E, k, renorm, wave, topk_idx, topk_w, nullptr);
-    if (lane < k) sel_s[lane * T + wave] = valid_expert(sel, E);  // assignment j * T + t
-  }
-  __syncthreads();
-  if (wave != 0) return;
-  // the tables: 64 assignments at a time, ranked per expert in order (E <= 64)
-  cnt[lane] = 0;
-  asm volatile("" ::: "memory");
-  constexpr int R = GS_MAX_T * MOE_MAX_TOPK / 64;
-  int e_of[R], slot[R];
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const int a = q * 64 + lane;
-    e_of[q] = a < T * k ? sel_s[a] : -1;
-    slot[q] = place_in_expert(e_of[q], E, cnt, lane);
-  }
-  const int n = lane < E ? cnt[lane] : 0, kept = min(n, C);
-  int incl = kept;
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    const int up = __shfl_up(incl, m, 64);
-    incl += lane >= m ? up : 0;
-  }
-  off_s[lane] = incl - kept;
-  asm volatile("" ::: "memory");
-  if (lane < E) {
-    counts[lane] = n;
-    offsets[lane] = incl - kept;
-    if (lane == E - 1) offsets[E] = incl;
-  }
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const int a = q * 64 + lane;
-    if (a >= T * k) continue;
-    const int row = e_of[q] >= 0 && slot[q] < C ? off_s[e_of[q]] + slot[q] : -1;
-    a2r[a] = row;
-    if (row >= 0) r2a[row] = a;
-  }
-}
-
 // ------------------------------------------------------------------------------------------------
 // Fast path.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -349,73 +205,6 @@ constexpr int FT_ROW = (FT_KC + 8) * 2;  // LDS row of one expert's chunk, padde
 constexpr float GATE_MARGIN_REL = 1.0f / 32768.0f;
 
 __device__ __forceinline__ uint32_t bf16_bits_rne(float f) { return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)f); }
-
-// Softmax (fp32) + top-k of one token by a group of 8 adjacent lanes.  Lane `sub` of the group holds the
-// float64 logits of experts sub, sub+8, ... (NPL of them, -inf beyond E).  k+1 rounds of group-wide
-// arg-max (ties -> lower expert) pick the experts in rank order; the extra round only measures the gap
-// to the first expert NOT selected.  Returns true (to every lane of the group) if two neighbours among
-// those k+1 logits are closer than `margin`.
-template <int NPL>
-__device__ __forceinline__ bool finalize_group(double (&z)[NPL], int sub, int E, int k, int renorm, float margin,
-                                               int32_t* __restrict__ idx_out, float* __restrict__ w_out,
-                                               float* __restrict__ probs_out, bool mark_close = false) {
-  float mx = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < NPL; ++i) mx = fmaxf(mx, (float)z[i]);
-  group8_steps([&](auto st) { mx = fmaxf(mx, group8_partner<decltype(st)::value>(mx)); });
-  float ex[NPL], sum = 0.f;
-#pragma unroll
-  for (int i = 0; i < NPL; ++i) {
-    ex[i] = (sub + 8 * i) < E ? expf((float)z[i] - mx) : 0.f;
-    sum += ex[i];
-  }
-  // (the same pairs in the same order in every lane of the group: all eight hold the same sum, bit for bit)
-  group8_steps([&](auto st) { sum += group8_partner<decltype(st)::value>(sum); });
-#pragma unroll
-  for (int i = 0; i < NPL; ++i) {
-    ex[i] = ex[i] / sum;
-    if (probs_out && (sub + 8 * i) < E) probs_out[sub + 8 * i] = ex[i];
-  }
-  float my_w = 0.f, wsum = 0.f;
-  int my_idx = 0;
-  double prev = INFINITY;
-  bool close = false;
-  for (int r = 0; r <= k; ++r) {
-    double bz = -INFINITY;
-    int be = 0x7fffffff;
-    float bp = 0.f;
-#pragma unroll
-    for (int i = 0; i < NPL; ++i) {
-      const int e = sub + 8 * i;
-      if (e < E && (z[i] > bz || (z[i] == bz && e < be))) { bz = z[i]; be = e; bp = ex[i]; }
-    }
-    group8_steps([&](auto st) {
-      constexpr int S = decltype(st)::value;
-      const double oz = group8_partner<S>(bz);
-      const int oe = group8_partner<S>(be);
-      const float op = group8_partner<S>(bp);
-      if (oz > bz || (oz == bz && oe < be)) { bz = oz; be = oe; bp = op; }
-    });
-#pragma unroll
-    for (int i = 0; i < NPL; ++i)
-      if (sub + 8 * i == be) z[i] = NAN;  // retire the winner (every lane of the group agrees on be): no comparison picks it again
-    if (r < k) {
-      if (sub == r) { my_idx = be; my_w = bp; }
-      wsum += bp;
-    }
-    if (r > 0) close |= (float)(prev - bz) < margin;
-    prev = bz;
-  }
-  if (sub < k) {
-    idx_out[sub] = my_idx;
-    float w = renorm ? my_w / wsum : my_w;
-    // mark_close: a token within the margin carries the sign bit on its first weight (a probability, never
-    // negative otherwise) until the kernel that recomputes such tokens has replaced its results
-    if (mark_close && close && sub == 0) w = __uint_as_float(__float_as_uint(w) | 0x80000000u);
-    w_out[sub] = w;
-  }
-  return close;
-}
 
 // ------------------------------------------------------------------------------------------------
 // Exact path: 16 tokens per workgroup, every expert; the wavefronts split the contraction index and their float64 sums
@@ -435,13 +224,18 @@ __device__ __forceinline__ bool finalize_group(double (&z)[NPL], int sub, int E,
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int F64_TOK = 16;
 
-template <typename XT, int EV, int NG, bool VEC, int NW>
+// values of the contraction index per lane and chunk (two chunks have to fit the registers beside the sums)
+template <typename XT, int EV, int NG, bool VEC>
+constexpr int f64_values() { return sizeof(XT) == 4 || NG > 2 || (EV == 4 && (NG == 1 || !VEC)) ? 4 : 8; }
+
+// PART: workgroup (x, y) multiplies only the chunks [y chunks_per, (y + 1) chunks_per) and stores the sums of its 16 tokens, the
+// partial logits part[y][token][expert], for gate_rank_kernel or for a product that ranks by itself.
+template <typename XT, int EV, int NG, bool VEC, int NW, bool PART = false>
 __global__ __launch_bounds__(NW * 64) void gate_f64_kernel(const XT* __restrict__ x, const float* __restrict__ wr,
                                                            const float* __restrict__ br, int T, int d, int E, int k, int renorm,
                                                            int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
-                                                           float* __restrict__ probs) {
-  // values of the contraction index per lane and chunk (two chunks have to fit the registers beside the sums)
-  constexpr int KPL = sizeof(XT) == 4 || NG > 2 || (EV == 4 && (NG == 1 || !VEC)) ? 4 : 8;
+                                                           float* __restrict__ probs, int chunks_per, double* __restrict__ part) {
+  constexpr int KPL = f64_values<XT, EV, NG, VEC>();
   constexpr int KC = 4 * KPL, EP = 16 * EV * NG, NPL = EP / 8;
   extern __shared__ double part64[];  // [NW][EP][F64_TOK]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -506,11 +300,12 @@ __global__ __launch_bounds__(NW * 64) void gate_f64_kernel(const XT* __restrict_
         for (int j = 0; j < EV; ++j) acc[n][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)b.w[s][n][j], xd, acc[n][j], 0, 0, 0);
     }
   };
-  const int n_chunks = d / KC;  // d is a multiple of 64
-  if (wave < n_chunks) {
+  const int first = PART ? (int)blockIdx.y * chunks_per + wave : wave;
+  const int n_chunks = PART ? min(d / KC, ((int)blockIdx.y + 1) * chunks_per) : d / KC;  // (the end; d is a multiple of 64)
+  if (first < n_chunks) {
     Chunk b[2];
-    load(wave, b[0]);
-    int c = wave;
+    load(first, b[0]);
+    int c = first;
     for (; c + NW < n_chunks; c += 2 * NW) {
       load(c + NW, b[1]);
       multiply(b[0]);
@@ -528,6 +323,18 @@ __global__ __launch_bounds__(NW * 64) void gate_f64_kernel(const XT* __restrict_
       for (int i = 0; i < 4; ++i)
         part64[((size_t)wave * EP + (n * 16 + 4 * i + g) * EV + j) * F64_TOK + q] = acc[n][j][i];
   lds_barrier();
+  if constexpr (PART) {
+    double* dst = part + ((size_t)blockIdx.y * T + t0) * E;
+    for (int i = tid; i < EP * F64_TOK; i += NW * 64) {
+      const int e = i / F64_TOK, tok = i % F64_TOK;
+      if (e >= E || t0 + tok >= T) continue;
+      double v = part64[i];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += part64[(size_t)w * EP * F64_TOK + i];
+      dst[tok * E + e] = v;
+    }
+    return;
+  }
   for (int i = tid; i < EP * F64_TOK; i += NW * 64) {  // (a sum's first term is its own place: nobody else touches it)
     double v = part64[i];
 #pragma unroll
@@ -542,8 +349,8 @@ __global__ __launch_bounds__(NW * 64) void gate_f64_kernel(const XT* __restrict_
 #pragma unroll
     for (int m = 0; m < NPL; ++m) z[m] = sub + 8 * m < E ? part64[(sub + 8 * m) * F64_TOK + tok] : -INFINITY;
     if (t < T)
-      finalize_group<NPL>(z, sub, E, k, renorm, 0.f, topk_idx + (size_t)t * k, topk_w + (size_t)t * k,
-                          probs ? probs + (size_t)t * E : nullptr);
+      finalize_group<NPL, false>(z, sub, E, k, renorm, 0.f, topk_idx + (size_t)t * k, topk_w + (size_t)t * k,
+                                 probs ? probs + (size_t)t * E : nullptr);
   }
 }
 
@@ -559,7 +366,7 @@ int32_t launch_f64_shape(const moe_config* cfg, const void* x, const float* w_ro
     if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(gate LDS)");
   }
   hipLaunchKernelGGL(kern, dim3((cfg->T + F64_TOK - 1) / F64_TOK), dim3(NW * 64), shmem, s, (const XT*)x, w_router, b_router, cfg->T,
-                     cfg->d_model, cfg->E, cfg->k, cfg->renormalize, topk_idx, topk_w, probs);
+                     cfg->d_model, cfg->E, cfg->k, cfg->renormalize, topk_idx, topk_w, probs, 0, (double*)nullptr);
   return check_hip(hipGetLastError(), "gate launch");
 }
 
@@ -572,6 +379,113 @@ int32_t launch_f64(const moe_config* cfg, const void* x, const float* w_router, 
   if (cfg->E <= 64) return launch_f64_shape<XT, 4, 1, 16>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
   if (cfg->E <= 128) return launch_f64_shape<XT, 4, 2, 8>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
   return launch_f64_shape<XT, 4, 4, 4>(cfg, x, w_router, b_router, topk_idx, topk_w, probs, s);
+}
+
+// ------------------------------------------------------------------------------------------------
+// A step of a few hundred tokens at most: 16 tokens per workgroup leave most compute units without work and each with the whole
+// router to read, and the dispatch tables of so few assignments cost a launch of their own.  So the contraction index is cut into
+// slices as well (gate_f64_kernel with PART: float64 sums, nothing to recompute), and one workgroup adds the slices in order,
+// ranks every token in a group of eight lanes and writes the dispatch tables.  Bound by the latency of two launches.
+// Measured on MI355X inside layers whose weights drive everything else out of the caches (us, a workgroup per 16 tokens + dispatch
+// kernel / slices + this one): 96 tokens, d 4096, 8 experts 17.4 + 5.1 / 5.0 + 7.7; 96, d 2048, 64 23.9 + 4.9 / 7.5 + 11.3; 8, d 2048, 64
+// (32 slices on the vector ALU and a ranking wavefront per token before) 9.4 + 7.5 / 5.0 + 7.4; whole layers: 32 tokens, d 2048, 128
+// experts 191 / 162, 255, d 4096, 32 154 / 141, 3, d 1152, 24 43.4 / 38.3.  More than 96 tokens and short rows lose: 200, d 1024, 32
+// experts and 256, d 1024, 8 to 16 by 1 to 2 us; 128 to 255 at d 1536 gain 2 to 3.
+constexpr int GR_THREADS = ONE_WAVES * 64, GR_MAX_T = 256, GR_LOGITS = 8192;
+// slices that a thread adds for each of its logits_per_thread logits: all of its loads are in flight together
+constexpr int gr_slices(int logits_per_thread) { return logits_per_thread <= 4 ? 16 / logits_per_thread : 4; }
+constexpr int gr_logits_per_thread(int logits) { return logits <= GR_THREADS ? 1 : logits <= 2 * GR_THREADS ? 2 : logits <= 4 * GR_THREADS ? 4 : 8; }
+template <int NPL>
+__global__ __launch_bounds__(GR_THREADS) void gate_rank_kernel(const double* __restrict__ part, const float* __restrict__ br, int T, int E,
+                                                               int k, int C, int renorm, int slices, int32_t* __restrict__ topk_idx,
+                                                               float* __restrict__ topk_w, int32_t* __restrict__ counts,
+                                                               int32_t* __restrict__ offsets, int32_t* __restrict__ a2r,
+                                                               int32_t* __restrict__ r2a, int32_t* __restrict__ clear8) {
+  // logits [token][E + 8] (the pad spreads the groups' reads over the banks), then the tables
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_rank[];
+  __shared__ int sel[GR_THREADS];  // [T][k]
+  double* zs = reinterpret_cast<double*>(smem_rank);
+  const int tid = threadIdx.x, n = T * E;
+  if (clear8 && tid < 8) clear8[tid] = 0;
+  auto add_slices = [&](auto lpt) {
+    constexpr int LPT = decltype(lpt)::value, S = gr_slices(LPT);
+    double v[LPT][S];
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+      const double* p = part + (size_t)min(q, slices - 1) * n;  // (uniform)
+#pragma unroll
+      for (int l = 0; l < LPT; ++l) v[l][q] = p[(unsigned)min(l * GR_THREADS + tid, n - 1)];
+    }
+#pragma unroll
+    for (int l = 0; l < LPT; ++l) {
+      const int i = l * GR_THREADS + tid;
+      // i / E: at least 0.5 / E away from a whole number, which is 200 times what these float32 operations can be off
+      const int t = (int)(((float)i + 0.5f) * __builtin_amdgcn_rcpf((float)E));
+      double z = v[l][0];
+#pragma unroll
+      for (int q = 1; q < S; ++q) z += q < slices ? v[l][q] : 0.0;
+      if (i < n) zs[i + 8 * t] = z + (br ? (double)br[i - t * E] : 0.0);
+    }
+  };
+  switch (gr_logits_per_thread(n)) {
+    case 1: add_slices(std::integral_constant<int, 1>{}); break;
+    case 2: add_slices(std::integral_constant<int, 2>{}); break;
+    case 4: add_slices(std::integral_constant<int, 4>{}); break;
+    default: add_slices(std::integral_constant<int, 8>{});
+  }
+  __syncthreads();
+  const int sub = tid & 7;
+  for (int t = tid >> 3; t < T; t += GR_THREADS / 8) {  // (uniform per group)
+    double z[NPL];
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) z[i] = sub + 8 * i < E ? zs[t * (E + 8) + sub + 8 * i] : -INFINITY;
+    finalize_group<NPL, false>(z, sub, E, k, renorm, 0.f, sel + t * k, topk_w + (size_t)t * k, nullptr);
+  }
+  __syncthreads();
+  const int A = T * k, j = tid / T, t = tid - j * T;  // assignment j T + t
+  if (tid < A) topk_idx[tid] = sel[tid];
+  const int e_of[1] = {tid < A ? valid_expert(sel[t * k + j], E) : -1};
+  write_tables<1>(e_of, A, E, C, *reinterpret_cast<OneTables*>(smem_rank), counts, offsets, a2r, r2a);
+}
+
+// The slices of the kernel above: as many as its threads add and the scratch holds; no slice gives a wavefront less than one chunk.
+struct GateSlices { int slices, chunks_per, waves, logits; };
+GateSlices plan_gate_slices(const moe_config* cfg, const float* w_router, size_t scratch_bytes) {
+  const int T = cfg->T, E = cfg->E, ev = E <= 16 ? 1 : E <= 32 ? 2 : 4;
+  GateSlices p = {0, 0, E <= 128 ? 8 : 4, T * E};
+  const bool vec = E % ev == 0 && ((uintptr_t)w_router & (4 * ev - 1)) == 0;
+  const int kc = 4 * (E <= 32 ? f64_values<uint16_t, 1, 1, true>() : E <= 64 || E > 128 || !vec ? 4 : f64_values<uint16_t, 4, 2, true>());
+  int64_t most = gr_slices(gr_logits_per_thread(p.logits));
+  const int64_t room = (int64_t)(scratch_bytes / ((size_t)p.logits * sizeof(double)));
+  if (room < most) most = room;
+  if (most < 1) return p;
+  const int chunks = cfg->d_model / kc;
+  p.chunks_per = (int)((chunks + most - 1) / most);
+  if (p.chunks_per < p.waves) p.chunks_per = p.waves;
+  p.slices = (chunks + p.chunks_per - 1) / p.chunks_per;
+  return p;
+}
+
+template <int EV, int NG, int NW>
+int32_t launch_gate_parts_shape(const moe_config* cfg, const GateSlices& p, const void* x, const float* w_router, double* part, hipStream_t s) {
+  constexpr size_t shmem = (size_t)NW * 16 * EV * NG * F64_TOK * sizeof(double);
+  const bool vec = cfg->E % EV == 0 && ((uintptr_t)w_router & (4 * EV - 1)) == 0;
+  auto kern = vec ? gate_f64_kernel<uint16_t, EV, NG, true, NW, true> : gate_f64_kernel<uint16_t, EV, NG, false, NW, true>;
+  if (shmem > 65536) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(gate LDS)");
+  }
+  hipLaunchKernelGGL(kern, dim3((cfg->T + F64_TOK - 1) / F64_TOK, p.slices), dim3(NW * 64), shmem, s, (const uint16_t*)x, w_router,
+                     (const float*)nullptr, cfg->T, cfg->d_model, cfg->E, cfg->k, cfg->renormalize, (int32_t*)nullptr, (float*)nullptr,
+                     (float*)nullptr, p.chunks_per, part);
+  return check_hip(hipGetLastError(), "gate launch");
+}
+int32_t launch_gate_parts(const moe_config* cfg, const GateSlices& p, const void* x, const float* w_router, double* part, hipStream_t s) {
+  if (cfg->E <= 16) return launch_gate_parts_shape<1, 1, 8>(cfg, p, x, w_router, part, s);
+  if (cfg->E <= 32) return launch_gate_parts_shape<2, 1, 8>(cfg, p, x, w_router, part, s);
+  if (cfg->E <= 64) return launch_gate_parts_shape<4, 1, 8>(cfg, p, x, w_router, part, s);
+  if (cfg->E <= 128) return launch_gate_parts_shape<4, 2, 8>(cfg, p, x, w_router, part, s);
+  return launch_gate_parts_shape<4, 4, 4>(cfg, p, x, w_router, part, s);
 }
 
 // EB = number of 16-expert blocks (E <= 16*EB).  One workgroup = 16 tokens (one MFMA token tile); its NWV
@@ -1224,28 +1138,47 @@ int32_t launch_packed(const moe_config* cfg, const void* x, const void* packed, 
 bool gate_dispatch_one_token_applies(const moe_config* cfg, const float* w_router) {
   return cfg->T == 1 && cfg->dtype == MOE_BF16 && gate_few_applies(cfg, w_router);
 }
-// Gate and dispatch tables of a step of few tokens through slices of the router; scratch: bytes for the partial logits
-// (eight slices at least).
-static int gate_slices(const moe_config* cfg, size_t scratch_bytes) {
-  int64_t s = (int64_t)(scratch_bytes / ((size_t)cfg->T * cfg->E * sizeof(double)));
-  if (s > GS_SLICES) s = GS_SLICES;
-  return (int)s;
+// Gate and dispatch tables of a step of few tokens through slices of the contraction index; scratch: room for the partial logits.
+static bool gate_slices_fit(const moe_config* cfg, const float* w_router, size_t scratch_bytes) {
+  const GateSlices p = plan_gate_slices(cfg, w_router, scratch_bytes);
+  return p.slices >= 1 && p.logits <= GR_LOGITS;
 }
 bool gate_dispatch_slices_applies(const moe_config* cfg, const float* w_router, size_t scratch_bytes) {
-  return cfg->T >= 1 && cfg->T <= GS_MAX_T && cfg->dtype == MOE_BF16 && gate_few_applies(cfg, w_router) &&
-         (int64_t)cfg->d_model * cfg->E >= 131072 &&
-         gate_slices(cfg, scratch_bytes) >= 8;
+  if (!tuning(MOE_TUNE_FEW_TOKEN_KERNELS) || cfg->dtype != MOE_BF16 || cfg->T < 1 || cfg->T > GR_MAX_T ||
+      (int64_t)cfg->T * cfg->k > GR_THREADS)
+    return false;
+  // (measured: see gate_rank_kernel; one token on a small router: one workgroup does it all)
+  if (cfg->T > 96 && cfg->d_model < 1536) return false;
+  if (gate_dispatch_one_token_applies(cfg, w_router) && (int64_t)cfg->d_model * cfg->E < 131072) return false;
+  return gate_slices_fit(cfg, w_router, scratch_bytes);
 }
 int32_t launch_gate_dispatch_slices(const moe_config* cfg, const void* x, const float* w_router, const float* b_router, int32_t* topk_idx,
                                     float* topk_w, int32_t* counts, int32_t* offsets, int32_t* a2r, int32_t* r2a, int32_t* clear8,
                                     void* scratch, size_t scratch_bytes, hipStream_t s) {
-  const int T = cfg->T, d = cfg->d_model, E = cfg->E, most = gate_slices(cfg, scratch_bytes);
-  const int rows_per = (d + most - 1) / most, slices = (d + rows_per - 1) / rows_per;
-  hipLaunchKernelGGL(T < 4 ? gate_slice_kernel<true> : gate_slice_kernel<false>, dim3(slices), dim3(256), 0, s, (const uint16_t*)x, w_router, T, d, E,
-                     rows_per, (double*)scratch);
-  hipLaunchKernelGGL(gate_finish_kernel, dim3(1), dim3(GS_MAX_T * 64), 0, s, (const double*)scratch, b_router, T, E, cfg->k, moe_capacity(cfg),
-                     cfg->renormalize, slices, topk_idx, topk_w, counts, offsets, a2r, r2a, clear8);
+  const GateSlices p = plan_gate_slices(cfg, w_router, scratch_bytes);
+  const int32_t st = launch_gate_parts(cfg, p, x, w_router, (double*)scratch, s);
+  if (st != MOE_OK) return st;
+  const int E = cfg->E;
+  auto kern = E <= 16 ? gate_rank_kernel<2> : E <= 32 ? gate_rank_kernel<4> : E <= 64 ? gate_rank_kernel<8> : E <= 128 ? gate_rank_kernel<16> : gate_rank_kernel<32>;
+  size_t shmem = ((size_t)p.logits + 8 * (size_t)cfg->T) * sizeof(double);
+  if (shmem < sizeof(OneTables)) shmem = sizeof(OneTables);
+  if (shmem > 48 * 1024) {
+    const hipError_t err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    if (err != hipSuccess) return check_hip(err, "hipFuncSetAttribute(gate LDS)");
+  }
+  hipLaunchKernelGGL(kern, dim3(1), dim3(GR_THREADS), shmem, s, (const double*)scratch, b_router, cfg->T, E, cfg->k, moe_capacity(cfg),
+                     cfg->renormalize, p.slices, topk_idx, topk_w, counts, offsets, a2r, r2a, clear8);
   return check_hip(hipGetLastError(), "gate launch");
+}
+
+// The slices alone, for a one-token step whose first product ranks (expert_gemv_ranked_applies): their number, 0 where the step does
+// not take slices.
+int gate_parts_one_token(const moe_config* cfg, const float* w_router, size_t scratch_bytes) {
+  if (!tuning(MOE_TUNE_FEW_TOKEN_KERNELS) || cfg->dtype != MOE_BF16 || cfg->T != 1 || !gate_slices_fit(cfg, w_router, scratch_bytes)) return 0;
+  return plan_gate_slices(cfg, w_router, scratch_bytes).slices;
+}
+int32_t launch_gate_parts_one_token(const moe_config* cfg, const void* x, const float* w_router, double* part, size_t scratch_bytes, hipStream_t s) {
+  return launch_gate_parts(cfg, plan_gate_slices(cfg, w_router, scratch_bytes), x, w_router, part, s);
 }
 
 int32_t launch_gate_dispatch_one_token(const moe_config* cfg, const void* x, const float* w_router, const float* b_router,

@@ -1,0 +1,113 @@
+"""Routing of up to 256 tokens through slices of the contraction index and one ranking workgroup: tables exact against float64 at the
+edges of token tiles, of the logits per thread, of the expert groups and of the rule; and one-token layers whose first product ranks."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2205_10034_amd as M
+
+pytestmark = pytest.mark.gpu
+
+
+def tables(cfg, x, router, bias):
+    T, E, k = cfg.T, cfg.E, cfg.k
+    z = (x.double() @ router.double() + bias.double()).cpu()
+    idx = torch.sort(z, dim=1, descending=True, stable=True).indices[:, :k].numpy()
+    p = np.take_along_axis(torch.softmax(z, 1).numpy(), idx, 1)
+    if cfg.renormalize:
+        p = p / p.sum(1, keepdims=True)
+    cap = max(1, int(np.ceil(k * T * cfg.capacity_factor / E))) if cfg.capacity_factor else k * T
+    counts, a2r = np.bincount(idx.reshape(-1), minlength=E), np.full(T * k, -1)
+    offsets = np.concatenate([[0], np.cumsum(np.minimum(counts, cap))])
+    seen, r2a = np.zeros(E, int), np.zeros(offsets[-1], int)
+    for a, e in enumerate(idx.T.reshape(-1)):
+        if seen[e] < cap:
+            a2r[a] = offsets[e] + seen[e]
+            r2a[a2r[a]] = a
+        seen[e] += 1
+    return idx, p, counts, offsets, a2r, r2a
+
+
+def reader(ws, cfg):
+    lay = M.moe_workspace_layout(cfg)
+    return lambda n, c, dt=torch.int32: ws[lay[n]:lay[n] + 4 * c].view(dt).cpu().numpy()
+
+
+def check_tables(read, cfg, x, router, bias):
+    T, E, k = cfg.T, cfg.E, cfg.k
+    idx, p, counts, offsets, a2r, r2a = tables(cfg, x, router, bias)
+    assert np.array_equal(read("topk_idx", T * k).reshape(T, k), idx)
+    # float32 exponentials, their sum and one division: a few units in the last place
+    assert np.abs(read("topk_w", T * k, torch.float32).reshape(T, k) - p).max() < 16 * 2.0 ** -24
+    assert np.array_equal(read("expert_counts", E), counts) and np.array_equal(read("expert_offsets", E + 1), offsets)
+    assert np.array_equal(read("assign_to_row", T * k), a2r) and np.array_equal(read("row_to_assign", offsets[-1]), r2a)
+    assert not read("tile_counters", 8).any()
+
+
+def problem(T, d, E):
+    g = torch.Generator(device="cuda").manual_seed(d + E + T)
+    x = torch.randn(T, d, generator=g, device="cuda").bfloat16()
+    router = torch.randn(d, E, generator=g, device="cuda") * d ** -0.5
+    router[:, 3] = router[:, 1]                            # exact ties
+    bias = torch.randn(E, generator=g, device="cuda")
+    bias[3] = bias[1] = 1.5
+    return g, x, router, bias
+
+
+@pytest.mark.parametrize("T,d,E,k,cf", [
+    (1, 64, 5, 1, 0.0), (2, 64, 4, 4, 1.0), (15, 192, 17, 3, 0.0), (16, 1024, 64, 8, 1.0), (17, 2112, 65, 2, 0.0), (31, 1600, 128, 6, 1.25),
+    (32, 256, 256, 8, 0.0), (33, 320, 200, 2, 0.0), (64, 1088, 64, 2, 1.0), (96, 4096, 8, 2, 0.0), (97, 1472, 9, 2, 1.0), (97, 1536, 9, 2, 1.0),
+    (128, 2048, 64, 8, 0.0), (129, 2048, 64, 2, 0.0), (255, 1536, 12, 4, 0.5), (256, 2048, 32, 4, 0.0), (256, 4160, 33, 2, 0.0), (257, 2048, 8, 1, 0.0)])
+def test_gate_rank(T, d, E, k, cf):
+    print(T, d, E, k, cf, flush=True)
+    cfg = M.MoEConfig(T=T, d_model=d, d_ff=2048, E=E, k=k, capacity_factor=cf, renormalize=bool(T & 1))
+    _, x, router, bias = problem(T, d, E)
+    one = torch.zeros(1, dtype=torch.bfloat16, device="cuda")
+    W = M.Weights({"w1": one, "w2": one, "w_router": router, "b_router": bias}, "output_major")
+    W.need = lambda c: None                                # (routing reads no expert)
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda").fill_(0xAB)
+    for _ in range(2):
+        M.moe_layer_route(cfg, W, x, ws)
+        torch.cuda.synchronize()
+        check_tables(reader(ws, cfg), cfg, x, router, bias)
+
+
+@pytest.mark.parametrize("d,f,E,k,act,special", [
+    (64, 64, 4, 2, "gelu", ""), (128, 512, 64, 8, "gelu", ""), (576, 192, 24, 2, "swiglu", ""), (1088, 8192, 9, 2, "gelu", ""), (1024, 16384, 8, 2, "gelu", ""),
+    (2048, 8192, 64, 4, "swiglu", ""), (1024, 2048, 33, 8, "gelu", "nan"), (1024, 2048, 16, 4, "swiglu", "masked"), (1024, 2048, 16, 2, "gelu", "inf")])
+def test_one_token_layer(d, f, E, k, act, special):
+    """The whole layer against the two calls that rank in a kernel of their own."""
+    print(d, f, E, k, act, special, flush=True)
+    cfg = M.MoEConfig(T=1, d_model=d, d_ff=f, E=E, k=k, act=act, renormalize=bool(E & 1))
+    g, x, router, bias = problem(1, d, E)
+    if special == "nan":
+        x[0, 7] = float("nan")
+    if special == "masked":
+        bias[2:] = -float("inf")
+    if special == "inf":
+        bias[3] = float("inf")
+    mat = lambda n, k_: (torch.randn(E, n, k_, generator=g, device="cuda") * k_ ** -0.5).bfloat16()
+    t = {"w_router": router, "b_router": bias}
+    if act == "gelu":
+        t.update(w1=mat(f, d), w2=mat(d, f), b1=torch.randn(E, f, generator=g, device="cuda").bfloat16(), b2=torch.randn(E, d, generator=g, device="cuda").bfloat16())
+    else:
+        t.update(w_gate_proj=mat(f, d), w_up=mat(f, d), w_down=mat(d, f))
+    W = M.Weights(t, "output_major")
+    ws, ws2 = (torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda").fill_(0xAB) for _ in range(2))
+    out, out2 = torch.empty_like(x), torch.empty_like(x)
+    M.moe_layer_route(cfg, W, x, ws2)
+    M.moe_layer_experts(cfg, W, x, x, out2, ws2)
+    for _ in range(2):
+        M.moe_layer_forward(cfg, W, x, x, out, ws)
+        torch.cuda.synchronize()
+        a, b = reader(ws, cfg), reader(ws2, cfg)
+        for n, c in (("topk_idx", k), ("expert_counts", E), ("expert_offsets", E + 1), ("assign_to_row", k), ("tile_counters", 8)):
+            assert np.array_equal(a(n, c), b(n, c)), n
+        rows = int(a("expert_offsets", E + 1)[-1])
+        assert np.array_equal(a("row_to_assign", rows), b("row_to_assign", rows))
+        assert np.array_equal(a("h", rows * f // 2), b("h", rows * f // 2))  # the same sums in the same order
+        if not special:
+            check_tables(a, cfg, x, router, bias)
+        # gate weights: the router's float64 partial sums meet in another order
+        assert np.allclose(a("topk_w", k, torch.float32), b("topk_w", k, torch.float32), rtol=4e-7, atol=0, equal_nan=True)
+        assert torch.allclose(out.float(), out2.float(), rtol=2.0 ** -7, atol=1e-5, equal_nan=True)
