@@ -16,6 +16,7 @@
 // assignments the weight-streaming MFMA kernels (expert_stream_bf16.hip) are faster: 16 assignments over 64 experts of
 // 2048 x 8192 118 + 111 us here, 99 + 95 there; with 8 assignments 56 + 52 here, 58 + 57 there.  The 4 x 16 shape serves
 // what those kernels leave: contraction lengths beyond their 32-bit offsets, and calls whose tuning keys keep them out.
+#include "gate_rank.h"
 #include "moesys_internal.h"
 #include "wave_util.h"
 
@@ -27,6 +28,7 @@ namespace {
 
 constexpr int GV_MAX_ROWS = 16;  // rows of one expert, at most (= assignments of the whole step)
 constexpr int GV_WAVES = 4;
+constexpr int RANKED_SLICES = 16;  // slices of partial logits that expert_gemv_ranked_kernel adds, at most
 
 // NT: non-temporal (nobody else reads a weight, and the call's weights exceed the last-level cache, weights_exceed_cache)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -211,77 +213,199 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
   }
 }
 
+// A step of ONE token: ranking, routing tables and the first product in one kernel.  The router's partial logits (float64, E
+// values per slice of the contraction index) are a few KB in L2: every workgroup adds them in slice order and ranks the token by
+// itself, so that the product starts at the experts' weights where a kernel of its own would rank first and the product then
+// walk offsets -> row -> token -> weights; workgroup (0, 0) writes the tables that the second product reads.  Row r is the r-th
+// selected expert in expert order and there is one row per expert, so the sums of two 1 KB pieces of FPW weight rows fit the
+// registers at once.  E <= 64.  Measured on MI355X, 64 experts 2048 x 8192, k 2: ranking kernel 5.6 us + product 19.5, now 18.6 together;
+// whole one-token layers (us, before / now, the wider combine kernel below included): that one 45.3 / 37.4; 16 experts 1792 x 2816
+// 25.8 / 16.8; 24 of 1536 x 4096, k 4 42.1 / 28.0; 8 SwiGLU of 4096 x 14336 127 / 119.
+template <int EPI, int FPW, bool NT>
+__global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
+    const uint16_t* __restrict__ x, const double* __restrict__ part, int slices, const float* __restrict__ br, int renorm,
+    const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb, const uint16_t* __restrict__ bias, uint16_t* __restrict__ out,
+    const int64_t* __restrict__ eoff, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ a2r, int32_t* __restrict__ r2a, int32_t* __restrict__ clear8, int E, int N,
+    int K, int k) {
+  constexpr int OUTF = EPI == GV_SWIGLU ? FPW / 2 : FPW;  // output features per wavefront
+  __shared__ double zs[GV_WAVES][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int sel;  // lane j < k: the j-th selection (every wavefront ranks for itself)
+  float sel_w;
+  {
+    double v[RANKED_SLICES / GV_WAVES], z = 0.0;
+#pragma unroll
+    for (int q = 0; q < RANKED_SLICES / GV_WAVES; ++q)
+      v[q] = part[(size_t)min(q * GV_WAVES + wave, slices - 1) * E + min(lane, E - 1)];
+#pragma unroll
+    for (int q = 0; q < RANKED_SLICES / GV_WAVES; ++q) z += q * GV_WAVES + wave < slices ? v[q] : 0.0;
+    zs[wave][lane] = z;
+    __syncthreads();
+    const int e = min(lane, E - 1);
+    z = zs[0][e] + zs[1][e] + zs[2][e] + zs[3][e] + (br ? (double)br[e] : 0.0);
+    static_assert(GV_WAVES == 4, "four partial sums");
+    sel = rank_wave(lane < E ? z : -INFINITY, lane, E, k, renorm, sel_w);
+  }
+  unsigned long long chosen = 0;  // bit e: expert e selected; a selection that is no expert (NaN logits) gets no row
+  for (int j = 0; j < k; ++j) {
+    const int e = valid_expert(__builtin_amdgcn_readlane(sel, j), E);
+    if (e >= 0) chosen |= 1ull << e;
+  }
+  if (blockIdx.x == 0 && blockIdx.y == 0 && wave == 0) {
+    if (lane < E) {
+      counts[lane] = (int)((chosen >> lane) & 1ull);
+      offsets[lane] = __popcll(chosen & ((1ull << lane) - 1ull));
+    }
+    if (lane == 0) offsets[E] = __popcll(chosen);
+    if (lane < k) {
+      const int e = valid_expert(sel, E), row = e >= 0 ? __popcll(chosen & ((1ull << e) - 1ull)) : -1;
+      topk_idx[lane] = sel;
+      topk_w[lane] = sel_w;
+      a2r[lane] = row;
+      if (row >= 0) r2a[row] = lane;
+    }
+    if (lane < 8) clear8[lane] = 0;
+  }
+  const int row = blockIdx.y;
+  if (row >= __popcll(chosen)) return;
+  for (int r = 0; r < row; ++r) chosen &= chosen - 1;
+  const int e = __builtin_ctzll(chosen);
+  const int64_t wbase = eoff ? eoff[e] : (int64_t)e * N * K;
+  const int n0 = (blockIdx.x * GV_WAVES + wave) * OUTF;  // first output feature of this wavefront
+  const uint16_t* wrow[FPW];
+#pragma unroll
+  for (int j = 0; j < FPW; ++j)
+    wrow[j] = (EPI == GV_SWIGLU && j >= OUTF ? wb : wa) + wbase + (int64_t)(n0 + j % OUTF) * K;
+  float acc[FPW];
+#pragma unroll
+  for (int j = 0; j < FPW; ++j) acc[j] = 0.f;
+  auto add = [&](const uint4 (&wv)[FPW], const uint4& xv) {
+    const float x0 = lo16(xv.x), x1 = hi16(xv.x), x2 = lo16(xv.y), x3 = hi16(xv.y);
+    const float x4 = lo16(xv.z), x5 = hi16(xv.z), x6 = lo16(xv.w), x7 = hi16(xv.w);
+#pragma unroll
+    for (int j = 0; j < FPW; ++j) {
+      float a = acc[j];
+      a = fmaf(lo16(wv[j].x), x0, a); a = fmaf(hi16(wv[j].x), x1, a);
+      a = fmaf(lo16(wv[j].y), x2, a); a = fmaf(hi16(wv[j].y), x3, a);
+      a = fmaf(lo16(wv[j].z), x4, a); a = fmaf(hi16(wv[j].z), x5, a);
+      a = fmaf(lo16(wv[j].w), x6, a); a = fmaf(hi16(wv[j].w), x7, a);
+      acc[j] = a;
+    }
+  };
+  for (int kb = lane * 8; kb < K; kb += 2 * 64 * 8) {
+    const bool two = kb + 64 * 8 < K;
+    const int kb2 = two ? kb + 64 * 8 : kb;  // (a lane without a second piece re-reads the first and does not use it)
+    uint4 wv[FPW], wv2[FPW];
+#pragma unroll
+    for (int j = 0; j < FPW; ++j) wv[j] = load_weights<NT>(wrow[j] + kb);
+#pragma unroll
+    for (int j = 0; j < FPW; ++j) wv2[j] = load_weights<NT>(wrow[j] + kb2);
+    const uint4 xv = *reinterpret_cast<const uint4*>(x + kb), xv2 = *reinterpret_cast<const uint4*>(x + kb2);
+    add(wv, xv);
+    if (two) add(wv2, xv2);
+  }
+#pragma unroll
+  for (int j = 0; j < FPW; ++j) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) acc[j] += __shfl_xor(acc[j], m, 64);
+  }
+  if (lane < OUTF) {
+    const int n = n0 + lane;
+    float v = acc[0];
+#pragma unroll
+    for (int j = 1; j < OUTF; ++j) v = lane == j ? acc[j] : v;
+    if (EPI == GV_SWIGLU) {
+      float u = acc[FPW - OUTF];
+#pragma unroll
+      for (int j = 1; j < OUTF; ++j) u = lane == j ? acc[FPW - OUTF + j] : u;
+      v = v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * u;
+    } else {
+      v = gelu_exact(v + (bias ? lo16((uint32_t)bias[(eoff ? eoff[e] : (int64_t)e * N) + n]) : 0.f));
+    }
+    out[(size_t)row * N + n] = bf16_of(v);
+  }
+}
+
 // A step of ONE token with k >= 2 experts: the second product and the combine in one kernel.  A workgroup owns
-// C1_FPW output features; for the k choices in turn (row = assign_to_row[j], its expert from the offsets table)
-// its four wavefronts split the contraction index, the sums meet in LDS in wavefront order, the result (+ bias)
+// C1_FPW output features; two groups of four wavefronts take the k choices in turn (row = assign_to_row[j], its expert
+// from the offsets table), split the contraction index, the sums meet in LDS in wavefront order, the result (+ bias)
 // is rounded to bf16 and stored in yd as the separate product would store it, and out accumulates
 // residual + sum_j w_j * yd[row_j] from those rounded values, in float32 and in the order of the combine kernel.
-constexpr int C1_FPW = 8;
+// One group (all choices one after the other) had half the loads in flight: 14.1 us for 64 experts of 2048 x 8192, k 2, 13.1 with two.
+constexpr int C1_FPW = 8, C1_GROUPS = 2;
 
 template <bool NT>
-__global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_combine1_kernel(
+__global__ __launch_bounds__(C1_GROUPS * GV_WAVES * 64) void expert_gemv_combine1_kernel(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w2, const uint16_t* __restrict__ bias,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ a2r, const float* __restrict__ topk_w,
     const uint16_t* residual, uint16_t* __restrict__ yd, uint16_t* out, const int64_t* __restrict__ eoff, int E, int N,
     int K, int k) {
   __shared__ int s_e[MOE_MAX_TOPK];  // expert of dispatched row r (T = 1: at most k rows)
-  __shared__ float red[GV_WAVES][C1_FPW];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int e = threadIdx.x; e < E; e += GV_WAVES * 64)
+  __shared__ float red[C1_GROUPS][GV_WAVES][C1_FPW];
+  __shared__ float ys[MOE_MAX_TOPK][C1_FPW];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) % GV_WAVES);
+  const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / (GV_WAVES * 64)), gt = threadIdx.x % (GV_WAVES * 64);
+  for (int e = threadIdx.x; e < E; e += C1_GROUPS * GV_WAVES * 64)
     for (int r = offsets[e]; r < offsets[e + 1] && r < MOE_MAX_TOPK; ++r) s_e[r] = e;
   __syncthreads();
   const int n0 = blockIdx.x * C1_FPW;
-  float o = 0.f;  // (used by lanes < C1_FPW of wavefront 0: output feature n0 + lane)
-  if (wave == 0 && lane < C1_FPW && residual) o = lo16((uint32_t)residual[n0 + lane]);
-  for (int j = 0; j < k; ++j) {
-    const int row = a2r[j];
-    if (row < 0) continue;  // (a selection that is no expert: NaN logits; uniform)
-    const int e = s_e[row];
-    const uint16_t* wbase = w2 + (eoff ? eoff[e] : (int64_t)e * N * K) + (int64_t)n0 * K;
-    const uint16_t* xrow = h + (int64_t)row * K;
-    float acc[C1_FPW];
+  float o = 0.f;  // (used by the first C1_FPW threads: output feature n0 + lane)
+  if (threadIdx.x < C1_FPW && residual) o = lo16((uint32_t)residual[n0 + lane]);
+  for (int j0 = 0; j0 < k; j0 += C1_GROUPS) {
+    const int j = j0 + group, row = j < k ? a2r[j] : -1;
+    if (row >= 0) {  // (else no choice, or a selection that is no expert: NaN logits; uniform per group)
+      const int e = s_e[row];
+      const uint16_t* wbase = w2 + (eoff ? eoff[e] : (int64_t)e * N * K) + (int64_t)n0 * K;
+      const uint16_t* xrow = h + (int64_t)row * K;
+      float acc[C1_FPW];
 #pragma unroll
-    for (int f = 0; f < C1_FPW; ++f) acc[f] = 0.f;
+      for (int f = 0; f < C1_FPW; ++f) acc[f] = 0.f;
 #pragma unroll 2
-    for (int kb = (int)threadIdx.x * 8; kb < K; kb += GV_WAVES * 64 * 8) {
-      uint4 wv[C1_FPW];
+      for (int kb = gt * 8; kb < K; kb += GV_WAVES * 64 * 8) {
+        uint4 wv[C1_FPW];
 #pragma unroll
-      for (int f = 0; f < C1_FPW; ++f) wv[f] = load_weights<NT>(wbase + (int64_t)f * K + kb);
-      const uint4 xv = *reinterpret_cast<const uint4*>(xrow + kb);
-      const float x0 = lo16(xv.x), x1 = hi16(xv.x), x2 = lo16(xv.y), x3 = hi16(xv.y);
-      const float x4 = lo16(xv.z), x5 = hi16(xv.z), x6 = lo16(xv.w), x7 = hi16(xv.w);
+        for (int f = 0; f < C1_FPW; ++f) wv[f] = load_weights<NT>(wbase + (int64_t)f * K + kb);
+        const uint4 xv = *reinterpret_cast<const uint4*>(xrow + kb);
+        const float x0 = lo16(xv.x), x1 = hi16(xv.x), x2 = lo16(xv.y), x3 = hi16(xv.y);
+        const float x4 = lo16(xv.z), x5 = hi16(xv.z), x6 = lo16(xv.w), x7 = hi16(xv.w);
+#pragma unroll
+        for (int f = 0; f < C1_FPW; ++f) {
+          float a = acc[f];
+          a = fmaf(lo16(wv[f].x), x0, a); a = fmaf(hi16(wv[f].x), x1, a);
+          a = fmaf(lo16(wv[f].y), x2, a); a = fmaf(hi16(wv[f].y), x3, a);
+          a = fmaf(lo16(wv[f].z), x4, a); a = fmaf(hi16(wv[f].z), x5, a);
+          a = fmaf(lo16(wv[f].w), x6, a); a = fmaf(hi16(wv[f].w), x7, a);
+          acc[f] = a;
+        }
+      }
+      float mine = 0.f;  // lane f < C1_FPW: the wavefront's sum for output feature n0 + f
 #pragma unroll
       for (int f = 0; f < C1_FPW; ++f) {
-        float a = acc[f];
-        a = fmaf(lo16(wv[f].x), x0, a); a = fmaf(hi16(wv[f].x), x1, a);
-        a = fmaf(lo16(wv[f].y), x2, a); a = fmaf(hi16(wv[f].y), x3, a);
-        a = fmaf(lo16(wv[f].z), x4, a); a = fmaf(hi16(wv[f].z), x5, a);
-        a = fmaf(lo16(wv[f].w), x6, a); a = fmaf(hi16(wv[f].w), x7, a);
-        acc[f] = a;
+        float v = acc[f];
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+        mine = lane == f ? v : mine;
       }
+      if (lane < C1_FPW) red[group][wave][lane] = mine;
     }
-    float mine = 0.f;  // lane f < C1_FPW: the wavefront's sum for output feature n0 + f
-#pragma unroll
-    for (int f = 0; f < C1_FPW; ++f) {
-      float v = acc[f];
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-      mine = lane == f ? v : mine;
-    }
-    if (lane < C1_FPW) red[wave][lane] = mine;
     __syncthreads();
-    if (wave == 0 && lane < C1_FPW) {
-      float v = red[0][lane];
+    if (row >= 0 && gt < C1_FPW) {
+      float v = red[group][0][lane];
 #pragma unroll
-      for (int w = 1; w < GV_WAVES; ++w) v += red[w][lane];
-      if (bias) v += lo16((uint32_t)bias[(eoff ? eoff[e] : (int64_t)e * N) + n0 + lane]);
+      for (int w = 1; w < GV_WAVES; ++w) v += red[group][w][lane];
+      if (bias) v += lo16((uint32_t)bias[(eoff ? eoff[s_e[row]] : (int64_t)s_e[row] * N) + n0 + lane]);
       const uint16_t yb = bf16_of(v);
       yd[(size_t)row * N + n0 + lane] = yb;
-      o = fmaf(topk_w[j], lo16((uint32_t)yb), o);
+      ys[j][lane] = lo16((uint32_t)yb);
     }
-    __syncthreads();  // (red is free for the next choice)
+    __syncthreads();  // (red is free for the next choices)
   }
-  if (wave == 0 && lane < C1_FPW) out[n0 + lane] = bf16_of(o);
+  if (threadIdx.x < C1_FPW) {
+    for (int j = 0; j < k; ++j)
+      if (a2r[j] >= 0) o = fmaf(topk_w[j], ys[j][lane], o);
+    out[n0 + lane] = bf16_of(o);
+  }
 }
 
 template <int EPI, int ROWS, int FPW>
@@ -339,9 +463,33 @@ int32_t launch_expert_gemv_combine_one_token(const moe_config* cfg, const void* 
                                              const int32_t* offsets, const int32_t* a2r, const float* topk_w,
                                              const void* residual, void* yd, void* out, const int64_t* eoff, hipStream_t s) {
   if (!expert_gemv_combine_one_token_applies(cfg)) return fail(MOE_ERR_UNSUPPORTED, "expert GEMV: not a one-token step");
-  hipLaunchKernelGGL(weights_exceed_cache(cfg) ? expert_gemv_combine1_kernel<true> : expert_gemv_combine1_kernel<false>, dim3(cfg->d_model / C1_FPW), dim3(GV_WAVES * 64), 0, s, (const uint16_t*)h,
+  hipLaunchKernelGGL(weights_exceed_cache(cfg) ? expert_gemv_combine1_kernel<true> : expert_gemv_combine1_kernel<false>, dim3(cfg->d_model / C1_FPW), dim3(C1_GROUPS * GV_WAVES * 64), 0, s, (const uint16_t*)h,
                      (const uint16_t*)w2, (const uint16_t*)bias, offsets, a2r, topk_w, (const uint16_t*)residual, (uint16_t*)yd,
                      (uint16_t*)out, eoff, cfg->E, cfg->d_model, cfg->d_ff, cfg->k);
+  return check_hip(hipGetLastError(), "expert GEMV launch");
+}
+
+// Ranking + first product of a one-token step, from the partial logits of launch_gate_parts_one_token (at most 16 slices).
+bool expert_gemv_ranked_applies(const moe_config* cfg) {
+  return expert_gemv_combine_one_token_applies(cfg) && cfg->E <= 64 && expert_gemv_applies(cfg, cfg->d_ff, cfg->d_model);
+}
+int32_t launch_expert_gemv_ranked(const moe_config* cfg, const void* x, const double* part, int slices, const float* b_router, const void* wa,
+                                  const void* wb, const void* bias, void* h, const int64_t* eoff, int32_t* topk_idx, float* topk_w,
+                                  int32_t* counts, int32_t* offsets, int32_t* a2r, int32_t* r2a, int32_t* clear8, hipStream_t s) {
+  if (!expert_gemv_ranked_applies(cfg) || slices < 1 || slices > RANKED_SLICES) return fail(MOE_ERR_UNSUPPORTED, "expert GEMV: not a ranked one-token step");
+  const int N = cfg->d_ff;
+  const bool sw = cfg->act == MOE_ACT_SWIGLU, nt = weights_exceed_cache(cfg);
+  const int per8 = GV_WAVES * (sw ? 4 : 8);  // output features per workgroup with eight weight rows per wavefront
+  const bool eight = (int64_t)(N / per8) * cfg->k >= 512;  // about two workgroups per CU, else half the rows
+  const dim3 grid(N / (eight ? per8 : per8 / 2), cfg->k), block(GV_WAVES * 64);
+#define MOESYS_RANKED(EP, F)                                                                                                      \
+  hipLaunchKernelGGL((nt ? expert_gemv_ranked_kernel<EP, F, true> : expert_gemv_ranked_kernel<EP, F, false>), grid, block, 0, s,   \
+                     (const uint16_t*)x, part, slices, b_router, cfg->renormalize, (const uint16_t*)wa, (const uint16_t*)wb,       \
+                     (const uint16_t*)bias, (uint16_t*)h, eoff, topk_idx, topk_w, counts, offsets, a2r, r2a, clear8, cfg->E, N,    \
+                     cfg->d_model, cfg->k)
+  if (sw) { if (eight) MOESYS_RANKED(GV_SWIGLU, 8); else MOESYS_RANKED(GV_SWIGLU, 4); }
+  else { if (eight) MOESYS_RANKED(GV_GELU, 8); else MOESYS_RANKED(GV_GELU, 4); }
+#undef MOESYS_RANKED
   return check_hip(hipGetLastError(), "expert GEMV launch");
 }
 

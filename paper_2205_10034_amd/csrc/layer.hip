@@ -84,9 +84,31 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   return mark(timer, 2, s);
 }
 
-// expert FFN -> combine, from the routing tables in the workspace
+// A one-token step: the gate's partial logits, then ranking, tables and first product in one kernel.  The partial logits take the
+// place of yd, which only the second product writes.
+bool ranked_product_applies(const moe_config* cfg, const moe_weights* w) {
+  return expert_gemv_ranked_applies(cfg) && gate_parts_one_token(cfg, w->w_router, (size_t)max_rows(cfg) * cfg->d_model * 2) > 0;
+}
+int32_t route_and_first_product(const char* who, const moe_config* cfg, const moe_weights* w, const void* x, void* ws, size_t ws_bytes,
+                                hipStream_t s, moe_timer* timer) {
+  Segments sg;
+  int32_t st = open_workspace(who, cfg, w, x, ws, ws_bytes, &sg);
+  if (st != MOE_OK) return st;
+  const size_t yd_bytes = (size_t)max_rows(cfg) * cfg->d_model * 2;
+  const bool sw = cfg->act == MOE_ACT_SWIGLU;
+  double* part = (double*)sg.yd;
+  if ((st = mark(timer, 0, s)) != MOE_OK) return st;
+  if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, part, yd_bytes, s)) != MOE_OK) return st;
+  if ((st = mark(timer, 1, s)) != MOE_OK) return st;
+  if ((st = mark(timer, 2, s)) != MOE_OK) return st;
+  return launch_expert_gemv_ranked(cfg, x, part, gate_parts_one_token(cfg, w->w_router, yd_bytes), w->b_router, sw ? w->w_gate_proj : w->w1,
+                                   sw ? w->w_up : nullptr, sw ? nullptr : w->b1, sg.h, w->expert_elem_offset, sg.topk_idx, sg.topk_w,
+                                   sg.counts, sg.offsets, sg.a2r, sg.r2a, sg.tile_ctr, s);
+}
+
+// expert FFN -> combine, from the routing tables in the workspace (after_first: the first product has run)
 int32_t experts_impl(const char* who, const moe_config* cfg, const moe_weights* w, const void* x, const void* residual,
-                     void* out, void* ws, size_t ws_bytes, hipStream_t s, moe_timer* timer) {
+                     void* out, void* ws, size_t ws_bytes, hipStream_t s, moe_timer* timer, bool after_first = false) {
   Segments sg;
   int32_t st = open_workspace(who, cfg, w, x, ws, ws_bytes, &sg);
   if (st != MOE_OK) return st;
@@ -94,7 +116,7 @@ int32_t experts_impl(const char* who, const moe_config* cfg, const moe_weights* 
   if (cfg->T > 0 && !out) return fail(MOE_ERR_INVALID_ARG, "%s: out must be non-NULL", who);
   if (out == x && residual != x) return fail(MOE_ERR_INVALID_ARG, "%s: out aliases x", who);
   const bool gather = gemm1_can_gather(cfg);
-  if ((st = launch_gemm1(cfg, w, gather ? x : sg.xd, sg.offsets, sg.h, gather ? sg.r2a : nullptr, sg.tile_ctr, s)) != MOE_OK)
+  if (!after_first && (st = launch_gemm1(cfg, w, gather ? x : sg.xd, sg.offsets, sg.h, gather ? sg.r2a : nullptr, sg.tile_ctr, s)) != MOE_OK)
     return st;
   if ((st = mark(timer, 3, s)) != MOE_OK) return st;
   if (gemm2_can_combine(cfg)) {
@@ -133,6 +155,10 @@ int32_t layer_impl(const moe_config* cfg, const moe_weights* w, const void* x, c
   if ((st = check_weights(cfg, w)) != MOE_OK) return st;
   if (cfg->T > 0 && (!x || !out)) return fail(MOE_ERR_INVALID_ARG, "moe_layer_forward: x and out must be non-NULL");
   if (out == x && residual != x) return fail(MOE_ERR_INVALID_ARG, "moe_layer_forward: out aliases x");
+  if (w->w_router && ranked_product_applies(cfg, w)) {
+    if ((st = route_and_first_product("moe_layer_forward", cfg, w, x, ws, ws_bytes, s, timer)) != MOE_OK) return st;
+    return experts_impl("moe_layer_forward", cfg, w, x, residual, out, ws, ws_bytes, s, timer, true);
+  }
   if ((st = route_impl("moe_layer_forward", cfg, w, x, ws, ws_bytes, s, timer)) != MOE_OK) return st;
   return experts_impl("moe_layer_forward", cfg, w, x, residual, out, ws, ws_bytes, s, timer);
 }
