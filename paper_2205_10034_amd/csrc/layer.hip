@@ -48,9 +48,9 @@ int32_t mark(moe_timer* timer, int i, hipStream_t s) {
   return check_hip(hipEventRecord(timer->ev[i], s), "hipEventRecord");
 }
 
-// gate -> dispatch bookkeeping (and, on the fp32 path, the dispatched copy)
+// gate -> dispatch bookkeeping (and, on the fp32 path, the dispatched copy, unless the first product makes it: rows = false)
 int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w, const void* x, void* ws,
-                   size_t ws_bytes, hipStream_t s, moe_timer* timer) {
+                   size_t ws_bytes, hipStream_t s, moe_timer* timer, bool rows = true) {
   Segments sg;
   int32_t st = open_workspace(who, cfg, w, x, ws, ws_bytes, &sg);
   if (st != MOE_OK) return st;
@@ -78,7 +78,7 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   if ((st = launch_gate_of(cfg, w, x, sg.topk_idx, sg.topk_w, nullptr, s)) != MOE_OK) return st;
   if ((st = mark(timer, 1, s)) != MOE_OK) return st;
   // bf16: the first GEMM gathers its rows from x through row_to_assign, so no dispatched copy is made
-  if ((st = launch_dispatch(cfg, x, sg.topk_idx, sg.counts, sg.offsets, sg.a2r, sg.r2a, gather ? nullptr : sg.xd,
+  if ((st = launch_dispatch(cfg, x, sg.topk_idx, sg.counts, sg.offsets, sg.a2r, sg.r2a, gather || !rows ? nullptr : sg.xd,
                             sg.scratch, sg.tile_ctr, s)) != MOE_OK)
     return st;
   return mark(timer, 2, s);
@@ -106,9 +106,11 @@ int32_t route_and_first_product(const char* who, const moe_config* cfg, const mo
                                    sg.counts, sg.offsets, sg.a2r, sg.r2a, sg.tile_ctr, s);
 }
 
-// expert FFN -> combine, from the routing tables in the workspace (after_first: the first product has run)
+// expert FFN -> combine, from the routing tables in the workspace (after_first: the first product has run; rows = false: float32,
+// the dispatched rows are still to be made, from x)
 int32_t experts_impl(const char* who, const moe_config* cfg, const moe_weights* w, const void* x, const void* residual,
-                     void* out, void* ws, size_t ws_bytes, hipStream_t s, moe_timer* timer, bool after_first = false) {
+                     void* out, void* ws, size_t ws_bytes, hipStream_t s, moe_timer* timer, bool after_first = false,
+                     bool rows = true) {
   Segments sg;
   int32_t st = open_workspace(who, cfg, w, x, ws, ws_bytes, &sg);
   if (st != MOE_OK) return st;
@@ -116,16 +118,19 @@ int32_t experts_impl(const char* who, const moe_config* cfg, const moe_weights* 
   if (cfg->T > 0 && !out) return fail(MOE_ERR_INVALID_ARG, "%s: out must be non-NULL", who);
   if (out == x && residual != x) return fail(MOE_ERR_INVALID_ARG, "%s: out aliases x", who);
   const bool gather = gemm1_can_gather(cfg);
-  if (!after_first && (st = launch_gemm1(cfg, w, gather ? x : sg.xd, sg.offsets, sg.h, gather ? sg.r2a : nullptr, sg.tile_ctr, s)) != MOE_OK)
+  const bool direct = gather || !rows;  // the first product reads x
+  if (!after_first && (st = launch_gemm1(cfg, w, direct ? x : sg.xd, sg.offsets, sg.h, direct ? sg.r2a : nullptr, sg.tile_ctr, s,
+                                         rows ? nullptr : sg.xd)) != MOE_OK)
     return st;
   if ((st = mark(timer, 3, s)) != MOE_OK) return st;
-  if (gemm2_can_combine(cfg)) {
+  if (cfg->k == 1) {
     // one expert per token: the second GEMM scales each row by its gate weight, adds the residual and writes
     // it to its token's place; what is left of the combine stage are the rows of dropped tokens.  An expert gets at most T
     // rows: unless C is smaller only tokens with NaN logits have none, and the second GEMM writes those as well
     const int64_t C = moe_capacity(cfg);
-    const bool drops = C != MOE_DROPLESS && C < cfg->T;
-    if ((st = launch_gemm2_combine(cfg, w, sg.h, sg.offsets, sg.r2a, sg.topk_w, residual, out, drops ? nullptr : sg.a2r, sg.tile_ctr, s)) != MOE_OK)
+    // (float32: its kernels write those in any case)
+    const bool drops = cfg->dtype == MOE_BF16 && C != MOE_DROPLESS && C < cfg->T;
+    if ((st = launch_gemm2_combine(cfg, w, sg.h, sg.offsets, sg.r2a, sg.topk_w, residual, out, drops ? nullptr : sg.a2r, sg.tile_ctr, s, sg.yd)) != MOE_OK)
       return st;
     if ((st = mark(timer, 4, s)) != MOE_OK) return st;
     if (drops)
@@ -159,8 +164,10 @@ int32_t layer_impl(const moe_config* cfg, const moe_weights* w, const void* x, c
     if ((st = route_and_first_product("moe_layer_forward", cfg, w, x, ws, ws_bytes, s, timer)) != MOE_OK) return st;
     return experts_impl("moe_layer_forward", cfg, w, x, residual, out, ws, ws_bytes, s, timer, true);
   }
-  if ((st = route_impl("moe_layer_forward", cfg, w, x, ws, ws_bytes, s, timer)) != MOE_OK) return st;
-  return experts_impl("moe_layer_forward", cfg, w, x, residual, out, ws, ws_bytes, s, timer);
+  // float32: the first product gathers its rows from x and stores them on the way
+  const bool rows = cfg->dtype == MOE_BF16;
+  if ((st = route_impl("moe_layer_forward", cfg, w, x, ws, ws_bytes, s, timer, rows)) != MOE_OK) return st;
+  return experts_impl("moe_layer_forward", cfg, w, x, residual, out, ws, ws_bytes, s, timer, false, rows);
 }
 
 }  // namespace

@@ -75,21 +75,22 @@ int32_t launch_gate_of(const moe_config* cfg, const moe_weights* w, const void* 
 int32_t launch_dispatch(const moe_config* cfg, const void* x, const int32_t* topk_idx, int32_t* counts,
                         int32_t* offsets, int32_t* a2r, int32_t* r2a, void* xd, void* ws, int32_t* clear8,
                         hipStream_t s);
-// row_map (nullable, bf16 only): row_to_assign; xd is then x itself and the rows are gathered on the fly.
+// row_map (nullable): row_to_assign; xd is then x itself and the rows are gathered on the fly (float32: and stored in xd_out).
 // tile_counters: the 16-int block above (bf16 only; the fp32 kernels ignore it).
 int32_t launch_gemm1(const moe_config* cfg, const moe_weights* w, const void* xd, const int32_t* offsets,
-                     void* h, const int32_t* row_map, int32_t* tile_counters, hipStream_t s);
+                     void* h, const int32_t* row_map, int32_t* tile_counters, hipStream_t s, void* xd_out = nullptr);
 bool gemm1_can_gather(const moe_config* cfg);
 int32_t launch_gemm2(const moe_config* cfg, const moe_weights* w, const void* h, const int32_t* offsets,
                      void* yd, int32_t* tile_counters, hipStream_t s);
-// k = 1, bf16: the second GEMM writes out[t] = residual[t] + topk_w[t] * FFN row for every token that kept its
+// k = 1: the second GEMM writes out[t] = residual[t] + topk_w[t] * FFN row for every token that kept its
 // expert.  The others (residual[t], or zero) are written by launch_fill_dropped where the capacity can drop (a2r NULL), and
 // by the same kernel where only tokens with NaN logits have no row (a2r = assign_to_row): a launch of its own costs a step of few
-// tokens 2 to 3 us.  Together they replace launch_gemm2 + launch_combine and the dispatched-order output yd.
+// tokens 2 to 3 us.  Together they replace launch_gemm2 + launch_combine and, in bf16, the dispatched-order output yd.  float32
+// kernels store yd as well and write the dropped tokens themselves (a2r always).
 bool gemm2_can_combine(const moe_config* cfg);
 int32_t launch_gemm2_combine(const moe_config* cfg, const moe_weights* w, const void* h, const int32_t* offsets,
                              const int32_t* r2a, const float* topk_w, const void* residual, void* out,
-                             const int32_t* a2r, int32_t* tile_counters, hipStream_t s);
+                             const int32_t* a2r, int32_t* tile_counters, hipStream_t s, void* yd);
 int32_t launch_fill_dropped(const moe_config* cfg, const int32_t* a2r, const void* residual, void* out, hipStream_t s);
 int32_t launch_combine(const moe_config* cfg, const void* yd, const int32_t* a2r, const float* topk_w,
                        const void* residual, void* out, hipStream_t s);

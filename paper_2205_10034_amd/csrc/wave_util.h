@@ -35,16 +35,17 @@ __device__ __forceinline__ int place_in_expert(int e, int E, int* cnt, int lane)
 // k = 1, combine in the second product's kernel, no capacity that drops: a token may still have no row (NaN logits).  Its
 // output row, which no tile writes, is its residual or zero.  a2r: row of every token (NULL: the caller writes such rows
 // itself); kept = offsets[E], rows there are.  The workgroups share the tokens; with a row for everyone this is one comparison.
-template <int WAVES>
-__device__ __forceinline__ void fill_rowless_tokens(const int32_t* __restrict__ a2r, int kept, int T, int N, const uint16_t* residual, uint16_t* out) {
+template <int WAVES, typename X>
+__device__ __forceinline__ void fill_rowless_tokens(const int32_t* __restrict__ a2r, int kept, int T, int N, const X* residual, X* out) {
+  constexpr int V = 16 / sizeof(X);
   if (!a2r || kept == T || residual == out) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int first = ((int)(blockIdx.y * gridDim.x + blockIdx.x)) * WAVES + wave, step = (int)(gridDim.x * gridDim.y) * WAVES;
   for (int t = first; t < T; t += step)
     if (a2r[t] < 0)
-      for (int v = lane; v < N / 8; v += 64)
-        reinterpret_cast<uint4*>(out)[(size_t)t * (N / 8) + v] =
-            residual ? reinterpret_cast<const uint4*>(residual)[(size_t)t * (N / 8) + v] : uint4{0u, 0u, 0u, 0u};
+      for (int v = lane; v < N / V; v += 64)
+        reinterpret_cast<uint4*>(out)[(size_t)t * (N / V) + v] =
+            residual ? reinterpret_cast<const uint4*>(residual)[(size_t)t * (N / V) + v] : uint4{0u, 0u, 0u, 0u};
 }
 
 }  // namespace moesys
