@@ -7,12 +7,13 @@
 // have one 64 KB stage in flight per CU, half of it rows that are not there, and their number is too small for the chip
 // when the feature count is: 8 experts x 4096 features are 128 tiles for 256 CUs.  Here a workgroup owns 64 to 256 weight
 // rows and 32 to 192 rows of one expert and requests the stages of all but one of its three to five LDS buffers (64 values of the
-// contraction index each) ahead, though the queue drains once per pass through the buffers (see the K loop): weights and
+// contraction index each) ahead, though the queue drains once per 24 steps (see the K loop): weights and
 // rows go from global memory straight into LDS, swizzled like the grouped GEMM's, one barrier per stage.  A wavefront multiplies blocks of 16 weight rows by blocks of 16 rows
 // (v_mfma_f32_16x16x32_bf16, weights as the first operand: a lane ends up with four consecutive features of one row).
 // SwiGLU: half of the weight rows are the gate's and half the up projection's; a block of 16 is eight and eight of the
 // same features.
 #include <type_traits>
+#include <utility>
 #include "moesys_internal.h"
 #include "phi_table.h"
 #include "row_tiles.h"
@@ -53,6 +54,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t stream_rsrc(const void* base, 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
 }
 #endif
+
+// f(integral_constant<int, 0>{}, ..., integral_constant<int, N - 1>{})
+template <typename F, int... I>
+__device__ __forceinline__ bool unrolled_of(F& f, std::integer_sequence<int, I...>) { return f(std::integral_constant<int, I>{}...); }
+template <int N, typename F>
+__device__ __forceinline__ bool unrolled(F& f) { return unrolled_of(f, std::make_integer_sequence<int, N>{}); }
 
 // NT: the call's weights exceed the last-level cache (weights_exceed_cache)
 template <int EPI, bool GATHER, bool NT, typename S>
@@ -118,7 +125,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   // of an expert finds them in the XCD's L2).  MI355X, us, first / second product: 8 tokens top-2 of 64 experts 2048 x 8192
   // 91 / 86 -> 83 / 76 (5.6 and 6.2 TB/s); 96 tokens top-2 of 8 SwiGLU experts 4096 x 14336 338 / 180 -> 297 / 162 (6.3 and 5.8).
   // (past the last stage the descriptors are empty: nothing is read, and the number of loads in flight is always the same)
-  auto issue_w = [&](auto policy, int kt, unsigned char* stage) {
+  auto issue_w = [&](auto policy, int kt, unsigned char* stage) __attribute__((always_inline)) {
     const bool live = kt < KT;
     const __amdgpu_buffer_rsrc_t rw = stream_rsrc(wa + wbase, live ? w_bytes : 0u);
 #pragma unroll
@@ -130,7 +137,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
                                                decltype(policy)::value);
     }
   };
-  auto issue_a = [&](int kt, unsigned char* stage) {
+  auto issue_a = [&](int kt, unsigned char* stage) __attribute__((always_inline)) {
     const __amdgpu_buffer_rsrc_t ra = stream_rsrc(a_ptr, kt < KT ? a_bytes : 0u);
 #pragma unroll
     for (int i = W_LOADS; i < LOADS; ++i)
@@ -146,7 +153,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   for (int f = 0; f < FB; ++f)
 #pragma unroll
     for (int b = 0; b < RB; ++b) acc[f][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](const unsigned char* ws, const unsigned char* as) {
+  auto compute = [&](const unsigned char* ws, const unsigned char* as) __attribute__((always_inline)) {
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       bf16x8 w[FB];
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   // weights) and for its reads of the stage before, then the workgroup meets: stage kt is whole and the buffers of stage
   // kt-1 are free.
   constexpr int AHEAD = ROW_STAGES == STAGES ? (STAGES - 2) * LOADS : (ROW_STAGES - 2) * LOADS + W_LOADS;
-  auto step = [&](auto policy, auto i, int kt) {
+  auto step = [&](auto policy, auto i, int kt) __attribute__((always_inline)) {
     constexpr int I = decltype(i)::value;
     __builtin_amdgcn_s_waitcnt(wait_vm(AHEAD));
     __builtin_amdgcn_s_barrier();
@@ -201,6 +208,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     issue_w(policy, kt + STAGES - 1, w_of(std::integral_constant<int, I + STAGES - 1>{}));
     compute(w_of(i), a_of(i));
   };
+  constexpr int CYCLE = ROW_STAGES == STAGES ? STAGES : STAGES * ROW_STAGES, PASS = 24 / CYCLE * CYCLE;  // (3 and 2 stages: 6 steps)
   auto contract = [&](auto policy) {
     if constexpr (ROW_STAGES == STAGES) issue_a(0, a0);
     issue_w(policy, 0, w0);
@@ -209,20 +217,14 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     issue_w(policy, 1, w1);
     if constexpr (STAGES > 3) { issue_a(2, a2); issue_w(policy, 2, w2); }
     if constexpr (STAGES > 4) { issue_a(3, a3); issue_w(policy, 3, w3); }
-    // Left by breaks: on every way round the loop all stages were requested, and inside a pass the compiler adds no wait of
-    // its own.  At the head of the loop, where the passes and the prologue meet, it does: the first step of every pass waits for
-    // all loads (vmcnt(0) behind the barrier), whichever stages they belong to.
-    for (int kt = 0;;) {
-      step(policy, std::integral_constant<int, 0>{}, kt);
-      if (++kt == KT) break;
-      step(policy, std::integral_constant<int, 1>{}, kt);
-      if (++kt == KT) break;
-      step(policy, std::integral_constant<int, 2>{}, kt);
-      if (++kt == KT) break;
-      if constexpr (STAGES > 3 || ROW_STAGES == 2) { step(policy, std::integral_constant<int, 3>{}, kt); if (++kt == KT) break; }
-      if constexpr (STAGES > 4 || ROW_STAGES == 2) { step(policy, std::integral_constant<int, 4>{}, kt); if (++kt == KT) break; }
-      if constexpr (ROW_STAGES == 2) { step(policy, std::integral_constant<int, 5>{}, kt); if (++kt == KT) break; }
-    }
+    // On every way round the loop all stages were requested, and inside a pass the compiler adds no wait of its own.  At the head
+    // of the loop, where the passes and the prologue meet, it does: the first step of every pass waits for all loads (vmcnt(0)
+    // behind the barrier), whichever stages they belong to.  So a pass is as many steps as come to about 24.
+    // MI355X, whole layers against passes of three to six steps (us): 32 SwiGLU experts 4096 x 2048, 1500 tokens 396 / 373; 8 of
+    // 2176 x 2048, 138 tokens, k 4 75.7 / 71.0; 64 of 2048 x 8192, 8 tokens 173 / 170, 4096 tokens: the second product 440 / 427.
+    int kt = 0;
+    auto pass = [&](auto... i) __attribute__((always_inline)) { return ((step(policy, i, kt), ++kt < KT) && ...); };
+    while (unrolled<PASS>(pass)) {}
   };
   if (NT && t.tiles == 1) contract(std::integral_constant<int, LOAD_NT>{});
   else contract(std::integral_constant<int, 0>{});
