@@ -350,9 +350,17 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    on: random routing spreads rows by a tenth to an eighth) and the tiles leave no room for it in their last round (64 experts, 142
 //    rows, 2752 -> 896 94 / 128; 238 products 1.03, a fifth of them slower), nor for combines below 2560 values, whose ends
 //    wait for row numbers, gate weights and residual rows in turn (32 experts, 134 rows, 1984 -> 4032 142 / 156; 161 products 1.00).
-//    Of 3266 random products of 97 to 160 rows in whole layers, three sets of weights in turn, the 2867 that remain gain 1.14, six of
+//    (Before passes of 24 steps; what they moved follows.)  Of 3266 random products of 97 to 160 rows in whole layers, three sets of weights in turn, the 2867 that remain gain 1.14, six of
 //    them lose more than 3 %, by up to 6 %; 290 with a capacity 1.14, three; 278 under Zipf routing without one 1.14, but 31, by up to
 //    29 %, where a hot expert's tiles open a further round.
+//  - since the K loop's passes have 24 steps, measured over 842 random whole layers of 25 to 176 rows, both products of each on every
+//    shape in turn (gain of the layer): 25 to 96 rows that no line above serves, 256x128 instead of the grouped GEMM 1.10 over 300
+//    products, three of them not faster, by at most 1.6 %; one round of 256x128 where 128x128 makes more than one round 1.06 over 54,
+//    none slower (beyond 4608 values 1.02 to 1.04, and a tenth slower where Zipf routing leaves a few experts most rows); 97 to 160
+//    rows, 256x192 from 704 values on and for one round with an activation 1.07 over 87, none slower.  GELU products keep the lines
+//    that they had for short or few-round tiles (K below 1088, at most 192 tiles), where its end weighs.  150 other layers: 1.043,
+//    under Zipf routing 1.036, of 50 two slower by 5 and 13 %.  64 SwiGLU experts 1280 x 1088, 82 rows: 201 / 173; 96 experts 2304
+//    x 1344, 92 rows 408 / 360; 128 of 1600 x 832, 141 rows 356 / 345.
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128, STREAM_256x192 };
 int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   const bool swiglu = epi == ST_SWIGLU, activation = epi == ST_GELU || swiglu;
@@ -386,15 +394,19 @@ int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   if (tiles(128, 192) < 128 && tiles(64, 64) <= 512) return STREAM_64x64;
   const bool long_rows = K >= 4096 || big < 256;
   if (rows <= 96 && fill(128) >= (long_rows ? 0.95 : 0.85) && (one_round(256, 128) || K >= (swiglu ? 768 : 832))) return STREAM_256x128;
-  if (wide && rows <= 96 && long_rows && (one_round(128, 128) || K >= 2048)) return STREAM_128x128;
+  // (one round of the wider tiles where 128 weight rows make more than one)
+  const bool one_of_256 = N >= (swiglu ? 768 : epi == ST_GELU ? 2048 : 256) && K <= 4608 && tiles(256, 128) > 128 && one_round(256, 128);
+  if (wide && rows <= 96 && long_rows && (one_round(128, 128) || K >= 2048)) return one_of_256 ? STREAM_256x128 : STREAM_128x128;
   if (wide && (big <= 96 || (big <= 128 && rows <= 152)) && tiles(128, 192) <= (K >= 4096 ? 512 : 256)) return STREAM_128x192;
   // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)
   if (wide && rows > 192 && big > 128 && big <= 192 && tiles_of(128, 128, rows + (rows * 2 + 24) / 25) <= 512) return STREAM_128x128;
-  if (N >= (swiglu ? 128 : 256) && rows > 96 && rows <= 160) {
+  if (N < (swiglu ? 128 : 256)) return STREAM_NONE;
+  if (rows <= 96 && (epi == ST_GELU ? K >= 1088 || (K >= 640 && fill(128) >= 0.83) : K >= (swiglu ? 768 : 512))) return STREAM_256x128;
+  if (rows > 96 && rows <= 160) {
     const int64_t t = tiles(256, 192), rounds = (t + 255) / 256;
     if (rows > 134 && C > 192 && 100 * t > 97 * 256 * rounds) return STREAM_NONE;
     if (epi == ST_COMBINE) return K >= 2560 ? STREAM_256x192 : STREAM_NONE;
-    if (!activation ? K >= (rows > 136 ? 1408 : 1152) : !one_round(256, 192) && K >= (t > 6 * 256 ? 2240 : 1152)) return STREAM_256x192;
+    if (K >= (activation && t > 6 * 256 ? 2240 : 704) && !(epi == ST_GELU && t <= 192)) return STREAM_256x192;
   }
   return STREAM_NONE;
 }
