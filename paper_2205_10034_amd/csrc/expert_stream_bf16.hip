@@ -83,6 +83,14 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned char w2[W_BYTES], a2[ROW_STAGES > 2 ? A_BYTES : 16];
   __shared__ __attribute__((aligned(1024))) unsigned char w3[STAGES > 3 ? W_BYTES : 16], a3[ROW_STAGES > 3 ? A_BYTES : 16];
   __shared__ __attribute__((aligned(1024))) unsigned char w4[STAGES > 4 ? W_BYTES : 16], a4[ROW_STAGES > 4 ? A_BYTES : 16];
+  // GELU: by the exact function for a few elements per lane, by the table for many: filled while the first stages are on their way
+  // where the LDS has room for it beside them, else in the first stage's buffer behind the K loop.  Measured on MI355X, whole layers
+  // (us, behind the loop / beside the stages): 64 experts 1024 x 4096, 128 rows 307.5 / 303.0; 64 of 1600 x 6144, 88 rows 624 / 618;
+  // 32 of 1024 x 2048, 94 rows 106.8 / 105.3.
+  constexpr bool TABLE = EPI == ST_GELU && FB * RB >= 8;
+  constexpr bool OWN_TABLE = TABLE && STAGES * W_BYTES + ROW_STAGES * A_BYTES + PHI_N * 8 <= 159 * 1024;
+  static_assert(PHI_N * 8 <= W_BYTES, "the table fits a stage of weights");
+  __shared__ __attribute__((aligned(16))) unsigned char table[OWN_TABLE ? PHI_N * 8 : 16];
   if (clear_ctr && blockIdx.x == 0 && threadIdx.x < 8) clear_ctr[threadIdx.x] = 0;  // (a grouped GEMM may run next)
   RowTile t;
   const int kept = EPI == ST_COMBINE ? offsets[E] : 0;
@@ -217,6 +225,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     issue_w(policy, 1, w1);
     if constexpr (STAGES > 3) { issue_a(2, a2); issue_w(policy, 2, w2); }
     if constexpr (STAGES > 4) { issue_a(3, a3); issue_w(policy, 3, w3); }
+    if constexpr (OWN_TABLE) fill_phi_table(reinterpret_cast<phi_f32x2*>(table));  // (the steps' barriers are between it and its readers)
     // On every way round the loop all stages were requested, and inside a pass the compiler adds no wait of its own.  At the head
     // of the loop, where the passes and the prologue meet, it does: the first step of every pass waits for all loads (vmcnt(0)
     // behind the barrier), whichever stages they belong to.  So a pass is as many steps as come to about 24.
@@ -230,12 +239,9 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   else contract(std::integral_constant<int, 0>{});
   __builtin_amdgcn_s_waitcnt(wait_vm(0));  // (the empty loads retire)
 
-  // GELU: by the exact function for a few elements per lane, by the table (built in the first stage's buffer) for many
-  constexpr bool TABLE = EPI == ST_GELU && FB * RB >= 8;
-  static_assert(PHI_N * 8 <= W_BYTES, "the table fits a stage of weights");
-  phi_f32x2* const phi = reinterpret_cast<phi_f32x2*>(w0);
+  phi_f32x2* const phi = reinterpret_cast<phi_f32x2*>(OWN_TABLE ? table : w0);
   const float phi_add = phi_addend(phi);
-  if constexpr (TABLE) {
+  if constexpr (TABLE && !OWN_TABLE) {
     __syncthreads();
     fill_phi_table(phi);
     __syncthreads();
