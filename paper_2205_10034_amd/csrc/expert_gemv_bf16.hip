@@ -213,22 +213,13 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
   }
 }
 
-// A step of ONE token: ranking, routing tables and the first product in one kernel.  The router's partial logits (float64, E
-// values per slice of the contraction index) are a few KB in L2: every workgroup adds them in slice order and ranks the token by
-// itself, so that the product starts at the experts' weights where a kernel of its own would rank first and the product then
-// walk offsets -> row -> token -> weights; workgroup (0, 0) writes the tables that the second product reads.  Row r is the r-th
-// selected expert in expert order and there is one row per expert, so the sums of two 1 KB pieces of FPW weight rows fit the
-// registers at once.  E <= 64.  Measured on MI355X, 64 experts 2048 x 8192, k 2: ranking kernel 5.6 us + product 19.5, now 18.6 together;
-// whole one-token layers (us, before / now, the wider combine kernel below included): that one 45.3 / 37.4; 16 experts 1792 x 2816
-// 25.8 / 16.8; 24 of 1536 x 4096, k 4 42.1 / 28.0; 8 SwiGLU of 4096 x 14336 127 / 119.
-template <int EPI, int FPW, bool NT>
-__global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
-    const uint16_t* __restrict__ x, const double* __restrict__ part, int slices, const float* __restrict__ br, int renorm,
-    const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb, const uint16_t* __restrict__ bias, uint16_t* __restrict__ out,
-    const int64_t* __restrict__ eoff, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts,
-    int32_t* __restrict__ offsets, int32_t* __restrict__ a2r, int32_t* __restrict__ r2a, int32_t* __restrict__ clear8, int E, int N,
-    int K, int k) {
-  constexpr int OUTF = EPI == GV_SWIGLU ? FPW / 2 : FPW;  // output features per wavefront
+// Ranks the token of a one-token step from its partial logits, in every wavefront; returns the selected experts, bit e for expert e.
+// write: the workgroup writes the routing tables.
+__device__ __forceinline__ unsigned long long rank_one_token(const double* __restrict__ part, int slices, const float* __restrict__ br, int renorm,
+                                                             int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+                                                             int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                                             int32_t* __restrict__ a2r, int32_t* __restrict__ r2a,
+                                                             int32_t* __restrict__ clear8, int E, int k, bool write) {
   __shared__ double zs[GV_WAVES][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int sel;  // lane j < k: the j-th selection (every wavefront ranks for itself)
@@ -252,7 +243,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
     const int e = valid_expert(__builtin_amdgcn_readlane(sel, j), E);
     if (e >= 0) chosen |= 1ull << e;
   }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && wave == 0) {
+  if (write && wave == 0) {
     if (lane < E) {
       counts[lane] = (int)((chosen >> lane) & 1ull);
       offsets[lane] = __popcll(chosen & ((1ull << lane) - 1ull));
@@ -267,6 +258,37 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
     }
     if (lane < 8) clear8[lane] = 0;
   }
+  return chosen;
+}
+
+// The same alone, for a caller that routes and runs the experts in two calls: the same bits as below.
+__global__ __launch_bounds__(GV_WAVES * 64) void rank_one_token_kernel(const double* __restrict__ part, int slices, const float* __restrict__ br,
+                                                                      int renorm, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+                                                                      int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                                                      int32_t* __restrict__ a2r, int32_t* __restrict__ r2a,
+                                                                      int32_t* __restrict__ clear8, int E, int k) {
+  rank_one_token(part, slices, br, renorm, topk_idx, topk_w, counts, offsets, a2r, r2a, clear8, E, k, true);
+}
+
+// A step of ONE token: ranking, routing tables and the first product in one kernel.  The router's partial logits (float64, E
+// values per slice of the contraction index) are a few KB in L2: every workgroup adds them in slice order and ranks the token by
+// itself, so that the product starts at the experts' weights where a kernel of its own would rank first and the product then
+// walk offsets -> row -> token -> weights; workgroup (0, 0) writes the tables that the second product reads.  Row r is the r-th
+// selected expert in expert order and there is one row per expert, so the sums of two 1 KB pieces of FPW weight rows fit the
+// registers at once.  E <= 64.  Measured on MI355X, 64 experts 2048 x 8192, k 2: ranking kernel 5.6 us + product 19.5, now 18.6 together;
+// whole one-token layers (us, before / now, the wider combine kernel below included): that one 45.3 / 37.4; 16 experts 1792 x 2816
+// 25.8 / 16.8; 24 of 1536 x 4096, k 4 42.1 / 28.0; 8 SwiGLU of 4096 x 14336 127 / 119.
+template <int EPI, int FPW, bool NT>
+__global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
+    const uint16_t* __restrict__ x, const double* __restrict__ part, int slices, const float* __restrict__ br, int renorm,
+    const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb, const uint16_t* __restrict__ bias, uint16_t* __restrict__ out,
+    const int64_t* __restrict__ eoff, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ a2r, int32_t* __restrict__ r2a, int32_t* __restrict__ clear8, int E, int N,
+    int K, int k) {
+  constexpr int OUTF = EPI == GV_SWIGLU ? FPW / 2 : FPW;  // output features per wavefront
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  unsigned long long chosen = rank_one_token(part, slices, br, renorm, topk_idx, topk_w, counts, offsets, a2r, r2a, clear8, E, k,
+                                             blockIdx.x == 0 && blockIdx.y == 0);
   const int row = blockIdx.y;
   if (row >= __popcll(chosen)) return;
   for (int r = 0; r < row; ++r) chosen &= chosen - 1;
@@ -472,6 +494,13 @@ int32_t launch_expert_gemv_combine_one_token(const moe_config* cfg, const void* 
 // Ranking + first product of a one-token step, from the partial logits of launch_gate_parts_one_token (at most 16 slices).
 bool expert_gemv_ranked_applies(const moe_config* cfg) {
   return expert_gemv_combine_one_token_applies(cfg) && cfg->E <= 64 && expert_gemv_applies(cfg, cfg->d_ff, cfg->d_model);
+}
+int32_t launch_rank_one_token(const moe_config* cfg, const double* part, int slices, const float* b_router, int32_t* topk_idx, float* topk_w,
+                              int32_t* counts, int32_t* offsets, int32_t* a2r, int32_t* r2a, int32_t* clear8, hipStream_t s) {
+  if (!expert_gemv_ranked_applies(cfg) || slices < 1 || slices > RANKED_SLICES) return fail(MOE_ERR_UNSUPPORTED, "expert GEMV: not a ranked one-token step");
+  hipLaunchKernelGGL(rank_one_token_kernel, dim3(1), dim3(GV_WAVES * 64), 0, s, part, slices, b_router, cfg->renormalize, topk_idx, topk_w,
+                     counts, offsets, a2r, r2a, clear8, cfg->E, cfg->k);
+  return check_hip(hipGetLastError(), "gate launch");
 }
 int32_t launch_expert_gemv_ranked(const moe_config* cfg, const void* x, const double* part, int slices, const float* b_router, const void* wa,
                                   const void* wb, const void* bias, void* h, const int64_t* eoff, int32_t* topk_idx, float* topk_w,

@@ -48,6 +48,12 @@ int32_t mark(moe_timer* timer, int i, hipStream_t s) {
   return check_hip(hipEventRecord(timer->ev[i], s), "hipEventRecord");
 }
 
+// A one-token step: the gate's partial logits, then ranking and tables, inside a layer in the first product's kernel, in routing alone
+// in one of their own with the same bits.  The partial logits take the place of yd, which only the second product writes.
+bool ranked_product_applies(const moe_config* cfg, const moe_weights* w) {
+  return expert_gemv_ranked_applies(cfg) && gate_parts_one_token(cfg, w->w_router, (size_t)max_rows(cfg) * cfg->d_model * 2) > 0;
+}
+
 // gate -> dispatch bookkeeping (and, on the fp32 path, the dispatched copy, unless the first product makes it: rows = false)
 int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w, const void* x, void* ws,
                    size_t ws_bytes, hipStream_t s, moe_timer* timer, bool rows = true) {
@@ -57,7 +63,16 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   if (!w->w_router) return fail(MOE_ERR_INVALID_ARG, "%s: w_router is NULL", who);
   if ((st = mark(timer, 0, s)) != MOE_OK) return st;
   const bool gather = gemm1_can_gather(cfg);
-  // few tokens, a large router: the gate runs on many compute units and writes the dispatch tables as well (the partial logits go
+  if (ranked_product_applies(cfg, w)) {
+    const size_t yd_bytes = (size_t)max_rows(cfg) * cfg->d_model * 2;
+    if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, (double*)sg.yd, yd_bytes, s)) != MOE_OK) return st;
+    if ((st = launch_rank_one_token(cfg, (const double*)sg.yd, gate_parts_one_token(cfg, w->w_router, yd_bytes), w->b_router, sg.topk_idx,
+                                    sg.topk_w, sg.counts, sg.offsets, sg.a2r, sg.r2a, sg.tile_ctr, s)) != MOE_OK)
+      return st;
+    if ((st = mark(timer, 1, s)) != MOE_OK) return st;
+    return mark(timer, 2, s);
+  }
+  // few tokens: the gate runs on many compute units and writes the dispatch tables as well (the partial logits go
   // where the first product will write)
   const size_t h_bytes = (size_t)max_rows(cfg) * cfg->d_ff * elem_size(cfg->dtype);
   if (gather && gate_dispatch_slices_applies(cfg, w->w_router, h_bytes)) {
@@ -84,11 +99,6 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   return mark(timer, 2, s);
 }
 
-// A one-token step: the gate's partial logits, then ranking, tables and first product in one kernel.  The partial logits take the
-// place of yd, which only the second product writes.
-bool ranked_product_applies(const moe_config* cfg, const moe_weights* w) {
-  return expert_gemv_ranked_applies(cfg) && gate_parts_one_token(cfg, w->w_router, (size_t)max_rows(cfg) * cfg->d_model * 2) > 0;
-}
 int32_t route_and_first_product(const char* who, const moe_config* cfg, const moe_weights* w, const void* x, void* ws, size_t ws_bytes,
                                 hipStream_t s, moe_timer* timer) {
   Segments sg;

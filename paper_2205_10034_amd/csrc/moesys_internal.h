@@ -53,6 +53,8 @@ int32_t launch_expert_gemv_combine_one_token(const moe_config* cfg, const void* 
                                              const int32_t* offsets, const int32_t* a2r, const float* topk_w,
                                              const void* residual, void* yd, void* out, const int64_t* eoff, hipStream_t s);
 bool expert_gemv_ranked_applies(const moe_config* cfg);
+int32_t launch_rank_one_token(const moe_config* cfg, const double* part, int slices, const float* b_router, int32_t* topk_idx, float* topk_w,
+                              int32_t* counts, int32_t* offsets, int32_t* a2r, int32_t* r2a, int32_t* clear8, hipStream_t s);
 int32_t launch_expert_gemv_ranked(const moe_config* cfg, const void* x, const double* part, int slices, const float* b_router, const void* wa,
                                   const void* wb, const void* bias, void* h, const int64_t* eoff, int32_t* topk_idx, float* topk_w,
                                   int32_t* counts, int32_t* offsets, int32_t* a2r, int32_t* r2a, int32_t* clear8, hipStream_t s);

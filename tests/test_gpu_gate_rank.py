@@ -76,7 +76,7 @@ def test_gate_rank(T, d, E, k, cf):
     (64, 64, 4, 2, "gelu", ""), (128, 512, 64, 8, "gelu", ""), (576, 192, 24, 2, "swiglu", ""), (1088, 8192, 9, 2, "gelu", ""), (1024, 16384, 8, 2, "gelu", ""),
     (2048, 8192, 64, 4, "swiglu", ""), (1024, 2048, 33, 8, "gelu", "nan"), (1024, 2048, 16, 4, "swiglu", "masked"), (1024, 2048, 16, 2, "gelu", "inf")])
 def test_one_token_layer(d, f, E, k, act, special):
-    """The whole layer against the two calls that rank in a kernel of their own."""
+    """The whole layer against routing and experts in two calls, which rank in a kernel of their own: the same bits."""
     print(d, f, E, k, act, special, flush=True)
     cfg = M.MoEConfig(T=1, d_model=d, d_ff=f, E=E, k=k, act=act, renormalize=bool(E & 1))
     g, x, router, bias = problem(1, d, E)
@@ -108,6 +108,5 @@ def test_one_token_layer(d, f, E, k, act, special):
         assert np.array_equal(a("h", rows * f // 2), b("h", rows * f // 2))  # the same sums in the same order
         if not special:
             check_tables(a, cfg, x, router, bias)
-        # gate weights: the router's float64 partial sums meet in another order
-        assert np.allclose(a("topk_w", k, torch.float32), b("topk_w", k, torch.float32), rtol=4e-7, atol=0, equal_nan=True)
-        assert torch.allclose(out.float(), out2.float(), rtol=2.0 ** -7, atol=1e-5, equal_nan=True)
+        assert np.array_equal(a("topk_w", k), b("topk_w", k))    # bits
+        assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
