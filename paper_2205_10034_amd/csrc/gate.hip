@@ -395,7 +395,8 @@ constexpr int GR_THREADS = ONE_WAVES * 64, GR_MAX_T = 256, GR_LOGITS = 8192;
 // slices that a thread adds for each of its logits_per_thread logits: all of its loads are in flight together
 constexpr int gr_slices(int logits_per_thread) { return logits_per_thread <= 4 ? 16 / logits_per_thread : 4; }
 constexpr int gr_logits_per_thread(int logits) { return logits <= GR_THREADS ? 1 : logits <= 2 * GR_THREADS ? 2 : logits <= 4 * GR_THREADS ? 4 : 8; }
-template <int NPL>
+// WAVE_ORDER: steps whose gate alone would be gate_few_kernel get that kernel's weights, bit for bit, and so do their gradients.
+template <int NPL, bool WAVE_ORDER>
 __global__ __launch_bounds__(GR_THREADS) void gate_rank_kernel(const double* __restrict__ part, const float* __restrict__ br, int T, int E,
                                                                int k, int C, int renorm, int slices, int32_t* __restrict__ topk_idx,
                                                                float* __restrict__ topk_w, int32_t* __restrict__ counts,
@@ -439,7 +440,7 @@ __global__ __launch_bounds__(GR_THREADS) void gate_rank_kernel(const double* __r
     double z[NPL];
 #pragma unroll
     for (int i = 0; i < NPL; ++i) z[i] = sub + 8 * i < E ? zs[t * (E + 8) + sub + 8 * i] : -INFINITY;
-    finalize_group<NPL, false>(z, sub, E, k, renorm, 0.f, sel + t * k, topk_w + (size_t)t * k, nullptr);
+    finalize_group<NPL, false, WAVE_ORDER>(z, sub, E, k, renorm, 0.f, sel + t * k, topk_w + (size_t)t * k, nullptr);
   }
   __syncthreads();
   const int A = T * k, j = tid / T, t = tid - j * T;  // assignment j T + t
@@ -1159,7 +1160,10 @@ int32_t launch_gate_dispatch_slices(const moe_config* cfg, const void* x, const 
   const int32_t st = launch_gate_parts(cfg, p, x, w_router, (double*)scratch, s);
   if (st != MOE_OK) return st;
   const int E = cfg->E;
-  auto kern = E <= 16 ? gate_rank_kernel<2> : E <= 32 ? gate_rank_kernel<4> : E <= 64 ? gate_rank_kernel<8> : E <= 128 ? gate_rank_kernel<16> : gate_rank_kernel<32>;
+  auto kern = gate_few_applies(cfg, w_router)
+                  ? (E <= 16 ? gate_rank_kernel<2, true> : E <= 32 ? gate_rank_kernel<4, true> : gate_rank_kernel<8, true>)
+                  : E <= 16 ? gate_rank_kernel<2, false> : E <= 32 ? gate_rank_kernel<4, false> : E <= 64 ? gate_rank_kernel<8, false>
+                  : E <= 128 ? gate_rank_kernel<16, false> : gate_rank_kernel<32, false>;
   size_t shmem = ((size_t)p.logits + 8 * (size_t)cfg->T) * sizeof(double);
   if (shmem < sizeof(OneTables)) shmem = sizeof(OneTables);
   if (shmem > 48 * 1024) {

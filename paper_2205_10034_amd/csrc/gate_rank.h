@@ -21,6 +21,9 @@ template <int STEP>
 __device__ __forceinline__ double group8_partner(double v) {
   return __hiloint2double(group8_partner<STEP>(__double2hiint(v)), group8_partner<STEP>(__double2loint(v)));
 }
+__device__ __forceinline__ float quad_mirror(float v) {  // quad_perm 3,2,1,0
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x1B, 0xF, 0xF, true));
+}
 // f(step) for the three steps, unrolled
 template <typename F>
 __device__ __forceinline__ void group8_steps(F&& f) {
@@ -35,7 +38,9 @@ __device__ __forceinline__ void group8_steps(F&& f) {
 // to the first expert NOT selected.  Returns true (to every lane of the group) if two neighbours among
 // those k+1 logits are closer than `margin`.
 // MARGIN = false (logits that are exact): no extra round, returns false.
-template <int NPL, bool MARGIN = true>
+// WAVE_ORDER (E <= 64): the exponentials are added in the order of a butterfly over a wavefront with one expert per lane, so that the
+// weights carry the bits of the kernel that ranks up to 16 tokens that way.
+template <int NPL, bool MARGIN = true, bool WAVE_ORDER = false>
 __device__ __forceinline__ bool finalize_group(double (&z)[NPL], int sub, int E, int k, int renorm, float margin,
                                                int32_t* __restrict__ idx_out, float* __restrict__ w_out,
                                                float* __restrict__ probs_out, bool mark_close = false) {
@@ -50,7 +55,22 @@ __device__ __forceinline__ bool finalize_group(double (&z)[NPL], int sub, int E,
     sum += ex[i];
   }
   // (the same pairs in the same order in every lane of the group: all eight hold the same sum, bit for bit)
-  group8_steps([&](auto st) { sum += group8_partner<decltype(st)::value>(sum); });
+  if constexpr (WAVE_ORDER) {
+    static_assert(NPL <= 8, "a lane of the wavefront has one expert");
+    float t[NPL];
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) t[i] = ex[i];
+#pragma unroll
+    for (int w = NPL / 2; w >= 1; w /= 2)  // lanes 32, 16 and 8 apart
+#pragma unroll
+      for (int i = 0; i < w; ++i) t[i] += t[i + w];
+    sum = t[0];
+    sum += quad_mirror(group8_partner<2>(sum));  // 4 (7 - i, then 3 - i inside the quad), 2 and 1 apart
+    sum += group8_partner<1>(sum);
+    sum += group8_partner<0>(sum);
+  } else {
+    group8_steps([&](auto st) { sum += group8_partner<decltype(st)::value>(sum); });
+  }
 #pragma unroll
   for (int i = 0; i < NPL; ++i) {
     ex[i] = ex[i] / sum;
@@ -98,7 +118,7 @@ __device__ __forceinline__ bool finalize_group(double (&z)[NPL], int sub, int E,
 }
 
 // The same by a whole wavefront for up to 64 experts, lane e holding expert e's logit (-inf beyond E): the steps of a reduction
-// over the lanes are moves on the vector ALU that end in lane 63.  The j-th selection is returned in lane j < k, with its weight.
+// over the lanes are moves on the vector ALU.  The j-th selection is returned in lane j < k, with its weight.
 template <int CTRL, int ROWS, typename T>
 __device__ __forceinline__ T wave_step(T v, T other) {  // `other` where the step has no source lane
   if constexpr (sizeof(T) == 8)
@@ -108,13 +128,28 @@ __device__ __forceinline__ T wave_step(T v, T other) {  // `other` where the ste
     return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(other), __float_as_int(v), CTRL, ROWS, 0xF, false));
 }
 template <typename T, typename F>
-__device__ __forceinline__ T wave_reduce(T v, T neutral, F&& f) {  // valid in lane 63
+__device__ __forceinline__ T wave_reduce(T v, T neutral, F&& f) {  // valid in lane 63 (f: any order gives the same)
   v = f(v, wave_step<0x111, 0xF>(v, neutral));  // row_shr 1, 2, 4, 8: the last lane of a row of 16 has the row's result
   v = f(v, wave_step<0x112, 0xF>(v, neutral));
   v = f(v, wave_step<0x114, 0xF>(v, neutral));
   v = f(v, wave_step<0x118, 0xF>(v, neutral));
   v = f(v, wave_step<0x142, 0xA>(v, neutral));  // row_bcast 15 into rows 1 and 3, then 31 into rows 2 and 3
   return f(v, wave_step<0x143, 0xC>(v, neutral));
+}
+// Sum over the lanes by a butterfly, 32, 16, 8, 4, 2 and 1 lanes apart: the bits of the same steps through __shfl_xor, in every lane.
+__device__ __forceinline__ float wave_sum(float v) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  uint32_t u = __float_as_uint(v);
+  const u32x2 a = __builtin_amdgcn_permlane32_swap(u, u, false, false);  // lanes 0..31 twice, lanes 32..63 twice
+  u = __float_as_uint(__uint_as_float(a.x) + __uint_as_float(a.y));
+  const u32x2 b = __builtin_amdgcn_permlane16_swap(u, u, false, false);  // rows of 16: the even ones twice, the odd ones twice
+  v = __uint_as_float(b.x) + __uint_as_float(b.y);
+  auto step = [&](auto ctrl) { v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true)); };
+  step(std::integral_constant<int, 0x128>{});  // row_ror 8
+  step(std::integral_constant<int, 0x124>{});  // row_ror 4: lanes 8 apart agree, so this is 4 apart
+  step(std::integral_constant<int, 0x4E>{});   // quad_perm 2,3,0,1
+  step(std::integral_constant<int, 0xB1>{});   // quad_perm 1,0,3,2
+  return v;
 }
 __device__ __forceinline__ int rank_wave(double z, int lane, int E, int k, int renorm, float& weight) {
   float ex = 0.f, sum = 1.f, wsel = 0.f, wsum = 0.f;
@@ -124,7 +159,7 @@ __device__ __forceinline__ int rank_wave(double z, int lane, int E, int k, int r
     const double best = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(m), 63), __builtin_amdgcn_readlane(__double2loint(m), 63));
     if (j == 0) {
       ex = lane < E ? expf((float)z - (float)best) : 0.f;
-      sum = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_reduce(ex, 0.f, [](float a, float b) { return a + b; })), 63));
+      sum = wave_sum(ex);
     }
     const unsigned long long at = __ballot(lane < E && z == best);  // ties: the lower expert; nothing that compares (NaN): none
     const int e = at ? __builtin_ctzll(at) : 0x7fffffff;

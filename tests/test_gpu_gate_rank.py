@@ -110,3 +110,28 @@ def test_one_token_layer(d, f, E, k, act, special):
             check_tables(a, cfg, x, router, bias)
         assert np.array_equal(a("topk_w", k), b("topk_w", k))    # bits
         assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+
+
+@pytest.mark.parametrize("T,d,E,k", [(1, 2048, 64, 2), (1, 1024, 16, 4), (1, 4096, 32, 8), (1, 576, 8, 2), (1, 512, 4, 4), (2, 1024, 8, 2), (3, 2048, 64, 8),
+                                     (5, 320, 4, 2), (8, 2048, 64, 2), (9, 4096, 32, 2), (15, 1088, 16, 3), (16, 2048, 64, 8), (16, 64, 4, 4)])
+@pytest.mark.parametrize("renorm", [False, True])
+def test_weights_are_those_of_the_gate_alone(T, d, E, k, renorm):
+    """Up to 16 tokens on 4, 8, 16, 32 or 64 experts: whichever kernel ranks inside a layer, its weights are moe_gate's, bit for bit
+    (logits: float64 sums of exact products, so that their order does not show in float32; the softmax in the same order)."""
+    print(T, d, E, k, renorm, flush=True)
+    cfg = M.MoEConfig(T=T, d_model=d, d_ff=512, E=E, k=k, renormalize=renorm)
+    for seed in range(8):
+        g, x, router, bias = problem(T, d + seed, E)
+        x, router = x[:, :d].contiguous(), router[:d].contiguous()
+        mat = lambda n, m: (torch.randn(E, n, m, generator=g, device="cuda") * m ** -0.5).bfloat16()
+        W = M.Weights({"w_router": router, "b_router": bias, "w1": mat(512, d), "w2": mat(d, 512)}, "output_major")
+        idx, w = torch.empty(T, k, dtype=torch.int32, device="cuda"), torch.empty(T, k, device="cuda")
+        M.moe_gate(cfg, x, router, bias, idx, w)
+        out = torch.empty_like(x)
+        for call in (lambda ws: M.moe_layer_route(cfg, W, x, ws), lambda ws: M.moe_layer_forward(cfg, W, x, None, out, ws)):
+            ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda").fill_(0xAB)
+            call(ws)
+            torch.cuda.synchronize()
+            read = reader(ws, cfg)
+            assert np.array_equal(read("topk_idx", T * k).reshape(T, k), idx.cpu().numpy())
+            assert np.array_equal(read("topk_w", T * k).reshape(T, k), w.view(torch.int32).cpu().numpy())
