@@ -278,14 +278,18 @@ __global__ __launch_bounds__(GV_WAVES * 64) void rank_one_token_kernel(const dou
 // registers at once.  E <= 64.  Measured on MI355X, 64 experts 2048 x 8192, k 2: ranking kernel 5.6 us + product 19.5, now 18.6 together;
 // whole one-token layers (us, before / now, the wider combine kernel below included): that one 45.3 / 37.4; 16 experts 1792 x 2816
 // 25.8 / 16.8; 24 of 1536 x 4096, k 4 42.1 / 28.0; 8 SwiGLU of 4096 x 14336 127 / 119.
-template <int EPI, int FPW, bool NT>
+// KSPLIT: as in the kernel above and by the same rule, so that a sum has the same terms in the same order in both.  Whole layers (us,
+// never split / split): 8 experts 4096 x 2048 20.8 / 20.2, 4096 x 7168 50.8 / 48.7, SwiGLU 4096 x 3584 41.6 / 38.5.
+template <int EPI, int FPW, bool NT, bool KSPLIT>
 __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
     const uint16_t* __restrict__ x, const double* __restrict__ part, int slices, const float* __restrict__ br, int renorm,
     const uint16_t* __restrict__ wa, const uint16_t* __restrict__ wb, const uint16_t* __restrict__ bias, uint16_t* __restrict__ out,
     const int64_t* __restrict__ eoff, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ a2r, int32_t* __restrict__ r2a, int32_t* __restrict__ clear8, int E, int N,
     int K, int k) {
-  constexpr int OUTF = EPI == GV_SWIGLU ? FPW / 2 : FPW;  // output features per wavefront
+  constexpr int OUTF = EPI == GV_SWIGLU ? FPW / 2 : FPW;  // output features per wavefront (KSPLIT: per workgroup)
+  constexpr int PIECE = (KSPLIT ? GV_WAVES : 1) * 64 * 8;
+  __shared__ float red[KSPLIT ? GV_WAVES : 1][FPW];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned long long chosen = rank_one_token(part, slices, br, renorm, topk_idx, topk_w, counts, offsets, a2r, r2a, clear8, E, k,
                                              blockIdx.x == 0 && blockIdx.y == 0);
@@ -294,7 +298,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
   for (int r = 0; r < row; ++r) chosen &= chosen - 1;
   const int e = __builtin_ctzll(chosen);
   const int64_t wbase = eoff ? eoff[e] : (int64_t)e * N * K;
-  const int n0 = (blockIdx.x * GV_WAVES + wave) * OUTF;  // first output feature of this wavefront
+  const int n0 = (KSPLIT ? (int)blockIdx.x : (int)blockIdx.x * GV_WAVES + wave) * OUTF;  // first output feature of this wavefront
   const uint16_t* wrow[FPW];
 #pragma unroll
   for (int j = 0; j < FPW; ++j)
@@ -315,9 +319,9 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
       acc[j] = a;
     }
   };
-  for (int kb = lane * 8; kb < K; kb += 2 * 64 * 8) {
-    const bool two = kb + 64 * 8 < K;
-    const int kb2 = two ? kb + 64 * 8 : kb;  // (a lane without a second piece re-reads the first and does not use it)
+  for (int kb = (KSPLIT ? (int)threadIdx.x : lane) * 8; kb < K; kb += 2 * PIECE) {
+    const bool two = kb + PIECE < K;
+    const int kb2 = two ? kb + PIECE : kb;  // (a lane without a second piece re-reads the first and does not use it)
     uint4 wv[FPW], wv2[FPW];
 #pragma unroll
     for (int j = 0; j < FPW; ++j) wv[j] = load_weights<NT>(wrow[j] + kb);
@@ -331,6 +335,23 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
   for (int j = 0; j < FPW; ++j) {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) acc[j] += __shfl_xor(acc[j], m, 64);
+  }
+  if constexpr (KSPLIT) {  // the wavefronts' sums meet, in wavefront order
+    if (lane < FPW) {
+      float v = acc[0];
+#pragma unroll
+      for (int j = 1; j < FPW; ++j) v = lane == j ? acc[j] : v;
+      red[wave][lane] = v;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int j = 0; j < FPW; ++j) {
+      float v = red[0][j];
+#pragma unroll
+      for (int w = 1; w < GV_WAVES; ++w) v += red[w][j];
+      acc[j] = v;
+    }
   }
   if (lane < OUTF) {
     const int n = n0 + lane;
@@ -430,17 +451,20 @@ __global__ __launch_bounds__(C1_GROUPS * GV_WAVES * 64) void expert_gemv_combine
   }
 }
 
+// Long rows and too few workgroups even so (`blocks` blocks of output features for `rows` rows): the wavefronts of a workgroup split
+// the contraction index instead of the output features.
+bool splits_contraction(int K, int blocks, int rows) { return K >= 4096 && (int64_t)blocks * rows < 512; }
+
 template <int EPI, int ROWS, int FPW>
 int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t* wa, const uint16_t* wb, const uint16_t* bias,
                      const int32_t* offsets, uint16_t* out, const int32_t* row_map, const float* gate_w, const uint16_t* residual,
                      const int32_t* a2r, const int64_t* eoff, int N, int K, bool gather, hipStream_t s) {
   constexpr int OUTF = EPI == GV_SWIGLU ? FPW / 2 : FPW;
   // About 256 KB of weights per workgroup, in whole blocks of output features, as long as that leaves about two
-  // workgroups per CU (the experts with rows are at most k*T).  Long rows and too few workgroups even so: the
-  // wavefronts of a workgroup split the contraction index instead of the output features.
+  // workgroups per CU (the experts with rows are at most k*T).
   const int A = cfg->k * cfg->T;
   int blocks = N / (GV_WAVES * OUTF);
-  const bool ksplit = K >= 4096 && (int64_t)blocks * A < 512;
+  const bool ksplit = splits_contraction(K, blocks, A);
   if (ksplit) blocks *= GV_WAVES;
   int reps = ksplit ? 1 : (int)((256 * 1024) / ((int64_t)GV_WAVES * FPW * K * 2));
   reps = reps < 1 ? 1 : reps > 8 ? 8 : reps;
@@ -509,10 +533,14 @@ int32_t launch_expert_gemv_ranked(const moe_config* cfg, const void* x, const do
   const int N = cfg->d_ff;
   const bool sw = cfg->act == MOE_ACT_SWIGLU, nt = weights_exceed_cache(cfg);
   const int per8 = GV_WAVES * (sw ? 4 : 8);  // output features per workgroup with eight weight rows per wavefront
-  const bool eight = (int64_t)(N / per8) * cfg->k >= 512;  // about two workgroups per CU, else half the rows
-  const dim3 grid(N / (eight ? per8 : per8 / 2), cfg->k), block(GV_WAVES * 64);
+  const bool ksplit = splits_contraction(cfg->d_model, N / per8, cfg->k);
+  const int of8 = ksplit ? per8 / GV_WAVES : per8;
+  const bool eight = (int64_t)(N / of8) * cfg->k >= 512;  // about two workgroups per CU, else half the rows
+  const dim3 grid(N / (eight ? of8 : of8 / 2), cfg->k), block(GV_WAVES * 64);
 #define MOESYS_RANKED(EP, F)                                                                                                      \
-  hipLaunchKernelGGL((nt ? expert_gemv_ranked_kernel<EP, F, true> : expert_gemv_ranked_kernel<EP, F, false>), grid, block, 0, s,   \
+  hipLaunchKernelGGL((ksplit ? (nt ? expert_gemv_ranked_kernel<EP, F, true, true> : expert_gemv_ranked_kernel<EP, F, false, true>)  \
+                             : (nt ? expert_gemv_ranked_kernel<EP, F, true, false> : expert_gemv_ranked_kernel<EP, F, false, false>)), \
+                     grid, block, 0, s,                                                                                           \
                      (const uint16_t*)x, part, slices, b_router, cfg->renormalize, (const uint16_t*)wa, (const uint16_t*)wb,       \
                      (const uint16_t*)bias, (uint16_t*)h, eoff, topk_idx, topk_w, counts, offsets, a2r, r2a, clear8, cfg->E, N,    \
                      cfg->d_model, cfg->k)

@@ -74,6 +74,8 @@ def test_gate_rank(T, d, E, k, cf):
 
 @pytest.mark.parametrize("d,f,E,k,act,special", [
     (64, 64, 4, 2, "gelu", ""), (128, 512, 64, 8, "gelu", ""), (576, 192, 24, 2, "swiglu", ""), (1088, 8192, 9, 2, "gelu", ""), (1024, 16384, 8, 2, "gelu", ""),
+    (4096, 2048, 8, 2, "gelu", ""), (4096, 3584, 8, 2, "swiglu", ""), (4160, 8128, 9, 2, "gelu", ""), (4608, 64, 16, 2, "swiglu", ""), (6208, 64, 4, 3, "gelu", ""),
+    (4096, 8192, 4, 2, "gelu", ""), (4096, 4096, 8, 2, "swiglu", ""),
     (2048, 8192, 64, 4, "swiglu", ""), (1024, 2048, 33, 8, "gelu", "nan"), (1024, 2048, 16, 4, "swiglu", "masked"), (1024, 2048, 16, 2, "gelu", "inf")])
 def test_one_token_layer(d, f, E, k, act, special):
     """The whole layer against routing and experts in two calls, which rank in a kernel of their own: the same bits."""
