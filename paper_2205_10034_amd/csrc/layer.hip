@@ -49,9 +49,13 @@ int32_t mark(moe_timer* timer, int i, hipStream_t s) {
 }
 
 // A one-token step: the gate's partial logits, then ranking and tables, inside a layer in the first product's kernel, in routing alone
-// in one of their own with the same bits.  The partial logits take the place of yd, which only the second product writes.
+// in one of their own with the same bits.  The partial logits lie in yd inside a layer, whose first product reads them while it writes
+// h, and in h in routing alone, which leaves yd as it is; as many slices as either holds, so that the sums are the same.
+size_t one_token_parts_room(const moe_config* cfg) {
+  return (size_t)max_rows(cfg) * (cfg->d_model < cfg->d_ff ? cfg->d_model : cfg->d_ff) * 2;
+}
 bool ranked_product_applies(const moe_config* cfg, const moe_weights* w) {
-  return expert_gemv_ranked_applies(cfg) && gate_parts_one_token(cfg, w->w_router, (size_t)max_rows(cfg) * cfg->d_model * 2) > 0;
+  return expert_gemv_ranked_applies(cfg) && gate_parts_one_token(cfg, w->w_router, one_token_parts_room(cfg)) > 0;
 }
 
 // gate -> dispatch bookkeeping (and, on the fp32 path, the dispatched copy, unless the first product makes it: rows = false)
@@ -64,9 +68,9 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   if ((st = mark(timer, 0, s)) != MOE_OK) return st;
   const bool gather = gemm1_can_gather(cfg);
   if (ranked_product_applies(cfg, w)) {
-    const size_t yd_bytes = (size_t)max_rows(cfg) * cfg->d_model * 2;
-    if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, (double*)sg.yd, yd_bytes, s)) != MOE_OK) return st;
-    if ((st = launch_rank_one_token(cfg, (const double*)sg.yd, gate_parts_one_token(cfg, w->w_router, yd_bytes), w->b_router, sg.topk_idx,
+    const size_t room = one_token_parts_room(cfg);
+    if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, (double*)sg.h, room, s)) != MOE_OK) return st;
+    if ((st = launch_rank_one_token(cfg, (const double*)sg.h, gate_parts_one_token(cfg, w->w_router, room), w->b_router, sg.topk_idx,
                                     sg.topk_w, sg.counts, sg.offsets, sg.a2r, sg.r2a, sg.tile_ctr, s)) != MOE_OK)
       return st;
     if ((st = mark(timer, 1, s)) != MOE_OK) return st;
@@ -104,14 +108,14 @@ int32_t route_and_first_product(const char* who, const moe_config* cfg, const mo
   Segments sg;
   int32_t st = open_workspace(who, cfg, w, x, ws, ws_bytes, &sg);
   if (st != MOE_OK) return st;
-  const size_t yd_bytes = (size_t)max_rows(cfg) * cfg->d_model * 2;
+  const size_t room = one_token_parts_room(cfg);
   const bool sw = cfg->act == MOE_ACT_SWIGLU;
   double* part = (double*)sg.yd;
   if ((st = mark(timer, 0, s)) != MOE_OK) return st;
-  if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, part, yd_bytes, s)) != MOE_OK) return st;
+  if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, part, room, s)) != MOE_OK) return st;
   if ((st = mark(timer, 1, s)) != MOE_OK) return st;
   if ((st = mark(timer, 2, s)) != MOE_OK) return st;
-  return launch_expert_gemv_ranked(cfg, x, part, gate_parts_one_token(cfg, w->w_router, yd_bytes), w->b_router, sw ? w->w_gate_proj : w->w1,
+  return launch_expert_gemv_ranked(cfg, x, part, gate_parts_one_token(cfg, w->w_router, room), w->b_router, sw ? w->w_gate_proj : w->w1,
                                    sw ? w->w_up : nullptr, sw ? nullptr : w->b1, sg.h, w->expert_elem_offset, sg.topk_idx, sg.topk_w,
                                    sg.counts, sg.offsets, sg.a2r, sg.r2a, sg.tile_ctr, s);
 }

@@ -137,3 +137,20 @@ def test_weights_are_those_of_the_gate_alone(T, d, E, k, renorm):
             read = reader(ws, cfg)
             assert np.array_equal(read("topk_idx", T * k).reshape(T, k), idx.cpu().numpy())
             assert np.array_equal(read("topk_w", T * k).reshape(T, k), w.view(torch.int32).cpu().numpy())
+
+
+@pytest.mark.parametrize("T,d,f,E,k", [(1, 2048, 8192, 64, 2), (1, 1024, 2048, 33, 8), (1, 512, 64, 16, 2), (1, 576, 192, 24, 2), (8, 2048, 2048, 64, 2), (96, 1024, 512, 8, 2)])
+def test_routing_leaves_the_experts_outputs(T, d, f, E, k):
+    """moe_layer_route may use h as scratch, and nothing else of what a pass before left in the workspace: yd stays as it is."""
+    print(T, d, f, E, k, flush=True)
+    cfg = M.MoEConfig(T=T, d_model=d, d_ff=f, E=E, k=k)
+    _, x, router, bias = problem(T, d, E)
+    one = torch.zeros(1, dtype=torch.bfloat16, device="cuda")
+    W = M.Weights({"w1": one, "w2": one, "w_router": router, "b_router": bias}, "output_major")
+    W.need = lambda c: None                                # (routing reads no expert)
+    ws = torch.empty(M.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda").fill_(0xAB)
+    M.moe_layer_route(cfg, W, x, ws)
+    torch.cuda.synchronize()
+    check_tables(reader(ws, cfg), cfg, x, router, bias)
+    lay = M.moe_workspace_layout(cfg)
+    assert (ws[lay["yd"]:lay["yd"] + k * T * d * 2] == 0xAB).all()
