@@ -1303,8 +1303,9 @@ extern "C" int32_t moe_gate(const moe_config* cfg, const void* x, const float* w
   return launch_gate(cfg, x, w_router, b_router, topk_idx, topk_w, probs, (hipStream_t)stream);
 }
 
-// Which kernel the gate of a layer takes, with or without a packed router (16-byte aligned weights): for the tests of the
-// rules above.  Host only; not part of the interface in moesys.h.
+// Which kernel moe_gate takes (packed: moe_gate_packed where it pays) for 16-byte aligned weights, and a layer that neither cuts the
+// contraction index into slices nor has one token (moe_test_layer_routing): for the tests of the rules above.  Host only; not part
+// of the interface in moesys.h.
 extern "C" const char* moe_test_gate_kernel(const moe_config* cfg, int32_t packed) {
   if (moe_config_check(cfg) != MOE_OK) return "";
   if (packed && gate_packed_applies(cfg, nullptr) && gate_packed_pays(cfg)) return "packed";

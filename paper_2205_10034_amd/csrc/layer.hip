@@ -48,6 +48,8 @@ int32_t mark(moe_timer* timer, int i, hipStream_t s) {
   return check_hip(hipEventRecord(timer->ev[i], s), "hipEventRecord");
 }
 
+size_t h_bytes(const moe_config* cfg) { return (size_t)max_rows(cfg) * cfg->d_ff * elem_size(cfg->dtype); }
+
 // A one-token step: the gate's partial logits, then ranking and tables, inside a layer in the first product's kernel, in routing alone
 // in one of their own with the same bits.  The partial logits lie in yd inside a layer, whose first product reads them while it writes
 // h, and in h in routing alone, which leaves yd as it is; as many slices as either holds, so that the sums are the same.
@@ -56,6 +58,16 @@ size_t one_token_parts_room(const moe_config* cfg) {
 }
 bool ranked_product_applies(const moe_config* cfg, const moe_weights* w) {
   return expert_gemv_ranked_applies(cfg) && gate_parts_one_token(cfg, w->w_router, one_token_parts_room(cfg)) > 0;
+}
+
+// Inside a layer or, alone, in moe_layer_route: a one-token step's partial logits, ranked by a kernel of their own or by the first
+// product; slices and one ranking workgroup; one kernel for gate and tables of a token; the gate's kernels and the dispatch's.
+enum Routing { ROUTE_RANK_ONE, ROUTE_RANKED_PRODUCT, ROUTE_SLICES, ROUTE_ONE_TOKEN, ROUTE_GATE };
+Routing pick_routing(const moe_config* cfg, const moe_weights* w, bool alone) {
+  if (ranked_product_applies(cfg, w)) return alone ? ROUTE_RANK_ONE : ROUTE_RANKED_PRODUCT;
+  if (!gemm1_can_gather(cfg)) return ROUTE_GATE;
+  if (gate_dispatch_slices_applies(cfg, w->w_router, h_bytes(cfg))) return ROUTE_SLICES;
+  return gate_dispatch_one_token_applies(cfg, w->w_router) ? ROUTE_ONE_TOKEN : ROUTE_GATE;
 }
 
 // gate -> dispatch bookkeeping (and, on the fp32 path, the dispatched copy, unless the first product makes it: rows = false)
@@ -67,7 +79,8 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   if (!w->w_router) return fail(MOE_ERR_INVALID_ARG, "%s: w_router is NULL", who);
   if ((st = mark(timer, 0, s)) != MOE_OK) return st;
   const bool gather = gemm1_can_gather(cfg);
-  if (ranked_product_applies(cfg, w)) {
+  const Routing how = pick_routing(cfg, w, true);
+  if (how == ROUTE_RANK_ONE) {
     const size_t room = one_token_parts_room(cfg);
     if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, (double*)sg.h, room, s)) != MOE_OK) return st;
     if ((st = launch_rank_one_token(cfg, (const double*)sg.h, gate_parts_one_token(cfg, w->w_router, room), w->b_router, sg.topk_idx,
@@ -78,15 +91,14 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   }
   // few tokens: the gate runs on many compute units and writes the dispatch tables as well (the partial logits go
   // where the first product will write)
-  const size_t h_bytes = (size_t)max_rows(cfg) * cfg->d_ff * elem_size(cfg->dtype);
-  if (gather && gate_dispatch_slices_applies(cfg, w->w_router, h_bytes)) {
+  if (how == ROUTE_SLICES) {
     if ((st = launch_gate_dispatch_slices(cfg, x, w->w_router, w->b_router, sg.topk_idx, sg.topk_w, sg.counts, sg.offsets, sg.a2r,
-                                          sg.r2a, sg.tile_ctr, sg.h, h_bytes, s)) != MOE_OK)
+                                          sg.r2a, sg.tile_ctr, sg.h, h_bytes(cfg), s)) != MOE_OK)
       return st;
     if ((st = mark(timer, 1, s)) != MOE_OK) return st;
     return mark(timer, 2, s);
   }
-  if (gather && gate_dispatch_one_token_applies(cfg, w->w_router)) {
+  if (how == ROUTE_ONE_TOKEN) {
     // a step of one token: the gate's kernel writes the dispatch tables as well
     if ((st = launch_gate_dispatch_one_token(cfg, x, w->w_router, w->b_router, sg.topk_idx, sg.topk_w, sg.counts, sg.offsets,
                                              sg.a2r, sg.r2a, sg.tile_ctr, s)) != MOE_OK)
@@ -174,7 +186,7 @@ int32_t layer_impl(const moe_config* cfg, const moe_weights* w, const void* x, c
   if ((st = check_weights(cfg, w)) != MOE_OK) return st;
   if (cfg->T > 0 && (!x || !out)) return fail(MOE_ERR_INVALID_ARG, "moe_layer_forward: x and out must be non-NULL");
   if (out == x && residual != x) return fail(MOE_ERR_INVALID_ARG, "moe_layer_forward: out aliases x");
-  if (w->w_router && ranked_product_applies(cfg, w)) {
+  if (w->w_router && pick_routing(cfg, w, false) == ROUTE_RANKED_PRODUCT) {
     if ((st = route_and_first_product("moe_layer_forward", cfg, w, x, ws, ws_bytes, s, timer)) != MOE_OK) return st;
     return experts_impl("moe_layer_forward", cfg, w, x, residual, out, ws, ws_bytes, s, timer, true);
   }
@@ -190,6 +202,8 @@ int32_t layer_impl(const moe_config* cfg, const moe_weights* w, const void* x, c
 using namespace moesys;
 
 extern "C" {
+
+const char* moe_test_gate_kernel(const moe_config* cfg, int32_t packed);
 
 int32_t moe_layer_forward(const moe_config* cfg, const moe_weights* w, const void* x, const void* residual,
                           void* out, void* ws, size_t ws_bytes, void* stream) {
@@ -246,6 +260,21 @@ int32_t moe_timer_read(moe_timer* t, float* stage_ms) {
     if (st != MOE_OK) return st;
   }
   return MOE_OK;
+}
+
+// How a layer (alone = 0) or moe_layer_route (alone = 1) gets its routing tables, with or without a packed router (16-byte aligned
+// weights): for the tests of the rules.  Host only; not part of the interface in moesys.h.
+const char* moe_test_layer_routing(const moe_config* cfg, int32_t packed, int32_t alone) {
+  if (moe_config_check(cfg) != MOE_OK) return "";
+  const moe_weights w = {};
+  switch (pick_routing(cfg, &w, alone != 0)) {
+    case ROUTE_RANK_ONE: return "parts + ranking";
+    case ROUTE_RANKED_PRODUCT: return "parts + ranking product";
+    case ROUTE_SLICES: return "slices";
+    case ROUTE_ONE_TOKEN: return "one token";
+    case ROUTE_GATE: break;
+  }
+  return moe_test_gate_kernel(cfg, packed);
 }
 
 }  // extern "C"

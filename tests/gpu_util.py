@@ -55,3 +55,10 @@ def rel_fro(a: np.ndarray, b: np.ndarray) -> float:
     num = np.linalg.norm(a - b)
     return float(num / den) if den > 0 else float(num)
 
+
+def routing(cfg, alone):
+    """How a layer (alone = 0) or moe_layer_route (alone = 1) gets its routing tables."""
+    f = M.lib().moe_test_layer_routing
+    f.restype, f.argtypes = C.c_char_p, [C.c_void_p, C.c_int32, C.c_int32]
+    c = cfg.c()
+    return f(C.byref(c), 0, alone).decode()

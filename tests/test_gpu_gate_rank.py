@@ -6,6 +6,8 @@ import torch
 
 import paper_2205_10034_amd as M
 
+from gpu_util import routing
+
 pytestmark = pytest.mark.gpu
 
 
@@ -61,6 +63,7 @@ def problem(T, d, E):
 def test_gate_rank(T, d, E, k, cf):
     print(T, d, E, k, cf, flush=True)
     cfg = M.MoEConfig(T=T, d_model=d, d_ff=2048, E=E, k=k, capacity_factor=cf, renormalize=bool(T & 1))
+    assert routing(cfg, 1) == ("split" if T == 257 or (T, d) == (97, 1472) or T * E > 8192 else "slices")
     _, x, router, bias = problem(T, d, E)
     one = torch.zeros(1, dtype=torch.bfloat16, device="cuda")
     W = M.Weights({"w1": one, "w2": one, "w_router": router, "b_router": bias}, "output_major")
@@ -81,6 +84,7 @@ def test_one_token_layer(d, f, E, k, act, special):
     """The whole layer against routing and experts in two calls, which rank in a kernel of their own: the same bits."""
     print(d, f, E, k, act, special, flush=True)
     cfg = M.MoEConfig(T=1, d_model=d, d_ff=f, E=E, k=k, act=act, renormalize=bool(E & 1))
+    assert (routing(cfg, 0), routing(cfg, 1)) == ("parts + ranking product", "parts + ranking")
     g, x, router, bias = problem(1, d, E)
     if special == "nan":
         x[0, 7] = float("nan")

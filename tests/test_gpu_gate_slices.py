@@ -1,11 +1,12 @@
-"""Routing of a few tokens through slices of a large router: routing and tables exact against float64 at every token count the
-slices serve and the first beyond, experts preferred by all tokens, capacities that drop, exact ties (lower expert first),
-widths that leave the last slice short."""
+"""Routing of a few tokens through slices of a large router: routing and tables exact against float64 at one to nine tokens,
+experts preferred by all tokens, capacities that drop, exact ties (lower expert first), widths that leave the last slice short."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2205_10034_amd as M
+
+from gpu_util import routing
 
 pytestmark = pytest.mark.gpu
 
@@ -14,6 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,k,cf", [(1, 1, 0.0), (1, 2, 0.0), (2, 8, 0.0), (3, 2, 0.5), (4, 2, 0.0), (5, 3, 0.0), (7, 2, 0.5), (8, 8, 0.0), (8, 1, 0.5), (9, 2, 0.0)])
 def test_gate_slices(d, E, T, k, cf):
     cfg = M.MoEConfig(T=T, d_model=d, d_ff=4096, E=E, k=k, capacity_factor=cf, renormalize=bool(T & 1))
+    assert routing(cfg, 1) == ("parts + ranking" if T == 1 and k > 1 else "slices")
     g = torch.Generator(device="cuda").manual_seed(d + E + T)
     x = torch.randn(T, d, generator=g, device="cuda").bfloat16()
     router = torch.randn(d, E, generator=g, device="cuda") * d ** -0.5
