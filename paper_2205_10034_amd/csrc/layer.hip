@@ -62,6 +62,10 @@ bool ranked_product_applies(const moe_config* cfg, const moe_weights* w) {
 
 // Inside a layer or, alone, in moe_layer_route: a one-token step's partial logits, ranked by a kernel of their own or by the first
 // product; slices and one ranking workgroup; one kernel for gate and tables of a token; the gate's kernels and the dispatch's.
+// Routing alone in two launches where one kernel (gate_few_kernel) could serve, for the layer's bits.  Measured on MI355X, routers of
+// 8 x 512 to 64 x 1920, one kernel / two (us): 6.5 to 9 / 3.1 + 2.4 on the card; a call and a wait for its tables, as an expert pool
+// makes it, 24.3 to 27.4 / 23.7 to 24.7, then the experts and a wait 63.7 / 60.1 (16 x 2048 x 2816); calls one after the other without a
+// look at the tables, which moe_layer_forward serves, are bound by the host's launches: 9.8 / 12.1 to 13.4.
 enum Routing { ROUTE_RANK_ONE, ROUTE_RANKED_PRODUCT, ROUTE_SLICES, ROUTE_ONE_TOKEN, ROUTE_GATE };
 Routing pick_routing(const moe_config* cfg, const moe_weights* w, bool alone) {
   if (ranked_product_applies(cfg, w)) return alone ? ROUTE_RANK_ONE : ROUTE_RANKED_PRODUCT;
