@@ -53,6 +53,17 @@ def measured_traffic(workload, stage):
     return None
 
 
+def hbm_stage_bytes(wl, R):
+    """Algorithmic bytes of the HBM-bound stages of a layer with R kept rows.  Dispatch has no bandwidth figure: the stage
+    only builds routing tables, the first product gathers the rows (float32: and stores the dispatched copy).  With one
+    expert per token the second product does the combine, and that stage is empty."""
+    s = 2 if wl.dtype == "bf16" else 4
+    b = {"gate": wl.T * wl.d_model * s + 8 * wl.k * wl.T}
+    if wl.k > 1:
+        b["combine"] = (R + wl.T) * wl.d_model * s + 8 * wl.k * wl.T
+    return b
+
+
 def cpu_baseline(wl, L):
     """The oracle as it stands (whole layer: gate, dispatch, FFN, combine) on the host cores, over the first
     tokens of the workload: as many as make about CPU_SAMPLE_FLOPS of expert products."""
@@ -163,13 +174,7 @@ def main():
     dom_flops = flops1 if dom == "gemm1" else flops2
     achieved = dom_flops / (stage_ms[dom] * 1e-3) / 1e12
     s = 2 if wl.dtype == "bf16" else 4
-    # algorithmic bytes of the HBM-bound stages (the dispatch stage of the bf16 path only builds routing tables
-    # - the rows are gathered by the first GEMM - so it is latency-bound and has no bandwidth figure)
-    hbm = {"gate": (wl.T * wl.d_model * s + 8 * wl.k * wl.T) / (stage_ms["gate"] * 1e-3) / 1e9}
-    if wl.dtype != "bf16":
-        hbm["dispatch"] = ((wl.T + R) * wl.d_model * s + 12 * wl.k * wl.T) / (stage_ms["dispatch"] * 1e-3) / 1e9
-    if not (wl.k == 1 and wl.dtype == "bf16"):  # (k = 1: the second GEMM's epilogue does the combine)
-        hbm["combine"] = ((R + wl.T) * wl.d_model * s + 8 * wl.k * wl.T) / (stage_ms["combine"] * 1e-3) / 1e9
+    hbm = {st: b / (stage_ms[st] * 1e-3) / 1e9 for st, b in hbm_stage_bytes(wl, R).items()}
     other = "gemm2" if dom == "gemm1" else "gemm1"
     other_flops = flops2 if dom == "gemm1" else flops1
     if wl.dtype == "bf16":
