@@ -51,13 +51,13 @@ int32_t mark(moe_timer* timer, int i, hipStream_t s) {
 size_t h_bytes(const moe_config* cfg) { return (size_t)max_rows(cfg) * cfg->d_ff * elem_size(cfg->dtype); }
 
 // A one-token step: the gate's partial logits, then ranking and tables, inside a layer in the first product's kernel, in routing alone
-// in one of their own with the same bits.  The partial logits lie in yd inside a layer, whose first product reads them while it writes
-// h, and in h in routing alone, which leaves yd as it is; as many slices as either holds, so that the sums are the same.
-size_t one_token_parts_room(const moe_config* cfg) {
-  return (size_t)max_rows(cfg) * (cfg->d_model < cfg->d_ff ? cfg->d_model : cfg->d_ff) * 2;
-}
-bool ranked_product_applies(const moe_config* cfg, const moe_weights* w) {
-  return expert_gemv_ranked_applies(cfg) && gate_parts_one_token(cfg, w->w_router, one_token_parts_room(cfg)) > 0;
+// in one of their own.  The partial logits lie in yd inside a layer, whose first product reads them while it writes h, and in h in
+// routing alone, which leaves yd as it is.  The same bits in both: the same sums in the same order, or, where h has room for fewer
+// slices than yd, float64 sums in another order (as many slices as either holds would cost the layer: 64 experts 4096 x 512, k 2 18.7
+// us with the sixteen of yd, 22.8 with the four of h).
+size_t yd_bytes(const moe_config* cfg) { return (size_t)max_rows(cfg) * cfg->d_model * elem_size(cfg->dtype); }
+int one_token_parts(const moe_config* cfg, const moe_weights* w, bool alone) {  // 0: not such a step, or no room
+  return expert_gemv_ranked_applies(cfg) ? gate_parts_one_token(cfg, w->w_router, alone ? h_bytes(cfg) : yd_bytes(cfg)) : 0;
 }
 
 // Inside a layer or, alone, in moe_layer_route: a one-token step's partial logits, ranked by a kernel of their own or by the first
@@ -68,7 +68,7 @@ bool ranked_product_applies(const moe_config* cfg, const moe_weights* w) {
 // look at the tables, which moe_layer_forward serves, are bound by the host's launches: 9.8 / 12.1 to 13.4.
 enum Routing { ROUTE_RANK_ONE, ROUTE_RANKED_PRODUCT, ROUTE_SLICES, ROUTE_ONE_TOKEN, ROUTE_GATE };
 Routing pick_routing(const moe_config* cfg, const moe_weights* w, bool alone) {
-  if (ranked_product_applies(cfg, w)) return alone ? ROUTE_RANK_ONE : ROUTE_RANKED_PRODUCT;
+  if (one_token_parts(cfg, w, true) > 0) return !alone && one_token_parts(cfg, w, false) > 0 ? ROUTE_RANKED_PRODUCT : ROUTE_RANK_ONE;
   if (!gemm1_can_gather(cfg)) return ROUTE_GATE;
   if (gate_dispatch_slices_applies(cfg, w->w_router, h_bytes(cfg))) return ROUTE_SLICES;
   return gate_dispatch_one_token_applies(cfg, w->w_router) ? ROUTE_ONE_TOKEN : ROUTE_GATE;
@@ -85,10 +85,9 @@ int32_t route_impl(const char* who, const moe_config* cfg, const moe_weights* w,
   const bool gather = gemm1_can_gather(cfg);
   const Routing how = pick_routing(cfg, w, true);
   if (how == ROUTE_RANK_ONE) {
-    const size_t room = one_token_parts_room(cfg);
-    if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, (double*)sg.h, room, s)) != MOE_OK) return st;
-    if ((st = launch_rank_one_token(cfg, (const double*)sg.h, gate_parts_one_token(cfg, w->w_router, room), w->b_router, sg.topk_idx,
-                                    sg.topk_w, sg.counts, sg.offsets, sg.a2r, sg.r2a, sg.tile_ctr, s)) != MOE_OK)
+    if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, (double*)sg.h, h_bytes(cfg), s)) != MOE_OK) return st;
+    if ((st = launch_rank_one_token(cfg, (const double*)sg.h, one_token_parts(cfg, w, true), w->b_router, sg.topk_idx, sg.topk_w,
+                                    sg.counts, sg.offsets, sg.a2r, sg.r2a, sg.tile_ctr, s)) != MOE_OK)
       return st;
     if ((st = mark(timer, 1, s)) != MOE_OK) return st;
     return mark(timer, 2, s);
@@ -124,14 +123,13 @@ int32_t route_and_first_product(const char* who, const moe_config* cfg, const mo
   Segments sg;
   int32_t st = open_workspace(who, cfg, w, x, ws, ws_bytes, &sg);
   if (st != MOE_OK) return st;
-  const size_t room = one_token_parts_room(cfg);
   const bool sw = cfg->act == MOE_ACT_SWIGLU;
   double* part = (double*)sg.yd;
   if ((st = mark(timer, 0, s)) != MOE_OK) return st;
-  if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, part, room, s)) != MOE_OK) return st;
+  if ((st = launch_gate_parts_one_token(cfg, x, w->w_router, part, yd_bytes(cfg), s)) != MOE_OK) return st;
   if ((st = mark(timer, 1, s)) != MOE_OK) return st;
   if ((st = mark(timer, 2, s)) != MOE_OK) return st;
-  return launch_expert_gemv_ranked(cfg, x, part, gate_parts_one_token(cfg, w->w_router, room), w->b_router, sw ? w->w_gate_proj : w->w1,
+  return launch_expert_gemv_ranked(cfg, x, part, one_token_parts(cfg, w, false), w->b_router, sw ? w->w_gate_proj : w->w1,
                                    sw ? w->w_up : nullptr, sw ? nullptr : w->b1, sg.h, w->expert_elem_offset, sg.topk_idx, sg.topk_w,
                                    sg.counts, sg.offsets, sg.a2r, sg.r2a, sg.tile_ctr, s);
 }

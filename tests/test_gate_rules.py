@@ -68,8 +68,8 @@ def test_routing_of_a_layer_needs_room_for_the_partial_logits():
 
 @pytest.mark.parametrize("d,E,k,f,layer,alone", [
     (2048, 64, 2, 8192, RANKED, RANK), (4096, 33, 8, 2048, RANKED, RANK), (2048, 65, 2, 8192, SLICES, SLICES), (1024, 24, 2, 2048, RANKED, RANK),
-    (64, 64, 2, 64, ONE, ONE), (64, 33, 2, 64, "split", "split"),
-    (64, 33, 2, 128, SLICES, SLICES)])  # (the last three: no room for a slice in yd, nor, but for the last, in h)
+    (64, 64, 2, 64, ONE, ONE), (64, 33, 2, 64, "split", "split"), (64, 33, 2, 128, RANK, RANK), (128, 33, 2, 64, "split", "split")])
+    # (the last four: no room for a slice in yd and h, in yd, in h)
 def test_routing_of_a_one_token_layer(d, E, k, f, layer, alone):
     assert layer_routing(1, d, E, k, f) == layer and layer_routing(1, d, E, k, f, alone=1) == alone
 
