@@ -158,9 +158,10 @@ int32_t moe_workspace_layout(const moe_config* cfg, moe_ws_layout* out);
  *                              weight-streaming kernels out
  *   MOE_TUNE_FEW_TOKEN_KERNELS 1 (default): steps of few tokens use the matrix-vector (at most 8
  *                              assignments; 16 where the weight-streaming kernels do not serve)
- *                              and weight-streaming expert kernels and the
- *                              one-workgroup-per-token gate (at most 16 tokens); 0: the general
- *                              kernels at every size
+ *                              and weight-streaming expert kernels, the one-workgroup-per-token
+ *                              gate (at most 16 tokens) and, inside a layer (MOE_BF16, at most 256
+ *                              tokens), the gate in slices that writes the routing tables as well;
+ *                              0: the general kernels at every size
  *   MOE_TUNE_GATE_TOKENS       tokens per workgroup of the gate on a packed router: 32, 64 or 128 (where
  *                              the expert count allows; otherwise the next smaller); 0 (default) = by T
  *   MOE_TUNE_GEMM_MFMA         matrix instruction of the 256-row grouped GEMM kernels: 16 (16x16x32) or 32
@@ -262,12 +263,15 @@ int32_t moe_combine(const moe_config* cfg, const void* yd, const int32_t* assign
  * device is never synchronised, so the call can be captured in a HIP graph.
  * x device [T,d_model]; residual device [T,d_model] or NULL; out device
  * [T,d_model] (may alias residual, must not alias x unless residual == x).
- * Fusions inside the call (MOE_BF16): the first GEMM gathers its rows from x
- * through row_to_assign, so no dispatched copy xd is made; with k == 1 the
- * second GEMM scales each row by its gate weight, adds the residual in fp32
- * and stores it at its token's place in `out` (one rounding; no yd, and the
- * combine stage only fills the rows of dropped tokens) -- the kernel fusion
- * the paper asks for in Section 3.3.1. */
+ * Fusions inside the call: the first GEMM gathers its rows from x through
+ * row_to_assign (MOE_BF16: no dispatched copy xd is made; MOE_F32: the same
+ * kernel stores xd on its way); with k == 1 the second GEMM scales each row by
+ * its gate weight, adds the residual in fp32 and stores it at its token's place
+ * in `out` (MOE_BF16: one rounding, no yd; MOE_F32: yd is stored as well), and
+ * what is left of the combine are the rows of dropped tokens; a step of one
+ * token with k >= 2 and E <= 64 (MOE_BF16) ranks in the first GEMM's kernel and
+ * combines in the second's -- the kernel fusion the paper asks for in Section
+ * 3.3.1. */
 int32_t moe_layer_forward(const moe_config* cfg, const moe_weights* w, const void* x,
                           const void* residual, void* out, void* ws, size_t ws_bytes, void* stream);
 
@@ -279,7 +283,7 @@ int32_t moe_layer_forward(const moe_config* cfg, const moe_weights* w, const voi
  * from what moe_layer_route left in the same workspace.  Same arguments,
  * workspace and rules as moe_layer_forward; calling one after the other is
  * moe_layer_forward.  moe_layer_route may use the h segment as scratch (the
- * next moe_layer_experts writes it).  moe_layer_experts leaves the routing tables as it found
+ * next moe_layer_experts writes it); yd stays as it was.  moe_layer_experts leaves the routing tables as it found
  * them, so it may run again on the same workspace (e.g. with other expert
  * weights, or after a failed load) without a new moe_layer_route. */
 int32_t moe_layer_route(const moe_config* cfg, const moe_weights* w, const void* x, void* ws,
@@ -290,7 +294,12 @@ int32_t moe_layer_experts(const moe_config* cfg, const moe_weights* w, const voi
 /* Same as moe_layer_forward, additionally recording HIP events on `stream`
  * around every kernel so that a bench can attribute time per stage.  `timer`
  * comes from moe_timer_create.  Adds event-record overhead; not the call to
- * time end to end. */
+ * time end to end.  A stage's time is that of its kernels, and fused work counts
+ * where it runs: routing tables written by the gate's kernels (steps of few
+ * tokens) under MOE_STAGE_GATE, with MOE_STAGE_DISPATCH empty; a one-token step
+ * that ranks in its first product has softmax, top-k and tables under
+ * MOE_STAGE_GEMM1, and its combine under MOE_STAGE_GEMM2; the dispatched copy of
+ * MOE_F32 under MOE_STAGE_GEMM1; with k == 1 the combine under MOE_STAGE_GEMM2. */
 typedef struct moe_timer moe_timer;
 enum { MOE_STAGE_GATE = 0, MOE_STAGE_DISPATCH = 1, MOE_STAGE_GEMM1 = 2, MOE_STAGE_GEMM2 = 3,
        MOE_STAGE_COMBINE = 4, MOE_STAGE_COUNT = 5 };

@@ -9,9 +9,10 @@
 // k+1 leading logits have two neighbours closer than GATE_MARGIN_REL times its largest |logit| is recomputed by the whole workgroup
 // with float64 accumulation of the (exact) products and ranked on those values.
 //
-// Exact path (float32 activations, E > 64, or many tokens on more than 16 experts by gate_f64_pays): the products of two float32 / bfloat16 values are exact in float64, and
+// Exact path (float32 activations, E > 64, many tokens on more than 16 experts by gate_f64_pays, and inside a layer steps of up to
+// 256 tokens, in slices of the contraction index): the products of two float32 / bfloat16 values are exact in float64, and
 // v_mfma_f64_16x16x4_f64 accumulates them there, so only the summation rounds, at 2^-53 relative, and nothing has to be
-// recomputed; see gate_f64_kernel.
+// recomputed; see gate_f64_kernel and gate_rank_kernel.
 #include "gate_rank.h"
 #include "moesys_internal.h"
 #include "routing_tables.h"
