@@ -361,12 +361,15 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    29 %, where a hot expert's tiles open a further round.
 //  - since the K loop's passes have 24 steps, measured over 842 random whole layers of 25 to 176 rows, both products of each on every
 //    shape in turn (gain of the layer): 25 to 96 rows that no line above serves, 256x128 instead of the grouped GEMM 1.10 over 300
-//    products, three of them not faster, by at most 1.6 %; one round of 256x128 where 128x128 makes more than one round 1.06 over 54,
-//    none slower (beyond 4608 values 1.02 to 1.04, and a tenth slower where Zipf routing leaves a few experts most rows); 97 to 160
-//    rows, 256x192 from 704 values on and for one round with an activation 1.07 over 87, none slower.  GELU products keep the lines
+//    products, three of them not faster, by at most 1.6 %; 97 to 160 rows, 256x192 from 704 values on and for one round with an activation 1.07 over 87, none slower.  GELU products keep the lines
 //    that they had for short or few-round tiles (K below 1088, at most 192 tiles), where its end weighs.  150 other layers: 1.043,
 //    under Zipf routing 1.036, of 50 two slower by 5 and 13 %.  64 SwiGLU experts 1280 x 1088, 82 rows: 201 / 173; 96 experts 2304
 //    x 1344, 92 rows 408 / 360; 128 of 1600 x 832, 141 rows 356 / 345.
+//  - up to 96 rows, long rows of weights: one round of 256x128 where 128x128 makes more than one (layers, 128x128 / 256x128, products
+//    of any width and length): even routing 1.085 over 840, one more than 2 % slower; Zipf(1.2) 1.047 over 656.  Where 128x128 is one
+//    round too, 0.90 over 3332 (12 SwiGLU experts 3584 -> 1344, 83 rows, 132 tiles against 252: 92 / 110).  Under Zipf a hot expert's
+//    further row tiles open a second round: 129 to 176 tiles 1.05 (27 of 488 more than 2 % slower), more of up to 12 experts 1.03, more
+//    of 16 to 96 experts 1.00 (256 of 728; 24 experts 4608 -> 1088, 55 rows, 216 tiles: 202 / 239), though 1.06 under even routing.
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128, STREAM_256x192 };
 int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   const bool swiglu = epi == ST_SWIGLU, activation = epi == ST_GELU || swiglu;
@@ -400,8 +403,8 @@ int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   if (tiles(128, 192) < 128 && tiles(64, 64) <= 512) return STREAM_64x64;
   const bool long_rows = K >= 4096 || big < 256;
   if (rows <= 96 && fill(128) >= (long_rows ? 0.95 : 0.85) && (one_round(256, 128) || K >= (swiglu ? 768 : 832))) return STREAM_256x128;
-  // (one round of the wider tiles where 128 weight rows make more than one)
-  const bool one_of_256 = N >= (swiglu ? 768 : epi == ST_GELU ? 2048 : 256) && K <= 4608 && tiles(256, 128) > 128 && one_round(256, 128);
+  // (one round of the wider tiles where 128 weight rows make more than one; more experts: with room for a hot one's further row tiles)
+  const bool one_of_256 = N >= (swiglu ? 128 : 256) && !one_round(128, 128) && tiles(256, 128) <= (cfg->E < 16 ? 256 : 176);
   if (wide && rows <= 96 && long_rows && (one_round(128, 128) || K >= 2048)) return one_of_256 ? STREAM_256x128 : STREAM_128x128;
   if (wide && (big <= 96 || (big <= 128 && rows <= 152)) && tiles(128, 192) <= (K >= 4096 ? 512 : 256)) return STREAM_128x192;
   // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)

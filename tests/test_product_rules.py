@@ -113,6 +113,20 @@ def test_products_of_97_to_160_rows_that_stay_with_the_grouped_kernel():
         assert kernel(rows, E, N, K, k, cf) == "stream 256x192", (rows, E, N, K, k, cf)
 
 
+def test_one_round_of_256_weight_rows():
+    """Up to 96 rows, long rows of weights: 256 x 128 only where 128 x 128 makes more than one round (with 16 experts and more only with
+    room for a hot expert's further row tiles).  Shapes on both sides, either product."""
+    for rows, E, N, K, act, want in ((43, 12, 1344, 3584, "swiglu", "128x128"), (86, 12, 1344, 4032, "swiglu", "128x128"), (82, 12, 2624, 1216, "gelu", "128x128"),  # 252 tiles
+                                     (90, 12, 1472, 3584, "swiglu", "256x128"), (82, 12, 2752, 2048, "gelu", "256x128"),
+                                     (60, 16, 2816, 2304, "gelu", "256x128"), (60, 16, 2880, 2304, "gelu", "128x128"),   # 176 and 192 tiles of 256
+                                     (60, 8, 8192, 2304, "gelu", "256x128"), (72, 24, 1088, 4416, "swiglu", "128x128"),
+                                     (60, 176, 192, 4096, "gelu", "128x128")):                                          # fewer features than a tile
+        assert product_kernel(M.MoEConfig(T=rows * E // 2, d_model=K, d_ff=N, E=E, k=2, act=act), 0) == "stream " + want, (rows, E, N, K, act)
+    for rows, E, N, K, k, want in ((96, 12, 2688, 2624, 1, "128x128"), (54, 48, 576, 4288, 1, "128x128"), (78, 12, 2688, 2560, 2, "128x128"),
+                                   (66, 48, 576, 3776, 2, "128x128"), (60, 24, 1536, 2304, 2, "256x128"), (54, 12, 2752, 3584, 1, "256x128")):
+        assert product_kernel(M.MoEConfig(T=rows * E // k, d_model=N, d_ff=K, E=E, k=k), 1) == "stream " + want, (rows, E, N, K, k)
+
+
 def f32_rows(rows, E, N, K, cf=0.0, act="gelu", layout="output_major", second=1):
     """Tile rows of a float32 product [rows E, K] -> N."""
     f = M.lib().moe_test_f32_tile_rows
