@@ -365,6 +365,11 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    that they had for short or few-round tiles (K below 1088, at most 192 tiles), where its end weighs.  150 other layers: 1.043,
 //    under Zipf routing 1.036, of 50 two slower by 5 and 13 %.  64 SwiGLU experts 1280 x 1088, 82 rows: 201 / 173; 96 experts 2304
 //    x 1344, 92 rows 408 / 360; 128 of 1600 x 832, 141 rows 356 / 345.
+//  - 37 to 96 rows otherwise: 256x128 instead of the grouped GEMM, by what the tile's end costs.  Layers under even / Zipf(1.2)
+//    routing, in brackets how many are more than 2 % slower: SwiGLU from 768 values 1.130 over 841 (0) / 1.135 over 553 (43); plain from
+//    512 1.077 over 1518 (4) / 1.096 over 945 (41); combine, whose end waits for row numbers, gate weights and residual rows, from
+//    832 1.075 over 439 (2) / 1.092 over 266 (18), but 512 to 831 1.012 over 290 (30) / 1.004 over 214 (63; 64 experts 640 -> 832, 77
+//    rows, even 96 / 107).  Up to a quarter below its line each has 1.02 to 1.06 and 2 to 4 % of its layers slower, under Zipf up to 18 %.
 //  - up to 96 rows, long rows of weights: one round of 256x128 where 128x128 makes more than one (layers, 128x128 / 256x128, products
 //    of any width and length): even routing 1.085 over 840, one more than 2 % slower; Zipf(1.2) 1.047 over 656.  Where 128x128 is one
 //    round too, 0.90 over 3332 (12 SwiGLU experts 3584 -> 1344, 83 rows, 132 tiles against 252: 92 / 110).  Under Zipf a hot expert's
@@ -410,7 +415,8 @@ int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)
   if (wide && rows > 192 && big > 128 && big <= 192 && tiles_of(128, 128, rows + (rows * 2 + 24) / 25) <= 512) return STREAM_128x128;
   if (N < (swiglu ? 128 : 256)) return STREAM_NONE;
-  if (rows <= 96 && (epi == ST_GELU ? K >= 1088 || (K >= 640 && fill(128) >= 0.83) : K >= (swiglu ? 768 : 512))) return STREAM_256x128;
+  const int shortest = swiglu ? 768 : epi == ST_COMBINE ? 832 : 512;
+  if (rows <= 96 && (epi == ST_GELU ? K >= 1088 || (K >= 640 && fill(128) >= 0.83) : K >= shortest)) return STREAM_256x128;
   if (rows > 96 && rows <= 160) {
     const int64_t t = tiles(256, 192), rounds = (t + 255) / 256;
     if (rows > 134 && C > 192 && 100 * t > 97 * 256 * rounds) return STREAM_NONE;

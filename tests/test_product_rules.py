@@ -127,6 +127,14 @@ def test_one_round_of_256_weight_rows():
         assert product_kernel(M.MoEConfig(T=rows * E // k, d_model=N, d_ff=K, E=E, k=k), 1) == "stream " + want, (rows, E, N, K, k)
 
 
+def test_short_rows_of_weights_on_256_weight_rows():
+    """Up to 96 rows, several rounds of tiles: the line of each end, lowest for the plain one, highest for the combine."""
+    second = lambda rows, E, N, K, k: product_kernel(M.MoEConfig(T=rows * E // k, d_model=N, d_ff=K, E=E, k=k), 1)
+    for rows, E, N, K, k, want in ((64, 64, 2048, 512, 2, "stream 256x128"), (64, 64, 2048, 448, 2, "grouped 256"), (64, 64, 2048, 512, 1, "grouped 256"),
+                                   (64, 64, 2048, 768, 1, "grouped 256"), (70, 32, 2176, 768, 1, "grouped 256"), (64, 64, 2048, 832, 1, "stream 256x128")):
+        assert second(rows, E, N, K, k) == want, (rows, E, N, K, k)
+
+
 def f32_rows(rows, E, N, K, cf=0.0, act="gelu", layout="output_major", second=1):
     """Tile rows of a float32 product [rows E, K] -> N."""
     f = M.lib().moe_test_f32_tile_rows
