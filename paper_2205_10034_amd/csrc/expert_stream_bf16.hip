@@ -339,42 +339,41 @@ int32_t launch_shape(const moe_config* cfg, const uint16_t* act, const uint16_t*
 //    768 0.9 (0.74), from 832 1.0 to 1.1 where the big tiles leave a fifth of their rounds empty, where they do not 0.86 to
 //    1.07 up to 1024 and 1.05 and more above; 256x128 up to 704 0.97 to 1.02 (0.86), above 1.04 to 1.14; 128x128 below 2048 1.02
 //    (0.90).
-// Skewed routing costs row tiles that the rule does not see.  Over the same shapes under Zipf(1.2) masses the mean gain is
-// within a tenth of that under even routing, but 128x192 loses 7 to 14 % where the hot expert's extra tiles open a second
-// round (16 experts, f 1600 -> d 1792, 115 rows: even 33 / 22, Zipf 35 / 40), and 64x32 up to 20 % with every row of a
-// step on one expert of 64.  Of 1300 whole expert blocks under even or random routing none was more than 3 % slower than on
-// the grouped GEMM, of 1300 under Zipf or half-on-one-expert routing 16 were, by up to 9 % (before the shape that follows).
-//  - 97 to 160 rows otherwise: 256x192, three stages of weights and two of rows in the LDS; the grouped GEMM has one stage of
-//    weights on its way and waits for it.  Over 126 random products of 97 to 180 rows 1.12 on average (grouped / here): 64
-//    experts, 131 rows, f 3456 -> d 3264 366 / 314; 16 SwiGLU, 112 rows, 3008 -> 8704 467 / 398; 64 SwiGLU, 128 rows, 2048 -> 4096
-//    523 / 466 and 283 / 210; few tiles 1.2 to 1.3.  Not beyond 160 rows, where experts need a second tile (32 experts, 169
-//    rows, 5248 -> 3904 326 / 350), nor for short rows, where the start and end of these tiles weigh: below 1152 values (128, 132
-//    rows, 896 -> 3840 299 / 352), from 137 rows below 1408 (128, 148 rows, 832 -> 1920 151 / 204; 45 products 0.97 on average),
-//    products with an activation in their end below 1152 (32, 113 rows, 896 -> 9152 148 / 154) and in more than six rounds
-//    below 2240 (64, 128 rows, 2048 -> 8192 469 / 479).  Those of at most a round stay with the grouped GEMM too, where the
-//    line below 128x192 has them; they would gain 1.05 to 1.2.  Nor where an expert is likely to need a second tile (from 135 rows
-//    on: random routing spreads rows by a tenth to an eighth) and the tiles leave no room for it in their last round (64 experts, 142
-//    rows, 2752 -> 896 94 / 128; 238 products 1.03, a fifth of them slower), nor for combines below 2560 values, whose ends
-//    wait for row numbers, gate weights and residual rows in turn (32 experts, 134 rows, 1984 -> 4032 142 / 156; 161 products 1.00).
-//    (Before passes of 24 steps; what they moved follows.)  Of 3266 random products of 97 to 160 rows in whole layers, three sets of weights in turn, the 2867 that remain gain 1.14, six of
-//    them lose more than 3 %, by up to 6 %; 290 with a capacity 1.14, three; 278 under Zipf routing without one 1.14, but 31, by up to
-//    29 %, where a hot expert's tiles open a further round.
-//  - since the K loop's passes have 24 steps, measured over 842 random whole layers of 25 to 176 rows, both products of each on every
-//    shape in turn (gain of the layer): 25 to 96 rows that no line above serves, 256x128 instead of the grouped GEMM 1.10 over 300
-//    products, three of them not faster, by at most 1.6 %; 97 to 160 rows, 256x192 from 704 values on and for one round with an activation 1.07 over 87, none slower.  GELU products keep the lines
-//    that they had for short or few-round tiles (K below 1088, at most 192 tiles), where its end weighs.  150 other layers: 1.043,
-//    under Zipf routing 1.036, of 50 two slower by 5 and 13 %.  64 SwiGLU experts 1280 x 1088, 82 rows: 201 / 173; 96 experts 2304
-//    x 1344, 92 rows 408 / 360; 128 of 1600 x 832, 141 rows 356 / 345.
 //  - 37 to 96 rows otherwise: 256x128 instead of the grouped GEMM, by what the tile's end costs.  Layers under even / Zipf(1.2)
 //    routing, in brackets how many are more than 2 % slower: SwiGLU from 768 values 1.130 over 841 (0) / 1.135 over 553 (43); plain from
 //    512 1.077 over 1518 (4) / 1.096 over 945 (41); combine, whose end waits for row numbers, gate weights and residual rows, from
 //    832 1.075 over 439 (2) / 1.092 over 266 (18), but 512 to 831 1.012 over 290 (30) / 1.004 over 214 (63; 64 experts 640 -> 832, 77
 //    rows, even 96 / 107).  Up to a quarter below its line each has 1.02 to 1.06 and 2 to 4 % of its layers slower, under Zipf up to 18 %.
-//  - up to 96 rows, long rows of weights: one round of 256x128 where 128x128 makes more than one (layers, 128x128 / 256x128, products
-//    of any width and length): even routing 1.085 over 840, one more than 2 % slower; Zipf(1.2) 1.047 over 656.  Where 128x128 is one
-//    round too, 0.90 over 3332 (12 SwiGLU experts 3584 -> 1344, 83 rows, 132 tiles against 252: 92 / 110).  Under Zipf a hot expert's
-//    further row tiles open a second round: 129 to 176 tiles 1.05 (27 of 488 more than 2 % slower), more of up to 12 experts 1.03, more
-//    of 16 to 96 experts 1.00 (256 of 728; 24 experts 4608 -> 1088, 55 rows, 216 tiles: 202 / 239), though 1.06 under even routing.
+//    GELU ends do not wait longer than plain ones: from 640 values on 1.108 over 1001 (1) / 1.126 over 519 (30).  The rule takes fewer,
+//    1.113 over 512 (1) / 1.136 over 314 (18): below 1088 values only where the last round is nearly full; the rest (489 products 1.10,
+//    none slower) stays on the lines of the time when the table was built behind the K loop.
+//  - up to 96 rows, long rows of weights: one round of 256x128 where 128x128 makes more than one (128x128 / 256x128): even routing
+//    1.075 over 377 (0), Zipf(1.2) 1.037 over 329 (29).  Where 128x128 is one round too, 0.90 over 3332 (12 SwiGLU experts 3584 -> 1344, 83
+//    rows, 132 tiles against 252: 92 / 110).  Under Zipf a hot expert's further row tiles open a second round: of the products of any
+//    width 129 to 176 tiles 1.05 over 488 (27), more of up to 12 experts 1.03 over 168 (44), more of 16 to 96 experts 1.00 over 728 (256;
+//    24 experts 4608 -> 1088, 55 rows, 216 tiles: 202 / 239), though 1.06 under even routing.  Narrower products with an activation
+//    and lengths beyond 4608 gain as much (1.080 over 384 (0) / 1.036 over 270 (24)) and stay on 128x128 all the same: the rule keeps
+//    to what it had.
+//  - 97 to 160 rows otherwise: 256x192, three stages of weights and two of rows in the LDS; the grouped GEMM has one stage of
+//    weights on its way and waits for it.  Over 126 random products of 97 to 180 rows 1.12 on average (grouped / here): 64
+//    experts, 131 rows, f 3456 -> d 3264 366 / 314; 16 SwiGLU, 112 rows, 3008 -> 8704 467 / 398; 64 SwiGLU, 128 rows, 2048 -> 4096
+//    523 / 466 and 283 / 210; few tiles 1.2 to 1.3.  Layers under even / Zipf(1.2) routing, as above: GELU 1.071 over 493 (5) / 1.062
+//    over 216 (20), SwiGLU 1.072 over 749 (3) / 1.092 over 396 (39), plain 1.060 over 833 (9) / 1.072 over 381 (31), combine 1.068 over
+//    129 (4) / 1.096 over 52 (4).  Not beyond 160 rows, where experts need a second tile (32 experts, 169 rows, 5248 -> 3904 326 /
+//    350).  Not for rows of weights below 704 values, where the start and end of these tiles weigh: 512 to 703 SwiGLU 1.013 over 306 (60) /
+//    0.975, plain 1.031 over 143 (3) / 1.009 over 77 (15), GELU 1.041 over 287 (5) / 0.992 over 52 (21).  More than six rounds
+//    with an activation: from 2240 on, as the grouped GEMM's persistent workgroups hide ends (SwiGLU 704 to 2239 0.987 over 52).
+//    Combines from 2560 on (1152 to 2559 1.020 over 173 (7) / 1.014 over 66 (16); 32 experts, 134 rows, 1984 -> 4032 142 / 156).  GELU products
+//    of at most 192 tiles stay with the grouped GEMM on an older line; they would gain 1.07 (204 from 704 values on, none slower).
+//    Nor where an expert is likely to need a second tile (from 135 rows on: random routing spreads rows by a tenth to an eighth) and
+//    the tiles leave no room for it in their last round (64 experts, 142 rows, 2752 -> 896 94 / 128).
+//  Whole layers above: 20900 random ones of 25 to 176 rows, both products on every shape in turn, two to four sets of weights in turn.
+// Skewed routing costs row tiles that the rule does not see.  Over the same shapes under Zipf(1.2) masses the mean gain is
+// within a tenth of that under even routing, but 128x192 loses 7 to 14 % where the hot expert's extra tiles open a second
+// round (16 experts, f 1600 -> d 1792, 115 rows: even 33 / 22, Zipf 35 / 40), and 64x32 up to 20 % with every row of a
+// step on one expert of 64.  Of 1300 whole expert blocks under even or random routing none was more than 3 % slower than on
+// the grouped GEMM, of 1300 under Zipf or half-on-one-expert routing 16 were, by up to 9 % (before the shapes of 256 weight rows;
+// theirs stand with them).
 enum { STREAM_NONE, STREAM_64x32, STREAM_64x64, STREAM_128x64, STREAM_128x128, STREAM_128x192, STREAM_256x64, STREAM_256x128, STREAM_256x192 };
 int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   const bool swiglu = epi == ST_SWIGLU, activation = epi == ST_GELU || swiglu;
@@ -409,7 +408,8 @@ int pick_stream(const moe_config* cfg, int N, int K, int epi) {
   const bool long_rows = K >= 4096 || big < 256;
   if (rows <= 96 && fill(128) >= (long_rows ? 0.95 : 0.85) && (one_round(256, 128) || K >= (swiglu ? 768 : 832))) return STREAM_256x128;
   // (one round of the wider tiles where 128 weight rows make more than one; more experts: with room for a hot one's further row tiles)
-  const bool one_of_256 = N >= (swiglu ? 128 : 256) && !one_round(128, 128) && tiles(256, 128) <= (cfg->E < 16 ? 256 : 176);
+  const bool one_of_256 = N >= (swiglu ? 768 : epi == ST_GELU ? 2048 : 256) && K <= 4608 && !one_round(128, 128) &&
+                          tiles(256, 128) <= (cfg->E < 16 ? 256 : 176);
   if (wide && rows <= 96 && long_rows && (one_round(128, 128) || K >= 2048)) return one_of_256 ? STREAM_256x128 : STREAM_128x128;
   if (wide && (big <= 96 || (big <= 128 && rows <= 152)) && tiles(128, 192) <= (K >= 4096 ? 512 : 256)) return STREAM_128x192;
   // (8 % head-room for uneven routing, like the grouped GEMM's choice: a row tile more would be a round more)
