@@ -7,7 +7,7 @@
 // have one 64 KB stage in flight per CU, half of it rows that are not there, and their number is too small for the chip
 // when the feature count is: 8 experts x 4096 features are 128 tiles for 256 CUs.  Here a workgroup owns 64 to 256 weight
 // rows and 32 to 192 rows of one expert and requests the stages of all but one of its three to five LDS buffers (64 values of the
-// contraction index each) ahead, though the queue drains once per 8 to 24 steps (see the K loop): weights and
+// contraction index each) ahead, though the queue drains once per 24 steps (see the K loop): weights and
 // rows go from global memory straight into LDS, swizzled like the grouped GEMM's, one barrier per stage.  A wavefront multiplies blocks of 16 weight rows by blocks of 16 rows
 // (v_mfma_f32_16x16x32_bf16, weights as the first operand: a lane ends up with four consecutive features of one row).
 // SwiGLU: half of the weight rows are the gate's and half the up projection's; a block of 16 is eight and eight of the
@@ -216,8 +216,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     issue_w(policy, kt + STAGES - 1, w_of(std::integral_constant<int, I + STAGES - 1>{}));
     compute(w_of(i), a_of(i));
   };
-  constexpr int CYCLE = ROW_STAGES == STAGES ? STAGES : STAGES * ROW_STAGES;  // (3 and 2 stages: 6 steps)
-  constexpr int PASS = (EPI == ST_SWIGLU && S::WROWS == 64 && TM == 32 ? 8 : 24) / CYCLE * CYCLE;
+  constexpr int CYCLE = ROW_STAGES == STAGES ? STAGES : STAGES * ROW_STAGES, PASS = 24 / CYCLE * CYCLE;  // (3 and 2 stages: 6 steps)
   auto contract = [&](auto policy) {
     if constexpr (ROW_STAGES == STAGES) issue_a(0, a0);
     issue_w(policy, 0, w0);
@@ -229,13 +228,9 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
     if constexpr (OWN_TABLE) fill_phi_table(reinterpret_cast<phi_f32x2*>(table));  // (the steps' barriers are between it and its readers)
     // On every way round the loop all stages were requested, and inside a pass the compiler adds no wait of its own.  At the head
     // of the loop, where the passes and the prologue meet, it does: the first step of every pass waits for all loads (vmcnt(0)
-    // behind the barrier), whichever stages they belong to.  So a pass is as many steps as come to about 24, but for one shape.
+    // behind the barrier), whichever stages they belong to.  So a pass is as many steps as come to about 24.
     // MI355X, whole layers against passes of three to six steps (us): 32 SwiGLU experts 4096 x 2048, 1500 tokens 396 / 373; 8 of
     // 2176 x 2048, 138 tokens, k 4 75.7 / 71.0; 64 of 2048 x 8192, 8 tokens 173 / 170, 4096 tokens: the second product 440 / 427.
-    // SwiGLU on 64x32 has 8: three workgroups per CU already hide most drains, and where rows of weights are 8 KB apart (4096 values)
-    // workgroups that never drain stay in step on the same memory channels.  Whole layers (218 of 4 to 128 experts, 6 and 20 rows; passes
-    // of 4, 8, 12, 16 and 32 steps against 24): 4096 values 0.960, 0.969, 0.990, 0.992 and 1.001 of the time, the ten other
-    // lengths from 512 to 8192 1.008 to 1.034, 1.002 to 1.012, 1.000 to 1.010, 0.997 to 1.005 and 0.999 to 1.003.
     int kt = 0;
     auto pass = [&](auto... i) __attribute__((always_inline)) { return ((step(policy, i, kt), ++kt < KT) && ...); };
     while (unrolled<PASS>(pass)) {}
