@@ -94,7 +94,14 @@ __global__ __launch_bounds__(S::WAVES * 64) void expert_stream_kernel(
   if (clear_ctr && blockIdx.x == 0 && threadIdx.x < 8) clear_ctr[threadIdx.x] = 0;  // (a grouped GEMM may run next)
   RowTile t;
   const int kept = EPI == ST_COMBINE ? offsets[E] : 0;
-  const bool have = find_row_tile<TM>(offsets, E, n_tiles, t);
+  // SwiGLU on 64x32, the XCDs' eighths a multiple of 16 MB apart (as the two matrices then are as well): in step they meet on the same memory
+  // channels, the more so the longer they run without a drain (8 experts 4096 x 14336, 12 and 24 rows: 485 us a layer, with passes of four steps
+  // 462).  MI355X, whole layers of 1 to 24 rows against eighths that all start in front: 4096 values 1.048 over 55, up to 1.152 (16 experts
+  // x 2048: 166 / 191), 2048 1.018 over 54, 12288 1.037 over 10, 1024, 5120, 6144 and 8192 1.000 to 1.010.  Where the eighths lie otherwise the
+  // shift loses as often (a multiple of 4 MB, 4096 values 0.972 over 40), and GELU, the second product and the larger shapes measured 0.99 to
+  // 1.01 with it.  7, 13, 21 and 29 tiles are within 1 %, but 21 at 12288 values 0.97.
+  constexpr int SHIFT = EPI == ST_SWIGLU && TM == 32 ? 13 : 0;
+  const bool have = find_row_tile<TM, 0, SHIFT>(offsets, E, n_tiles, t, (uint32_t)(OUTF * K * 2));
   if constexpr (EPI == ST_COMBINE) fill_rowless_tokens<ST_WAVES>(a2r, kept, T, N, residual, out);
   if (!have) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

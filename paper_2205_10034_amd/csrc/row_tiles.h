@@ -19,8 +19,10 @@ struct RowTile { int expert, row0, rows, nt, tiles; };  // first dispatched row,
 // tile, row tiles innermost, and every XCD (workgroup b runs on XCD b mod 8) takes one contiguous eighth: the row tiles
 // that share a weight tile, and the feature tiles that share the rows, meet in one L2.  Every wavefront finds its tile
 // by itself (lane l looks at the experts 4l .. 4l+3), so no barrier is spent on it.  An expert has the fewest tiles of at most TM rows.
-template <int TM, int UNIT = 0>
-__device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ offsets, int E, int n_tiles, RowTile& t) {
+// SHIFT: where the eighths' weights (weight_bytes a tile) lie a multiple of 16 MB apart, XCD x starts its eighth SHIFT x tiles further on and
+// comes round, so that the XCDs do not meet on the same memory channels.
+template <int TM, int UNIT = 0, int SHIFT = 0>
+__device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ offsets, int E, int n_tiles, RowTile& t, uint32_t weight_bytes = 0) {
   const int lane = threadIdx.x & 63;
   static_assert(MOE_MAX_EXPERTS == 256, "four experts per lane");
   int cnt[4], sum = 0;
@@ -37,8 +39,12 @@ __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ offset
   }
   // (the first E / 4 + 1 lanes have met; the later ones hold no expert)
   const int total = __builtin_amdgcn_readlane(incl, min((E + 3) / 4, 64) - 1) * n_tiles;
-  const int chunk = (total + 7) / 8, i = blockIdx.x / 8, id = (int)(blockIdx.x % 8) * chunk + i;
-  if (i >= chunk || id >= total) return false;
+  const int chunk = (total + 7) / 8, i = blockIdx.x / 8, xcd = blockIdx.x % 8;
+  if (i >= chunk) return false;
+  int at = i;
+  if (SHIFT && (uint32_t)chunk * weight_bytes % (16u << 20) == 0) at = (i + SHIFT * xcd) % chunk;
+  const int id = xcd * chunk + at;
+  if (id >= total) return false;
   int p = incl - sum, e = -1, base = 0, tiles = 1;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
