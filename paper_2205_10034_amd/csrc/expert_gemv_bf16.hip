@@ -51,6 +51,29 @@ __device__ __forceinline__ uint16_t bf16_of(float v) {  // round to nearest even
 }
 __device__ __forceinline__ float gelu_exact(float u) { return 0.5f * u * erfcf(-u * 0.70710678118654752f); }
 
+// What the kernels below share, so that a product has the same bits in each: eight terms in order, the sum over the lanes (in every
+// lane), the end of the first product (u: the up projection's sum, b: the bias).
+struct Row8 { float v[8]; };
+__device__ __forceinline__ Row8 unpack8(const uint4& x) {
+  return Row8{{lo16(x.x), hi16(x.x), lo16(x.y), hi16(x.y), lo16(x.z), hi16(x.z), lo16(x.w), hi16(x.w)}};
+}
+__device__ __forceinline__ float add8(float a, const uint4& w, const Row8& x) {
+  a = fmaf(lo16(w.x), x.v[0], a); a = fmaf(hi16(w.x), x.v[1], a);
+  a = fmaf(lo16(w.y), x.v[2], a); a = fmaf(hi16(w.y), x.v[3], a);
+  a = fmaf(lo16(w.z), x.v[4], a); a = fmaf(hi16(w.z), x.v[5], a);
+  a = fmaf(lo16(w.w), x.v[6], a); a = fmaf(hi16(w.w), x.v[7], a);
+  return a;
+}
+__device__ __forceinline__ float sum_lanes(float v) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+  return v;
+}
+template <int EPI>
+__device__ __forceinline__ float first_end(float v, float u, float b) {
+  return EPI == GV_SWIGLU ? v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * u : gelu_exact(v + b);
+}
+
 // EPI: GV_GELU out = gelu(. + bias); GV_SWIGLU out = silu(. Wg) * (. Wu) (a wavefront's weight rows are
 // FPW/2 of Wg and the same FPW/2 of Wu); GV_BIAS out = . + bias; GV_COMBINE (k = 1) out[token] =
 // residual[token] + gate_w[token] * (. + bias) with token = row_map[r].
@@ -121,17 +144,9 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
   #pragma unroll
       for (int r = 0; r < GV_ROWS; ++r) {
         if (r < rows) {  // (wave-uniform)
-          const float x0 = lo16(xv[r].x), x1 = hi16(xv[r].x), x2 = lo16(xv[r].y), x3 = hi16(xv[r].y);
-          const float x4 = lo16(xv[r].z), x5 = hi16(xv[r].z), x6 = lo16(xv[r].w), x7 = hi16(xv[r].w);
+          const Row8 x = unpack8(xv[r]);
   #pragma unroll
-          for (int j = 0; j < GV_FPW; ++j) {
-            float a = acc[j][r];
-            a = fmaf(lo16(wv[j].x), x0, a); a = fmaf(hi16(wv[j].x), x1, a);
-            a = fmaf(lo16(wv[j].y), x2, a); a = fmaf(hi16(wv[j].y), x3, a);
-            a = fmaf(lo16(wv[j].z), x4, a); a = fmaf(hi16(wv[j].z), x5, a);
-            a = fmaf(lo16(wv[j].w), x6, a); a = fmaf(hi16(wv[j].w), x7, a);
-            acc[j][r] = a;
-          }
+          for (int j = 0; j < GV_FPW; ++j) acc[j][r] = add8(acc[j][r], wv[j], x);
         }
       }
     }
@@ -141,12 +156,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
     for (int r = 0; r < GV_ROWS; ++r) {
       if (r < rows) {
   #pragma unroll
-        for (int j = 0; j < GV_FPW; ++j) {
-          float v = acc[j][r];
-  #pragma unroll
-          for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-          acc[j][r] = v;
-        }
+        for (int j = 0; j < GV_FPW; ++j) acc[j][r] = sum_lanes(acc[j][r]);
       }
     }
 
@@ -195,11 +205,9 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_kernel(
             u = acc[OUTF][r];
   #pragma unroll
             for (int j = 1; j < OUTF; ++j) u = lane == j ? acc[OUTF + j][r] : u;
-            v = v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * u;
-          } else {
-            v += b;
-            if (EPI == GV_GELU) v = gelu_exact(v);
           }
+          if (EPI == GV_SWIGLU || EPI == GV_GELU) v = first_end<EPI>(v, u, b);
+          else v += b;
           if (EPI == GV_COMBINE) {
             const size_t o = (size_t)token[r] * N + n;
             const float res = residual ? lo16((uint32_t)residual[o]) : 0.f;
@@ -307,17 +315,9 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
 #pragma unroll
   for (int j = 0; j < FPW; ++j) acc[j] = 0.f;
   auto add = [&](const uint4 (&wv)[FPW], const uint4& xv) {
-    const float x0 = lo16(xv.x), x1 = hi16(xv.x), x2 = lo16(xv.y), x3 = hi16(xv.y);
-    const float x4 = lo16(xv.z), x5 = hi16(xv.z), x6 = lo16(xv.w), x7 = hi16(xv.w);
+    const Row8 x8 = unpack8(xv);
 #pragma unroll
-    for (int j = 0; j < FPW; ++j) {
-      float a = acc[j];
-      a = fmaf(lo16(wv[j].x), x0, a); a = fmaf(hi16(wv[j].x), x1, a);
-      a = fmaf(lo16(wv[j].y), x2, a); a = fmaf(hi16(wv[j].y), x3, a);
-      a = fmaf(lo16(wv[j].z), x4, a); a = fmaf(hi16(wv[j].z), x5, a);
-      a = fmaf(lo16(wv[j].w), x6, a); a = fmaf(hi16(wv[j].w), x7, a);
-      acc[j] = a;
-    }
+    for (int j = 0; j < FPW; ++j) acc[j] = add8(acc[j], wv[j], x8);
   };
   for (int kb = (KSPLIT ? (int)threadIdx.x : lane) * 8; kb < K; kb += 2 * PIECE) {
     const bool two = kb + PIECE < K;
@@ -332,10 +332,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
     if (two) add(wv2, xv2);
   }
 #pragma unroll
-  for (int j = 0; j < FPW; ++j) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) acc[j] += __shfl_xor(acc[j], m, 64);
-  }
+  for (int j = 0; j < FPW; ++j) acc[j] = sum_lanes(acc[j]);
   if constexpr (KSPLIT) {  // the wavefronts' sums meet, in wavefront order
     if (lane < FPW) {
       float v = acc[0];
@@ -358,15 +355,14 @@ __global__ __launch_bounds__(GV_WAVES * 64) void expert_gemv_ranked_kernel(
     float v = acc[0];
 #pragma unroll
     for (int j = 1; j < OUTF; ++j) v = lane == j ? acc[j] : v;
+    float u = acc[FPW - OUTF], b = 0.f;
     if (EPI == GV_SWIGLU) {
-      float u = acc[FPW - OUTF];
 #pragma unroll
       for (int j = 1; j < OUTF; ++j) u = lane == j ? acc[FPW - OUTF + j] : u;
-      v = v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * u;
-    } else {
-      v = gelu_exact(v + (bias ? lo16((uint32_t)bias[(eoff ? eoff[e] : (int64_t)e * N) + n]) : 0.f));
+    } else if (bias) {
+      b = lo16((uint32_t)bias[(eoff ? eoff[e] : (int64_t)e * N) + n]);
     }
-    out[(size_t)row * N + n] = bf16_of(v);
+    out[(size_t)row * N + n] = bf16_of(first_end<EPI>(v, u, b));
   }
 }
 
@@ -410,24 +406,14 @@ __global__ __launch_bounds__(C1_GROUPS * GV_WAVES * 64) void expert_gemv_combine
 #pragma unroll
         for (int f = 0; f < C1_FPW; ++f) wv[f] = load_weights<NT>(wbase + (int64_t)f * K + kb);
         const uint4 xv = *reinterpret_cast<const uint4*>(xrow + kb);
-        const float x0 = lo16(xv.x), x1 = hi16(xv.x), x2 = lo16(xv.y), x3 = hi16(xv.y);
-        const float x4 = lo16(xv.z), x5 = hi16(xv.z), x6 = lo16(xv.w), x7 = hi16(xv.w);
+        const Row8 x = unpack8(xv);
 #pragma unroll
-        for (int f = 0; f < C1_FPW; ++f) {
-          float a = acc[f];
-          a = fmaf(lo16(wv[f].x), x0, a); a = fmaf(hi16(wv[f].x), x1, a);
-          a = fmaf(lo16(wv[f].y), x2, a); a = fmaf(hi16(wv[f].y), x3, a);
-          a = fmaf(lo16(wv[f].z), x4, a); a = fmaf(hi16(wv[f].z), x5, a);
-          a = fmaf(lo16(wv[f].w), x6, a); a = fmaf(hi16(wv[f].w), x7, a);
-          acc[f] = a;
-        }
+        for (int f = 0; f < C1_FPW; ++f) acc[f] = add8(acc[f], wv[f], x);
       }
       float mine = 0.f;  // lane f < C1_FPW: the wavefront's sum for output feature n0 + f
 #pragma unroll
       for (int f = 0; f < C1_FPW; ++f) {
-        float v = acc[f];
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+        const float v = sum_lanes(acc[f]);
         mine = lane == f ? v : mine;
       }
       if (lane < C1_FPW) red[group][wave][lane] = mine;
