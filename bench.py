@@ -55,8 +55,9 @@ def measured_traffic(workload, stage):
 
 def hbm_stage_bytes(wl, R):
     """Algorithmic bytes of the HBM-bound stages of a layer with R kept rows.  Dispatch has no bandwidth figure: the stage
-    only builds routing tables, the first product gathers the rows (float32: and stores the dispatched copy).  With one
-    expert per token the second product does the combine, and that stage is empty."""
+    only builds routing tables, the first product gathers the rows (float32: and stores the dispatched copy, but for large copies
+    and narrow products, which no workload here has).  With one expert per token the second product does the combine, and that
+    stage is empty."""
     s = 2 if wl.dtype == "bf16" else 4
     b = {"gate": wl.T * wl.d_model * s + 8 * wl.k * wl.T}
     if wl.k > 1:

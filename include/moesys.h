@@ -265,7 +265,7 @@ int32_t moe_combine(const moe_config* cfg, const void* yd, const int32_t* assign
  * [T,d_model] (may alias residual, must not alias x unless residual == x).
  * Fusions inside the call: the first GEMM gathers its rows from x through
  * row_to_assign (MOE_BF16: no dispatched copy xd is made; MOE_F32: the same
- * kernel stores xd on its way); with k == 1 the second GEMM scales each row by
+ * kernel stores xd on its way, unless a large copy is faster apart); with k == 1 the second GEMM scales each row by
  * its gate weight, adds the residual in fp32 and stores it at its token's place
  * in `out` (MOE_BF16: one rounding, no yd; MOE_F32: yd is stored as well), and
  * what is left of the combine are the rows of dropped tokens; a step of one
@@ -299,7 +299,7 @@ int32_t moe_layer_experts(const moe_config* cfg, const moe_weights* w, const voi
  * tokens) under MOE_STAGE_GATE, with MOE_STAGE_DISPATCH empty; a one-token step
  * that ranks in its first product has softmax, top-k and tables under
  * MOE_STAGE_GEMM1, and its combine under MOE_STAGE_GEMM2; the dispatched copy of
- * MOE_F32 under MOE_STAGE_GEMM1; with k == 1 the combine under MOE_STAGE_GEMM2. */
+ * MOE_F32 under MOE_STAGE_GEMM1 (made apart: MOE_STAGE_DISPATCH); with k == 1 the combine under MOE_STAGE_GEMM2. */
 typedef struct moe_timer moe_timer;
 enum { MOE_STAGE_GATE = 0, MOE_STAGE_DISPATCH = 1, MOE_STAGE_GEMM1 = 2, MOE_STAGE_GEMM2 = 3,
        MOE_STAGE_COMBINE = 4, MOE_STAGE_COUNT = 5 };

@@ -180,6 +180,15 @@ int32_t experts_impl(const char* who, const moe_config* cfg, const moe_weights* 
   return MOE_OK;
 }
 
+// float32 inside a layer: the first product gathers its rows from x and its tiles store the dispatched copy on their way, which saves a
+// launch, but the more a tile has to copy for the features it computes, the longer it holds its compute unit.  MI355X, layers of 16 MB of
+// dispatched rows and more, copied by a kernel of its own / by the first product: below 768 features 0.98 over 295 (111 of them more than
+// 2 % slower; 8 experts, 4399 tokens, k 2, 1984 x 128: 183 / 215 us), from 768 on 1.002 over 216 (2).  8 to 16 MB 1.006 and 1.003, less 1.064 and
+// 1.026.
+bool first_product_copies(const moe_config* cfg) {
+  return cfg->dtype == MOE_F32 && ((size_t)max_rows(cfg) * cfg->d_model * 4 < ((size_t)16 << 20) || cfg->d_ff >= 768);
+}
+
 int32_t layer_impl(const moe_config* cfg, const moe_weights* w, const void* x, const void* residual, void* out,
                    void* ws, size_t ws_bytes, hipStream_t s, moe_timer* timer) {
   // everything is validated before anything is launched
@@ -192,8 +201,7 @@ int32_t layer_impl(const moe_config* cfg, const moe_weights* w, const void* x, c
     if ((st = route_and_first_product("moe_layer_forward", cfg, w, x, ws, ws_bytes, s, timer)) != MOE_OK) return st;
     return experts_impl("moe_layer_forward", cfg, w, x, residual, out, ws, ws_bytes, s, timer, true);
   }
-  // float32: the first product gathers its rows from x and stores them on the way
-  const bool rows = cfg->dtype == MOE_BF16;
+  const bool rows = !first_product_copies(cfg);
   if ((st = route_impl("moe_layer_forward", cfg, w, x, ws, ws_bytes, s, timer, rows)) != MOE_OK) return st;
   return experts_impl("moe_layer_forward", cfg, w, x, residual, out, ws, ws_bytes, s, timer, false, rows);
 }
@@ -278,5 +286,8 @@ const char* moe_test_layer_routing(const moe_config* cfg, int32_t packed, int32_
   }
   return moe_test_gate_kernel(cfg, packed);
 }
+
+// Whether the first product of a float32 layer makes the dispatched copy: for the test of the rule.
+int32_t moe_test_first_product_copies(const moe_config* cfg) { return moe_config_check(cfg) == MOE_OK && first_product_copies(cfg); }
 
 }  // extern "C"

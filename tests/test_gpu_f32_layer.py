@@ -23,7 +23,8 @@ def tile_rows(cfg, which):
     (3001, 256, 1088, 7, 1, 1.0, "gelu", "output_major", None), (1000, 960, 1408, 16, 2, 1.25, "gelu", "input_major", None),
     (900, 576, 1024, 8, 1, 0.0, "swiglu", "output_major", None), (1111, 320, 4096, 8, 1, 0.5, "swiglu", "input_major", None),
     (2048, 1024, 4096, 16, 2, 1.25, "gelu", "input_major", (160, 160)), (4096, 1024, 4096, 16, 1, 1.0, "gelu", "output_major", (160, 160)),
-    (2500, 768, 3072, 8, 1, 0.0, "gelu", "output_major", None)])
+    (2500, 768, 3072, 8, 1, 0.0, "gelu", "output_major", None),
+    (4096, 1024, 128, 4, 1, 0.0, "gelu", "output_major", None), (2048, 1024, 704, 8, 2, 0.0, "swiglu", "input_major", None)])   # (rows copied apart)
 @pytest.mark.parametrize("mode", ["plain", "in_place", "nan"])
 def test_f32_layer(T, d, f, E, k, cf, act, layout, rows, mode):
     cfg = M.MoEConfig(T=T, d_model=d, d_ff=f, E=E, k=k, capacity_factor=cf, act=act, dtype="f32")

@@ -166,3 +166,12 @@ def test_float32_tiles_of_80_rows():
         E = 8 if rows == 375 else 16
         assert f32_rows(rows, E, N, 512, 1.25, "swiglu", "output_major", 0) == 80
         assert f32_rows(rows, E, N, 512, 1.25, "swiglu", "input_major", 0) == first
+
+
+def test_float32_copy_in_the_first_product():
+    """16 MB of dispatched rows and more are copied by a kernel of their own where the product has fewer than 768 features."""
+    copies = M.lib().moe_test_first_product_copies
+    copies.restype = C.c_int32
+    for T, d, f, E, k, cf, dtype, want in ((4096, 1024, 704, 8, 1, 0.0, "f32", 0), (4095, 1024, 704, 8, 1, 0.0, "f32", 1), (4096, 1024, 768, 8, 1, 0.0, "f32", 1),
+                                           (2048, 1024, 64, 8, 2, 0.0, "f32", 0), (2048, 1024, 64, 8, 2, 0.5, "f32", 1), (8192, 1024, 128, 8, 2, 0.0, "bf16", 0)):
+        assert copies(C.byref(M.MoEConfig(T=T, d_model=d, d_ff=f, E=E, k=k, capacity_factor=cf, dtype=dtype).c())) == want, (T, d, f, E, k, cf, dtype)
